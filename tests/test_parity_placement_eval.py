@@ -63,6 +63,24 @@ def test_traffic_matches_oracle(lib, E1, E2, G):
     assert C.sum() == R.sum()                                # Eq. 9 conserves the routed tokens
 
 
+# the traffic kernel's stripes of GPU rows (one up to G = 90), its lane-private copies (32 for few GPUs, none for many) and
+# column padding, with a map that leaves GPUs empty and names GPUs that do not exist (their rows count nowhere)
+@pytest.mark.parametrize("E1,E2,G", [(1, 1, 1), (256, 256, 1), (3, 200, 90), (200, 3, 91), (256, 256, 256), (65, 129, 128)])
+def test_traffic_stripes_and_copies(lib, E1, E2, G):
+    rng = np.random.default_rng(E1 + 1000 * G)
+    R = rng.integers(0, 1 << 44, (E1, E2))
+    pa, pb = rng.integers(0, G, E1).astype(np.int32), rng.integers(0, G, E2).astype(np.int32)
+    B = rng.uniform(1.0, 9.0, (G, G))
+    C, mc = gpu_traffic(lib, R, pa, pb, G, B)
+    Cref = O.cluster_traffic(R, pa, pb, G)
+    np.testing.assert_array_equal(C, Cref)
+    assert mc == pytest.approx(O.max_pair_cost(Cref, B), rel=1e-12)
+    pa[0], pb[-1] = -1, G
+    C, _ = gpu_traffic(lib, R, pa, pb, G)
+    ok_a, ok_b = pa >= 0, pb < G
+    np.testing.assert_array_equal(C, O.cluster_traffic(R[ok_a][:, ok_b], pa[ok_a], pb[ok_b], G) if ok_a.any() and ok_b.any() else 0 * C)
+
+
 def test_accumulate_counts_over_batches(lib):
     E = 8
     P = torch.zeros(E, dtype=torch.int64, device="cuda")

@@ -34,22 +34,4 @@ int launch_ffn_plan(const int32_t* counts, const int32_t* starts, const int32_t*
                     const int32_t* group_expert, int n_weights, int E, int N, int bm0, int bm1, int choice, int32_t* plan,
                     hipStream_t s);
 
-struct RowTile { int expert; int row0; int rows; };
-
-// Which expert does global row tile `mt` belong to?  `prefix` is one of the two
-// prefix arrays of the plan.  Returns false when mt is past the last tile.
-__device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ plan, const int32_t* __restrict__ prefix,
-                                              int mt, int bm, RowTile& out) {
-    const int n = plan[0];
-    if (mt >= prefix[n]) return false;
-    int i = 0;
-    while (i + 1 < n && prefix[i + 1] <= mt) ++i;
-    const int r0 = (mt - prefix[i]) * bm;
-    out.expert = plan[kPlanExpert + i];
-    out.row0 = plan[kPlanStart + i] + r0;
-    const int left = plan[kPlanCount + i] - r0;
-    out.rows = left < bm ? left : bm;
-    return true;
-}
-
 }  // namespace moe

@@ -72,6 +72,29 @@ def test_ffn_matches_oracle(lib, dtype, T, d, f, E, k, G, local):
     assert np.all(got[~is_local] == 7.0)
 
 
+@pytest.mark.parametrize("sizes,d,f", [
+    ([1, 31, 32, 33, 0, 63, 64, 65, 129], 36, 100),   # bucket ends on every side of a tile, ragged last stage and columns
+    ([1], 4, 4),                                      # the smallest problem there is
+    ([5, 0, 97], 1028, 28),                           # long reduction with a 4-wide last stage; one shorter than a stage
+    ([40, 1700], 64, 96),                             # exact stages and columns, an even and an odd number of stages
+])
+@pytest.mark.parametrize("local", [-1, 0])
+def test_ffn_f32_tiles(lib, sizes, d, f, local):
+    E, T = len(sizes), sum(sizes)
+    x, w1, w3, w2, _, _ = make_problem(T + d, T, d, f, E, 1, 1, "f32")
+    idx = np.random.default_rng(T).permutation(np.repeat(np.arange(E), sizes)).astype(np.int32)[:, None]
+    pl = np.zeros(E, dtype=np.int32) if E == 1 else (np.arange(E) % 2).astype(np.int32)
+    L = gpu_ffn(lib, x, w1, w3, w2, idx, pl, 2, local, "f32")
+    dsp = O.dispatch(x, idx, pl, 2)
+    ref = O.expert_ffn_grouped(dsp["send_buf"], w1, w3, w2, dsp["expert_counts"], dsp["expert_start"], pl, local)
+    got = to_host(L.ffn_out)
+    e_sorted = idx.reshape(-1)[dsp["perm"]]
+    is_local = np.ones(T, dtype=bool) if local < 0 else (pl[e_sorted] == local)
+    # fp32 sums of at most 1028 products of unit variance: rounding stays below K * 2^-24 = 6e-5 of the row's rms
+    assert rel_err(got[is_local], ref[is_local]) <= TOL_F32
+    assert np.all(got[~is_local] == 7.0)
+
+
 @pytest.mark.parametrize("seed", [1, 2])
 def test_ffn_random_shapes_and_routings(lib, seed):
     """25 seeded random bf16 problems per seed: sizes from a handful of rows to several thousand, 1-64 experts,

@@ -92,7 +92,8 @@ typedef enum {
     MOE_K_COMBINE = 8,
     MOE_K_TRANSITION = 9,
     MOE_K_ROUTER = 10,         /* x.W_g + bias of moe_router_gate              */
-    MOE_K_COUNT = 11
+    MOE_K_FRONT = 11,          /* gate, dispatch and tile plan of moe_layer_forward in one launch */
+    MOE_K_COUNT = 12
 } moe_kernel_id_t;
 
 /* Thread-local description of the last failure on this thread; never NULL. */
@@ -337,6 +338,28 @@ int moe_combine(const void* ffn_out, moe_dtype_t dt, const int32_t* inv_perm,
                 const int32_t* topk_idx, const float* topk_w,
                 const int32_t* placement, int local_gpu,
                 int T, int d, int E, int k, void* y, void* stream);
+
+/* ------------------------------------------------------------------------
+ * moe_layer_forward - one layer's share in one call:
+ *   moe_topk_gate -> moe_dispatch -> moe_expert_ffn_grouped -> moe_combine
+ * with those calls' arguments, buffers, results (bit for bit), requirements and
+ * errors.  The calls are enqueued back to back, and where the batch allows it
+ * stages are merged: small batches run gate, dispatch and the FFN's tile plan
+ * as one kernel (timed as MOE_K_FRONT), decode-sized bf16 batches fold the
+ * combine into the last kernel of the FFN (timed with MOE_K_FFN_DOWN).
+ * dispatch_workspace and ffn_workspace must not overlap.
+ * ---------------------------------------------------------------------- */
+int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits,
+                      int T, int d, int f, int E, int k,
+                      const int32_t* placement, int G, int local_gpu,
+                      const void* packed_weights,
+                      int32_t* topk_idx, float* topk_w,
+                      void* send_buf, int32_t* perm, int32_t* inv_perm,
+                      int32_t* expert_counts, int32_t* expert_start,
+                      int32_t* gpu_counts, int32_t* gpu_offsets,
+                      void* ffn_out, void* y,
+                      void* dispatch_workspace, size_t dispatch_workspace_bytes,
+                      void* ffn_workspace, size_t ffn_workspace_bytes, void* stream);
 
 /* ------------------------------------------------------------------------
  * moe_transition_counts - routing history table between neighbouring layers

@@ -2,6 +2,7 @@
 // The numerical work is in the launchers (gate.hip, dispatch.hip, ffn_*.hip,
 // combine.hip, transition.hip).
 #include "common.h"
+#include "front.h"
 #include <cstdarg>
 #include <atomic>
 #include <cstdio>
@@ -107,15 +108,21 @@ int moe_timing_end(double* sum_ms, int* launches) {
     return rc;
 }
 
+static int check_gate_args(const char* who, const float* logits, int T, int E, int k, const int32_t* topk_idx, const float* topk_w) {
+    REQUIRE(T >= 0, "%s: T=%d < 0", who, T);
+    REQUIRE(E >= 1 && E <= MOE_MAX_EXPERTS, "%s: E=%d outside [1,%d]", who, E, MOE_MAX_EXPERTS);
+    REQUIRE(k >= 1 && k <= E && k <= MOE_MAX_TOPK, "%s: k=%d outside [1,min(E=%d,%d)]", who, k, E, MOE_MAX_TOPK);
+    REQUIRE((long long)T * E < (1ll << 31), "%s: T*E too large", who);
+    if (T == 0) return MOE_OK;
+    REQUIRE(logits && topk_idx && topk_w, "%s: NULL pointer", who);
+    REQUIRE(aligned16(logits) && aligned16(topk_idx) && aligned16(topk_w), "%s: pointers must be 16-byte aligned", who);
+    return MOE_OK;
+}
+
 int moe_topk_gate_norm(const float* logits, int T, int E, int k, moe_norm_t norm, int32_t* topk_idx, float* topk_w, void* stream) {
     REQUIRE(norm == MOE_NORM_SOFTMAX_SELECTED || norm == MOE_NORM_SOFTMAX_ALL, "moe_topk_gate: unknown norm %d", (int)norm);
-    REQUIRE(T >= 0, "moe_topk_gate: T=%d < 0", T);
-    REQUIRE(E >= 1 && E <= MOE_MAX_EXPERTS, "moe_topk_gate: E=%d outside [1,%d]", E, MOE_MAX_EXPERTS);
-    REQUIRE(k >= 1 && k <= E && k <= MOE_MAX_TOPK, "moe_topk_gate: k=%d outside [1,min(E=%d,%d)]", k, E, MOE_MAX_TOPK);
-    REQUIRE((long long)T * E < (1ll << 31) , "moe_topk_gate: T*E too large");
-    if (T == 0) return MOE_OK;
-    REQUIRE(logits && topk_idx && topk_w, "moe_topk_gate: NULL pointer");
-    REQUIRE(aligned16(logits) && aligned16(topk_idx) && aligned16(topk_w), "moe_topk_gate: pointers must be 16-byte aligned");
+    int rc = check_gate_args("moe_topk_gate", logits, T, E, k, topk_idx, topk_w);
+    if (rc != MOE_OK || T == 0) return rc;
     return launch_gate(logits, T, E, k, norm == MOE_NORM_SOFTMAX_ALL, topk_idx, topk_w, (hipStream_t)stream);
 }
 
@@ -262,29 +269,44 @@ size_t moe_ffn_workspace_bytes(int N, int d, int f, int E, moe_dtype_t dt) {
     return kPlanBytes + round_up((size_t)N * f * elt_bytes(dt), 256) + 256 + (dt == MOE_BF16 ? ffn_bf16_scratch_bytes() : 0);
 }
 
+static int check_ffn_args(const char* who, const void* send_buf, moe_dtype_t dt, int N, int d, int f, int E,
+                          const void* packed_weights, const int32_t* expert_counts, const int32_t* expert_start,
+                          const int32_t* placement, int local_gpu, const void* ffn_out, const void* workspace, size_t workspace_bytes) {
+    int rc = check_ffn_shape(who, E, d, f, dt);
+    if (rc != MOE_OK) return rc;
+    REQUIRE(N >= 0, "%s: N=%d < 0", who, N);
+    REQUIRE(local_gpu >= -1 && local_gpu < MOE_MAX_GPUS, "%s: local_gpu=%d outside [-1,%d)", who, local_gpu, MOE_MAX_GPUS);
+    if (N == 0) return MOE_OK;
+    REQUIRE(send_buf && packed_weights && expert_counts && expert_start && placement && ffn_out && workspace, "%s: NULL pointer", who);
+    REQUIRE(aligned16(send_buf) && aligned16(packed_weights) && aligned16(ffn_out) && aligned16(workspace),
+            "%s: pointers must be 16-byte aligned", who);
+    size_t need = moe_ffn_workspace_bytes(N, d, f, E, dt);
+    if (workspace_bytes < need) return fail(MOE_ERR_WORKSPACE, "%s: workspace %zu < %zu bytes", who, workspace_bytes, need);
+    return MOE_OK;
+}
+
+// the expert FFN of checked arguments; tail: see CombineTail
+static int run_ffn(const void* send_buf, moe_dtype_t dt, int N, int d, int f, int E, const void* packed_weights,
+                   const int32_t* expert_counts, const int32_t* expert_start, const int32_t* placement, int local_gpu, void* ffn_out,
+                   void* workspace, bool plan_ready, CombineTail* tail, hipStream_t s) {
+    int32_t* plan = (int32_t*)workspace;
+    void* H = (char*)workspace + kPlanBytes;
+    if (dt == MOE_BF16)
+        return launch_ffn_bf16(send_buf, N, d, f, E, packed_weights, expert_counts, expert_start, placement, local_gpu, nullptr, E,
+                               ffn_out, plan, plan_ready, H, tail, s);
+    return launch_ffn_f32((const float*)send_buf, N, d, f, E, (const float*)packed_weights, expert_counts, expert_start,
+                          placement, local_gpu, nullptr, E, (float*)ffn_out, plan, plan_ready, (float*)H, s);
+}
+
 int moe_expert_ffn_grouped(const void* send_buf, moe_dtype_t dt, int N, int d, int f, int E,
                            const void* packed_weights, const int32_t* expert_counts, const int32_t* expert_start,
                            const int32_t* placement, int local_gpu, void* ffn_out,
                            void* workspace, size_t workspace_bytes, void* stream) {
-    int rc = check_ffn_shape("moe_expert_ffn_grouped", E, d, f, dt);
-    if (rc != MOE_OK) return rc;
-    REQUIRE(N >= 0, "moe_expert_ffn_grouped: N=%d < 0", N);
-    REQUIRE(local_gpu >= -1 && local_gpu < MOE_MAX_GPUS, "moe_expert_ffn_grouped: local_gpu=%d outside [-1,%d)", local_gpu, MOE_MAX_GPUS);
-    if (N == 0) return MOE_OK;
-    REQUIRE(send_buf && packed_weights && expert_counts && expert_start && placement && ffn_out && workspace,
-            "moe_expert_ffn_grouped: NULL pointer");
-    REQUIRE(aligned16(send_buf) && aligned16(packed_weights) && aligned16(ffn_out) && aligned16(workspace),
-            "moe_expert_ffn_grouped: pointers must be 16-byte aligned");
-    size_t need = moe_ffn_workspace_bytes(N, d, f, E, dt);
-    if (workspace_bytes < need) return fail(MOE_ERR_WORKSPACE, "moe_expert_ffn_grouped: workspace %zu < %zu bytes", workspace_bytes, need);
-    int32_t* plan = (int32_t*)workspace;
-    void* H = (char*)workspace + kPlanBytes;
-    hipStream_t s = (hipStream_t)stream;
-    if (dt == MOE_BF16)
-        return launch_ffn_bf16(send_buf, N, d, f, E, packed_weights, expert_counts, expert_start, placement, local_gpu, nullptr, E,
-                               ffn_out, plan, H, s);
-    return launch_ffn_f32((const float*)send_buf, N, d, f, E, (const float*)packed_weights, expert_counts, expert_start,
-                          placement, local_gpu, nullptr, E, (float*)ffn_out, plan, (float*)H, s);
+    int rc = check_ffn_args("moe_expert_ffn_grouped", send_buf, dt, N, d, f, E, packed_weights, expert_counts, expert_start, placement,
+                            local_gpu, ffn_out, workspace, workspace_bytes);
+    if (rc != MOE_OK || N == 0) return rc;
+    return run_ffn(send_buf, dt, N, d, f, E, packed_weights, expert_counts, expert_start, placement, local_gpu, ffn_out, workspace,
+                   false, nullptr, (hipStream_t)stream);
 }
 
 int moe_expert_ffn_segments(const void* recv_buf, moe_dtype_t dt, int N, int d, int f, int E,
@@ -305,9 +327,10 @@ int moe_expert_ffn_segments(const void* recv_buf, moe_dtype_t dt, int N, int d, 
     void* H = (char*)workspace + kPlanBytes;
     hipStream_t s = (hipStream_t)stream;
     if (dt == MOE_BF16)
-        return launch_ffn_bf16(recv_buf, N, d, f, n_seg, packed_weights, seg_counts, seg_start, nullptr, -1, seg_expert, E, ffn_out, plan, H, s);
+        return launch_ffn_bf16(recv_buf, N, d, f, n_seg, packed_weights, seg_counts, seg_start, nullptr, -1, seg_expert, E, ffn_out, plan,
+                               false, H, nullptr, s);
     return launch_ffn_f32((const float*)recv_buf, N, d, f, n_seg, (const float*)packed_weights, seg_counts, seg_start, nullptr, -1,
-                          seg_expert, E, (float*)ffn_out, plan, (float*)H, s);
+                          seg_expert, E, (float*)ffn_out, plan, false, (float*)H, s);
 }
 
 int moe_receive_segments(const int32_t* expert_counts_all, const int32_t* placement, int E, int G, int dest, int max_seg,
@@ -322,21 +345,71 @@ int moe_receive_segments(const int32_t* expert_counts_all, const int32_t* placem
                                    n_seg, (hipStream_t)stream);
 }
 
+static int check_combine_args(const char* who, const void* ffn_out, moe_dtype_t dt, const int32_t* inv_perm, const int32_t* topk_idx,
+                              const float* topk_w, const int32_t* placement, int local_gpu, int T, int d, int E, int k, const void* y) {
+    REQUIRE(dt == MOE_F32 || dt == MOE_BF16, "%s: unknown dtype %d", who, (int)dt);
+    REQUIRE(T >= 0, "%s: T=%d < 0", who, T);
+    REQUIRE(E >= 1 && E <= MOE_MAX_EXPERTS, "%s: E=%d outside [1,%d]", who, E, MOE_MAX_EXPERTS);
+    REQUIRE(k >= 1 && k <= E && k <= MOE_MAX_TOPK, "%s: k=%d outside [1,min(E=%d,%d)]", who, k, E, MOE_MAX_TOPK);
+    REQUIRE(d >= 1 && ((long long)d * elt_bytes(dt)) % 16 == 0, "%s: a row (d=%d) must be a positive multiple of 16 bytes", who, d);
+    REQUIRE(local_gpu >= -1 && local_gpu < MOE_MAX_GPUS, "%s: local_gpu=%d outside [-1,%d)", who, local_gpu, MOE_MAX_GPUS);
+    REQUIRE((long long)T * k < (1ll << 31), "%s: T*k does not fit int32", who);
+    if (T == 0) return MOE_OK;
+    REQUIRE(ffn_out && inv_perm && topk_idx && topk_w && y, "%s: NULL pointer", who);
+    REQUIRE(local_gpu < 0 || placement, "%s: placement is required when local_gpu >= 0", who);
+    REQUIRE(aligned16(ffn_out) && aligned16(y), "%s: ffn_out/y must be 16-byte aligned", who);
+    return MOE_OK;
+}
+
 int moe_combine(const void* ffn_out, moe_dtype_t dt, const int32_t* inv_perm, const int32_t* topk_idx,
                 const float* topk_w, const int32_t* placement, int local_gpu, int T, int d, int E, int k,
                 void* y, void* stream) {
-    REQUIRE(dt == MOE_F32 || dt == MOE_BF16, "moe_combine: unknown dtype %d", (int)dt);
-    REQUIRE(T >= 0, "moe_combine: T=%d < 0", T);
-    REQUIRE(E >= 1 && E <= MOE_MAX_EXPERTS, "moe_combine: E=%d outside [1,%d]", E, MOE_MAX_EXPERTS);
-    REQUIRE(k >= 1 && k <= E && k <= MOE_MAX_TOPK, "moe_combine: k=%d outside [1,min(E=%d,%d)]", k, E, MOE_MAX_TOPK);
-    REQUIRE(d >= 1 && ((long long)d * elt_bytes(dt)) % 16 == 0, "moe_combine: a row (d=%d) must be a positive multiple of 16 bytes", d);
-    REQUIRE(local_gpu >= -1 && local_gpu < MOE_MAX_GPUS, "moe_combine: local_gpu=%d outside [-1,%d)", local_gpu, MOE_MAX_GPUS);
-    REQUIRE((long long)T * k < (1ll << 31), "moe_combine: T*k does not fit int32");
-    if (T == 0) return MOE_OK;
-    REQUIRE(ffn_out && inv_perm && topk_idx && topk_w && y, "moe_combine: NULL pointer");
-    REQUIRE(local_gpu < 0 || placement, "moe_combine: placement is required when local_gpu >= 0");
-    REQUIRE(aligned16(ffn_out) && aligned16(y), "moe_combine: ffn_out/y must be 16-byte aligned");
+    int rc = check_combine_args("moe_combine", ffn_out, dt, inv_perm, topk_idx, topk_w, placement, local_gpu, T, d, E, k, y);
+    if (rc != MOE_OK || T == 0) return rc;
     return launch_combine(ffn_out, dt, inv_perm, topk_idx, topk_w, placement, local_gpu, T, d, E, k, y, (hipStream_t)stream);
+}
+
+int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T, int d, int f, int E, int k,
+                      const int32_t* placement, int G, int local_gpu, const void* packed_weights,
+                      int32_t* topk_idx, float* topk_w, void* send_buf, int32_t* perm, int32_t* inv_perm,
+                      int32_t* expert_counts, int32_t* expert_start, int32_t* gpu_counts, int32_t* gpu_offsets,
+                      void* ffn_out, void* y, void* dispatch_workspace, size_t dispatch_workspace_bytes,
+                      void* ffn_workspace, size_t ffn_workspace_bytes, void* stream) {
+    const char* who = "moe_layer_forward";
+    int rc, row_bytes = 0;
+    if ((rc = check_gate_args(who, logits, T, E, k, topk_idx, topk_w)) != MOE_OK) return rc;
+    if ((rc = check_dispatch_args(who, x, dt, topk_idx, T, d, E, k, placement, G, send_buf, perm, inv_perm, expert_counts, expert_start,
+                                  gpu_counts, gpu_offsets, &row_bytes)) != MOE_OK) return rc;
+    const int N = T * k;
+    if ((rc = check_ffn_args(who, send_buf, dt, N, d, f, E, packed_weights, expert_counts, expert_start, placement, local_gpu, ffn_out,
+                             ffn_workspace, ffn_workspace_bytes)) != MOE_OK) return rc;
+    if ((rc = check_combine_args(who, ffn_out, dt, inv_perm, topk_idx, topk_w, placement, local_gpu, T, d, E, k, y)) != MOE_OK) return rc;
+    REQUIRE(T == 0 || x, "%s: NULL x", who);
+    REQUIRE(dispatch_workspace != nullptr, "%s: NULL workspace", who);
+    if (dispatch_workspace_bytes < moe_dispatch_workspace_bytes(T, E, k))
+        return fail(MOE_ERR_WORKSPACE, "%s: dispatch workspace %zu < %zu bytes", who, dispatch_workspace_bytes,
+                    moe_dispatch_workspace_bytes(T, E, k));
+    hipStream_t s = (hipStream_t)stream;
+    const bool fused = front_fits(T, E, k);
+    if (fused) {
+        FrontArgs a;
+        a.x = (const uint4*)x; a.logits = logits; a.T = T; a.E = E; a.k = k; a.G = G; a.local_gpu = local_gpu;
+        a.units_per_row = row_bytes / 16; a.placement = placement; a.topk_idx = topk_idx; a.topk_w = topk_w; a.perm = perm;
+        a.inv_perm = inv_perm; a.expert_counts = expert_counts; a.expert_start = expert_start; a.gpu_counts = gpu_counts;
+        a.gpu_offsets = gpu_offsets; a.send_buf = (uint4*)send_buf; a.shape = ffn_plan_shape(dt, N, E, local_gpu < 0);
+        a.plan = (int32_t*)ffn_workspace;
+        if ((rc = launch_front(a, s)) != MOE_OK) return rc;
+    } else {
+        if (T > 0 && (rc = launch_gate(logits, T, E, k, false, topk_idx, topk_w, s)) != MOE_OK) return rc;
+        if ((rc = launch_dispatch(x, row_bytes, topk_idx, T, E, k, placement, G, send_buf, perm, inv_perm, expert_counts, expert_start,
+                                  gpu_counts, gpu_offsets, (int32_t*)dispatch_workspace, s)) != MOE_OK) return rc;
+        if (T == 0) return MOE_OK;
+    }
+    CombineTail tail = {inv_perm, topk_idx, topk_w, placement, local_gpu, T, E, k, y, false};
+    if ((rc = run_ffn(send_buf, dt, N, d, f, E, packed_weights, expert_counts, expert_start, placement, local_gpu, ffn_out, ffn_workspace,
+                      fused, &tail, s)) != MOE_OK) return rc;
+    if (tail.done) return MOE_OK;
+    return launch_combine(ffn_out, dt, inv_perm, topk_idx, topk_w, placement, local_gpu, T, d, E, k, y, s);
 }
 
 int moe_transition_counts_pairs(const int32_t* idx_l, const int32_t* idx_l1, int T, int k_l, int k_l1, int E_l, int E_l1,

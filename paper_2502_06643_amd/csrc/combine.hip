@@ -5,20 +5,10 @@
 // the token's k routes in ascending j, so the fp32 sum has a fixed order and no
 // atomics are needed.  Routes whose expert is not on local_gpu are skipped;
 // a token with no local route writes zeros.
+#include "bf16.h"
 #include "common.h"
 
 namespace moe {
-
-__device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
-
-// two fp32 -> packed bf16 pair, round to nearest even (finite inputs)
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-    ua += 0x7FFFu + ((ua >> 16) & 1u);
-    ub += 0x7FFFu + ((ub >> 16) & 1u);
-    return (ua >> 16) | (ub & 0xFFFF0000u);
-}
 
 template <bool BF16>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ ffn_out, const int32_t* __restrict__ inv_perm,

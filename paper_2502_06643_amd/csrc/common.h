@@ -78,11 +78,14 @@ size_t packed_bytes_bf16(int E, int d, int f);
 size_t ffn_bf16_scratch_bytes();      // fp32 partial tiles of the split tail, sized for the largest supported XCD
 int launch_pack_f32(const float* w1, const float* w3, const float* w2, int E, int d, int f, float* packed, hipStream_t s);
 int launch_pack_bf16(const void* w1, const void* w3, const void* w2, int E, int d, int f, void* packed, hipStream_t s);
+// How the expert FFN wants its tile plan built for N rows in E groups (arguments of launch_ffn_plan).
+struct PlanShape { int bm0, bm1, choice; };
+PlanShape ffn_plan_shape(moe_dtype_t dt, int N, int E, bool every_row_resident);
 // E row groups (counts/starts); group g uses the weights of expert group_expert[g] of n_weights
-// (g itself when group_expert is NULL)
+// (g itself when group_expert is NULL).  plan_ready: the plan has been built already (ffn_plan_shape's way)
 int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* packed, const int32_t* counts,
                    const int32_t* starts, const int32_t* placement, int local_gpu, const int32_t* group_expert,
-                   int n_weights, float* out, int32_t* plan, float* H, hipStream_t s);
+                   int n_weights, float* out, int32_t* plan, bool plan_ready, float* H, hipStream_t s);
 // bf16, N <= kFfnSkinnyMaxRows: weight-streaming kernels for decode-sized batches (plan already built).
 // Measured at the Mixtral shape with skewed top-2 routing: they win up to N = 128 rows (+13 to +18 %) and lose from
 // N = 256 on (-7 %), where the largest bucket needs several passes of 64 rows over its weights.
@@ -90,10 +93,15 @@ int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* pack
 #define MOE_SKINNY_MAX_ROWS 160
 #endif
 constexpr int kFfnSkinnyMaxRows = MOE_SKINNY_MAX_ROWS;
+// What the combine needs besides ffn_out; done: set when the FFN launches have written y as well.
+struct CombineTail {
+    const int32_t* inv_perm; const int32_t* topk_idx; const float* topk_w; const int32_t* placement;
+    int local_gpu, T, E, k; void* y; bool done;
+};
 int launch_ffn_skinny(const void* a, int N, int d, int f, int E, const void* packed, size_t s13, size_t expert_stride,
-                      const int32_t* plan, void* H, float* partial, size_t scratch_bytes, void* out, hipStream_t s);
+                      const int32_t* plan, void* H, float* partial, size_t scratch_bytes, void* out, CombineTail* tail, hipStream_t s);
 int launch_ffn_bf16(const void* a, int N, int d, int f, int E, const void* packed, const int32_t* counts,
                     const int32_t* starts, const int32_t* placement, int local_gpu, const int32_t* group_expert,
-                    int n_weights, void* out, int32_t* plan, void* H, hipStream_t s);
+                    int n_weights, void* out, int32_t* plan, bool plan_ready, void* H, CombineTail* tail, hipStream_t s);
 
 }  // namespace moe

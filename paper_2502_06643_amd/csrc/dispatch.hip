@@ -16,7 +16,7 @@
 // The result does not depend on how workgroups are scheduled: every position
 // is a pure function of the route id.
 #include <mutex>
-#include "common.h"
+#include "dispatch_index.h"
 
 namespace moe {
 
@@ -111,17 +111,6 @@ __global__ __launch_bounds__(kScanThreads) void dispatch_scan_kernel(int32_t* __
     }
 }
 
-// lanes of this wavefront that hold the same expert as the calling lane
-__device__ __forceinline__ unsigned long long match_expert(int e, bool valid, int ebits) {
-    unsigned long long m = __ballot(valid);
-    for (int b = 0; b < ebits; ++b) {
-        const bool bit = (e >> b) & 1;
-        const unsigned long long v = __ballot(bit);
-        m &= bit ? v : ~v;
-    }
-    return m;
-}
-
 __global__ __launch_bounds__(kDispatchBlock) void dispatch_rank_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits, int items,
                                                                        const int32_t* __restrict__ block_counts,
                                                                        const int32_t* __restrict__ expert_start,
@@ -176,29 +165,25 @@ __global__ __launch_bounds__(kDispatchBlock) void dispatch_rank_kernel(const int
 // sizes (every launch costs more than the work it does).  A thread keeps its ITEMS expert ids in
 // registers: they are loaded once, all loads in flight together, and serve both passes.  Same
 // results: positions are a pure function of the route id.
-constexpr int kFusedThreads = 1024, kFusedWaves = kFusedThreads / 64, kFusedMaxItems = 16;
-constexpr int kFusedMaxRoutes = kFusedThreads * kFusedMaxItems;
+constexpr int kFusedMaxItems = 16;
+constexpr int kFusedMaxRoutes = kIndexThreads * kFusedMaxItems;
 
 template <int ITEMS>
-__global__ __launch_bounds__(kFusedThreads) void dispatch_index_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits,
+__global__ __launch_bounds__(kIndexThreads) void dispatch_index_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits,
                                                                        const int32_t* __restrict__ placement, int G,
                                                                        int32_t* __restrict__ expert_counts,
                                                                        int32_t* __restrict__ expert_start,
                                                                        int32_t* __restrict__ gpu_counts,
                                                                        int32_t* __restrict__ gpu_offsets,
                                                                        int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
-    // per wavefront: first the number of routes of each expert in its slice, then its running write offset
-    __shared__ int woff[kFusedWaves][MOE_MAX_EXPERTS];
-    __shared__ int pl[MOE_MAX_EXPERTS];
-    __shared__ int tot[MOE_MAX_EXPERTS];
+    __shared__ IndexTables s;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    for (int i = threadIdx.x; i < kFusedWaves * MOE_MAX_EXPERTS; i += kFusedThreads) (&woff[0][0])[i] = 0;
-    if ((int)threadIdx.x < E) pl[threadIdx.x] = placement[threadIdx.x];
+    index_clear(s, E);
+    if ((int)threadIdx.x < E) s.pl[threadIdx.x] = placement[threadIdx.x];
     __syncthreads();
 
     const int wbase = wave * ITEMS * 64;                                // ITEMS 64-route steps per wavefront
     const unsigned long long lower = (1ull << lane) - 1ull;
-    volatile int* my = woff[wave];
     int exs[ITEMS];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
@@ -207,57 +192,15 @@ __global__ __launch_bounds__(kFusedThreads) void dispatch_index_kernel(const int
     }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i)
-        if ((unsigned)exs[i] < (unsigned)E) atomicAdd(&woff[wave][exs[i]], 1);   // LDS atomics: counts need no order
+        if ((unsigned)exs[i] < (unsigned)E) atomicAdd(&s.woff[wave][exs[i]], 1);   // LDS atomics: counts need no order
     __syncthreads();
-    if ((int)threadIdx.x < E) {
-        int t = 0;
-#pragma unroll
-        for (int w = 0; w < kFusedWaves; ++w) t += woff[w][threadIdx.x];
-        tot[threadIdx.x] = t;
-        expert_counts[threadIdx.x] = t;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < E) {
-        const int me = threadIdx.x, ge = pl[me];
-        int start = 0;
-#pragma unroll 8
-        for (int o = 0; o < E; ++o) {
-            const int go = pl[o];
-            start += ((go < ge) | ((go == ge) & (o < me))) ? tot[o] : 0;
-        }
-        expert_start[me] = start;
-        int run = start;
-#pragma unroll
-        for (int w = 0; w < kFusedWaves; ++w) {
-            const int c = woff[w][me];
-            woff[w][me] = run;
-            run += c;
-        }
-    }
-    for (int g = threadIdx.x; g < G; g += kFusedThreads) {
-        int cnt = 0, off = 0;
-#pragma unroll 8
-        for (int o = 0; o < E; ++o) {
-            const int go = pl[o], to = tot[o];
-            cnt += (go == g) ? to : 0;
-            off += ((go >= 0) & (go < g)) ? to : 0;
-        }
-        gpu_counts[g] = cnt;
-        gpu_offsets[g] = off;
-        if (g == G - 1) gpu_offsets[G] = off + cnt;
-    }
-    __syncthreads();
+    index_totals(s, E);
+    index_write_tables(s, E, G, expert_counts, expert_start, gpu_counts, gpu_offsets);
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int r = wbase + i * 64 + lane;
-        const int ex = exs[i];
-        const bool ok = (unsigned)ex < (unsigned)E;
-        const unsigned long long m = match_expert(ex, ok, ebits);
-        int pos = 0;
-        if (ok) pos = my[ex] + __popcll(m & lower);
-        __builtin_amdgcn_wave_barrier();
-        if (ok && (m & lower) == 0ull) my[ex] += __popcll(m);
-        __builtin_amdgcn_wave_barrier();
+        const bool ok = (unsigned)exs[i] < (unsigned)E;
+        const int pos = index_next(s.woff[wave], exs[i], ok, ebits, lower);
         if (ok) {
             perm[pos] = (int32_t)r;
             inv_perm[r] = pos;
@@ -323,12 +266,12 @@ int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T
     if (N <= kFusedMaxRoutes) {
         LaunchTimer timer(MOE_K_DISPATCH_RANK, s);
 #define MOE_LAUNCH_INDEX(ITEMS)                                                                                          \
-    hipLaunchKernelGGL(dispatch_index_kernel<ITEMS>, dim3(1), dim3(kFusedThreads), 0, s, topk_idx, N, E, ebits, placement, G, \
+    hipLaunchKernelGGL(dispatch_index_kernel<ITEMS>, dim3(1), dim3(kIndexThreads), 0, s, topk_idx, N, E, ebits, placement, G, \
                        expert_counts, expert_start, gpu_counts, gpu_offsets, perm, inv_perm)
-        if (N <= kFusedThreads) MOE_LAUNCH_INDEX(1);
-        else if (N <= 2 * kFusedThreads) MOE_LAUNCH_INDEX(2);
-        else if (N <= 4 * kFusedThreads) MOE_LAUNCH_INDEX(4);
-        else if (N <= 8 * kFusedThreads) MOE_LAUNCH_INDEX(8);
+        if (N <= kIndexThreads) MOE_LAUNCH_INDEX(1);
+        else if (N <= 2 * kIndexThreads) MOE_LAUNCH_INDEX(2);
+        else if (N <= 4 * kIndexThreads) MOE_LAUNCH_INDEX(4);
+        else if (N <= 8 * kIndexThreads) MOE_LAUNCH_INDEX(8);
         else MOE_LAUNCH_INDEX(kFusedMaxItems);
 #undef MOE_LAUNCH_INDEX
         if ((rc = check_launch("moe_dispatch index launch")) != MOE_OK) return rc;

@@ -97,6 +97,7 @@ template <int FM> struct Tile {
     static constexpr int A_CHUNKS = BM / 8, A_PER_WAVE = A_CHUNKS / NW;
     static constexpr size_t kPartialFloats = (size_t)BM * BN;
 };
+static_assert(Tile<3>::BM == kTallTileRows && Tile<2>::BM == kShortTileRows, "the plan counts row tiles of these heights");
 constexpr int kPanelCols = 16;
 constexpr size_t kMaxPartialFloats = (size_t)384 * BN;          // one fp32 partial tile of the largest tile
 
@@ -653,26 +654,21 @@ static int run_down(const FfnCall& c, int bm, int fm_max) {
 
 int launch_ffn_bf16(const void* a, int N, int d, int f, int E, const void* packed, const int32_t* counts,
                     const int32_t* starts, const int32_t* placement, int local_gpu, const int32_t* group_expert,
-                    int n_weights, void* out, int32_t* plan, void* H, hipStream_t s) {
+                    int n_weights, void* out, int32_t* plan, bool plan_ready, void* H, CombineTail* tail, hipStream_t s) {
+    const PlanShape shape = ffn_plan_shape(MOE_BF16, N, E, local_gpu < 0 && group_expert == nullptr);
     int rc;
     if (N <= kFfnSkinnyMaxRows) {
         // decode-sized batch: every weight is read once and hardly used; stream them without LDS or barriers
-        rc = launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, 256, 256, 0, plan, s);
+        rc = plan_ready ? MOE_OK : launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, shape, plan, s);
         if (rc != MOE_OK) return rc;
         const size_t s13 = npad13(f) * d, s2 = npad2(d) * f;
         float* partials = (float*)((char*)H + round_up((size_t)N * f * 2, 256));
-        return launch_ffn_skinny(a, N, d, f, E, packed, s13, s13 + s2, plan, H, partials, ffn_bf16_scratch_bytes(), out, s);
+        return launch_ffn_skinny(a, N, d, f, E, packed, s13, s13 + s2, plan, H, partials, ffn_bf16_scratch_bytes(), out, tail, s);
     }
-    // Row tiles of 384 move about a sixth fewer bytes per flop than tiles of 256, but waste more on
-    // ragged buckets and leave compute units idle when there are few tiles: 384 when the resident buckets
-    // hold kLargeBucketRows rows or more on average.  When every row is in a resident bucket the host
-    // knows that average; otherwise only the device does and the plan decides.  Either way the choice
-    // reaches the kernels through the plan's header.
     int cpx = 0;
     if ((rc = device_setup(&cpx)) != MOE_OK) return rc;
-    const bool every_row_resident = local_gpu < 0 && group_expert == nullptr;
-    const int choice = every_row_resident ? ((long long)N >= (long long)kLargeBucketRows * E ? 0 : 1) : -1;
-    rc = launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, Tile<3>::BM, Tile<2>::BM, choice, plan, s);
+    const int choice = shape.choice;
+    rc = plan_ready ? MOE_OK : launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, shape, plan, s);
     if (rc != MOE_OK) return rc;
     FfnCall c;
     c.a = a; c.N = N; c.d = d; c.f = f; c.E = E; c.packed = packed; c.out = out; c.plan = plan; c.H = H; c.s = s;

@@ -37,7 +37,7 @@ namespace moe {
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-constexpr int kF32Tile = 32;         // rows and columns of a tile
+constexpr int kF32Tile = kF32TileRows;   // rows and columns of a tile
 constexpr int kF32Stage = 32;        // k of one LDS stage
 constexpr int kF32Waves = 4;         // wavefronts of a workgroup, each 8 k of a stage
 constexpr int kF32Xcds = 8;
@@ -194,8 +194,9 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
 
 int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* packed, const int32_t* counts,
                    const int32_t* starts, const int32_t* placement, int local_gpu, const int32_t* group_expert,
-                   int n_weights, float* out, int32_t* plan, float* H, hipStream_t s) {
-    int rc = launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, kF32Tile, kF32Tile, 0, plan, s);
+                   int n_weights, float* out, int32_t* plan, bool plan_ready, float* H, hipStream_t s) {
+    int rc = plan_ready ? MOE_OK : launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N,
+                                                   ffn_plan_shape(MOE_F32, N, E, group_expert == nullptr && local_gpu < 0), plan, s);
     if (rc != MOE_OK) return rc;
     const long long mt_max = (N + kF32Tile - 1) / kF32Tile + (E < N ? E : N);     // sum of ceil(n_e / 32) never exceeds this
     auto grid_for = [&](int columns) { return (mt_max * ((columns + kF32Tile - 1) / kF32Tile) + kF32Xcds - 1) / kF32Xcds * kF32Xcds; };

@@ -6,10 +6,7 @@ __global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict
                                                        const int32_t* __restrict__ placement, int local_gpu,
                                                        const int32_t* __restrict__ group_expert, int n_weights, int E, int N,
                                                        int bm0, int bm1, int choice, int32_t* __restrict__ plan) {
-    __shared__ __attribute__((aligned(16))) int cnt[MOE_MAX_EXPERTS];
-    __shared__ __attribute__((aligned(16))) int rank[MOE_MAX_EXPERTS];
-    __shared__ __attribute__((aligned(16))) int tiles0[MOE_MAX_EXPERTS];
-    __shared__ __attribute__((aligned(16))) int tiles1[MOE_MAX_EXPERTS];
+    __shared__ PlanScratch scratch;
     const int e = threadIdx.x;
     int c = 0, st = 0, wt = e;                    // wt: whose weights this group multiplies with
     if (e < E) {
@@ -20,68 +17,26 @@ __global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict
         // a bucket that does not lie inside [0,N), or names weights that do not exist, is ignored rather than trusted
         if (!local || c <= 0 || st < 0 || (long long)st + c > N || (unsigned)wt >= (unsigned)n_weights) c = 0;
     }
-    cnt[e] = c;
-    tiles0[e] = (c + bm0 - 1) / bm0;
-    tiles1[e] = (c + bm1 - 1) / bm1;
-    __syncthreads();
-    // the loops below read the shared arrays four entries at a time; entries from E on hold zeros / -1
-    const int E4 = (E + 3) / 4;
-    int r = 0;
-    if (c > 0) {
-        const int4* cnt4 = reinterpret_cast<const int4*>(cnt);
-        for (int q = 0; q < E4; ++q) {
-            const int4 co = cnt4[q];
-            const int o = 4 * q;
-            r += ((co.x > c) | ((co.x == c) & (o < e))) + ((co.y > c) | ((co.y == c) & (o + 1 < e))) +
-                 ((co.z > c) | ((co.z == c) & (o + 2 < e))) + ((co.w > c) | ((co.w == c) & (o + 3 < e)));
-        }
-    }
-    rank[e] = (c > 0) ? r : -1;
-    __syncthreads();
-    if (c > 0) {
-        int t0 = 0, t1 = 0;
-        const int4* rank4 = reinterpret_cast<const int4*>(rank);
-        const int4* tl0 = reinterpret_cast<const int4*>(tiles0);
-        const int4* tl1 = reinterpret_cast<const int4*>(tiles1);
-        for (int q = 0; q < E4; ++q) {
-            const int4 ro = rank4[q], a = tl0[q], b = tl1[q];
-            const bool k0 = (ro.x >= 0) & (ro.x < r), k1 = (ro.y >= 0) & (ro.y < r), k2 = (ro.z >= 0) & (ro.z < r), k3 = (ro.w >= 0) & (ro.w < r);
-            t0 += (k0 ? a.x : 0) + (k1 ? a.y : 0) + (k2 ? a.z : 0) + (k3 ? a.w : 0);
-            t1 += (k0 ? b.x : 0) + (k1 ? b.y : 0) + (k2 ? b.z : 0) + (k3 ? b.w : 0);
-        }
-        plan[kPlanExpert + r] = wt;
-        plan[kPlanStart + r] = st;
-        plan[kPlanCount + r] = c;
-        plan[kPlanTiles0 + r] = t0;
-        plan[kPlanTiles1 + r] = t1;
-    }
-    if (e == 0) {
-        int n = 0, t0 = 0, t1 = 0;
-        long long rows = 0;
-        const int4* cnt4 = reinterpret_cast<const int4*>(cnt);
-        const int4* tl0 = reinterpret_cast<const int4*>(tiles0);
-        const int4* tl1 = reinterpret_cast<const int4*>(tiles1);
-        for (int q = 0; q < E4; ++q) {
-            const int4 co = cnt4[q], a = tl0[q], b = tl1[q];
-            n += (co.x > 0) + (co.y > 0) + (co.z > 0) + (co.w > 0);
-            rows += (long long)co.x + co.y + co.z + co.w;
-            t0 += a.x + a.y + a.z + a.w;
-            t1 += b.x + b.y + b.z + b.w;
-        }
-        plan[0] = n;
-        plan[1] = t0;
-        plan[2] = t1;
-        plan[3] = choice >= 0 ? choice : (rows >= (long long)kLargeBucketRows * n ? 0 : 1);
-        plan[kPlanTiles0 + n] = t0;
-        plan[kPlanTiles1 + n] = t1;
-    }
+    build_plan(scratch, e, c, st, wt, E, bm0, bm1, choice, plan);
+}
+
+PlanShape ffn_plan_shape(moe_dtype_t dt, int N, int E, bool every_row_resident) {
+    if (dt == MOE_F32) return {kF32TileRows, kF32TileRows, 0};
+    if (N <= kFfnSkinnyMaxRows) return {kShortTileRows, kShortTileRows, 0};
+    // Row tiles of 384 move about a sixth fewer bytes per flop than tiles of 256, but waste more on
+    // ragged buckets and leave compute units idle when there are few tiles: 384 when the resident buckets
+    // hold kLargeBucketRows rows or more on average.  When every row is in a resident bucket the host
+    // knows that average; otherwise only the device does and the plan decides.  Either way the choice
+    // reaches the kernels through the plan's header.
+    const int choice = every_row_resident ? ((long long)N >= (long long)kLargeBucketRows * E ? 0 : 1) : -1;
+    return {kTallTileRows, kShortTileRows, choice};
 }
 
 int launch_ffn_plan(const int32_t* counts, const int32_t* starts, const int32_t* placement, int local_gpu,
-                    const int32_t* group_expert, int n_weights, int E, int N, int bm0, int bm1, int choice, int32_t* plan,
-                    hipStream_t s) {
+                    const int32_t* group_expert, int n_weights, int E, int N, const PlanShape& shape, int32_t* plan, hipStream_t s) {
     LaunchTimer timer(MOE_K_FFN_PLAN, s);
-    hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(256), 0, s, counts, starts, placement, local_gpu, group_expert, n_weights, E, N, bm0, bm1, choice, plan);
+    hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(256), 0, s, counts, starts, placement, local_gpu, group_expert, n_weights, E, N,
+                       shape.bm0, shape.bm1, shape.choice, plan);
     return check_launch("moe_expert_ffn_grouped plan launch");
 }
 

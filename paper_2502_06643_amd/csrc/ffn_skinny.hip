@@ -23,6 +23,7 @@
 // separate workgroups and write fp32 partial sums; a small kernel adds the
 // parts in a fixed order (bitwise reproducible) and rounds to bf16.
 // Buckets of more than 64 rows are walked in passes of 64 rows.
+#include "bf16.h"
 #include "ffn_plan.h"
 
 namespace moe {
@@ -167,10 +168,38 @@ __global__ __launch_bounds__(256) void ffn_skinny_reduce_kernel(const float* __r
     }
 }
 
+// The same sums followed by moe_combine, for a layer that goes on to it: each route's row belongs to one token, so
+// the token's workgroup finishes the rows (and writes them to out, as the reduce does) and weights them into y.
+// One launch instead of two; a workgroup takes one token and 1024 columns.
+__global__ __launch_bounds__(256) void ffn_skinny_combine_kernel(const float* __restrict__ partial, int parts, int N, int d,
+                                                                 CombineTail tail, uint16_t* __restrict__ out) {
+    const int t = blockIdx.x, c = blockIdx.y * 1024 + threadIdx.x * 4;
+    if (c >= d) return;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j = 0; j < tail.k; ++j) {
+        const int r = t * tail.k + j, e = tail.topk_idx[r];
+        if ((unsigned)e >= (unsigned)tail.E || (tail.local_gpu >= 0 && tail.placement[e] != tail.local_gpu)) continue;
+        const int row = tail.inv_perm[r];
+        if ((unsigned)row >= (unsigned)N) continue;
+        const float w = tail.topk_w[r];
+        float4 s = *reinterpret_cast<const float4*>(partial + (size_t)row * d + c);
+#pragma unroll 4
+        for (int p = 1; p < parts; ++p) {
+            const float4 q = *reinterpret_cast<const float4*>(partial + ((size_t)p * N + row) * d + c);
+            s.x += q.x; s.y += q.y; s.z += q.z; s.w += q.w;
+        }
+        const uint2 o = make_uint2(__builtin_bit_cast(uint16_t, (__bf16)s.x) | (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)s.y) << 16,
+                                   __builtin_bit_cast(uint16_t, (__bf16)s.z) | (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)s.w) << 16);
+        *reinterpret_cast<uint2*>(out + (size_t)row * d + c) = o;
+        acc.x = fmaf(w, bf16_lo(o.x), acc.x); acc.y = fmaf(w, bf16_hi(o.x), acc.y);
+        acc.z = fmaf(w, bf16_lo(o.y), acc.z); acc.w = fmaf(w, bf16_hi(o.y), acc.w);
+    }
+    *reinterpret_cast<uint2*>((uint16_t*)tail.y + (size_t)t * d + c) = make_uint2(pack_bf16(acc.x, acc.y), pack_bf16(acc.z, acc.w));
+}
 
 // E row groups; plan has been built.  H [N, f] bf16 and the fp32 partial area (scratch_bytes) come from the workspace.
 int launch_ffn_skinny(const void* a, int N, int d, int f, int E, const void* packed, size_t s13, size_t expert_stride,
-                      const int32_t* plan, void* H, float* partial, size_t scratch_bytes, void* out, hipStream_t s) {
+                      const int32_t* plan, void* H, float* partial, size_t scratch_bytes, void* out, CombineTail* tail, hipStream_t s) {
     const int nt_up = (int)(round_up((size_t)2 * f, 256) / 256), nt_down = (int)(round_up((size_t)d, 256) / 256);
     const uint16_t* Wp = (const uint16_t*)packed;
     int rc;
@@ -191,6 +220,12 @@ int launch_ffn_skinny(const void* a, int N, int d, int f, int E, const void* pac
         hipLaunchKernelGGL(ffn_skinny_kernel<false>, dim3((unsigned)(E * nt_down * parts)), dim3(kSkinnyThreads), 0, s,
                            (const uint16_t*)H, Wp + s13, expert_stride, f, nt_down, d, plan, (uint16_t*)nullptr, partial, parts, N);
         if ((rc = check_launch("moe_expert_ffn_grouped down launch (small batch)")) != MOE_OK) return rc;
+        if (tail != nullptr) {
+            hipLaunchKernelGGL(ffn_skinny_combine_kernel, dim3((unsigned)tail->T, (unsigned)((d + 1023) / 1024)), dim3(256), 0, s, partial,
+                               parts, N, d, *tail, (uint16_t*)out);
+            tail->done = true;
+            return check_launch("moe_layer_forward reduce and combine launch (small batch)");
+        }
         hipLaunchKernelGGL(ffn_skinny_reduce_kernel, dim3((unsigned)N), dim3(256), 0, s, partial, parts, N, d, plan, (uint16_t*)out);
         if ((rc = check_launch("moe_expert_ffn_grouped reduce launch (small batch)")) != MOE_OK) return rc;
     }

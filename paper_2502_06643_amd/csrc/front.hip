@@ -1,0 +1,140 @@
+// The front of a layer in one launch: gate (moe_topk_gate), dispatch (moe_dispatch) and the tile plan of the expert
+// FFN, for batches small enough that a workgroup can route all of them by itself (paper Section 2.1, Section 2.2,
+// Section 3.1).
+//
+// At these sizes each of the four launches it replaces takes 4.5-10 us, nearly all of it launch latency.  Here every
+// workgroup works out the whole batch's routing redundantly - gate into LDS, the counting sort of the routes - and
+// then writes only its own share: the gate outputs, positions and send rows of its tokens.  Workgroup 0 also writes
+// the expert and GPU tables, the last workgroup the tile plan.  Nothing passes between workgroups.  The first pieces
+// of the workgroup's rows are loaded before anything else, so that they arrive while it routes.
+#include "dispatch_index.h"
+#include "ffn_plan.h"
+#include "gate_select.h"
+#include "front.h"
+
+namespace moe {
+
+constexpr int kFrontPrefetch = 4;        // 16-byte pieces of x per thread that are loaded up front
+
+template <int L, int VPL, int KMAX>
+__global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
+    __shared__ IndexTables s;
+    __shared__ PlanScratch plan_scratch;
+    __shared__ uint16_t ids[kFrontMaxRoutes];              // expert of every route
+    __shared__ int my_pos[kFrontMaxTokens * MOE_MAX_TOPK]; // positions of this workgroup's routes
+    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
+    const int T = a.T, E = a.E, k = a.k, N = T * k;
+    const int t0 = (int)((long long)blockIdx.x * T / gridDim.x), t1 = (int)((long long)(blockIdx.x + 1) * T / gridDim.x);
+    const int units = (t1 - t0) * a.units_per_row;
+    const uint4* rows = a.x + (long long)t0 * a.units_per_row;
+    uint4 pre[kFrontPrefetch];
+#pragma unroll
+    for (int i = 0; i < kFrontPrefetch; ++i) {
+        const int u = tid + i * kIndexThreads;
+        pre[i] = u < units ? rows[u] : make_uint4(0u, 0u, 0u, 0u);
+    }
+    index_clear(s, E);
+    if (tid < E) s.pl[tid] = a.placement[tid];
+
+    // gate: L lanes per token, the whole batch
+    const int sub = tid % L;
+    for (int base = 0; base < T; base += kIndexThreads / L) {
+        const int t = base + tid / L;
+        const bool live = t < T;
+        gate_select_emit<L, VPL, KMAX, false>(a.logits + (long long)(live ? t : 0) * E, false, sub, live, E, k,
+                                              [&](const int (&e_sel)[KMAX], const float (&p_sel)[KMAX], float denom) {
+#pragma unroll
+                                                  for (int j = 0; j < KMAX; ++j)
+                                                      if (j < k) ids[t * k + j] = (uint16_t)e_sel[j];
+                                                  if (t >= t0 && t < t1) gate_store<KMAX>(t, k, e_sel, p_sel, denom, a.topk_idx, a.topk_w);
+                                              });
+    }
+    __syncthreads();
+
+    // the counting sort: every wavefront counts its slice of the routes ...
+    const int per_wave = ((N + kIndexThreads - 1) / kIndexThreads) * 64, wbase = wave * per_wave, wend = min(N, wbase + per_wave);
+    const unsigned long long lower = (1ull << lane) - 1ull;
+    for (int r0 = wbase; r0 < wend; r0 += 64) {
+        const int r = r0 + lane, ex = r < wend ? ids[r] : MOE_MAX_EXPERTS;
+        const bool ok = ex < E;
+        const unsigned long long m = match_expert(ex, ok, a.ebits);
+        if (ok && (m & lower) == 0ull) atomicAdd(&s.woff[wave][ex], __popcll(m));       // first lane of the group
+    }
+    __syncthreads();
+    index_totals(s, E);
+    if (blockIdx.x == 0) index_write_tables(s, E, a.G, a.expert_counts, a.expert_start, a.gpu_counts, a.gpu_offsets);
+    // ... and walks it as far as this workgroup's own routes reach
+    const int own0 = t0 * k, own1 = t1 * k;
+    if (wbase < own1 && own0 < wend) {
+        for (int r0 = wbase; r0 < min(wend, own1); r0 += 64) {
+            const int r = r0 + lane, ex = r < wend ? ids[r] : MOE_MAX_EXPERTS;
+            const bool ok = ex < E;
+            const int pos = index_next(s.woff[wave], ex, ok, a.ebits, lower);
+            if (r >= own0 && r < own1) {
+                my_pos[r - own0] = ok ? pos : -1;
+                if (ok) {
+                    a.perm[pos] = r;
+                    a.inv_perm[r] = pos;
+                }
+            }
+        }
+    }
+    __syncthreads();
+
+    // rows: every 16-byte piece was or is read once and is written to its token's k positions
+    auto put = [&](int u, const uint4& v) {
+        const int t = u / a.units_per_row, c = u - t * a.units_per_row;
+        for (int j = 0; j < k; ++j) {
+            const int p = my_pos[t * k + j];
+            if ((unsigned)p < (unsigned)N) a.send_buf[(long long)p * a.units_per_row + c] = v;
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < kFrontPrefetch; ++i) {
+        const int u = tid + i * kIndexThreads;
+        if (u < units) put(u, pre[i]);
+    }
+    for (int u = tid + kFrontPrefetch * kIndexThreads; u < units; u += kIndexThreads) put(u, rows[u]);
+
+    if (blockIdx.x == gridDim.x - 1) {
+        int c = 0, st = 0;
+        if (tid < E && (a.local_gpu < 0 || s.pl[tid] == a.local_gpu)) {
+            c = s.tot[tid];
+            st = s.start[tid];
+        }
+        build_plan(plan_scratch, tid, c, st, tid, E, a.shape.bm0, a.shape.bm1, a.shape.choice, a.plan);
+    }
+}
+
+// lanes per token of the gate for E experts
+static int front_lanes(int E) { return E <= 8 ? 1 : (E <= 64 ? 4 : 16); }
+
+bool front_fits(int T, int E, int k) {
+    // every workgroup gates and sorts the whole batch: at most kFrontMaxRoutes routes and eight passes of the gate
+    const long long N = (long long)T * k;
+    static_assert(8 * kIndexThreads <= kFrontGroups * kFrontMaxTokens, "a workgroup's tokens fit its tables");
+    return T > 0 && N <= kFrontMaxRoutes && (long long)T * front_lanes(E) <= 8 * kIndexThreads;
+}
+
+int launch_front(const FrontArgs& args, hipStream_t s) {
+    FrontArgs a = args;
+    a.ebits = 0;
+    while ((1 << a.ebits) < a.E) ++a.ebits;
+    const int grid = a.T < kFrontGroups ? a.T : kFrontGroups;
+    LaunchTimer timer(MOE_K_FRONT, s);
+#define MOE_LAUNCH_FRONT(L, VPL)                                                                                        \
+    do {                                                                                                                \
+        if (a.k <= 2) hipLaunchKernelGGL((front_kernel<L, VPL, 2>), dim3(grid), dim3(kIndexThreads), 0, s, a);            \
+        else if (a.k <= 8) hipLaunchKernelGGL((front_kernel<L, VPL, 8>), dim3(grid), dim3(kIndexThreads), 0, s, a);       \
+        else hipLaunchKernelGGL((front_kernel<L, VPL, MOE_MAX_TOPK>), dim3(grid), dim3(kIndexThreads), 0, s, a);          \
+    } while (0)
+    switch (front_lanes(a.E)) {
+        case 1: MOE_LAUNCH_FRONT(1, 8); break;
+        case 4: MOE_LAUNCH_FRONT(4, 16); break;
+        default: MOE_LAUNCH_FRONT(16, 16); break;
+    }
+#undef MOE_LAUNCH_FRONT
+    return check_launch("moe_layer_forward front launch");
+}
+
+}  // namespace moe

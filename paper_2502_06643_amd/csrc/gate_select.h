@@ -20,10 +20,9 @@ __device__ __forceinline__ float from_orderable(uint32_t o) {
 // row: the token's E logits (global memory or LDS; 16-byte aligned when E % 4 == 0 or `padded`); sub = this lane's
 // index among the token's L lanes; live = the token exists.  `padded`: the row holds L * VPL readable floats and the
 // ones from E on are ignored (the fused router's LDS rows).  Every lane of the L-lane group must call this (shuffles);
-// lane sub == 0 of a live token writes topk_idx[t][0..k) and topk_w[t][0..k).
-template <int L, int VPL, int KMAX, bool ALL>
-__device__ __forceinline__ void gate_select(const float* row, bool padded, int sub, bool live, long long t, int E, int k,
-                                            int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+// lane sub == 0 of a live token hands its k experts (e_sel), their exponentials (p_sel) and the denominator to `emit`.
+template <int L, int VPL, int KMAX, bool ALL, class Emit>
+__device__ __forceinline__ void gate_select_emit(const float* row, bool padded, int sub, bool live, int E, int k, Emit emit) {
     const int e0 = sub * VPL;
     uint32_t key[VPL];
 #pragma unroll
@@ -90,19 +89,33 @@ __device__ __forceinline__ void gate_select(const float* row, bool padded, int s
             e_sel[j] = be;
         }
     }
-    if (live && sub == 0) {
-        if (KMAX == 2 && k == 2) {                  // the common top-2 case: one 8-byte store each
-            *reinterpret_cast<int2*>(topk_idx + t * 2) = make_int2(e_sel[0], e_sel[1]);
-            *reinterpret_cast<float2*>(topk_w + t * 2) = make_float2(p_sel[0] / denom, p_sel[1] / denom);
-        } else {
+    if (live && sub == 0) emit(e_sel, p_sel, denom);
+}
+
+// writes topk_idx[t][0..k) and topk_w[t][0..k)
+template <int KMAX>
+__device__ __forceinline__ void gate_store(long long t, int k, const int (&e_sel)[KMAX], const float (&p_sel)[KMAX], float denom,
+                                           int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+    if (KMAX == 2 && k == 2) {                      // the common top-2 case: one 8-byte store each
+        *reinterpret_cast<int2*>(topk_idx + t * 2) = make_int2(e_sel[0], e_sel[1]);
+        *reinterpret_cast<float2*>(topk_w + t * 2) = make_float2(p_sel[0] / denom, p_sel[1] / denom);
+    } else {
 #pragma unroll
-            for (int j = 0; j < KMAX; ++j)
-                if (j < k) {
-                    topk_idx[t * k + j] = e_sel[j];
-                    topk_w[t * k + j] = p_sel[j] / denom;
-                }
-        }
+        for (int j = 0; j < KMAX; ++j)
+            if (j < k) {
+                topk_idx[t * k + j] = e_sel[j];
+                topk_w[t * k + j] = p_sel[j] / denom;
+            }
     }
+}
+
+template <int L, int VPL, int KMAX, bool ALL>
+__device__ __forceinline__ void gate_select(const float* row, bool padded, int sub, bool live, long long t, int E, int k,
+                                            int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+    gate_select_emit<L, VPL, KMAX, ALL>(row, padded, sub, live, E, k,
+                                        [&](const int (&e_sel)[KMAX], const float (&p_sel)[KMAX], float denom) {
+                                            gate_store<KMAX>(t, k, e_sel, p_sel, denom, topk_idx, topk_w);
+                                        });
 }
 
 }  // namespace moe

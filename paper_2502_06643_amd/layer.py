@@ -89,9 +89,8 @@ class MoELayer:
                       self.local_gpu, self.T, self.d, self.E, self.k, self.y)
 
     def forward(self, x, logits):
-        """One pass of the hot path: gate -> dispatch -> expert FFN -> combine."""
-        self.gate(logits)
-        self.dispatch(x)
-        self.ffn()
-        self.combine()
+        """One pass of the hot path: gate -> dispatch -> expert FFN -> combine, in one library call."""
+        B.moe_layer_forward(x, self.dt, logits, self.T, self.d, self.f, self.E, self.k, self.placement, self.G, self.local_gpu,
+                            self.packed, self.topk_idx, self.topk_w, self.send_buf, self.perm, self.inv_perm, self.expert_counts,
+                            self.expert_start, self.gpu_counts, self.gpu_offsets, self.ffn_out, self.y, self.dispatch_ws, self.ffn_ws)
         return self.y

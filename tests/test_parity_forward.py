@@ -1,0 +1,70 @@
+"""moe_layer_forward against the four calls it stands for, bit for bit: every size where its merged kernels can go
+wrong (one token, a token per workgroup and more, slices of the in-workgroup sort, the last sizes of the fused front
+and of the decode-sized combine and the first ones past them), each lane layout of the gate, ragged expert counts."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_06643_amd import binding as B
+from paper_2502_06643_amd import synth
+from paper_2502_06643_amd.layer import MoELayer, to_device
+
+pytestmark = pytest.mark.gpu
+
+OUTPUTS = ("topk_idx", "topk_w", "send_buf", "perm", "inv_perm", "expert_counts", "expert_start", "gpu_counts", "gpu_offsets", "ffn_out", "y")
+
+
+@pytest.mark.parametrize("dtype,T,d,f,E,k,G,local", [
+    ("bf16", 1, 64, 64, 8, 2, 1, -1),
+    ("bf16", 80, 1088, 128, 8, 2, 4, 2),          # 160 routes: the last decode-sized batch, columns past a workgroup's 1024
+    ("bf16", 81, 64, 128, 8, 2, 4, 2),            # the first one past it
+    ("bf16", 10, 128, 64, 256, 16, 8, 3),         # 16 lanes per token, 16 routes per token
+    ("bf16", 255, 64, 64, 5, 3, 2, 1),            # logit rows that are no multiple of 16 bytes
+    ("bf16", 257, 64, 64, 64, 6, 8, 7),           # one workgroup owns two tokens
+    ("bf16", 2048, 64, 64, 64, 6, 8, 0),          # the last batch of the fused front: 12288 routes, eight gate passes
+    ("bf16", 2049, 64, 64, 64, 6, 8, 0),          # the first one past it
+    ("bf16", 6144, 4096, 64, 8, 2, 1, -1),        # 12288 routes again, more rows per workgroup than are prefetched
+    ("bf16", 512, 64, 64, 200, 1, 3, -1),         # eight gate passes of 16 lanes per token
+    ("bf16", 8192, 64, 64, 3, 1, 1, -1),          # 32 tokens per workgroup
+    ("f32", 1, 4, 4, 1, 1, 1, -1),
+    ("f32", 256, 128, 256, 8, 2, 4, 0),
+    ("f32", 1025, 36, 100, 9, 2, 2, 1),
+])
+def test_forward_equals_the_four_calls(lib, dtype, T, d, f, E, k, G, local):
+    rng = np.random.default_rng(T + E)
+    pl = rng.integers(0, G, E).astype(np.int32)
+    x = to_device(synth.normal(T, 0, (T, d), 1.0, dtype))
+    lg = rng.standard_normal((T, E)).astype(np.float32)
+    lg[T // 2] = np.round(lg[T // 2])              # ties
+    lg = torch.from_numpy(lg - np.log(np.arange(1, E + 1)).astype(np.float32)[None, :]).cuda()
+    w = [to_device(synth.normal(T, i, s, s[1] ** -0.5, dtype)) for i, s in ((2, (E, d, f)), (3, (E, d, f)), (4, (E, f, d)))]
+    got, want = (MoELayer(T, d, f, E, k, G, local, dtype) for _ in range(2))
+    for L in (got, want):
+        L.set_placement(pl)
+        L.set_weights(*w)
+        for n in OUTPUTS:
+            getattr(L, n).fill_(3)                 # what a call leaves untouched must be the same too
+    want.gate(lg)
+    want.dispatch(x)
+    want.ffn()
+    want.combine()
+    for rep in range(2):                           # the second call finds the first one's workspaces
+        got.forward(x, lg)
+        torch.cuda.synchronize()
+        for n in OUTPUTS:
+            a, b = (getattr(L, n).reshape(-1).view(torch.uint8) for L in (got, want))
+            assert torch.equal(a, b), f"call {rep}: {n}"
+
+
+def test_forward_reports_bad_arguments(lib):
+    L = MoELayer(4, 64, 64, 8, 2, 1, -1, "bf16")
+    L.set_placement(np.zeros(8, dtype=np.int32))
+    L.set_weights(*[torch.zeros(s, dtype=torch.bfloat16, device="cuda") for s in ((8, 64, 64),) * 3])
+    x, lg = torch.zeros((4, 64), dtype=torch.bfloat16, device="cuda"), torch.zeros((4, 8), device="cuda")
+    with pytest.raises(ValueError):
+        L.forward(x.t(), lg)
+    with pytest.raises(B.MoeError):
+        L.forward(None, lg)
+    L.ffn_ws = L.ffn_ws[:256]
+    with pytest.raises(B.MoeError):
+        L.forward(x, lg)

@@ -7,31 +7,31 @@
 // same hot bin mostly land on different addresses), counts its tokens'
 // k_l * k_l1 expert pairs (or only its top-1 pair) there with LDS atomics, and then adds its non-zero
 // bins to the int64 table in memory.  Integer adds commute, so the result is
-// exact whatever the order.  Tables too large for LDS are counted straight
-// into memory.
+// exact whatever the order.  A table too large for LDS is cut into stripes of
+// rows: a workgroup counts one stripe only.
 #include "common.h"
 
 namespace moe {
 
-constexpr int kLdsBins = 12288;          // 48 KB of int32 per workgroup
+constexpr int kTransThreads = 1024;
+constexpr int kLdsBins = 12288;          // 48 KB of int32: two workgroups fit a compute unit
+constexpr int kLdsBinsLarge = 32768;     // 128 KB: one does, with a 128 x 256 table
 constexpr int kTokPerThread = 4;
 
-template <bool USE_LDS, int kTransThreads>
+// rows: table rows of one stripe (blockIdx.y counts the stripes)
+template <int LDS_BINS>
 __global__ __launch_bounds__(kTransThreads) void transition_kernel(const int32_t* __restrict__ idx_l, const int32_t* __restrict__ idx_l1,
-                                                         int T, int k_l, int k_l1, int use_l, int use_l1, int E_l, int E_l1,
+                                                         int T, int k_l, int k_l1, int use_l, int use_l1, int E_l, int E_l1, int rows,
                                                          int copies, int pairs_of_two, unsigned long long* __restrict__ R) {
-    extern __shared__ int hist[];
-    const int bins = E_l * E_l1;
+    __shared__ __attribute__((aligned(16))) int hist[LDS_BINS];
+    const int row0 = blockIdx.y * rows, rows_here = min(rows, E_l - row0), bins = rows_here * E_l1;
     const int my_copy = threadIdx.x & (copies - 1);
-    if (USE_LDS) {
-        for (int b = threadIdx.x; b < bins * copies; b += kTransThreads) hist[b] = 0;
-        __syncthreads();
-    }
+    for (int b = threadIdx.x * 4; b < bins * copies; b += kTransThreads * 4) *reinterpret_cast<int4*>(hist + b) = make_int4(0, 0, 0, 0);
+    __syncthreads();
     const long long stride = (long long)gridDim.x * kTransThreads;
     auto count = [&](int e1, int e2) {
-        if ((unsigned)e1 >= (unsigned)E_l || (unsigned)e2 >= (unsigned)E_l1) return;
-        if (USE_LDS) atomicAdd(&hist[(e1 * E_l1 + e2) * copies + my_copy], 1);
-        else atomicAdd(&R[e1 * E_l1 + e2], 1ull);
+        if ((unsigned)(e1 - row0) >= (unsigned)rows_here || (unsigned)e2 >= (unsigned)E_l1) return;
+        atomicAdd(&hist[((e1 - row0) * E_l1 + e2) * copies + my_copy], 1);
     };
     long long t = (long long)blockIdx.x * kTransThreads + threadIdx.x;
     if (pairs_of_two) {
@@ -90,13 +90,11 @@ __global__ __launch_bounds__(kTransThreads) void transition_kernel(const int32_t
                 count(e1, idx_l1[t * k_l1 + j2]);         // re-read per pair: it stays in L1, and no private array is needed
         }
     }
-    if (USE_LDS) {
-        __syncthreads();
-        for (int b = threadIdx.x; b < bins; b += kTransThreads) {
-            int c = 0;
-            for (int i = 0; i < copies; ++i) c += hist[b * copies + ((i + threadIdx.x) & (copies - 1))];
-            if (c) atomicAdd(&R[b], (unsigned long long)c);
-        }
+    __syncthreads();
+    for (int b = threadIdx.x; b < bins; b += kTransThreads) {
+        int c = 0;
+        for (int i = 0; i < copies; ++i) c += hist[b * copies + ((i + threadIdx.x) & (copies - 1))];
+        if (c) atomicAdd(&R[(size_t)row0 * E_l1 + b], (unsigned long long)c);
     }
 }
 
@@ -104,33 +102,29 @@ int launch_transition(const int32_t* idx_l, const int32_t* idx_l1, int T, int k_
                       bool top1_only, int64_t* R, hipStream_t s) {
     const int use_l = top1_only ? 1 : k_l, use_l1 = top1_only ? 1 : k_l1;
     const int pairs_of_two = k_l == 2 && k_l1 == 2 && ((uintptr_t)idx_l & 7) == 0 && ((uintptr_t)idx_l1 & 7) == 0;
-    const int bins = E_l * E_l1;
+    const bool large = E_l * E_l1 > kLdsBins;
+    const int rows = large && E_l * E_l1 > kLdsBinsLarge ? kLdsBinsLarge / E_l1 : E_l;
+    const int stripes = (E_l + rows - 1) / rows, bins = rows * E_l1;
     // tokens per thread: four for top-2 x top-2, one when a token has 16 pairs or more
     const int pairs = use_l * use_l1;
     const int tpt = pairs >= 16 ? 1 : (pairs >= 8 ? 2 : kTokPerThread);
-    // Every workgroup ends with one global atomic per non-zero bin, all workgroups on the same few lines: at most 512
-    // workgroups of 256 threads; batches that would need more run 256 workgroups of 1024 threads instead (as many
-    // threads, half the atomics: 24.7 -> 18.5 us at 4 M tokens, top-2 x top-2), which a small batch cannot afford
-    // (one large workgroup starts more slowly than four small ones)
-    const long long want256 = ((long long)T + 256 * tpt - 1) / (256 * tpt);
-    const bool large = want256 > 512;
-    const long long want = large ? ((long long)T + 1024 * tpt - 1) / (1024 * tpt) : want256;
-    const long long cap = large ? 256 : 512;
-    const unsigned grid = (unsigned)(want < 1 ? 1 : (want > cap ? cap : want));
+    // Every workgroup ends with one global atomic per non-zero bin, all workgroups on the same lines, so their number is
+    // kept at 128 of 1024 threads.  Measured with 512 / 256 / 128 / 64 workgroups: 4 M tokens, 8 experts, top-2 19.4 / 16.1
+    // / 15.2 / 21.1 us; 100003 tokens, 64 experts, top-6 8.8 / 8.7 / 8.7 / 11.1 (15.6 with 391 workgroups of 256 threads);
+    // 65536 tokens, 128 experts, top-8 15.2 / 15.2 / 15.4 / 15.4.  Batches of a few thousand tokens do not care.  Tables of
+    // more than 110 x 110 used to be counted straight into memory: 32768 tokens, 128 experts, top-8 1177 us, now 14.4.
+    constexpr long long cap = 128;
+    const long long want = ((long long)T + (long long)kTransThreads * tpt - 1) / ((long long)kTransThreads * tpt);
+    const dim3 grid((unsigned)(want < 1 ? 1 : (want > cap ? cap : want)), (unsigned)stripes);
     int copies = 1;
     while (copies < 32 && bins * copies * 2 <= kLdsBins) copies *= 2;
     LaunchTimer timer(MOE_K_TRANSITION, s);
-#define MOE_LAUNCH_TRANSITION(LDS, THREADS, SMEM, COPIES)                                                                          \
-    hipLaunchKernelGGL((transition_kernel<LDS, THREADS>), dim3(grid), dim3(THREADS), SMEM, s, idx_l, idx_l1, T, k_l, k_l1, use_l, use_l1, \
-                       E_l, E_l1, COPIES, pairs_of_two, (unsigned long long*)R)
-    if (bins <= kLdsBins) {
-        if (large) MOE_LAUNCH_TRANSITION(true, 1024, bins * copies * sizeof(int), copies);
-        else MOE_LAUNCH_TRANSITION(true, 256, bins * copies * sizeof(int), copies);
-    } else {
-        if (large) MOE_LAUNCH_TRANSITION(false, 1024, 0, 1);
-        else MOE_LAUNCH_TRANSITION(false, 256, 0, 1);
-    }
-#undef MOE_LAUNCH_TRANSITION
+    if (large)
+        hipLaunchKernelGGL(transition_kernel<kLdsBinsLarge>, grid, dim3(kTransThreads), 0, s, idx_l, idx_l1, T, k_l, k_l1, use_l, use_l1,
+                           E_l, E_l1, rows, copies, pairs_of_two, (unsigned long long*)R);
+    else
+        hipLaunchKernelGGL(transition_kernel<kLdsBins>, grid, dim3(kTransThreads), 0, s, idx_l, idx_l1, T, k_l, k_l1, use_l, use_l1,
+                           E_l, E_l1, rows, copies, pairs_of_two, (unsigned long long*)R);
     return check_launch("moe_transition_counts launch");
 }
 

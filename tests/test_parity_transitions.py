@@ -24,6 +24,13 @@ def test_matches_oracle(lib, T, E1, E2, k1, k2):
     np.testing.assert_array_equal(run(lib, a, b, E1, E2), O.transition_counts(a, b, E1, E2))
 
 
+@pytest.mark.parametrize("E1,E2", [(96, 128), (97, 127), (128, 256), (129, 255), (256, 129)])
+def test_table_sizes_around_the_stripes(lib, E1, E2):
+    """The largest table of the small kernel, the smallest and the largest of one stripe, the first with two."""
+    a, b = synth.random_topk_idx(31, 1500, E1, 5), synth.random_topk_idx(32, 1500, E2, 8)
+    np.testing.assert_array_equal(run(lib, a, b, E1, E2), O.transition_counts(a, b, E1, E2))
+
+
 def test_accumulates_over_batches_and_large_start_values(lib):
     a = synth.random_topk_idx(1, 3000, 8, 2)
     b = synth.random_topk_idx(2, 3000, 8, 2)
@@ -72,8 +79,7 @@ def test_top1_pairs_match_oracle(lib, T, E1, E2, k1, k2):
 
 
 def test_many_pairs_per_token_at_a_size_that_takes_the_large_workgroups(lib):
-    """top-6 x top-6 over 64 experts, 150000 tokens: more than 512 workgroups of 256 threads would be needed, so the
-    launch switches to 1024-thread workgroups.  Marginal identities, the total, and sampled bins counted one by one."""
+    """top-6 x top-6 over 64 experts, 150000 tokens: more than one token per thread of the largest grid.  Marginal identities, the total, and sampled bins counted one by one."""
     T, E, k = 150000, 64, 6
     a = synth.random_topk_idx(23, T, E, k)
     b = synth.random_topk_idx(24, T, E, k)

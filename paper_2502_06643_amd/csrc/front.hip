@@ -41,12 +41,13 @@ __global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
     for (int base = 0; base < T; base += kIndexThreads / L) {
         const int t = base + tid / L;
         const bool live = t < T;
+        constexpr int S = kGateSlots<L, KMAX>;
         gate_select_emit<L, VPL, KMAX, false>(a.logits + (long long)(live ? t : 0) * E, false, sub, live, E, k,
-                                              [&](const int (&e_sel)[KMAX], const float (&p_sel)[KMAX], float denom) {
+                                              [&](const int (&e_sel)[S], const float (&p_sel)[S], float denom) {
 #pragma unroll
-                                                  for (int j = 0; j < KMAX; ++j)
-                                                      if (j < k) ids[t * k + j] = (uint16_t)e_sel[j];
-                                                  if (t >= t0 && t < t1) gate_store<KMAX>(t, k, e_sel, p_sel, denom, a.topk_idx, a.topk_w);
+                                                  for (int i = 0; i < S; ++i)
+                                                      if (sub + L * i < k) ids[t * k + sub + L * i] = (uint16_t)e_sel[i];
+                                                  if (t >= t0 && t < t1) gate_store<L, S>(t, sub, k, e_sel, p_sel, denom, a.topk_idx, a.topk_w);
                                               });
     }
     __syncthreads();

@@ -1,8 +1,8 @@
 // moe_topk_gate: top-k router (paper Section 2.1).
 //
-// A token's E logits are spread over L neighbouring lanes of a wavefront, VPL
-// consecutive logits per lane (16-byte loads when E % 4 == 0), so a wavefront
-// reads 64/L whole rows.  Each logit is mapped to an order-preserving unsigned
+// A token's E logits are spread over L neighbouring lanes of a wavefront in
+// pieces of four, VPL logits per lane (16-byte loads when E % 4 == 0), so a
+// wavefront reads 64/L whole rows, neighbouring lanes neighbouring pieces.  Each logit is mapped to an order-preserving unsigned
 // key (-0.0 is folded onto +0.0 first, so the two tie); key 0 is below every
 // finite logit and marks "no candidate".  One round = scan my VPL keys with a
 // strict '>' (ascending index, so the lowest index wins a tie), then an

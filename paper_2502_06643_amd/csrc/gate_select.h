@@ -1,6 +1,7 @@
 // The top-k selection of moe_topk_gate (paper Section 2.1) for one token whose E logits are spread over L
-// neighbouring lanes of a wavefront, VPL consecutive logits per lane: shared by the gate kernel (logits
-// from memory) and by the fused router (logits from LDS, where the projection left them).
+// neighbouring lanes of a wavefront, VPL logits per lane: shared by the gate kernel (logits from memory) and by the
+// fused router (logits from LDS, where the projection left them).  The lanes take turns in pieces of four logits
+// (lane sub holds pieces sub, sub + L, ...), so that the lanes of one load read neighbouring 16-byte pieces.
 #pragma once
 #include "common.h"
 
@@ -17,94 +18,208 @@ __device__ __forceinline__ float from_orderable(uint32_t o) {
     return __uint_as_float(u);
 }
 
+// ---- two or more lanes per token: sorted lists ------------------------------------------------------------------
+// A candidate is one double whose bit pattern orders as (key, lower expert first): a biased exponent of 1, then the 32
+// bits of the key and 255 - expert.  No two are equal, so the selection is nothing but v_max_f64 / v_min_f64 (full
+// rate on this chip) without an index beside the value; an empty slot is 0.0, below every candidate.
+__device__ __forceinline__ double candidate(float v, int e) {
+    const uint32_t key = orderable(v);
+    return __builtin_bit_cast(double, ((uint64_t)(0x00100000u | (key >> 24)) << 32) | ((key << 8) | (uint32_t)(255 - e)));
+}
+__device__ __forceinline__ int candidate_expert(double c) { return 255 - (int)(__builtin_bit_cast(uint64_t, c) & 255u); }
+__device__ __forceinline__ float candidate_logit(double c) { return from_orderable((uint32_t)(__builtin_bit_cast(uint64_t, c) >> 8)); }
+
+__device__ __forceinline__ void order_pair(double& hi, double& lo) {
+    const double a = hi, b = lo;
+    hi = __builtin_fmax(a, b);
+    lo = __builtin_fmin(a, b);
+}
+
+// bitonic a[0..K) -> descending
+template <int K>
+__device__ __forceinline__ void merge_bitonic(double (&a)[K]) {
+#pragma unroll
+    for (int st = K / 2; st > 0; st >>= 1)
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if ((i & st) == 0) order_pair(a[i], a[i | st]);
+}
+
+template <int K>
+__device__ __forceinline__ void sort_descending(double (&a)[K]) {
+#pragma unroll
+    for (int sz = 2; sz <= K; sz <<= 1)
+#pragma unroll
+        for (int st = sz >> 1; st > 0; st >>= 1)
+#pragma unroll
+            for (int i = 0; i < K; ++i)
+                if ((i & st) == 0) {
+                    if ((i & sz) == 0 || sz == K) order_pair(a[i], a[i | st]);
+                    else order_pair(a[i | st], a[i]);
+                }
+}
+
+// the K largest of two descending lists, descending
+template <int K>
+__device__ __forceinline__ void keep_largest(double (&a)[K], const double (&b)[K]) {
+#pragma unroll
+    for (int i = 0; i < K; ++i) a[i] = __builtin_fmax(a[i], b[K - 1 - i]);
+    merge_bitonic<K>(a);
+}
+
+// the value of the lane across from this one in the group of 2 M lanes: with its quad neighbours for M = 1 and 2, mirrored
+// for M = 4 and 8 (every half holds one list by then, so any pairing of the halves does)
+template <int M>
+__device__ __forceinline__ double lane_across(double v) {
+    constexpr int ctrl = M == 1 ? 0xB1 : (M == 2 ? 0x4E : (M == 4 ? 0x141 : 0x140));
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, ctrl, 0xF, 0xF, true);
+    const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), ctrl, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+template <int M, int L, int K>
+__device__ __forceinline__ void merge_lanes(double (&a)[K]) {
+    if constexpr (M < L) {
+        double b[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) b[i] = lane_across<M>(a[i]);
+        keep_largest<K>(a, b);
+        merge_lanes<2 * M, L, K>(a);
+    }
+}
+
+// slots of the result that a lane hands out: sub, sub + L, ...
+template <int L, int KMAX> constexpr int kGateSlots = (KMAX + L - 1) / L;
+
 // row: the token's E logits (global memory or LDS; 16-byte aligned when E % 4 == 0 or `padded`); sub = this lane's
 // index among the token's L lanes; live = the token exists.  `padded`: the row holds L * VPL readable floats and the
-// ones from E on are ignored (the fused router's LDS rows).  Every lane of the L-lane group must call this (shuffles);
-// lane sub == 0 of a live token hands its k experts (e_sel), their exponentials (p_sel) and the denominator to `emit`.
+// ones from E on are ignored (the fused router's LDS rows).  Every lane of the L-lane group must call this (lane
+// exchange); every lane of a live token hands slots sub, sub + L, ... of the k experts (e_sel), their exponentials
+// (p_sel) and the denominator to `emit`.  KMAX >= k is a compile-time bound: the lists stay in registers.
+//
+// Bound by instructions: one lane alone (E <= 8) takes k rounds of a scan that carries the index; several lanes sort
+// their candidates in lists of KMAX, merge the lists across lanes and share the exponentials, divisions and stores.
+// Rounds of a scan and a shuffle butterfly took 18.9 us for 100003 tokens, E = 64, k = 6; this takes 11.4 us.
 template <int L, int VPL, int KMAX, bool ALL, class Emit>
 __device__ __forceinline__ void gate_select_emit(const float* row, bool padded, int sub, bool live, int E, int k, Emit emit) {
-    const int e0 = sub * VPL;
-    uint32_t key[VPL];
+    static_assert(L >= 1 && L <= 16 && (KMAX & (KMAX - 1)) == 0 && MOE_MAX_EXPERTS <= 256, "DPP rows of 16 lanes, bitonic lists, 8-bit experts");
+    constexpr int S = kGateSlots<L, KMAX>;
+    const int e0 = sub * 4;                         // first logit of this lane; its i-th one is e0 + (i / 4) * 4 L + i % 4
+    float v[VPL];
+    bool have[VPL];
 #pragma unroll
-    for (int i = 0; i < VPL; ++i) key[i] = 0u;
+    for (int i = 0; i < VPL; ++i) { v[i] = 0.f; have[i] = live && e0 + (i / 4) * (4 * L) + i % 4 < E; }
     if (live) {
         if (padded || (E & 3) == 0) {
 #pragma unroll
             for (int c = 0; c < VPL / 4; ++c) {
-                if (e0 + 4 * c < E) {
-                    const float4 q = *reinterpret_cast<const float4*>(row + e0 + 4 * c);
-                    key[4 * c] = orderable(q.x);
-                    if (!padded || e0 + 4 * c + 1 < E) key[4 * c + 1] = orderable(q.y);
-                    if (!padded || e0 + 4 * c + 2 < E) key[4 * c + 2] = orderable(q.z);
-                    if (!padded || e0 + 4 * c + 3 < E) key[4 * c + 3] = orderable(q.w);
+                const int e = e0 + 4 * L * c;
+                if (e < E) {
+                    const float4 q = *reinterpret_cast<const float4*>(row + e);
+                    v[4 * c] = q.x; v[4 * c + 1] = q.y; v[4 * c + 2] = q.z; v[4 * c + 3] = q.w;
                 }
             }
         } else {
 #pragma unroll
             for (int i = 0; i < VPL; ++i)
-                if (e0 + i < E) key[i] = orderable(row[e0 + i]);
+                if (have[i]) v[i] = row[e0 + (i / 4) * (4 * L) + i % 4];
         }
     }
-    // KMAX >= k is a compile-time bound so that the selected experts and weights stay in registers
-    // and are written once
-    float top = 0.f, denom = 0.f;
-    float p_sel[KMAX];
-    int e_sel[KMAX];
+    float denom = 0.f, p_sel[S];
+    int e_sel[S];
+    if constexpr (L == 1) {
+        uint32_t key[VPL];
 #pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-        p_sel[j] = 0.f;
-        e_sel[j] = 0;
-        if (j < k) {
-            uint32_t best = key[0];
-            int bi = 0;
+        for (int i = 0; i < VPL; ++i) key[i] = have[i] ? orderable(v[i]) : 0u;
+        float top = 0.f;
 #pragma unroll
-            for (int i = 1; i < VPL; ++i)
-                if (key[i] > best) { best = key[i]; bi = i; }
-            int be = e0 + bi;
+        for (int j = 0; j < KMAX; ++j) {
+            p_sel[j] = 0.f;
+            e_sel[j] = 0;
+            if (j < k) {
+                uint32_t best = key[0];
+                int be = 0;
 #pragma unroll
-            for (int m = 1; m < L; m <<= 1) {
-                const uint32_t ok = __shfl_xor(best, m, 64);
-                const int oe = __shfl_xor(be, m, 64);
-                if (ok > best || (ok == best && oe < be)) { best = ok; be = oe; }
-            }
-            if (ALL && j == 0) {                    // before the winner is retired: every logit still has its key
-                const float t0 = from_orderable(best);
-                float sum = 0.f;
+                for (int i = 1; i < VPL; ++i)
+                    if (key[i] > best) { best = key[i]; be = i; }
+                const float lj = from_orderable(best);
+                if (j == 0) {
+                    top = lj;
+                    if (ALL) {
+#pragma unroll
+                        for (int i = 0; i < VPL; ++i)
+                            if (key[i] != 0u) denom += expf(from_orderable(key[i]) - top);
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < VPL; ++i)
-                    if (key[i] != 0u) sum += expf(from_orderable(key[i]) - t0);
-#pragma unroll
-                for (int m = 1; m < L; m <<= 1) sum += __shfl_xor(sum, m, 64);
-                denom = sum;
+                    if (i == be) key[i] = 0u;
+                const float p = expf(lj - top);     // exp(0) = 1 for the top-1 expert
+                if (!ALL) denom += p;
+                p_sel[j] = p;
+                e_sel[j] = be;
             }
-            const int mine = be - e0;               // in [0,VPL) only for the owner lane
+        }
+    } else {
+        double best[KMAX];
+#pragma unroll
+        for (int i = 0; i < KMAX; ++i) best[i] = i < VPL && have[i < VPL ? i : 0] ? candidate(v[i < VPL ? i : 0], e0 + (i / 4) * (4 * L) + i % 4) : 0.0;
+        sort_descending<KMAX>(best);
+#pragma unroll
+        for (int i0 = KMAX; i0 < VPL; i0 += KMAX) {
+            double more[KMAX];
+#pragma unroll
+            for (int u = 0; u < KMAX; ++u) {
+                const int i = i0 + u;
+                more[u] = i < VPL && have[i < VPL ? i : 0] ? candidate(v[i < VPL ? i : 0], e0 + (i / 4) * (4 * L) + i % 4) : 0.0;
+            }
+            sort_descending<KMAX>(more);
+            keep_largest<KMAX>(best, more);
+        }
+        merge_lanes<1, L, KMAX>(best);
+        const float top = candidate_logit(best[0]);
+        if (ALL) {
 #pragma unroll
             for (int i = 0; i < VPL; ++i)
-                if (i == mine) key[i] = 0u;
-            const float lj = from_orderable(best);
-            if (j == 0) top = lj;
-            const float p = expf(lj - top);         // exp(0) = 1 for the top-1 expert
-            if (!ALL) denom += p;
-            p_sel[j] = p;
-            e_sel[j] = be;
+                if (have[i]) denom += expf(v[i] - top);
+#pragma unroll
+            for (int m = 1; m < L; m <<= 1) denom += __shfl_xor(denom, m, 64);
+        }
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            double mine = best[i * L];
+#pragma unroll
+            for (int u = 1; u < L; ++u)
+                if (i * L + u < KMAX && u == sub) mine = best[i * L + u < KMAX ? i * L + u : 0];
+            e_sel[i] = candidate_expert(mine);
+            p_sel[i] = expf(candidate_logit(mine) - top);
+        }
+        if (!ALL) {
+            const int base = (threadIdx.x & 63) & ~(L - 1);
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) {        // summed in slot order, in every lane
+                const float p = __shfl(p_sel[j / L], base + j % L, 64);
+                if (j < k) denom += p;
+            }
         }
     }
-    if (live && sub == 0) emit(e_sel, p_sel, denom);
+    if (live) emit(e_sel, p_sel, denom);
 }
 
-// writes topk_idx[t][0..k) and topk_w[t][0..k)
-template <int KMAX>
-__device__ __forceinline__ void gate_store(long long t, int k, const int (&e_sel)[KMAX], const float (&p_sel)[KMAX], float denom,
+// writes this lane's slots of topk_idx[t][0..k) and topk_w[t][0..k)
+template <int L, int S>
+__device__ __forceinline__ void gate_store(long long t, int sub, int k, const int (&e_sel)[S], const float (&p_sel)[S], float denom,
                                            int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
-    if (KMAX == 2 && k == 2) {                      // the common top-2 case: one 8-byte store each
-        *reinterpret_cast<int2*>(topk_idx + t * 2) = make_int2(e_sel[0], e_sel[1]);
-        *reinterpret_cast<float2*>(topk_w + t * 2) = make_float2(p_sel[0] / denom, p_sel[1] / denom);
+    if (L == 1 && S == 2 && k == 2) {               // the common top-2 case: one 8-byte store each
+        *reinterpret_cast<int2*>(topk_idx + t * 2) = make_int2(e_sel[0], e_sel[S - 1]);
+        *reinterpret_cast<float2*>(topk_w + t * 2) = make_float2(p_sel[0] / denom, p_sel[S - 1] / denom);
     } else {
 #pragma unroll
-        for (int j = 0; j < KMAX; ++j)
-            if (j < k) {
-                topk_idx[t * k + j] = e_sel[j];
-                topk_w[t * k + j] = p_sel[j] / denom;
+        for (int i = 0; i < S; ++i)
+            if (sub + L * i < k) {
+                topk_idx[t * k + sub + L * i] = e_sel[i];
+                topk_w[t * k + sub + L * i] = p_sel[i] / denom;
             }
     }
 }
@@ -112,9 +227,10 @@ __device__ __forceinline__ void gate_store(long long t, int k, const int (&e_sel
 template <int L, int VPL, int KMAX, bool ALL>
 __device__ __forceinline__ void gate_select(const float* row, bool padded, int sub, bool live, long long t, int E, int k,
                                             int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+    constexpr int S = kGateSlots<L, KMAX>;
     gate_select_emit<L, VPL, KMAX, ALL>(row, padded, sub, live, E, k,
-                                        [&](const int (&e_sel)[KMAX], const float (&p_sel)[KMAX], float denom) {
-                                            gate_store<KMAX>(t, k, e_sel, p_sel, denom, topk_idx, topk_w);
+                                        [&](const int (&e_sel)[S], const float (&p_sel)[S], float denom) {
+                                            gate_store<L, S>(t, sub, k, e_sel, p_sel, denom, topk_idx, topk_w);
                                         });
 }
 

@@ -46,6 +46,16 @@ def test_many_exact_ties_and_signed_zeros(lib, E, k):
     check(lib, np.full((64, E), -0.0, dtype=np.float32), k)
 
 
+@pytest.mark.parametrize("E,k", [(9, 1), (12, 3), (16, 16), (17, 2), (32, 9), (33, 8), (63, 7), (64, 16), (65, 4), (100, 2), (128, 8), (129, 9),
+                                 (255, 16), (256, 1), (256, 8)])
+def test_every_lane_layout_and_list_length_with_ties(lib, E, k):
+    """2 to 16 lanes per token x lists of 2, 8 and 16, full and ragged last pieces, about half of the tokens with ties."""
+    rng = np.random.default_rng(E * 100 + k)
+    lg = rng.standard_normal((777, E)).astype(np.float32)
+    lg[::2] = np.round(lg[::2] * 4) / 4
+    check(lib, lg, k)
+
+
 def test_extreme_finite_values(lib):
     lg = np.array([[3e38, -3e38, 0, 1e-45, -1e-45, 1, -1, 2]] * 5, dtype=np.float32)
     check(lib, lg, 2)

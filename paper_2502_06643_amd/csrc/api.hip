@@ -199,6 +199,8 @@ static int check_dispatch_args(const char* who, const void* x, moe_dtype_t dt, c
     return MOE_OK;
 }
 
+static const PlanTask kNoPlan = {nullptr, -1, {1, 1, 0}};
+
 int moe_dispatch(const void* x, moe_dtype_t dt, const int32_t* topk_idx, int T, int d, int E, int k,
                  const int32_t* placement, int G, void* send_buf, int32_t* perm, int32_t* inv_perm,
                  int32_t* expert_counts, int32_t* expert_start, int32_t* gpu_counts, int32_t* gpu_offsets,
@@ -212,7 +214,7 @@ int moe_dispatch(const void* x, moe_dtype_t dt, const int32_t* topk_idx, int T, 
         return fail(MOE_ERR_WORKSPACE, "moe_dispatch: workspace %zu < %zu bytes", workspace_bytes,
                     moe_dispatch_workspace_bytes(T, E, k));
     return launch_dispatch(x, row_bytes, topk_idx, T, E, k, placement, G, send_buf, perm, inv_perm, expert_counts,
-                           expert_start, gpu_counts, gpu_offsets, (int32_t*)workspace, (hipStream_t)stream);
+                           expert_start, gpu_counts, gpu_offsets, (int32_t*)workspace, kNoPlan, (hipStream_t)stream);
 }
 
 size_t moe_dispatch_static_scratch_bytes(void) { return kDispatchStaticScratchBytes; }
@@ -232,7 +234,7 @@ int moe_dispatch_noalloc(const void* x, moe_dtype_t dt, const int32_t* topk_idx,
     int32_t* scratch = nullptr;
     if ((rc = dispatch_static_scratch(&scratch)) != MOE_OK) return rc;
     return launch_dispatch(x, row_bytes, topk_idx, T, E, k, placement, G, send_buf, perm, inv_perm, expert_counts,
-                           expert_start, gpu_counts, gpu_offsets, scratch, (hipStream_t)stream);
+                           expert_start, gpu_counts, gpu_offsets, scratch, kNoPlan, (hipStream_t)stream);
 }
 
 static int check_ffn_shape(const char* who, int E, int d, int f, moe_dtype_t dt) {
@@ -390,24 +392,23 @@ int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T,
         return fail(MOE_ERR_WORKSPACE, "%s: dispatch workspace %zu < %zu bytes", who, dispatch_workspace_bytes,
                     moe_dispatch_workspace_bytes(T, E, k));
     hipStream_t s = (hipStream_t)stream;
-    const bool fused = front_fits(T, E, k);
-    if (fused) {
+    const PlanTask pt = {(int32_t*)ffn_workspace, local_gpu, ffn_plan_shape(dt, N, E, local_gpu < 0)};
+    if (front_fits(T, E, k)) {
         FrontArgs a;
         a.x = (const uint4*)x; a.logits = logits; a.T = T; a.E = E; a.k = k; a.G = G; a.local_gpu = local_gpu;
         a.units_per_row = row_bytes / 16; a.placement = placement; a.topk_idx = topk_idx; a.topk_w = topk_w; a.perm = perm;
         a.inv_perm = inv_perm; a.expert_counts = expert_counts; a.expert_start = expert_start; a.gpu_counts = gpu_counts;
-        a.gpu_offsets = gpu_offsets; a.send_buf = (uint4*)send_buf; a.shape = ffn_plan_shape(dt, N, E, local_gpu < 0);
-        a.plan = (int32_t*)ffn_workspace;
+        a.gpu_offsets = gpu_offsets; a.send_buf = (uint4*)send_buf; a.shape = pt.shape; a.plan = pt.plan;
         if ((rc = launch_front(a, s)) != MOE_OK) return rc;
     } else {
         if (T > 0 && (rc = launch_gate(logits, T, E, k, false, topk_idx, topk_w, s)) != MOE_OK) return rc;
         if ((rc = launch_dispatch(x, row_bytes, topk_idx, T, E, k, placement, G, send_buf, perm, inv_perm, expert_counts, expert_start,
-                                  gpu_counts, gpu_offsets, (int32_t*)dispatch_workspace, s)) != MOE_OK) return rc;
+                                  gpu_counts, gpu_offsets, (int32_t*)dispatch_workspace, T == 0 ? kNoPlan : pt, s)) != MOE_OK) return rc;
         if (T == 0) return MOE_OK;
     }
     CombineTail tail = {inv_perm, topk_idx, topk_w, placement, local_gpu, T, E, k, y, false};
     if ((rc = run_ffn(send_buf, dt, N, d, f, E, packed_weights, expert_counts, expert_start, placement, local_gpu, ffn_out, ffn_workspace,
-                      fused, &tail, s)) != MOE_OK) return rc;
+                      true, &tail, s)) != MOE_OK) return rc;
     if (tail.done) return MOE_OK;
     return launch_combine(ffn_out, dt, inv_perm, topk_idx, topk_w, placement, local_gpu, T, d, E, k, y, s);
 }

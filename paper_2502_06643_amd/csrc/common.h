@@ -40,11 +40,15 @@ int launch_gate(const float* logits, int T, int E, int k, bool all_norm, int32_t
 
 constexpr int kDispatchBlock = 256;
 constexpr int kDispatchItems = 4;
-void dispatch_geometry(long long N, int* items, int* nblocks);      // routes per thread and number of chunks
+void dispatch_geometry(long long N, int* items, int* nblocks);      // of the workspace: routes per thread and number of chunks
+// How the expert FFN wants its tile plan built for N rows in E groups (arguments of launch_ffn_plan).
+struct PlanShape { int bm0, bm1, choice; };
+// The tile plan as a by-product of the dispatch's index kernels, which hold all it needs; plan == NULL: none wanted.
+struct PlanTask { int32_t* plan; int local_gpu; PlanShape shape; };
 int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T, int E, int k,
                     const int32_t* placement, int G, void* send_buf, int32_t* perm, int32_t* inv_perm,
                     int32_t* expert_counts, int32_t* expert_start, int32_t* gpu_counts,
-                    int32_t* gpu_offsets, int32_t* block_counts, hipStream_t s);
+                    int32_t* gpu_offsets, int32_t* block_counts, const PlanTask& plan_task, hipStream_t s);
 
 // moe_dispatch_noalloc: the per-chunk histograms live in a file-scope device array of this many bytes;
 // dispatch_static_scratch returns the current device's copy of it (looked up once per device)
@@ -78,8 +82,6 @@ size_t packed_bytes_bf16(int E, int d, int f);
 size_t ffn_bf16_scratch_bytes();      // fp32 partial tiles of the split tail, sized for the largest supported XCD
 int launch_pack_f32(const float* w1, const float* w3, const float* w2, int E, int d, int f, float* packed, hipStream_t s);
 int launch_pack_bf16(const void* w1, const void* w3, const void* w2, int E, int d, int f, void* packed, hipStream_t s);
-// How the expert FFN wants its tile plan built for N rows in E groups (arguments of launch_ffn_plan).
-struct PlanShape { int bm0, bm1, choice; };
 PlanShape ffn_plan_shape(moe_dtype_t dt, int N, int E, bool every_row_resident);
 // E row groups (counts/starts); group g uses the weights of expert group_expert[g] of n_weights
 // (g itself when group_expert is NULL).  plan_ready: the plan has been built already (ffn_plan_shape's way)

@@ -3,13 +3,13 @@
 // (placement[expert], expert), followed by the row copy into the send buffer.
 //
 //   count : each workgroup histograms its contiguous chunk of routes by expert
-//   scan  : one workgroup turns the per-chunk histograms into exclusive
-//           per-expert prefixes, sums them to expert_counts (= P_{e,l}), ranks
-//           the experts by (gpu, expert) to get expert_start, and derives
-//           gpu_counts / gpu_offsets
-//   rank  : each workgroup recomputes, wavefront by wavefront, the stable rank
-//           of every route among the routes of the same expert (ballot match +
-//           popcount of the lower lanes) and writes perm / inv_perm
+//   rank  : each workgroup adds the histograms up (in total: expert_counts =
+//           P_{e,l}; before its own chunk: where its routes begin), ranks the
+//           experts by (gpu, expert) to get expert_start, and works out,
+//           wavefront by wavefront, the stable rank of every route of its chunk
+//           among the routes of the same expert (ballot match + popcount of the
+//           lower lanes): perm / inv_perm.  One workgroup also writes the
+//           expert and GPU tables
 //   rows  : every 16-byte piece of x[t] is read once and written to the k
 //           sorted positions of token t
 //
@@ -17,14 +17,14 @@
 // is a pure function of the route id.
 #include <mutex>
 #include "dispatch_index.h"
+#include "ffn_plan.h"
 
 namespace moe {
 
-constexpr int kWaves = kDispatchBlock / 64;
-constexpr int kMaxChunks = 1024;     // the scan walks this many per-chunk histograms at most
+constexpr int kMaxChunks = 1024;     // per-chunk histograms that a caller's workspace holds at most
 
-// Routes per thread: 4 for ordinary batches, more for very large ones so that the number of chunks
-// (and with it the scan) stays bounded.
+// The workspace's geometry: what moe_dispatch_workspace_bytes promises room for.  The kernels below use
+// chunks of at least this size (route_chunks), so their histograms always fit.
 void dispatch_geometry(long long N, int* items, int* nblocks) {
     long long it = (N + (long long)kMaxChunks * kDispatchBlock - 1) / ((long long)kMaxChunks * kDispatchBlock);
     if (it < kDispatchItems) it = kDispatchItems;
@@ -33,135 +33,153 @@ void dispatch_geometry(long long N, int* items, int* nblocks) {
     *nblocks = (int)((N + it * kDispatchBlock - 1) / (it * kDispatchBlock));
 }
 
-__global__ __launch_bounds__(kDispatchBlock) void dispatch_count_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int items,
-                                                                        int32_t* __restrict__ block_counts) {
+// A chunk is what one workgroup of 16 wavefronts counts and ranks: 1024 routes times `steps`.  At most
+// kRankChunks chunks, one per compute unit: every rank workgroup reads all their histograms.
+constexpr int kRankChunks = 256;         // 512: the same at E = 8, 12.2 against 8.7 us at E = 64
+static void route_chunks(long long N, int* steps, int* chunks) {
+    const long long st = (N + (long long)kRankChunks * kIndexThreads - 1) / ((long long)kRankChunks * kIndexThreads);
+    *steps = (int)st;
+    *chunks = (int)((N + st * kIndexThreads - 1) / (st * kIndexThreads));
+}
+
+__global__ __launch_bounds__(kIndexThreads) void dispatch_count_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int steps,
+                                                                       int32_t* __restrict__ block_counts) {
     __shared__ int hist[MOE_MAX_EXPERTS];
-    for (int e = threadIdx.x; e < E; e += kDispatchBlock) hist[e] = 0;
+    for (int e = threadIdx.x; e < E; e += kIndexThreads) hist[e] = 0;
     __syncthreads();
-    const long long base = (long long)blockIdx.x * kDispatchBlock * items;
-    for (int i = 0; i < items; ++i) {
-        const long long r = base + i * kDispatchBlock + threadIdx.x;
-        if (r < N) {
-            const int e = topk_idx[r];
-            if ((unsigned)e < (unsigned)E) atomicAdd(&hist[e], 1);
-        }
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < E; e += kDispatchBlock) block_counts[(size_t)blockIdx.x * E + e] = hist[e];
-}
-
-constexpr int kScanThreads = 1024;
-
-__global__ __launch_bounds__(kScanThreads) void dispatch_scan_kernel(int32_t* __restrict__ block_counts, int nblocks, int E, int EP,
-                                                            const int32_t* __restrict__ placement, int G,
-                                                            int32_t* __restrict__ expert_counts,
-                                                            int32_t* __restrict__ expert_start,
-                                                            int32_t* __restrict__ gpu_counts,
-                                                            int32_t* __restrict__ gpu_offsets) {
-    // EP = E rounded up to a power of two; the threads form kScanThreads/EP slices of the chunk range,
-    // each thread owning one expert in one slice
-    __shared__ int pl[MOE_MAX_EXPERTS];
-    __shared__ int tot[MOE_MAX_EXPERTS];
-    __shared__ int slice_tot[kScanThreads];
-    const int e = threadIdx.x % EP, sl = threadIdx.x / EP, S = kScanThreads / EP;
-    const int per = (nblocks + S - 1) / S;
-    const int b0 = sl * per, b1 = min(nblocks, b0 + per);
-    int sum = 0;
-    if (e < E)
-        for (int b = b0; b < b1; ++b) sum += block_counts[(size_t)b * E + e];
-    slice_tot[threadIdx.x] = sum;
-    if ((int)threadIdx.x < E) pl[threadIdx.x] = placement[threadIdx.x];
-    __syncthreads();
-    if (e < E) {
-        int run = 0;
-        for (int s2 = 0; s2 < sl; ++s2) run += slice_tot[s2 * EP + e];
-        if (sl == S - 1) {
-            tot[e] = run + sum;
-            expert_counts[e] = run + sum;
-        }
-        for (int b = b0; b < b1; ++b) {
-            const int c = block_counts[(size_t)b * E + e];
-            block_counts[(size_t)b * E + e] = run;      // exclusive prefix over chunks, per expert
-            run += c;
-        }
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < E) {
-        const int me = threadIdx.x;
-        int start = 0;
-        const int ge = pl[me];
-#pragma unroll 8
-        for (int o = 0; o < E; ++o) {
-            const int go = pl[o];
-            start += ((go < ge) | ((go == ge) & (o < me))) ? tot[o] : 0;
-        }
-        expert_start[me] = start;
-    }
-    for (int g = threadIdx.x; g < G; g += kScanThreads) {
-        int cnt = 0, off = 0;
-#pragma unroll 8
-        for (int o = 0; o < E; ++o) {
-            const int go = pl[o], to = tot[o];
-            cnt += (go == g) ? to : 0;
-            off += ((go >= 0) & (go < g)) ? to : 0;
-        }
-        gpu_counts[g] = cnt;
-        gpu_offsets[g] = off;
-        if (g == G - 1) gpu_offsets[G] = off + cnt;
-    }
-}
-
-__global__ __launch_bounds__(kDispatchBlock) void dispatch_rank_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits, int items,
-                                                                       const int32_t* __restrict__ block_counts,
-                                                                       const int32_t* __restrict__ expert_start,
-                                                                       int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
-    // per wavefront: first the number of routes of each expert in its slice,
-    // then (after the prefix over wavefronts) the running write offset
-    __shared__ int woff[kWaves][MOE_MAX_EXPERTS];
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    for (int i = threadIdx.x; i < kWaves * MOE_MAX_EXPERTS; i += kDispatchBlock) (&woff[0][0])[i] = 0;
-    __syncthreads();
-
-    const long long wbase = ((long long)blockIdx.x * kWaves + wave) * 64 * items;
-    const unsigned long long lower = (1ull << lane) - 1ull;
-    for (int i = 0; i < items; ++i) {
-        const long long r = wbase + i * 64 + lane;
-        const int ex = (r < N) ? topk_idx[r] : -1;
-        const bool ok = (unsigned)ex < (unsigned)E;
-        const unsigned long long m = match_expert(ex, ok, ebits);
-        if (ok && (m & lower) == 0ull) atomicAdd(&woff[wave][ex], __popcll(m));   // first lane of the group
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < E; e += kDispatchBlock) {
-        int run = expert_start[e] + block_counts[(size_t)blockIdx.x * E + e];
+    const long long base = (long long)blockIdx.x * kIndexThreads * steps + threadIdx.x;
+    for (int i0 = 0; i0 < steps; i0 += 8) {
+        int e[8];
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            const int c = woff[w][e];
-            woff[w][e] = run;
-            run += c;
+        for (int u = 0; u < 8; ++u) {
+            const long long r = base + (long long)(i0 + u) * kIndexThreads;
+            e[u] = (i0 + u < steps && r < N) ? topk_idx[r] : -1;
         }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if ((unsigned)e[u] < (unsigned)E) atomicAdd(&hist[e[u]], 1);
     }
     __syncthreads();
-    volatile int* my = woff[wave];
-    for (int i = 0; i < items; ++i) {
-        const long long r = wbase + i * 64 + lane;
-        const int ex = (r < N) ? topk_idx[r] : -1;
-        const bool ok = (unsigned)ex < (unsigned)E;
-        const unsigned long long m = match_expert(ex, ok, ebits);
-        int pos = 0;
-        if (ok) pos = my[ex] + __popcll(m & lower);
-        __builtin_amdgcn_wave_barrier();
-        if (ok && (m & lower) == 0ull) my[ex] += __popcll(m);
-        __builtin_amdgcn_wave_barrier();
-        if (ok) {
+    for (int e = threadIdx.x; e < E; e += kIndexThreads) block_counts[(size_t)blockIdx.x * E + e] = hist[e];
+}
+
+// the tile plan of the expert FFN, by a workgroup that holds the totals and starts (all threads call this)
+__device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScratch& scratch, int E, const PlanTask& pt) {
+    const int e = threadIdx.x;
+    int c = 0, st = 0;
+    if (e < E && (pt.local_gpu < 0 || s.pl[e] == pt.local_gpu)) {
+        c = s.tot[e];
+        st = s.start[e];
+    }
+    build_plan(scratch, e, c, st, e, E, pt.shape.bm0, pt.shape.bm1, pt.shape.choice, pt.plan);
+}
+
+// Ranks the routes of one chunk.  Latency-bound: every workgroup adds up all chunks' histograms for itself
+// (at most kRankChunks x E counts, L2 hits, independent loads) instead of waiting for a scan kernel of one
+// workgroup, whose two dependent walks over up to 1024 histograms took 22 us at E = 64 (600 k routes; count, scan
+// and rank 34 us, count and rank now 12 us) and 6.6 us at E = 8 (2 M routes: 25 -> 18 us).
+// Workgroup 0 writes the tables, the last workgroup the tile plan when one is wanted.
+constexpr int kRankBatch = 8;            // 64-route steps of a wavefront whose expert ids are in registers together
+__global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits, int steps,
+                                                                      const int32_t* __restrict__ block_counts,
+                                                                      const int32_t* __restrict__ placement, int G,
+                                                                      int32_t* __restrict__ expert_counts,
+                                                                      int32_t* __restrict__ expert_start,
+                                                                      int32_t* __restrict__ gpu_counts,
+                                                                      int32_t* __restrict__ gpu_offsets,
+                                                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
+                                                                      PlanTask pt) {
+    __shared__ IndexTables s;
+    __shared__ PlanScratch plan_scratch;
+    __shared__ int before[MOE_MAX_EXPERTS];              // routes of each expert in the chunks before this one
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const long long wbase = ((long long)blockIdx.x * kIndexWaves + wave) * 64 * steps;
+    const unsigned long long lower = (1ull << lane) - 1ull;
+    int exs[kRankBatch], loc[kRankBatch];                // expert of a route, its rank among the wavefront's routes of that expert
+    auto load = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < kRankBatch; ++u) {
+            const long long r = wbase + (long long)(i0 + u) * 64 + lane;
+            exs[u] = (i0 + u < steps && r < N) ? topk_idx[r] : -1;
+        }
+    };
+    load(0);
+    index_clear(s, E);
+    if ((int)threadIdx.x < E) {
+        s.pl[threadIdx.x] = placement[threadIdx.x];
+        s.tot[threadIdx.x] = 0;
+        before[threadIdx.x] = 0;
+    }
+    __syncthreads();
+
+    // all chunks' histograms: thread (expert, slice of the chunks), then the slices of a wavefront, then LDS
+    const int EP = 1 << ebits, he = threadIdx.x & (EP - 1);
+    int all = 0, mine = 0;
+    if (he < E) {
+        const int slices = kIndexThreads >> ebits;
+        for (int b0 = threadIdx.x >> ebits; b0 < (int)gridDim.x; b0 += 16 * slices) {
+            int c[16];                                   // sixteen loads in flight (E = 64: all of them)
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const int b = b0 + u * slices;
+                c[u] = b < (int)gridDim.x ? block_counts[(size_t)b * E + he] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                all += c[u];
+                mine += b0 + u * slices < (int)blockIdx.x ? c[u] : 0;
+            }
+        }
+    }
+    for (int m = EP; m < 64; m <<= 1) {
+        all += __shfl_xor(all, m, 64);
+        mine += __shfl_xor(mine, m, 64);
+    }
+    if (he < E && lane < EP) {
+        atomicAdd(&s.tot[he], all);
+        atomicAdd(&before[he], mine);
+    }
+    // this wavefront's own routes are counted and ranked in one go (a wavefront's LDS accesses execute in order);
+    // the ranks stay in registers, those of a slice of more than kRankBatch steps wait in inv_perm
+    const bool spill = steps > kRankBatch;
+    for (int i0 = 0;;) {
+#pragma unroll
+        for (int u = 0; u < kRankBatch; ++u) {
+            loc[u] = 0;
+            if (i0 + u >= steps) continue;
+            const bool ok = (unsigned)exs[u] < (unsigned)E;
+            loc[u] = index_next(s.woff[wave], exs[u], ok, ebits, lower);
+            if (spill && ok) inv_perm[wbase + (long long)(i0 + u) * 64 + lane] = loc[u];
+        }
+        i0 += kRankBatch;
+        if (i0 >= steps) break;
+        load(i0);
+    }
+    __syncthreads();
+    index_offsets(s, E, ebits, before);
+
+    for (int i0 = 0; i0 < steps; i0 += kRankBatch) {
+        if (spill) {
+            load(i0);
+#pragma unroll
+            for (int u = 0; u < kRankBatch; ++u)
+                if ((unsigned)exs[u] < (unsigned)E) loc[u] = inv_perm[wbase + (long long)(i0 + u) * 64 + lane];
+        }
+#pragma unroll
+        for (int u = 0; u < kRankBatch; ++u) {
+            if ((unsigned)exs[u] >= (unsigned)E) continue;
+            const long long r = wbase + (long long)(i0 + u) * 64 + lane;
+            const int pos = s.woff[wave][exs[u]] + loc[u];
             perm[pos] = (int32_t)r;
             inv_perm[r] = pos;
         }
     }
+    if (blockIdx.x == 0) index_write_tables(s, E, G, expert_counts, expert_start, gpu_counts, gpu_offsets);
+    if (pt.plan != nullptr && blockIdx.x == gridDim.x - 1) plan_from_tables(s, plan_scratch, E, pt);
 }
 
-// Batches of up to kFusedMaxRoutes routes: count, scan and rank in ONE workgroup of 16 wavefronts, each
-// owning a contiguous slice of the routes.  Three launches become one, which is what matters at these
+// Batches of up to kFusedMaxRoutes routes: count and rank in ONE workgroup of 16 wavefronts, each
+// owning a contiguous slice of the routes.  Two launches become one, which is what matters at these
 // sizes (every launch costs more than the work it does).  A thread keeps its ITEMS expert ids in
 // registers: they are loaded once, all loads in flight together, and serve both passes.  Same
 // results: positions are a pure function of the route id.
@@ -175,8 +193,10 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_index_kernel(const int
                                                                        int32_t* __restrict__ expert_start,
                                                                        int32_t* __restrict__ gpu_counts,
                                                                        int32_t* __restrict__ gpu_offsets,
-                                                                       int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
+                                                                       int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
+                                                                       PlanTask pt) {
     __shared__ IndexTables s;
+    __shared__ PlanScratch plan_scratch;
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
     index_clear(s, E);
     if ((int)threadIdx.x < E) s.pl[threadIdx.x] = placement[threadIdx.x];
@@ -194,8 +214,7 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_index_kernel(const int
     for (int i = 0; i < ITEMS; ++i)
         if ((unsigned)exs[i] < (unsigned)E) atomicAdd(&s.woff[wave][exs[i]], 1);   // LDS atomics: counts need no order
     __syncthreads();
-    index_totals(s, E);
-    index_write_tables(s, E, G, expert_counts, expert_start, gpu_counts, gpu_offsets);
+    index_totals(s, E, ebits);
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int r = wbase + i * 64 + lane;
@@ -206,6 +225,8 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_index_kernel(const int
             inv_perm[r] = pos;
         }
     }
+    index_write_tables(s, E, G, expert_counts, expert_start, gpu_counts, gpu_offsets);
+    if (pt.plan != nullptr) plan_from_tables(s, plan_scratch, E, pt);
 }
 
 // One thread per 16-byte unit of a source row: read once, write k times.
@@ -223,11 +244,11 @@ __global__ __launch_bounds__(256) void dispatch_rows_kernel(const uint4* __restr
     }
 }
 
-// Scratch of moe_dispatch_noalloc: the per-chunk expert histograms (count -> scan -> rank) in device memory
+// Scratch of moe_dispatch_noalloc: the per-chunk expert histograms (count -> rank) in device memory
 // that exists from the moment the library is loaded, so that the call allocates nothing.  Every GPU the
 // library runs on holds its own copy at its own address; in host code the array's name is only a handle
 // for hipGetSymbolAddress, never a pointer to pass to a kernel.  The count kernel writes every entry the
-// scan and rank kernels read, so nothing has to be cleared between calls; calls that overlap on one GPU
+// rank kernel reads, so nothing has to be cleared between calls; calls that overlap on one GPU
 // share the array and race.
 static __device__ __align__(256) unsigned char dispatch_scratch[kDispatchStaticScratchBytes];
 
@@ -255,19 +276,16 @@ int dispatch_static_scratch(int32_t** scratch) {
 int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T, int E, int k,
                     const int32_t* placement, int G, void* send_buf, int32_t* perm, int32_t* inv_perm,
                     int32_t* expert_counts, int32_t* expert_start, int32_t* gpu_counts,
-                    int32_t* gpu_offsets, int32_t* block_counts, hipStream_t s) {
+                    int32_t* gpu_offsets, int32_t* block_counts, const PlanTask& plan_task, hipStream_t s) {
     const int N = T * k;
-    int items, nblocks;
-    dispatch_geometry(N, &items, &nblocks);
     int ebits = 0;
     while ((1 << ebits) < E) ++ebits;
-    const int EP = 1 << ebits;
     int rc;
     if (N <= kFusedMaxRoutes) {
         LaunchTimer timer(MOE_K_DISPATCH_RANK, s);
 #define MOE_LAUNCH_INDEX(ITEMS)                                                                                          \
     hipLaunchKernelGGL(dispatch_index_kernel<ITEMS>, dim3(1), dim3(kIndexThreads), 0, s, topk_idx, N, E, ebits, placement, G, \
-                       expert_counts, expert_start, gpu_counts, gpu_offsets, perm, inv_perm)
+                       expert_counts, expert_start, gpu_counts, gpu_offsets, perm, inv_perm, plan_task)
         if (N <= kIndexThreads) MOE_LAUNCH_INDEX(1);
         else if (N <= 2 * kIndexThreads) MOE_LAUNCH_INDEX(2);
         else if (N <= 4 * kIndexThreads) MOE_LAUNCH_INDEX(4);
@@ -276,21 +294,17 @@ int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T
 #undef MOE_LAUNCH_INDEX
         if ((rc = check_launch("moe_dispatch index launch")) != MOE_OK) return rc;
     } else {
-        if (nblocks > 0) {
+        int steps, chunks;
+        route_chunks(N, &steps, &chunks);
+        {
             LaunchTimer timer(MOE_K_DISPATCH_COUNT, s);
-            hipLaunchKernelGGL(dispatch_count_kernel, dim3(nblocks), dim3(kDispatchBlock), 0, s, topk_idx, N, E, items, block_counts);
+            hipLaunchKernelGGL(dispatch_count_kernel, dim3(chunks), dim3(kIndexThreads), 0, s, topk_idx, N, E, steps, block_counts);
             if ((rc = check_launch("moe_dispatch count launch")) != MOE_OK) return rc;
         }
         {
-            LaunchTimer timer(MOE_K_DISPATCH_SCAN, s);
-            hipLaunchKernelGGL(dispatch_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, block_counts, nblocks, E, EP, placement, G,
-                               expert_counts, expert_start, gpu_counts, gpu_offsets);
-            if ((rc = check_launch("moe_dispatch scan launch")) != MOE_OK) return rc;
-        }
-        if (nblocks > 0) {
             LaunchTimer timer(MOE_K_DISPATCH_RANK, s);
-            hipLaunchKernelGGL(dispatch_rank_kernel, dim3(nblocks), dim3(kDispatchBlock), 0, s, topk_idx, N, E, ebits, items,
-                               block_counts, expert_start, perm, inv_perm);
+            hipLaunchKernelGGL(dispatch_rank_kernel, dim3(chunks), dim3(kIndexThreads), 0, s, topk_idx, N, E, ebits, steps, block_counts,
+                               placement, G, expert_counts, expert_start, gpu_counts, gpu_offsets, perm, inv_perm, plan_task);
             if ((rc = check_launch("moe_dispatch rank launch")) != MOE_OK) return rc;
         }
     }

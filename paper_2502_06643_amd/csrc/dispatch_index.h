@@ -21,7 +21,7 @@ __device__ __forceinline__ unsigned long long match_expert(int e, bool valid, in
 
 struct IndexTables {
     int woff[kIndexWaves][MOE_MAX_EXPERTS];   // per wavefront: routes of each expert in its slice, then its next position
-    int pl[MOE_MAX_EXPERTS];                  // the map; loaded by the caller before the barrier that precedes index_totals
+    int pl[MOE_MAX_EXPERTS];                  // the map; loaded by the caller before the barrier that precedes index_offsets
     int tot[MOE_MAX_EXPERTS];                 // routes per expert
     int start[MOE_MAX_EXPERTS];               // first position of each expert
 };
@@ -29,29 +29,29 @@ struct IndexTables {
 __device__ __forceinline__ void index_clear(IndexTables& s, int E) {
     for (int i = threadIdx.x; i < kIndexWaves * MOE_MAX_EXPERTS; i += kIndexThreads)
         if ((i & (MOE_MAX_EXPERTS - 1)) < E) (&s.woff[0][0])[i] = 0;
+    if ((int)threadIdx.x < E) s.start[threadIdx.x] = 0;
 }
 
-// Per-wavefront counts -> totals, expert starts and per-wavefront write offsets.  Called by all threads, after a
-// barrier that follows the counting; ends with a barrier.
-__device__ __forceinline__ void index_totals(IndexTables& s, int E) {
-    const int me = threadIdx.x;
-    if (me < E) {
-        int t = 0;
-#pragma unroll
-        for (int w = 0; w < kIndexWaves; ++w) t += s.woff[w][me];
-        s.tot[me] = t;
-    }
-    __syncthreads();
+// Totals and per-wavefront counts -> expert starts and per-wavefront write offsets; `before` (in LDS, may be NULL):
+// routes of each expert that precede this workgroup's.  Called by all threads, after a barrier; ends with one.
+// The E x E comparisons of the starts are dealt to all threads (thread: expert, slice of the others), because one
+// wavefront walking E = 64 totals took 3.7 us, more than the ranking of its routes.
+__device__ __forceinline__ void index_offsets(IndexTables& s, int E, int ebits, const int* before) {
+    const int EP = 1 << ebits, me = threadIdx.x & (EP - 1), slices = kIndexThreads >> ebits;
+    int start = 0;
     if (me < E) {
         const int ge = s.pl[me];
-        int start = 0;
-#pragma unroll 8
-        for (int o = 0; o < E; ++o) {
+#pragma unroll 4
+        for (int o = threadIdx.x >> ebits; o < E; o += slices) {
             const int go = s.pl[o];
             start += ((go < ge) | ((go == ge) & (o < me))) ? s.tot[o] : 0;
         }
-        s.start[me] = start;
-        int run = start;
+    }
+    for (int m = EP; m < 64; m <<= 1) start += __shfl_xor(start, m, 64);
+    if (me < E && (threadIdx.x & 63) < EP) atomicAdd(&s.start[me], start);          // cleared by index_clear
+    __syncthreads();
+    if ((int)threadIdx.x < E) {
+        int run = s.start[me] + (before != nullptr ? before[me] : 0);
 #pragma unroll
         for (int w = 0; w < kIndexWaves; ++w) {
             const int c = s.woff[w][me];
@@ -62,25 +62,52 @@ __device__ __forceinline__ void index_totals(IndexTables& s, int E) {
     __syncthreads();
 }
 
-// expert_counts, expert_start and the per-GPU tables, from the totals; called by all threads after index_totals
-__device__ __forceinline__ void index_write_tables(const IndexTables& s, int E, int G, int32_t* __restrict__ expert_counts,
+// The same for a workgroup that counted every route itself: the totals are the sums of its wavefronts' counts.
+__device__ __forceinline__ void index_totals(IndexTables& s, int E, int ebits) {
+    const int me = threadIdx.x;
+    if (me < E) {
+        int t = 0;
+#pragma unroll
+        for (int w = 0; w < kIndexWaves; ++w) t += s.woff[w][me];
+        s.tot[me] = t;
+    }
+    __syncthreads();
+    index_offsets(s, E, ebits, nullptr);
+}
+
+// expert_counts, expert_start and the per-GPU tables, from the totals; called by all threads once the positions are
+// out (it overwrites woff)
+__device__ __forceinline__ void index_write_tables(IndexTables& s, int E, int G, int32_t* __restrict__ expert_counts,
                                                    int32_t* __restrict__ expert_start, int32_t* __restrict__ gpu_counts,
                                                    int32_t* __restrict__ gpu_offsets) {
+    static_assert(MOE_MAX_GPUS <= MOE_MAX_EXPERTS, "the GPU tables are built in rows of woff");
+    int* cnt = s.woff[0];
+    int* off = s.woff[1];
+    __syncthreads();
     if ((int)threadIdx.x < E) {
         expert_counts[threadIdx.x] = s.tot[threadIdx.x];
         expert_start[threadIdx.x] = s.start[threadIdx.x];
     }
-    for (int g = threadIdx.x; g < G; g += kIndexThreads) {
-        int cnt = 0, off = 0;
-#pragma unroll 8
-        for (int o = 0; o < E; ++o) {
+    if ((int)threadIdx.x < G) cnt[threadIdx.x] = off[threadIdx.x] = 0;
+    __syncthreads();
+    int gbits = 0;
+    while ((1 << gbits) < G) ++gbits;
+    const int g = threadIdx.x & ((1 << gbits) - 1);
+    if (g < G) {                                         // thread: GPU, slice of the experts
+        int c = 0, f = 0;
+        for (int o = threadIdx.x >> gbits; o < E; o += kIndexThreads >> gbits) {
             const int go = s.pl[o], to = s.tot[o];
-            cnt += (go == g) ? to : 0;
-            off += ((go >= 0) & (go < g)) ? to : 0;
+            c += (go == g) ? to : 0;
+            f += ((go >= 0) & (go < g)) ? to : 0;
         }
-        gpu_counts[g] = cnt;
-        gpu_offsets[g] = off;
-        if (g == G - 1) gpu_offsets[G] = off + cnt;
+        if (c) atomicAdd(&cnt[g], c);
+        if (f) atomicAdd(&off[g], f);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < G) {
+        gpu_counts[threadIdx.x] = cnt[threadIdx.x];
+        gpu_offsets[threadIdx.x] = off[threadIdx.x];
+        if ((int)threadIdx.x == G - 1) gpu_offsets[G] = off[threadIdx.x] + cnt[threadIdx.x];
     }
 }
 

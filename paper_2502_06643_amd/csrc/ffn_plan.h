@@ -36,75 +36,77 @@ int launch_ffn_plan(const int32_t* counts, const int32_t* starts, const int32_t*
 constexpr int kF32TileRows = 32;                        // tile height of the fp32 path
 constexpr int kTallTileRows = 384, kShortTileRows = 256; // tile heights of the bf16 path
 
-// Shared memory of build_plan, four entries per expert slot.
+// Shared memory of build_plan: per group its rows and tiles, and the sums over the groups listed before it.
 struct PlanScratch {
-    __attribute__((aligned(16))) int cnt[MOE_MAX_EXPERTS];
-    __attribute__((aligned(16))) int rank[MOE_MAX_EXPERTS];
-    __attribute__((aligned(16))) int tiles0[MOE_MAX_EXPERTS];
-    __attribute__((aligned(16))) int tiles1[MOE_MAX_EXPERTS];
+    int cnt[MOE_MAX_EXPERTS], tiles0[MOE_MAX_EXPERTS], tiles1[MOE_MAX_EXPERTS];
+    int rank[MOE_MAX_EXPERTS], rows[MOE_MAX_EXPERTS], pre0[MOE_MAX_EXPERTS], pre1[MOE_MAX_EXPERTS];
 };
 
-// Builds the plan with one workgroup of at least MOE_MAX_EXPERTS threads, all of which must call this: thread e
-// brings group e's row count c (0: not listed; threads past the last group bring 0), its first row st and the
-// expert wt whose weights it multiplies with.
+// Builds the plan with one workgroup of at least MOE_MAX_EXPERTS threads (a whole power of two), all of which must
+// call this: thread e brings group e's row count c (0: not listed; threads past the last group bring 0), its first
+// row st and the expert wt whose weights it multiplies with.  The E x E comparisons are dealt to all threads
+// (thread: group, slice of the others); walked by one thread per group they took 5.5 us for E = 64.
 __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st, int wt, int E, int bm0, int bm1, int choice,
                                            int32_t* __restrict__ plan) {
     if (e < MOE_MAX_EXPERTS) {
         s.cnt[e] = c;
         s.tiles0[e] = (c + bm0 - 1) / bm0;
         s.tiles1[e] = (c + bm1 - 1) / bm1;
+        s.rank[e] = s.rows[e] = s.pre0[e] = s.pre1[e] = 0;
     }
-    __syncthreads();
-    // the loops below read the shared arrays four entries at a time; entries from E on hold zeros / -1
-    const int E4 = (E + 3) / 4;
-    int r = 0;
-    if (c > 0) {
-        const int4* cnt4 = reinterpret_cast<const int4*>(s.cnt);
-        for (int q = 0; q < E4; ++q) {
-            const int4 co = cnt4[q];
-            const int o = 4 * q;
-            r += ((co.x > c) | ((co.x == c) & (o < e))) + ((co.y > c) | ((co.y == c) & (o + 1 < e))) +
-                 ((co.z > c) | ((co.z == c) & (o + 2 < e))) + ((co.w > c) | ((co.w == c) & (o + 3 < e)));
+    const int n = __syncthreads_count(c > 0);
+    int ebits = 0;
+    while ((1 << ebits) < E) ++ebits;
+    const int EP = 1 << ebits, me = e & (EP - 1), slices = (int)blockDim.x >> ebits;
+    int r = 0, rows = 0, t0 = 0, t1 = 0;
+    if (me < E && s.cnt[me] > 0) {
+        const int mine = s.cnt[me];
+#pragma unroll 4
+        for (int o = e >> ebits; o < E; o += slices) {
+            const int co = s.cnt[o], a = s.tiles0[o], b = s.tiles1[o];
+            const bool first = (co > mine) | ((co == mine) & (o < me));       // false for a group without rows
+            r += first;
+            rows += first ? co : 0;
+            t0 += first ? a : 0;
+            t1 += first ? b : 0;
         }
     }
-    if (e < MOE_MAX_EXPERTS) s.rank[e] = (c > 0) ? r : -1;
+    for (int m = EP; m < 64; m <<= 1) {
+        r += __shfl_xor(r, m, 64);
+        rows += __shfl_xor(rows, m, 64);
+        t0 += __shfl_xor(t0, m, 64);
+        t1 += __shfl_xor(t1, m, 64);
+    }
+    if (me < E && (e & 63) < EP) {
+        atomicAdd(&s.rank[me], r);
+        atomicAdd(&s.rows[me], rows);
+        atomicAdd(&s.pre0[me], t0);
+        atomicAdd(&s.pre1[me], t1);
+    }
     __syncthreads();
     if (c > 0) {
-        int t0 = 0, t1 = 0;
-        const int4* rank4 = reinterpret_cast<const int4*>(s.rank);
-        const int4* tl0 = reinterpret_cast<const int4*>(s.tiles0);
-        const int4* tl1 = reinterpret_cast<const int4*>(s.tiles1);
-        for (int q = 0; q < E4; ++q) {
-            const int4 ro = rank4[q], a = tl0[q], b = tl1[q];
-            const bool k0 = (ro.x >= 0) & (ro.x < r), k1 = (ro.y >= 0) & (ro.y < r), k2 = (ro.z >= 0) & (ro.z < r), k3 = (ro.w >= 0) & (ro.w < r);
-            t0 += (k0 ? a.x : 0) + (k1 ? a.y : 0) + (k2 ? a.z : 0) + (k3 ? a.w : 0);
-            t1 += (k0 ? b.x : 0) + (k1 ? b.y : 0) + (k2 ? b.z : 0) + (k3 ? b.w : 0);
-        }
+        r = s.rank[e];
+        t0 = s.pre0[e];
+        t1 = s.pre1[e];
         plan[kPlanExpert + r] = wt;
         plan[kPlanStart + r] = st;
         plan[kPlanCount + r] = c;
         plan[kPlanTiles0 + r] = t0;
         plan[kPlanTiles1 + r] = t1;
-    }
-    if (e == 0) {
-        int n = 0, t0 = 0, t1 = 0;
-        long long rows = 0;
-        const int4* cnt4 = reinterpret_cast<const int4*>(s.cnt);
-        const int4* tl0 = reinterpret_cast<const int4*>(s.tiles0);
-        const int4* tl1 = reinterpret_cast<const int4*>(s.tiles1);
-        for (int q = 0; q < E4; ++q) {
-            const int4 co = cnt4[q], a = tl0[q], b = tl1[q];
-            n += (co.x > 0) + (co.y > 0) + (co.z > 0) + (co.w > 0);
-            rows += (long long)co.x + co.y + co.z + co.w;
-            t0 += a.x + a.y + a.z + a.w;
-            t1 += b.x + b.y + b.z + b.w;
+        if (r == n - 1) {                                // the last listed group knows the totals
+            t0 += s.tiles0[e];
+            t1 += s.tiles1[e];
+            plan[0] = n;
+            plan[1] = t0;
+            plan[2] = t1;
+            plan[3] = choice >= 0 ? choice : ((long long)s.rows[e] + c >= (long long)kLargeBucketRows * n ? 0 : 1);
+            plan[kPlanTiles0 + n] = t0;
+            plan[kPlanTiles1 + n] = t1;
         }
-        plan[0] = n;
-        plan[1] = t0;
-        plan[2] = t1;
-        plan[3] = choice >= 0 ? choice : (rows >= (long long)kLargeBucketRows * n ? 0 : 1);
-        plan[kPlanTiles0 + n] = t0;
-        plan[kPlanTiles1 + n] = t1;
+    } else if (n == 0 && e == 0) {
+        plan[0] = plan[1] = plan[2] = 0;
+        plan[3] = choice >= 0 ? choice : 0;
+        plan[kPlanTiles0] = plan[kPlanTiles1] = 0;
     }
 }
 

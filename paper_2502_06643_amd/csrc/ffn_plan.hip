@@ -2,7 +2,8 @@
 
 namespace moe {
 
-__global__ __launch_bounds__(256) void ffn_plan_kernel(const int32_t* __restrict__ counts, const int32_t* __restrict__ starts,
+constexpr int kPlanThreads = 1024;
+__global__ __launch_bounds__(kPlanThreads) void ffn_plan_kernel(const int32_t* __restrict__ counts, const int32_t* __restrict__ starts,
                                                        const int32_t* __restrict__ placement, int local_gpu,
                                                        const int32_t* __restrict__ group_expert, int n_weights, int E, int N,
                                                        int bm0, int bm1, int choice, int32_t* __restrict__ plan) {
@@ -35,7 +36,7 @@ PlanShape ffn_plan_shape(moe_dtype_t dt, int N, int E, bool every_row_resident) 
 int launch_ffn_plan(const int32_t* counts, const int32_t* starts, const int32_t* placement, int local_gpu,
                     const int32_t* group_expert, int n_weights, int E, int N, const PlanShape& shape, int32_t* plan, hipStream_t s) {
     LaunchTimer timer(MOE_K_FFN_PLAN, s);
-    hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(256), 0, s, counts, starts, placement, local_gpu, group_expert, n_weights, E, N,
+    hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, counts, starts, placement, local_gpu, group_expert, n_weights, E, N,
                        shape.bm0, shape.bm1, shape.choice, plan);
     return check_launch("moe_expert_ffn_grouped plan launch");
 }

@@ -62,8 +62,7 @@ __global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
         if (ok && (m & lower) == 0ull) atomicAdd(&s.woff[wave][ex], __popcll(m));       // first lane of the group
     }
     __syncthreads();
-    index_totals(s, E);
-    if (blockIdx.x == 0) index_write_tables(s, E, a.G, a.expert_counts, a.expert_start, a.gpu_counts, a.gpu_offsets);
+    index_totals(s, E, a.ebits);
     // ... and walks it as far as this workgroup's own routes reach
     const int own0 = t0 * k, own1 = t1 * k;
     if (wbase < own1 && own0 < wend) {
@@ -97,6 +96,7 @@ __global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
     }
     for (int u = tid + kFrontPrefetch * kIndexThreads; u < units; u += kIndexThreads) put(u, rows[u]);
 
+    if (blockIdx.x == 0) index_write_tables(s, E, a.G, a.expert_counts, a.expert_start, a.gpu_counts, a.gpu_offsets);
     if (blockIdx.x == gridDim.x - 1) {
         int c = 0, st = 0;
         if (tid < E && (a.local_gpu < 0 || s.pl[tid] == a.local_gpu)) {

@@ -92,6 +92,17 @@ def test_large_batches_take_the_multi_workgroup_path(lib, T, E, k, G):
     check(lib, None, synth.random_topk_idx(T % 1000 + E, T, E, k), pl, G)
 
 
+@pytest.mark.parametrize("T,E,k,G", [(262144, 8, 1, 4), (262145, 3, 1, 2),      # one 64-route step per wavefront, and the first with two
+                                     (1048576, 5, 2, 256), (1048577, 8, 2, 4),  # eight steps: ranks in registers; nine: they wait in inv_perm
+                                     (150000, 129, 3, 7), (5000, 256, 16, 200)])
+def test_chunk_edges_of_the_multi_workgroup_path(lib, T, E, k, G):
+    """Every route counted once and ranked stably where the chunk geometry changes, with many experts and GPUs."""
+    rng = np.random.default_rng(T + E)
+    pl = rng.integers(0, G, E).astype(np.int32)
+    idx = np.minimum((rng.random((T, k)) ** 2 * E).astype(np.int32), E - 1)
+    check(lib, None, idx, pl, G)
+
+
 @pytest.mark.parametrize("name", ["c2", "c2b", "c3", "c4", "c5"])
 def test_config_shapes_full_size(lib, name):
     """Full-size batches with the skewed routing of the benchmark configs

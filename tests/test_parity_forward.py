@@ -26,6 +26,10 @@ OUTPUTS = ("topk_idx", "topk_w", "send_buf", "perm", "inv_perm", "expert_counts"
     ("bf16", 6144, 4096, 64, 8, 2, 1, -1),        # 12288 routes again, more rows per workgroup than are prefetched
     ("bf16", 512, 64, 64, 200, 1, 3, -1),         # eight gate passes of 16 lanes per token
     ("bf16", 8192, 64, 64, 3, 1, 1, -1),          # 32 tokens per workgroup
+    ("bf16", 8193, 64, 64, 3, 2, 2, 1),           # the plan comes from the one-workgroup index kernel: 16386 routes are past it, ...
+    ("bf16", 8192, 64, 64, 100, 2, 5, 1),         # ... 16384 the last
+    ("bf16", 20000, 64, 64, 256, 2, 256, 255),    # ... and from the rank kernel, widest tables
+    ("f32", 9000, 16, 16, 8, 2, 1, -1),
     ("f32", 1, 4, 4, 1, 1, 1, -1),
     ("f32", 256, 128, 256, 8, 2, 4, 0),
     ("f32", 1025, 36, 100, 9, 2, 2, 1),

@@ -199,7 +199,7 @@ static int check_dispatch_args(const char* who, const void* x, moe_dtype_t dt, c
     return MOE_OK;
 }
 
-static const PlanTask kNoPlan = {nullptr, -1, {1, 1, 0}};
+static const PlanTask kNoPlan = {nullptr, -1, {1, 1, 0, 0, 0, 0}};
 
 int moe_dispatch(const void* x, moe_dtype_t dt, const int32_t* topk_idx, int T, int d, int E, int k,
                  const int32_t* placement, int G, void* send_buf, int32_t* perm, int32_t* inv_perm,
@@ -392,7 +392,8 @@ int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T,
         return fail(MOE_ERR_WORKSPACE, "%s: dispatch workspace %zu < %zu bytes", who, dispatch_workspace_bytes,
                     moe_dispatch_workspace_bytes(T, E, k));
     hipStream_t s = (hipStream_t)stream;
-    const PlanTask pt = {(int32_t*)ffn_workspace, local_gpu, ffn_plan_shape(dt, N, E, local_gpu < 0)};
+    PlanTask pt = {(int32_t*)ffn_workspace, local_gpu, {}};
+    if ((rc = ffn_plan_shape(dt, N, d, f, E, local_gpu < 0, &pt.shape)) != MOE_OK) return rc;
     if (front_fits(T, E, k)) {
         FrontArgs a;
         a.x = (const uint4*)x; a.logits = logits; a.T = T; a.E = E; a.k = k; a.G = G; a.local_gpu = local_gpu;

@@ -41,8 +41,10 @@ int launch_gate(const float* logits, int T, int E, int k, bool all_norm, int32_t
 constexpr int kDispatchBlock = 256;
 constexpr int kDispatchItems = 4;
 void dispatch_geometry(long long N, int* items, int* nblocks);      // of the workspace: routes per thread and number of chunks
-// How the expert FFN wants its tile plan built for N rows in E groups (arguments of launch_ffn_plan).
-struct PlanShape { int bm0, bm1, choice; };
+// How the expert FFN wants its tile plan built for N rows in E groups: the two tile heights, which of them (see
+// launch_ffn_plan), and the column and k tiles of the down projection and the compute units per XCD (kt_down = 0: the
+// path that follows does not split it).
+struct PlanShape { int bm0, bm1, choice, nt_down, kt_down, cus_per_xcd; };
 // The tile plan as a by-product of the dispatch's index kernels, which hold all it needs; plan == NULL: none wanted.
 struct PlanTask { int32_t* plan; int local_gpu; PlanShape shape; };
 int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T, int E, int k,
@@ -82,7 +84,8 @@ size_t packed_bytes_bf16(int E, int d, int f);
 size_t ffn_bf16_scratch_bytes();      // fp32 partial tiles of the split tail, sized for the largest supported XCD
 int launch_pack_f32(const float* w1, const float* w3, const float* w2, int E, int d, int f, float* packed, hipStream_t s);
 int launch_pack_bf16(const void* w1, const void* w3, const void* w2, int E, int d, int f, void* packed, hipStream_t s);
-PlanShape ffn_plan_shape(moe_dtype_t dt, int N, int E, bool every_row_resident);
+int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_resident, PlanShape* shape);
+int ffn_bf16_device_setup(int* cus_per_xcd);      // of the tiled bf16 kernels, done by the first call on a device
 // E row groups (counts/starts); group g uses the weights of expert group_expert[g] of n_weights
 // (g itself when group_expert is NULL).  plan_ready: the plan has been built already (ffn_plan_shape's way)
 int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* packed, const int32_t* counts,

@@ -71,14 +71,14 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
         c = s.tot[e];
         st = s.start[e];
     }
-    build_plan(scratch, e, c, st, e, E, pt.shape.bm0, pt.shape.bm1, pt.shape.choice, pt.plan);
+    build_plan(scratch, e, c, st, e, E, pt.shape, pt.plan);
 }
 
 // Ranks the routes of one chunk.  Latency-bound: every workgroup adds up all chunks' histograms for itself
 // (at most kRankChunks x E counts, L2 hits, independent loads) instead of waiting for a scan kernel of one
 // workgroup, whose two dependent walks over up to 1024 histograms took 22 us at E = 64 (600 k routes; count, scan
 // and rank 34 us, count and rank now 12 us) and 6.6 us at E = 8 (2 M routes: 25 -> 18 us).
-// Workgroup 0 writes the tables, the last workgroup the tile plan when one is wanted.
+// The first workgroup also writes the tables; when a tile plan is wanted, it has no chunk and writes that too.
 constexpr int kRankBatch = 8;            // 64-route steps of a wavefront whose expert ids are in registers together
 __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits, int steps,
                                                                       const int32_t* __restrict__ block_counts,
@@ -93,7 +93,8 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
     __shared__ PlanScratch plan_scratch;
     __shared__ int before[MOE_MAX_EXPERTS];              // routes of each expert in the chunks before this one
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const long long wbase = ((long long)blockIdx.x * kIndexWaves + wave) * 64 * steps;
+    const int extra = pt.plan != nullptr ? 1 : 0, chunks = (int)gridDim.x - extra, chunk = (int)blockIdx.x - extra;
+    const long long wbase = chunk < 0 ? N : ((long long)chunk * kIndexWaves + wave) * 64 * steps;
     const unsigned long long lower = (1ull << lane) - 1ull;
     int exs[kRankBatch], loc[kRankBatch];                // expert of a route, its rank among the wavefront's routes of that expert
     auto load = [&](int i0) {
@@ -117,17 +118,17 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
     int all = 0, mine = 0;
     if (he < E) {
         const int slices = kIndexThreads >> ebits;
-        for (int b0 = threadIdx.x >> ebits; b0 < (int)gridDim.x; b0 += 16 * slices) {
+        for (int b0 = threadIdx.x >> ebits; b0 < chunks; b0 += 16 * slices) {
             int c[16];                                   // sixteen loads in flight (E = 64: all of them)
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
                 const int b = b0 + u * slices;
-                c[u] = b < (int)gridDim.x ? block_counts[(size_t)b * E + he] : 0;
+                c[u] = b < chunks ? block_counts[(size_t)b * E + he] : 0;
             }
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
                 all += c[u];
-                mine += b0 + u * slices < (int)blockIdx.x ? c[u] : 0;
+                mine += b0 + u * slices < chunk ? c[u] : 0;
             }
         }
     }
@@ -174,8 +175,9 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
             inv_perm[r] = pos;
         }
     }
-    if (blockIdx.x == 0) index_write_tables(s, E, G, expert_counts, expert_start, gpu_counts, gpu_offsets);
-    if (pt.plan != nullptr && blockIdx.x == gridDim.x - 1) plan_from_tables(s, plan_scratch, E, pt);
+    if (blockIdx.x != 0) return;
+    if (pt.plan != nullptr) plan_from_tables(s, plan_scratch, E, pt);
+    index_write_tables(s, E, G, expert_counts, expert_start, gpu_counts, gpu_offsets);
 }
 
 // Batches of up to kFusedMaxRoutes routes: count and rank in ONE workgroup of 16 wavefronts, each
@@ -303,7 +305,7 @@ int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T
         }
         {
             LaunchTimer timer(MOE_K_DISPATCH_RANK, s);
-            hipLaunchKernelGGL(dispatch_rank_kernel, dim3(chunks), dim3(kIndexThreads), 0, s, topk_idx, N, E, ebits, steps, block_counts,
+            hipLaunchKernelGGL(dispatch_rank_kernel, dim3(chunks + (plan_task.plan != nullptr ? 1 : 0)), dim3(kIndexThreads), 0, s, topk_idx, N, E, ebits, steps, block_counts,
                                placement, G, expert_counts, expert_start, gpu_counts, gpu_offsets, perm, inv_perm, plan_task);
             if ((rc = check_launch("moe_dispatch rank launch")) != MOE_OK) return rc;
         }

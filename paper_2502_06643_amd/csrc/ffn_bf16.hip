@@ -193,13 +193,17 @@ __device__ __forceinline__ int active_blocks(int rows, int wave_m, int fm) {
 // k tile in the older wavefronts' streams both projections gained 2-3 %; the younger four as loaders
 // lost 10 %, two loaders instead of four 25 %.
 // A loader's activation pieces are 8-row chunks NL * 8 rows apart: their per-lane offsets differ by a
-// constant (the swizzle term of a row depends on the chunk's parity only, which NL = 4 preserves), so one
-// offset register serves all of them; offsets past the bucket's last row are clamped into that row.
+// constant (the swizzle term of a row depends on the chunk's parity only, which NL = 4 preserves), so with
+// consecutive rows one offset register serves all of them and offsets past the bucket's last row are clamped into
+// that row.  The rows of a merged bucket (MERGED; 256-row tiles only, whose accumulators leave the registers) lie
+// anywhere: one offset per piece.
 constexpr int NL = 4;
-template <int FM>
+template <int FM, bool MERGED>
 struct Loader {
     static constexpr int A_PER_L = Tile<FM>::A_CHUNKS / NL, B_PER_L = B_CHUNKS / NL;
-    uint32_t a_voff0, a_vmax, a_step, b_voff0;
+    static_assert(!MERGED || FM == 2, "no registers for the offsets");
+    uint32_t a_voff0, a_vmax, a_step, b_voff0;               // a_voff0, a_vmax, a_step: rows that follow each other
+    uint32_t a_voff[MERGED ? A_PER_L : 1];                   // MERGED
     const uint16_t* Abase;
     const uint16_t* Bbase;
     uint32_t lds;
@@ -208,7 +212,7 @@ struct Loader {
     // tile ktb into weight stage sb
     __device__ __forceinline__ void issue(int j, int kta, int ktb, int sa, int sb) const {
         if (j < A_PER_L)
-            dma16(min(a_voff0 + (uint32_t)j * a_step, a_vmax), Abase + (size_t)kta * BK,
+            dma16(MERGED ? a_voff[MERGED ? j : 0] : min(a_voff0 + (uint32_t)j * a_step, a_vmax), Abase + (size_t)kta * BK,
                   lds + (uint32_t)sa * (Tile<FM>::A_STAGE * 2) + j * NL * 1024);
         else
             dma16(b_voff0, Bbase + (size_t)ktb * (BK * BN) + (size_t)(j - A_PER_L) * (NL * 512),
@@ -225,10 +229,10 @@ struct Loader {
 // Fragments are streamed: the weight fragment of the next column is read while the current column
 // multiplies, and each activation fragment of the next 32 k is read into place right after its last
 // use, so that a matrix instruction rarely waits for LDS.  The schedule is pinned.
-template <int FM, int NF, bool LOADER>
-__device__ __forceinline__ void ktile(f32x4 (&acc)[2 * FM][FN], const uint16_t* As, const uint16_t* Bs, const Loader<FM>& ld,
+template <int FM, int NF, bool LOADER, bool MERGED>
+__device__ __forceinline__ void ktile(f32x4 (&acc)[2 * FM][FN], const uint16_t* As, const uint16_t* Bs, const Loader<FM, MERGED>& ld,
                                       int kta, int ktb, int sa, int sb, int wave_m, int wave_n, int lane) {
-    constexpr int N_DMA = Loader<FM>::N_DMA, NR = 2 * NF;
+    constexpr int N_DMA = Loader<FM, MERGED>::N_DMA, NR = 2 * NF;
     constexpr int SLOTS = KB * NR * FN / kDmaEvery;
     constexpr int UPFRONT = N_DMA > SLOTS ? N_DMA - SLOTS : 0;
     // kta / ktb are the k tiles to fetch (into stages sa / sb), clamped to the last one: near the end the
@@ -277,11 +281,11 @@ __device__ __forceinline__ void ktile(f32x4 (&acc)[2 * FM][FN], const uint16_t* 
 }
 
 // the k loop of a wavefront with NF active 32-row blocks (NF = 0: it only fetches its share of the tiles)
-template <int FM, int NF, bool LOADER>
-__device__ __forceinline__ void kloop(f32x4 (&acc)[2 * FM][FN], const uint16_t* smem, const Loader<FM>& ld, const WorkItem& w,
+template <int FM, int NF, bool LOADER, bool MERGED>
+__device__ __forceinline__ void kloop(f32x4 (&acc)[2 * FM][FN], const uint16_t* smem, const Loader<FM, MERGED>& ld, const WorkItem& w,
                                       int wave_m, int wave_n, int lane) {
-    constexpr int NSB = Tile<FM>::NSB, A_STAGE = Tile<FM>::A_STAGE, B_STAGE = Tile<FM>::B_STAGE, N_DMA = Loader<FM>::N_DMA;
-    static_assert(Loader<FM>::B_PER_L == 8, "the wait below leaves eight weight pieces in flight");
+    constexpr int NSB = Tile<FM>::NSB, A_STAGE = Tile<FM>::A_STAGE, B_STAGE = Tile<FM>::B_STAGE, N_DMA = Loader<FM, MERGED>::N_DMA;
+    static_assert(Loader<FM, MERGED>::B_PER_L == 8, "the wait below leaves eight weight pieces in flight");
     const uint16_t* smem_b = smem + NS * A_STAGE;
     const int last = w.kt1 - 1;
     int sa = 0, sb = 0;
@@ -294,7 +298,7 @@ __device__ __forceinline__ void kloop(f32x4 (&acc)[2 * FM][FN], const uint16_t* 
         const int kta = min(kt + 1, last), ktb = min(kt + NSB - 1, last);
         const int sa_next = sa ^ 1, sb_next = sb == 0 ? NSB - 1 : sb - 1;      // (sb + NSB - 1) % NSB: the stage of tile kt-1
         if (NF > 0) {
-            ktile<FM, (NF > 0 ? NF : 1), LOADER>(acc, smem + sa * A_STAGE, smem_b + sb * B_STAGE, ld, kta, ktb, sa_next, sb_next,
+            ktile<FM, (NF > 0 ? NF : 1), LOADER, MERGED>(acc, smem + sa * A_STAGE, smem_b + sb * B_STAGE, ld, kta, ktb, sa_next, sb_next,
                                                  wave_m, wave_n, lane);
         } else if (LOADER) {
 #pragma unroll
@@ -306,14 +310,15 @@ __device__ __forceinline__ void kloop(f32x4 (&acc)[2 * FM][FN], const uint16_t* 
 }
 
 // acc += A[row0 .. row0+rows, k tiles kt0..kt1) * B(tile), everything through LDS
-template <int FM>
+template <int FM, bool MERGED>
 __device__ __forceinline__ void mainloop(f32x4 (&acc)[2 * FM][FN], uint16_t* smem, const uint16_t* __restrict__ A,
-                                         const uint16_t* __restrict__ Bbase, int K, const WorkItem& w, int wave, int lane,
-                                         int nfrag) {
-    constexpr int N_DMA = Loader<FM>::N_DMA;
+                                         const uint16_t* __restrict__ Bbase, int K, const WorkItem& w, const RowMap& rm, int wave,
+                                         int lane, int nfrag) {
+    constexpr int N_DMA = Loader<FM, MERGED>::N_DMA;
     const int wave_m = wave / WN, wave_n = wave % WN;
-    Loader<FM> ld;
-    ld.Abase = A + (size_t)w.row0 * K;
+    Loader<FM, MERGED> ld;
+    const bool merged = MERGED && rm.off != nullptr;
+    ld.Abase = merged ? A : A + (size_t)rm.row0 * K;
     ld.Bbase = Bbase + (size_t)(wave % NL) * 512;
     ld.lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem + (uint32_t)(wave % NL) * 1024u;
     {
@@ -322,6 +327,13 @@ __device__ __forceinline__ void mainloop(f32x4 (&acc)[2 * FM][FN], uint16_t* sme
         ld.a_vmax = (uint32_t)(w.rows - 1) * (uint32_t)K * 2u + 112u;   // rows past the bucket re-read the end of its last row
         ld.a_step = (uint32_t)(NL * 8) * (uint32_t)K * 2u;
         ld.b_voff0 = (uint32_t)lane * 16u;
+        if (MERGED) {
+#pragma unroll
+            for (int j = 0; j < (MERGED ? Loader<FM, MERGED>::A_PER_L : 1); ++j) {
+                const int rj = min(r + j * NL * 8, w.rows - 1);
+                ld.a_voff[j] = (uint32_t)(merged ? buffer_row(rm, rj) : rj) * (uint32_t)K * 2u + (uint32_t)swz(r, lane & 7) * 16u;
+            }
+        }
     }
     const bool loader = wave < NL;
     if (loader) {
@@ -329,13 +341,13 @@ __device__ __forceinline__ void mainloop(f32x4 (&acc)[2 * FM][FN], uint16_t* sme
         for (int j = 0; j < N_DMA; ++j) ld.issue(j, w.kt0, w.kt0, 0, 0);
         if (Tile<FM>::NSB == 3) {
 #pragma unroll
-            for (int j = Loader<FM>::A_PER_L; j < N_DMA; ++j) ld.issue(j, w.kt0, min(w.kt0 + 1, w.kt1 - 1), 0, 1);
+            for (int j = Loader<FM, MERGED>::A_PER_L; j < N_DMA; ++j) ld.issue(j, w.kt0, min(w.kt0 + 1, w.kt1 - 1), 0, 1);
         }
     }
 #define KLOOP(NFV)                                                              \
-    do {                                                                        \
-        if (loader) kloop<FM, NFV, true>(acc, smem, ld, w, wave_m, wave_n, lane); \
-        else kloop<FM, NFV, false>(acc, smem, ld, w, wave_m, wave_n, lane);       \
+    do {                                                                                \
+        if (loader) kloop<FM, NFV, true, MERGED>(acc, smem, ld, w, wave_m, wave_n, lane); \
+        else kloop<FM, NFV, false, MERGED>(acc, smem, ld, w, wave_m, wave_n, lane); \
     } while (0)
     if (nfrag == FM) KLOOP(FM);
     else if (FM >= 2 && nfrag == FM - 1) KLOOP((FM >= 2 ? FM - 1 : 0));
@@ -351,7 +363,7 @@ __device__ __forceinline__ void mainloop(f32x4 (&acc)[2 * FM][FN], uint16_t* sme
 // multiplied.  Row block 0 of every wavefront row covers the tile (rows 32 * wave_m .. +31).  Used by the
 // up projection only: in the down projection it gained at some batch sizes and lost at others (the small
 // tiles then take bandwidth from the large bucket's tiles, which finish last).
-constexpr int kSmallRows = 128, kSmallStages = 3;
+constexpr int kSmallRows = kSmallTileRows, kSmallStages = 3;
 constexpr int kSmallAChunks = kSmallRows / 8, kSmallAPerWave = kSmallAChunks / NW;
 constexpr int kSmallStage = (kSmallRows + BN) * BK;                     // elements per stage
 constexpr int kSmallDma = kSmallAPerWave + B_PER_WAVE;                   // pieces per wavefront and k tile
@@ -359,18 +371,20 @@ static_assert(kSmallDma == 6, "the wait below counts six pieces per k tile");
 
 template <int FM>
 __device__ __forceinline__ void mainloop_small(f32x4 (&acc)[2 * FM][FN], uint16_t* smem, const uint16_t* __restrict__ A,
-                                               const uint16_t* __restrict__ Bbase, int K, const WorkItem& w, int wave, int lane,
-                                               bool has_rows) {
+                                               const uint16_t* __restrict__ Bbase, int K, const WorkItem& w, const RowMap& rm,
+                                               int wave, int lane, bool has_rows) {
     const int wave_m = wave / WN, wave_n = wave % WN;
+    const bool merged = rm.off != nullptr;
     uint32_t a_voff[kSmallAPerWave], b_voff[B_PER_WAVE];
 #pragma unroll
     for (int j = 0; j < kSmallAPerWave; ++j) {
         const int r = (wave + j * NW) * 8 + (lane >> 3);
-        a_voff[j] = (uint32_t)min(r, w.rows - 1) * (uint32_t)K * 2u + (uint32_t)swz(r, lane & 7) * 16u;
+        const int rj = min(r, w.rows - 1);
+        a_voff[j] = (uint32_t)(merged ? buffer_row(rm, rj) : rj) * (uint32_t)K * 2u + (uint32_t)swz(r, lane & 7) * 16u;
     }
 #pragma unroll
     for (int j = 0; j < B_PER_WAVE; ++j) b_voff[j] = (uint32_t)(wave + j * NW) * 1024u + (uint32_t)lane * 16u;
-    const uint16_t* Abase = A + (size_t)w.row0 * K;
+    const uint16_t* Abase = merged ? A : A + (size_t)rm.row0 * K;
     const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem + (uint32_t)wave * 1024u;
     auto issue_tile = [&](int kt, int st) {
         const uint32_t l = lds + (uint32_t)st * (kSmallStage * 2);
@@ -423,7 +437,8 @@ __device__ __forceinline__ void mainloop_small(f32x4 (&acc)[2 * FM][FN], uint16_
 // One 32-row block (two fragment rows, blk[0] and blk[1]) whose first tile row is row_base:
 template <bool UP>
 __device__ __forceinline__ void epilogue_block(const f32x4 (&blk0)[FN], const f32x4 (&blk1)[FN], int row_base, uint16_t* smem,
-                                               uint16_t* __restrict__ C, int ldc, const WorkItem& w, int wave, int lane) {
+                                               uint16_t* __restrict__ C, int ldc, const WorkItem& w, const RowMap& rm, int wave,
+                                               int lane) {
     constexpr int OUTC = UP ? WTN / 2 : WTN;          // output columns of this wavefront
     constexpr int RS = OUTC + 8;                      // staging row stride (elements); the pad staggers the banks
     constexpr int CPR = OUTC / 8;                     // 16-byte chunks per row
@@ -456,17 +471,17 @@ __device__ __forceinline__ void epilogue_block(const f32x4 (&blk0)[FN], const f3
         const int r = it * RPI + lane / CPR;
         const int gr = row_base + r;
         if (gr < w.rows && col < ldc)
-            *reinterpret_cast<u32x4*>(C + (size_t)(w.row0 + gr) * ldc + col) =
+            *reinterpret_cast<u32x4*>(C + (size_t)buffer_row(rm, gr) * ldc + col) =
                 *reinterpret_cast<const u32x4*>(stg + r * RS + (lane % CPR) * 8);
     }
 }
 
 template <bool UP, int FM>
 __device__ __forceinline__ void epilogue(const f32x4 (&acc)[2 * FM][FN], uint16_t* smem, uint16_t* __restrict__ C, int ldc,
-                                         const WorkItem& w, int wave, int lane, int nfrag) {
+                                         const WorkItem& w, const RowMap& rm, int wave, int lane, int nfrag) {
 #pragma unroll
     for (int j = 0; j < FM; ++j)
-        if (j < nfrag) epilogue_block<UP>(acc[2 * j], acc[2 * j + 1], block_row(j, wave / WN), smem, C, ldc, w, wave, lane);
+        if (j < nfrag) epilogue_block<UP>(acc[2 * j], acc[2 * j + 1], block_row(j, wave / WN), smem, C, ldc, w, rm, wave, lane);
 }
 
 template <bool UP>
@@ -480,7 +495,7 @@ constexpr int smem_bytes() {
 }
 
 // one workgroup's tile (or k part of a tile) on row tiles of 128 * FM rows
-template <bool UP, bool SPLIT, int FM>
+template <bool UP, bool SPLIT, int FM, bool MERGED>
 __device__ __forceinline__ void ffn_tile(uint16_t* smem, const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
                                          size_t expert_stride, int K, int npad, uint16_t* __restrict__ C, int ldc,
                                          const int32_t* __restrict__ plan, float* __restrict__ partials, int cus_per_xcd,
@@ -495,6 +510,7 @@ __device__ __forceinline__ void ffn_tile(uint16_t* smem, const uint16_t* __restr
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nfrag = active_blocks(w.rows, wave / WN, FM);   // 32-row blocks of this wavefront that hold rows of the bucket
     const uint16_t* Bbase = Wp + (size_t)w.expert * expert_stride + (size_t)w.nt * ((size_t)K * BN);
+    const RowMap rm = row_map<MERGED>(plan, w.bucket, w.first, w.rows);
 
     f32x4 acc[2 * FM][FN];
 #pragma unroll
@@ -505,44 +521,46 @@ __device__ __forceinline__ void ffn_tile(uint16_t* smem, const uint16_t* __restr
             for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.f;
 
     if (UP && w.rows <= kSmallRows) {
-        mainloop_small<FM>(acc, smem, A, Bbase, K, w, wave, lane, nfrag > 0);
+        mainloop_small<FM>(acc, smem, A, Bbase, K, w, rm, wave, lane, nfrag > 0);
     } else if (UP && FM == 3 && w.rows <= Tile<2>::BM) {
         // a ragged tile of at most 256 rows: no wavefront has a third block, so it runs the loop of the
         // 256-row tiles (same row dealing) with its third weight stage and without the clamped loads of
         // the missing rows (up projection only, like the small tiles: the down projection lost 1.5 % with it)
-        mainloop<2>(reinterpret_cast<f32x4(&)[4][FN]>(acc), smem, A, Bbase, K, w, wave, lane, nfrag);
+        mainloop<2, false>(reinterpret_cast<f32x4(&)[4][FN]>(acc), smem, A, Bbase, K, w, rm, wave, lane, nfrag);
     } else {
-        mainloop<FM>(acc, smem, A, Bbase, K, w, wave, lane, nfrag);
+        mainloop<FM, MERGED>(acc, smem, A, Bbase, K, w, rm, wave, lane, nfrag);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the pieces fetched during the last k tile land in LDS: nothing may follow them there
 
     if (SPLIT && w.partial >= 0) {
         if (nfrag > 0) {
-            // 16 bytes per lane and store: [fragment][thread]; fragments past the bucket's end hold zeros
+            // 16 bytes per lane and store: [fragment][thread]; blocks past the bucket's end are neither written nor read
             f32x4* dst = reinterpret_cast<f32x4*>(partials + (size_t)w.partial * Tile<FM>::kPartialFloats) + tid;
 #pragma unroll
-            for (int a = 0; a < 2 * FM; ++a)
+            for (int a = 0; a < 2 * FM; ++a) {
+                if (a / 2 >= nfrag) break;
 #pragma unroll
                 for (int b = 0; b < FN; ++b) dst[(size_t)(a * FN + b) * kThreads] = acc[a][b];
+            }
         }
         return;
     }
     __syncthreads();                                  // the last tile's fragments have been read by everyone
-    epilogue<UP, FM>(acc, smem, C, ldc, w, wave, lane, nfrag);
+    epilogue<UP, FM>(acc, smem, C, ldc, w, rm, wave, lane, nfrag);
 }
 
 // One launch serves both tile heights: the plan's header says which one this call uses (the host's
 // choice, or the plan kernel's own when only the device knows the bucket sizes), and every workgroup
 // takes that branch.  Registers and LDS are those of the larger tile either way; one workgroup fits a
-// compute unit with both.
-template <bool UP, bool SPLIT>
+// compute unit with both.  MERGED: the plan may have merged the segments of an expert (then it chose the short tiles).
+template <bool UP, bool SPLIT, bool MERGED>
 __global__ __launch_bounds__(kThreads) void ffn_bf16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
                                                             size_t expert_stride, int K, int npad, uint16_t* __restrict__ C,
                                                             int ldc, const int32_t* __restrict__ plan, float* __restrict__ partials,
                                                             int cus_per_xcd, int row_chunk) {
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    if (plan[3] == 0) ffn_tile<UP, SPLIT, 3>(smem, A, Wp, expert_stride, K, npad, C, ldc, plan, partials, cus_per_xcd, row_chunk);
-    else ffn_tile<UP, SPLIT, 2>(smem, A, Wp, expert_stride, K, npad, C, ldc, plan, partials, cus_per_xcd, row_chunk);
+    if (plan[3] == 0) ffn_tile<UP, SPLIT, 3, false>(smem, A, Wp, expert_stride, K, npad, C, ldc, plan, partials, cus_per_xcd, row_chunk);
+    else ffn_tile<UP, SPLIT, 2, MERGED>(smem, A, Wp, expert_stride, K, npad, C, ldc, plan, partials, cus_per_xcd, row_chunk);
 }
 
 // adds the k parts of the split tail tiles in part order and writes the tiles; a workgroup handles
@@ -580,7 +598,7 @@ __global__ __launch_bounds__(kThreads) void ffn_bf16_fixup_kernel(int K, int npa
                 blk[h][b][0] += t[0]; blk[h][b][1] += t[1]; blk[h][b][2] += t[2]; blk[h][b][3] += t[3];
             }
     }
-    epilogue_block<false>(blk[0], blk[1], block_row(j, wave / WN), smem, C, ldc, w, wave, lane);
+    epilogue_block<false>(blk[0], blk[1], block_row(j, wave / WN), smem, C, ldc, w, row_map<true>(plan, w.bucket, w.first, w.rows), wave, lane);
 }
 
 template <typename Kernel>
@@ -592,6 +610,7 @@ static int set_smem(Kernel k, int bytes) {
 struct FfnCall {
     const void* a; int N, d, f, E; const void* packed; void* out; int32_t* plan; void* H; hipStream_t s;
     int cpx, chunk_up, chunk_down;
+    bool merge;
     size_t s13, stride;
     float* partials;
     long long grid_for(size_t npad, int bm, bool split) const { return ffn_grid(N, E, (long long)(npad / BN), bm, split, cpx); }
@@ -601,9 +620,9 @@ template <bool UP>
 constexpr int launch_smem() { return smem_bytes<UP, 3>() > smem_bytes<UP, 2>() ? smem_bytes<UP, 3>() : smem_bytes<UP, 2>(); }
 
 // Per-device set-up, done on the first call on each device (not during a stream capture: it calls
-// hipFuncSetAttribute): the LDS sizes of the three kernels are raised and the compute units per XCD are read.
+// hipFuncSetAttribute): the LDS sizes of the kernels are raised and the compute units per XCD are read.
 // A failure is reported and tried again by the next call rather than remembered.
-static int device_setup(int* cus_per_xcd) {
+int ffn_bf16_device_setup(int* cus_per_xcd) {
     constexpr int kMaxDevices = 64;
     struct Setup { bool done; int cpx; };
     static std::mutex mutex;
@@ -616,8 +635,10 @@ static int device_setup(int* cus_per_xcd) {
     Setup& st = setup[dev];
     if (!st.done) {
         int r, cus = 0;
-        if ((r = set_smem(&ffn_bf16_kernel<true, false>, launch_smem<true>())) != MOE_OK) return r;
-        if ((r = set_smem(&ffn_bf16_kernel<false, true>, launch_smem<false>())) != MOE_OK) return r;
+        if ((r = set_smem(&ffn_bf16_kernel<true, false, false>, launch_smem<true>())) != MOE_OK) return r;
+        if ((r = set_smem(&ffn_bf16_kernel<false, true, false>, launch_smem<false>())) != MOE_OK) return r;
+        if ((r = set_smem(&ffn_bf16_kernel<true, false, true>, launch_smem<true>())) != MOE_OK) return r;
+        if ((r = set_smem(&ffn_bf16_kernel<false, true, true>, launch_smem<false>())) != MOE_OK) return r;
         if ((r = set_smem(&ffn_bf16_fixup_kernel, epilogue_bytes<false>())) != MOE_OK) return r;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
@@ -632,7 +653,8 @@ static int device_setup(int* cus_per_xcd) {
 static int run_up(const FfnCall& c, int bm) {
     const long long grid = c.grid_for(npad13(c.f), bm, false);
     if (grid > 0x7FFFFFFFll) return fail(MOE_ERR_UNSUPPORTED, "moe_expert_ffn_grouped: too many tiles for one launch");
-    hipLaunchKernelGGL((ffn_bf16_kernel<true, false>), dim3((unsigned)grid), dim3(kThreads), (launch_smem<true>()), c.s,
+    const auto kernel = c.merge ? &ffn_bf16_kernel<true, false, true> : &ffn_bf16_kernel<true, false, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreads), (launch_smem<true>()), c.s,
                        (const uint16_t*)c.a, (const uint16_t*)c.packed, c.stride, c.d, (int)npad13(c.f), (uint16_t*)c.H, c.f, c.plan,
                        c.partials, c.cpx, c.chunk_up);
     return check_launch("moe_expert_ffn_grouped up launch");
@@ -642,11 +664,12 @@ static int run_down(const FfnCall& c, int bm, int fm_max) {
     const long long grid = c.grid_for(npad2(c.d), bm, true);
     if (grid > 0x7FFFFFFFll) return fail(MOE_ERR_UNSUPPORTED, "moe_expert_ffn_grouped: too many tiles for one launch");
     const uint16_t* W2 = (const uint16_t*)c.packed + c.s13;
-    hipLaunchKernelGGL((ffn_bf16_kernel<false, true>), dim3((unsigned)grid), dim3(kThreads), (launch_smem<false>()), c.s,
+    const auto kernel = c.merge ? &ffn_bf16_kernel<false, true, true> : &ffn_bf16_kernel<false, true, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreads), (launch_smem<false>()), c.s,
                        (const uint16_t*)c.H, W2, c.stride, c.f, (int)npad2(c.d), (uint16_t*)c.out, c.d, c.plan, c.partials, c.cpx,
                        c.chunk_down);
     int rc = check_launch("moe_expert_ffn_grouped down launch");
-    if (rc != MOE_OK) return rc;
+    if (rc != MOE_OK || !split_can_pay(c.f / BK)) return rc;
     hipLaunchKernelGGL(ffn_bf16_fixup_kernel, dim3(kXcds * c.cpx * fm_max), dim3(kThreads), (epilogue_bytes<false>()), c.s, c.f,
                        (int)npad2(c.d), (uint16_t*)c.out, c.d, c.plan, c.partials, c.cpx, c.chunk_down);
     return check_launch("moe_expert_ffn_grouped fix-up launch");
@@ -655,24 +678,27 @@ static int run_down(const FfnCall& c, int bm, int fm_max) {
 int launch_ffn_bf16(const void* a, int N, int d, int f, int E, const void* packed, const int32_t* counts,
                     const int32_t* starts, const int32_t* placement, int local_gpu, const int32_t* group_expert,
                     int n_weights, void* out, int32_t* plan, bool plan_ready, void* H, CombineTail* tail, hipStream_t s) {
-    const PlanShape shape = ffn_plan_shape(MOE_BF16, N, E, local_gpu < 0 && group_expert == nullptr);
-    int rc;
+    PlanShape shape;
+    int rc = ffn_plan_shape(MOE_BF16, N, d, f, E, local_gpu < 0 && group_expert == nullptr, &shape);
+    if (rc != MOE_OK) return rc;
+    // groups that may share an expert are merged; the row offsets of a merged bucket must fit 32 bits
+    const bool mergeable = group_expert != nullptr && (size_t)N * (d > f ? d : f) * 2 < ((size_t)1 << 32);
+    if (!plan_ready) {
+        rc = launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, shape,
+                             !mergeable ? 0 : (N <= kFfnSkinnyMaxRows ? 1 : 2), plan, s);
+        if (rc != MOE_OK) return rc;
+    }
     if (N <= kFfnSkinnyMaxRows) {
         // decode-sized batch: every weight is read once and hardly used; stream them without LDS or barriers
-        rc = plan_ready ? MOE_OK : launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, shape, plan, s);
-        if (rc != MOE_OK) return rc;
         const size_t s13 = npad13(f) * d, s2 = npad2(d) * f;
         float* partials = (float*)((char*)H + round_up((size_t)N * f * 2, 256));
         return launch_ffn_skinny(a, N, d, f, E, packed, s13, s13 + s2, plan, H, partials, ffn_bf16_scratch_bytes(), out, tail, s);
     }
-    int cpx = 0;
-    if ((rc = device_setup(&cpx)) != MOE_OK) return rc;
-    const int choice = shape.choice;
-    rc = plan_ready ? MOE_OK : launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, shape, plan, s);
-    if (rc != MOE_OK) return rc;
+    const int choice = shape.choice, cpx = shape.cus_per_xcd;
     FfnCall c;
     c.a = a; c.N = N; c.d = d; c.f = f; c.E = E; c.packed = packed; c.out = out; c.plan = plan; c.H = H; c.s = s;
     c.cpx = cpx;
+    c.merge = mergeable;
     c.chunk_up = row_chunk_for((size_t)N * d * 2);
     c.chunk_down = row_chunk_for((size_t)N * f * 2);
     c.s13 = npad13(f) * d;

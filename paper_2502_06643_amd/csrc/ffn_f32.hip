@@ -81,10 +81,12 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
     const int mt_e = prefix[lo + 1] - prefix[lo];
     const int rem = (int)(t - (long long)prefix[lo] * NT);
     const int nt = rem / mt_e, r0 = (rem - nt * mt_e) * kF32Tile;
-    const int rows = min(kF32Tile, plan[kPlanCount + lo] - r0), row0 = plan[kPlanStart + lo] + r0, n0 = nt * kF32Tile;
+    const int rows = min(kF32Tile, plan[kPlanCount + lo] - r0), n0 = nt * kF32Tile;
+    const RowMap rm = row_map<true>(plan, lo, r0, rows);
+    const bool merged = rm.off != nullptr;
     const float* We = packed + (size_t)plan[kPlanExpert + lo] * 3 * d * f;
     const float* Bbase = UP ? We : We + (size_t)2 * d * f;                // W1 (W3 follows it) or W2
-    const float* Abase = A + (size_t)row0 * K;
+    const float* Abase = merged ? A : A + (size_t)rm.row0 * K;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -94,7 +96,8 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
     // multiple of 32 reads the last 32 k and counts those that came before it as zero; a reduction shorter than 32
     // re-reads its last k and counts that as zero.
     const int ar = tid / 8, ak = (tid % 8) * 4, bk = tid / 8, bc = (tid % 8) * 4;
-    const uint32_t a_off = (uint32_t)min(ar, rows - 1) * (uint32_t)K + (uint32_t)min(ak, K - 4);
+    const int arow = min(ar, rows - 1);
+    const uint32_t a_off = (uint32_t)(merged ? buffer_row(rm, arow) : arow) * (uint32_t)K + (uint32_t)min(ak, K - 4);
     const uint32_t b_off = (uint32_t)min(bk, K - 1) * (uint32_t)NC + (uint32_t)min(n0 + bc, NC - 4);
     const int k_last = max(K - kF32Stage, 0);
     struct Regs { float4 a, b[NP]; };
@@ -188,16 +191,22 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
         // accumulator v: row 8 * (v / 4) + 4 * (lane / 32) + v % 4, column lane % 32
         const int r = 8 * wave + 4 * (lane >> 5) + i, c = n0 + (lane & 31);
         const float u = sum[0];
-        if (r < rows && c < NC) C[(size_t)(row0 + r) * NC + c] = UP ? u / (1.0f + expf(-u)) * sum[NP - 1] : u;
+        if (r < rows && c < NC) C[(size_t)buffer_row(rm, r) * NC + c] = UP ? u / (1.0f + expf(-u)) * sum[NP - 1] : u;
     }
 }
 
 int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* packed, const int32_t* counts,
                    const int32_t* starts, const int32_t* placement, int local_gpu, const int32_t* group_expert,
                    int n_weights, float* out, int32_t* plan, bool plan_ready, float* H, hipStream_t s) {
-    int rc = plan_ready ? MOE_OK : launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N,
-                                                   ffn_plan_shape(MOE_F32, N, E, group_expert == nullptr && local_gpu < 0), plan, s);
-    if (rc != MOE_OK) return rc;
+    int rc;
+    if (!plan_ready) {
+        PlanShape shape;
+        if ((rc = ffn_plan_shape(MOE_F32, N, d, f, E, false, &shape)) != MOE_OK) return rc;
+        // groups that may share an expert are merged; the row offsets of a merged bucket must fit 32 bits
+        const bool mergeable = group_expert != nullptr && (size_t)N * (d > f ? d : f) < ((size_t)1 << 32);
+        rc = launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, shape, mergeable, plan, s);
+        if (rc != MOE_OK) return rc;
+    }
     const long long mt_max = (N + kF32Tile - 1) / kF32Tile + (E < N ? E : N);     // sum of ceil(n_e / 32) never exceeds this
     auto grid_for = [&](int columns) { return (mt_max * ((columns + kF32Tile - 1) / kF32Tile) + kF32Xcds - 1) / kF32Xcds * kF32Xcds; };
     if (grid_for(f) > 0x7FFFFFFFll || grid_for(d) > 0x7FFFFFFFll)

@@ -3,11 +3,20 @@
 namespace moe {
 
 constexpr int kPlanThreads = 1024;
+
+struct MergeScratch {
+    int wt[MOE_MAX_EXPERTS], cnt[MOE_MAX_EXPERTS];           // per group
+    int off[MOE_MAX_EXPERTS], idx[MOE_MAX_EXPERTS];          // ... its first row and its number among its bucket's segments
+    int rows[MOE_MAX_EXPERTS], segs[MOE_MAX_EXPERTS];        // per expert
+    int total;
+};
+
 __global__ __launch_bounds__(kPlanThreads) void ffn_plan_kernel(const int32_t* __restrict__ counts, const int32_t* __restrict__ starts,
-                                                       const int32_t* __restrict__ placement, int local_gpu,
-                                                       const int32_t* __restrict__ group_expert, int n_weights, int E, int N,
-                                                       int bm0, int bm1, int choice, int32_t* __restrict__ plan) {
+                                                                const int32_t* __restrict__ placement, int local_gpu,
+                                                                const int32_t* __restrict__ group_expert, int n_weights, int E, int N,
+                                                                PlanShape shape, int merge, int32_t* __restrict__ plan) {
     __shared__ PlanScratch scratch;
+    __shared__ MergeScratch ms;
     const int e = threadIdx.x;
     int c = 0, st = 0, wt = e;                    // wt: whose weights this group multiplies with
     if (e < E) {
@@ -18,26 +27,84 @@ __global__ __launch_bounds__(kPlanThreads) void ffn_plan_kernel(const int32_t* _
         // a bucket that does not lie inside [0,N), or names weights that do not exist, is ignored rather than trusted
         if (!local || c <= 0 || st < 0 || (long long)st + c > N || (unsigned)wt >= (unsigned)n_weights) c = 0;
     }
-    build_plan(scratch, e, c, st, wt, E, bm0, bm1, choice, plan);
+    if (merge != 0) {
+        if (e < MOE_MAX_EXPERTS) {
+            ms.wt[e] = wt;
+            ms.cnt[e] = c;
+            ms.off[e] = ms.idx[e] = ms.rows[e] = ms.segs[e] = 0;
+        }
+        if (e == 0) ms.total = 0;
+        const int n = __syncthreads_count(c > 0);
+        if (c > 0) {
+            atomicAdd(&ms.rows[wt], c);
+            atomicAdd(&ms.segs[wt], 1);
+            atomicAdd(&ms.total, c);
+        }
+        __syncthreads();
+        const int n_buckets = __syncthreads_count(e < MOE_MAX_EXPERTS && ms.segs[e & (MOE_MAX_EXPERTS - 1)] > 0);
+        if (n_buckets == n || (merge == 2 && ms.total >= (long long)kLargeBucketRows * n)) merge = 0;
+    }
+    if (merge == 0) {
+        build_plan(scratch, e, c, st, wt, E, shape, plan);
+        return;
+    }
+    // rows and segments of the same expert in the groups before mine: thread (group, slice of the groups)
+    int ebits = 0;
+    while ((1 << ebits) < E) ++ebits;
+    const int EP = 1 << ebits, me = e & (EP - 1);
+    int off = 0, idx = 0;
+    if (me < E) {
+        const int w = ms.wt[me];
+        for (int o = e >> ebits; o < me; o += kPlanThreads >> ebits) {
+            const int co = ms.cnt[o];
+            const bool same = ms.wt[o] == w && co > 0;
+            off += same ? co : 0;
+            idx += same;
+        }
+    }
+    for (int m = EP; m < 64; m <<= 1) {
+        off += __shfl_xor(off, m, 64);
+        idx += __shfl_xor(idx, m, 64);
+    }
+    if (me < E && (e & 63) < EP) {
+        atomicAdd(&ms.off[me], off);
+        atomicAdd(&ms.idx[me], idx);
+    }
+    if (merge == 2) shape.choice = 1;             // the kernels of the short tiles know how to follow the segments
+    const bool expert = e < n_weights;
+    build_plan(scratch, e, expert ? ms.rows[e] : 0, 0, e, n_weights, shape, plan, true, expert ? ms.segs[e] : 0);
+    if (c > 0) {
+        const int j = scratch.pre_segs[wt] + ms.idx[e];
+        plan[kPlanSegOff + j] = ms.off[e];
+        plan[kPlanSegDelta + j] = st - ms.off[e];
+    }
+    const int n_segs = __syncthreads_count(c > 0);
+    if (e == 0) plan[kPlanSegOff + n_segs] = 0;
 }
 
-PlanShape ffn_plan_shape(moe_dtype_t dt, int N, int E, bool every_row_resident) {
-    if (dt == MOE_F32) return {kF32TileRows, kF32TileRows, 0};
-    if (N <= kFfnSkinnyMaxRows) return {kShortTileRows, kShortTileRows, 0};
+int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_resident, PlanShape* shape) {
+    *shape = {kF32TileRows, kF32TileRows, 0, 0, 0, 0};
+    if (dt == MOE_F32) return MOE_OK;
+    shape->bm0 = shape->bm1 = kShortTileRows;
+    if (N <= kFfnSkinnyMaxRows) return MOE_OK;
     // Row tiles of 384 move about a sixth fewer bytes per flop than tiles of 256, but waste more on
     // ragged buckets and leave compute units idle when there are few tiles: 384 when the resident buckets
     // hold kLargeBucketRows rows or more on average.  When every row is in a resident bucket the host
     // knows that average; otherwise only the device does and the plan decides.  Either way the choice
     // reaches the kernels through the plan's header.
-    const int choice = every_row_resident ? ((long long)N >= (long long)kLargeBucketRows * E ? 0 : 1) : -1;
-    return {kTallTileRows, kShortTileRows, choice};
+    shape->bm0 = kTallTileRows;
+    shape->choice = every_row_resident ? ((long long)N >= (long long)kLargeBucketRows * E ? 0 : 1) : -1;
+    shape->nt_down = (d + 255) / 256;
+    shape->kt_down = split_can_pay(f / 64) ? f / 64 : 0;
+    return ffn_bf16_device_setup(&shape->cus_per_xcd);
 }
 
 int launch_ffn_plan(const int32_t* counts, const int32_t* starts, const int32_t* placement, int local_gpu,
-                    const int32_t* group_expert, int n_weights, int E, int N, const PlanShape& shape, int32_t* plan, hipStream_t s) {
+                    const int32_t* group_expert, int n_weights, int E, int N, const PlanShape& shape, int merge, int32_t* plan,
+                    hipStream_t s) {
     LaunchTimer timer(MOE_K_FFN_PLAN, s);
     hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, counts, starts, placement, local_gpu, group_expert, n_weights, E, N,
-                       shape.bm0, shape.bm1, shape.choice, plan);
+                       shape, merge, plan);
     return check_launch("moe_expert_ffn_grouped plan launch");
 }
 

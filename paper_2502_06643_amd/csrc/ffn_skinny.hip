@@ -36,11 +36,18 @@ constexpr int kSkinnyRows = 64;          // rows per pass (four 16-row fragments
 constexpr int kSkinnyMaxParts = 16;
 constexpr int kSkinnyDownTasks = 512;    // workgroups the down projection is cut into
 
+// k parts of the down projection: two workgroups per compute unit (more, shorter parts were slower), at least 8 k tiles
+// each.  Decided on the device, which knows how many buckets there are.
+__device__ __forceinline__ int skinny_parts(int n_listed, int NT, int max_parts) {
+    const int tasks = n_listed * NT, parts = tasks > 0 ? (kSkinnyDownTasks + tasks - 1) / tasks : 1;
+    return parts < max_parts ? parts : max_parts;
+}
+
 __device__ __forceinline__ bf16x8 as_frag(const uint4& q) { return __builtin_bit_cast(bf16x8, q); }
 
 // one pass over MF * 16 rows starting at bucket row `row0`, k tiles [kt0, kt1)
 template <bool UP, int MF>
-__device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int K, const uint4* __restrict__ Bp, int start, int n,
+__device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int K, const uint4* __restrict__ Bp, const RowMap& rm, int n,
                                             int row0, int kt0, int kt1, int nt, int wave, int lane, int ldc,
                                             uint16_t* __restrict__ H, float* __restrict__ partial) {
     f32x4 acc[MF][4];
@@ -57,7 +64,7 @@ __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int 
 #pragma unroll
     for (int m = 0; m < MF; ++m) {
         const int r = min(row0 + m * 16 + (lane & 15), n - 1);
-        Ap[m] = reinterpret_cast<const uint4*>(A + (size_t)(start + r) * K) + (lane >> 4);
+        Ap[m] = reinterpret_cast<const uint4*>(A + (size_t)buffer_row(rm, r) * K) + (lane >> 4);
     }
     uint4 a[2][MF * 2], b[2][8];
     auto load = [&](int kt, int buf) {
@@ -97,19 +104,20 @@ __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int 
         for (int v = 0; v < 4; ++v) {
             const int r = row0 + m * 16 + 4 * (lane >> 4) + v;
             if (r >= n) continue;
+            const size_t at = buffer_row(rm, r);
             if (UP) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     const int col = nt * 128 + wave * 32 + j * 16 + (lane & 15);
                     const float u = acc[m][2 * j][v], g = acc[m][2 * j + 1][v];
                     const float hv = u * __builtin_amdgcn_rcpf(1.0f + __expf(-u)) * g;    // silu(u) * g
-                    if (col < ldc) H[(size_t)(start + r) * ldc + col] = __builtin_bit_cast(uint16_t, (__bf16)hv);
+                    if (col < ldc) H[at * ldc + col] = __builtin_bit_cast(uint16_t, (__bf16)hv);
                 }
             } else {
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
                     const int col = nt * 256 + wave * 64 + p * 16 + (lane & 15);
-                    if (col < ldc) partial[(size_t)(start + r) * ldc + col] = acc[m][p][v];
+                    if (col < ldc) partial[at * ldc + col] = acc[m][p][v];
                 }
             }
         }
@@ -121,13 +129,15 @@ template <bool UP>
 __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
                                                                     size_t expert_stride, int K, int NT, int ldc,
                                                                     const int32_t* __restrict__ plan, uint16_t* __restrict__ H,
-                                                                    float* __restrict__ partial, int parts, int N) {
-    int task = blockIdx.x;
+                                                                    float* __restrict__ partial, int max_parts, int N) {
+    int task = blockIdx.x, parts = 1;
+    if (!UP) parts = skinny_parts(plan[0], NT, max_parts);
     const int part = UP ? 0 : task % parts;
     if (!UP) task /= parts;
     const int nt = task % NT, i = task / NT;
     if (i >= plan[0]) return;
-    const int e = plan[kPlanExpert + i], start = plan[kPlanStart + i], n = plan[kPlanCount + i];
+    const int e = plan[kPlanExpert + i], n = plan[kPlanCount + i];
+    const RowMap rm = row_map<true>(plan, i, 0, n);
     const int KT = K / 64;
     const int kt0 = UP ? 0 : (int)((long long)part * KT / parts), kt1 = UP ? KT : (int)((long long)(part + 1) * KT / parts);
     const int lane = threadIdx.x & 63;
@@ -137,23 +147,31 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const uin
     float* my_partial = UP ? nullptr : partial + (size_t)part * N * ldc;
     for (int row0 = 0; row0 < n; row0 += kSkinnyRows) {
         const int mf = (min(kSkinnyRows, n - row0) + 15) >> 4;
-        if (mf == 1) skinny_pass<UP, 1>(A, K, Bp, start, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
-        else if (mf == 2) skinny_pass<UP, 2>(A, K, Bp, start, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
-        else if (mf == 3) skinny_pass<UP, 3>(A, K, Bp, start, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
-        else skinny_pass<UP, 4>(A, K, Bp, start, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
+        if (mf == 1) skinny_pass<UP, 1>(A, K, Bp, rm, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
+        else if (mf == 2) skinny_pass<UP, 2>(A, K, Bp, rm, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
+        else if (mf == 3) skinny_pass<UP, 3>(A, K, Bp, rm, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
+        else skinny_pass<UP, 4>(A, K, Bp, rm, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
     }
 }
 
 // out[row] = bf16(sum over parts, in part order) for the rows of the listed buckets; one workgroup per row
-__global__ __launch_bounds__(256) void ffn_skinny_reduce_kernel(const float* __restrict__ partial, int parts, int N, int d,
+__global__ __launch_bounds__(256) void ffn_skinny_reduce_kernel(const float* __restrict__ partial, int max_parts, int NT, int N, int d,
                                                                 const int32_t* __restrict__ plan, uint16_t* __restrict__ out) {
     const int row = blockIdx.x;
-    const int n_listed = plan[0];
+    const int n_listed = plan[0], parts = skinny_parts(n_listed, NT, max_parts);
     bool listed = false;
-    for (int i = 0; i < n_listed; ++i) {
-        const int st = plan[kPlanStart + i];
-        listed |= row >= st && row < st + plan[kPlanCount + i];
+    for (int i = threadIdx.x; i < n_listed; i += 256) {
+        const int st = plan[kPlanStart + i], n = plan[kPlanCount + i];
+        if (!plan[kPlanMerged]) {
+            listed |= row >= st && row < st + n;
+            continue;
+        }
+        for (int j = st; j == st || plan[kPlanSegOff + j] != 0; ++j) {
+            const int next = plan[kPlanSegOff + j + 1], r = row - plan[kPlanSegDelta + j];
+            listed |= r >= plan[kPlanSegOff + j] && r < (next != 0 ? next : n);
+        }
     }
+    listed = __syncthreads_or(listed);
     if (!listed) return;
     for (int c = threadIdx.x * 4; c < d; c += 1024) {
         float4 s = *reinterpret_cast<const float4*>(partial + (size_t)row * d + c);
@@ -171,10 +189,11 @@ __global__ __launch_bounds__(256) void ffn_skinny_reduce_kernel(const float* __r
 // The same sums followed by moe_combine, for a layer that goes on to it: each route's row belongs to one token, so
 // the token's workgroup finishes the rows (and writes them to out, as the reduce does) and weights them into y.
 // One launch instead of two; a workgroup takes one token and 1024 columns.
-__global__ __launch_bounds__(256) void ffn_skinny_combine_kernel(const float* __restrict__ partial, int parts, int N, int d,
-                                                                 CombineTail tail, uint16_t* __restrict__ out) {
+__global__ __launch_bounds__(256) void ffn_skinny_combine_kernel(const float* __restrict__ partial, int max_parts, int NT, int N, int d,
+                                                                 const int32_t* __restrict__ plan, CombineTail tail, uint16_t* __restrict__ out) {
     const int t = blockIdx.x, c = blockIdx.y * 1024 + threadIdx.x * 4;
     if (c >= d) return;
+    const int parts = skinny_parts(plan[0], NT, max_parts);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int j = 0; j < tail.k; ++j) {
         const int r = t * tail.k + j, e = tail.topk_idx[r];
@@ -209,24 +228,24 @@ int launch_ffn_skinny(const void* a, int N, int d, int f, int E, const void* pac
                            expert_stride, d, nt_up, f, plan, (uint16_t*)H, (float*)nullptr, 1, N);
         if ((rc = check_launch("moe_expert_ffn_grouped up launch (small batch)")) != MOE_OK) return rc;
     }
-    // k parts of the down projection: two workgroups per compute unit (more, shorter parts were slower), at least 8 k tiles each
-    int parts = (kSkinnyDownTasks + E * nt_down - 1) / (E * nt_down);
-    parts = parts < 1 ? 1 : (parts > kSkinnyMaxParts ? kSkinnyMaxParts : parts);
-    while (parts > 1 && ((f / 64) / parts < 8 || (size_t)parts * N * d * sizeof(float) > scratch_bytes)) --parts;
-    if ((size_t)parts * N * d * sizeof(float) > scratch_bytes)
+    int max_parts = kSkinnyMaxParts;
+    while (max_parts > 1 && ((f / 64) / max_parts < 8 || (size_t)max_parts * N * d * sizeof(float) > scratch_bytes)) --max_parts;
+    if ((size_t)max_parts * N * d * sizeof(float) > scratch_bytes)
         return fail(MOE_ERR_WORKSPACE, "moe_expert_ffn_grouped: partial sums of %d rows x %d do not fit the workspace", N, d);
+    // n buckets make n * nt_down * skinny_parts workgroups: fewer than kSkinnyDownTasks + n * nt_down, whatever n
+    const int tasks = E * nt_down, grid = tasks * max_parts < tasks + kSkinnyDownTasks ? tasks * max_parts : tasks + kSkinnyDownTasks;
     {
         LaunchTimer timer(MOE_K_FFN_DOWN, s);
-        hipLaunchKernelGGL(ffn_skinny_kernel<false>, dim3((unsigned)(E * nt_down * parts)), dim3(kSkinnyThreads), 0, s,
-                           (const uint16_t*)H, Wp + s13, expert_stride, f, nt_down, d, plan, (uint16_t*)nullptr, partial, parts, N);
+        hipLaunchKernelGGL(ffn_skinny_kernel<false>, dim3((unsigned)grid), dim3(kSkinnyThreads), 0, s,
+                           (const uint16_t*)H, Wp + s13, expert_stride, f, nt_down, d, plan, (uint16_t*)nullptr, partial, max_parts, N);
         if ((rc = check_launch("moe_expert_ffn_grouped down launch (small batch)")) != MOE_OK) return rc;
         if (tail != nullptr) {
             hipLaunchKernelGGL(ffn_skinny_combine_kernel, dim3((unsigned)tail->T, (unsigned)((d + 1023) / 1024)), dim3(256), 0, s, partial,
-                               parts, N, d, *tail, (uint16_t*)out);
+                               max_parts, nt_down, N, d, plan, *tail, (uint16_t*)out);
             tail->done = true;
             return check_launch("moe_layer_forward reduce and combine launch (small batch)");
         }
-        hipLaunchKernelGGL(ffn_skinny_reduce_kernel, dim3((unsigned)N), dim3(256), 0, s, partial, parts, N, d, plan, (uint16_t*)out);
+        hipLaunchKernelGGL(ffn_skinny_reduce_kernel, dim3((unsigned)N), dim3(256), 0, s, partial, max_parts, nt_down, N, d, plan, (uint16_t*)out);
         if ((rc = check_launch("moe_expert_ffn_grouped reduce launch (small batch)")) != MOE_OK) return rc;
     }
     return MOE_OK;

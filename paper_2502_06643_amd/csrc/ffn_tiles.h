@@ -9,14 +9,11 @@
 
 namespace moe {
 
-constexpr int kXcds = 8;
-constexpr int kMaxSplit = 8;
-constexpr int kMinSplitKT = 8;                  // a k part is at least this many k tiles
-constexpr int kMinSplitGain = 16;               // k tiles of time a split tail must save to be worth its fix-up
 constexpr int kMaxCusPerXcd = 48;               // two fp32 partial-tile slots exist per compute unit, for at most this many
 
 struct WorkItem {
     int expert, row0, rows, nt;
+    int bucket, first;   // listed bucket and the tile's first row in it (row0 is the buffer row unless buckets are merged)
     int kt0, kt1;        // k tile range
     int partial;         // slot of the fp32 partial tile, or -1 for a whole tile
 };
@@ -97,6 +94,8 @@ __host__ __device__ __forceinline__ void locate_tile(const int32_t* __restrict__
     w.nt = in_chunk / rows_here;
     const int mt = q * row_chunk + (in_chunk - w.nt * rows_here);
     w.expert = plan[kPlanExpert + i];
+    w.bucket = i;
+    w.first = mt * BM;
     w.row0 = plan[kPlanStart + i] + mt * BM;
     const int rows_left = plan[kPlanCount + i] - mt * BM;
     w.rows = BM < rows_left ? BM : rows_left;
@@ -114,6 +113,72 @@ __host__ __device__ __forceinline__ void locate_xcd_tile(const int32_t* __restri
     }
 }
 
+// A launch whose tiles all run in one round and are cut by cost; the plan says into how many parts (round_split in
+// ffn_plan.h: only with tiles of kShortTileRows rows).
+struct RoundSplit {
+    bool on;
+    int q, rem;               // column tiles owned outright by every XCD; left-over ones
+    int nb, ns;               // row tiles of more than kSmallTileRows rows, and of at most that
+    int big, small;           // k parts of either kind
+    int nbx, nsx;             // tiles of either kind on this XCD
+    int rb0, rs0;             // ... and its first ones in the lists of left-over-column tiles
+};
+
+__host__ __device__ __forceinline__ RoundSplit round_share(const int32_t* __restrict__ plan, int MT, int NT, int x, int BM) {
+    RoundSplit s;
+    s.big = plan[kPlanBigParts];
+    s.on = BM == kShortTileRows && s.big > 0;
+    if (!s.on) return s;
+    s.small = plan[kPlanSmallParts];
+    s.q = NT / kXcds;
+    s.rem = NT - s.q * kXcds;
+    s.ns = plan[kPlanSmallTiles] - 1;
+    s.nb = MT - s.ns;
+    const int cb = (s.nb * s.rem + kXcds - 1) / kXcds, cs = (s.ns * s.rem + kXcds - 1) / kXcds;
+    s.rb0 = x * cb;
+    s.rs0 = x * cs;
+    const int rb = s.nb * s.rem - s.rb0, rs = s.ns * s.rem - s.rs0;
+    s.nbx = s.nb * s.q + (rb < 0 ? 0 : (rb < cb ? rb : cb));
+    s.nsx = s.ns * s.q + (rs < 0 ? 0 : (rs < cs ? rs : cs));
+    return s;
+}
+
+// tile number `tile` of either kind, of a list that walks NT column tiles of every listed bucket
+__host__ __device__ __forceinline__ void locate_kind(const int32_t* __restrict__ plan, const int32_t* __restrict__ prefix, int NT, int tile,
+                                                     int BM, bool small, WorkItem& w) {
+    for (int i = 0; i < plan[0]; ++i) {
+        const int tiles = prefix[i + 1] - prefix[i], last = plan[kPlanCount + i] - (tiles - 1) * BM;
+        const int has_small = last <= kSmallTileRows ? 1 : 0, here = small ? has_small : tiles - has_small;
+        if (tile >= here * NT) {
+            tile -= here * NT;
+            continue;
+        }
+        w.nt = tile / here;
+        const int mt = small ? tiles - 1 : tile - w.nt * here;
+        w.expert = plan[kPlanExpert + i];
+        w.bucket = i;
+        w.first = mt * BM;
+        w.row0 = plan[kPlanStart + i] + mt * BM;
+        w.rows = mt == tiles - 1 ? last : BM;
+        return;
+    }
+}
+
+// tile idx (big ones first) of XCD x
+__host__ __device__ __forceinline__ void locate_round_tile(const int32_t* __restrict__ plan, const int32_t* __restrict__ prefix,
+                                                           const RoundSplit& s, int x, int idx, int BM, WorkItem& w) {
+    const bool small = idx >= s.nbx;
+    if (small) idx -= s.nbx;
+    const int own = (small ? s.ns : s.nb) * s.q;
+    if (idx < own) {
+        locate_kind(plan, prefix, s.q, idx, BM, small, w);
+        w.nt += x * s.q;
+    } else {
+        locate_kind(plan, prefix, s.rem, (small ? s.rs0 : s.rb0) + idx - own, BM, small, w);
+        w.nt += kXcds * s.q;
+    }
+}
+
 // The work of workgroup `block` of a GEMM launch (blocks are dealt round-robin to the XCDs by the hardware:
 // XCD = block % 8, and `slot` = block / 8 counts within the XCD): a whole tile, or one k part of a tail tile
 // with its partial-tile slot.  False when the launch holds more workgroups than this XCD has work.
@@ -121,6 +186,20 @@ __host__ __device__ __forceinline__ bool workgroup_item(const int32_t* __restric
                                                         int NT, int KT, int BM, unsigned block, int cus_per_xcd, int row_chunk,
                                                         bool allow_split, WorkItem& w) {
     const int x = (int)(block % kXcds), slot = (int)(block / kXcds);
+    if (allow_split) {
+        const RoundSplit rs = round_share(plan, prefix[plan[0]], NT, x, BM);
+        if (rs.on) {
+            const int big_slots = rs.nbx * rs.big;
+            if (slot >= big_slots + rs.nsx * rs.small) return false;
+            const int parts = slot < big_slots ? rs.big : rs.small, j = slot < big_slots ? slot : slot - big_slots;
+            const int part = j % parts;
+            locate_round_tile(plan, prefix, rs, x, (slot < big_slots ? 0 : rs.nbx) + j / parts, BM, w);
+            w.kt0 = (int)((long long)part * KT / parts);
+            w.kt1 = (int)((long long)(part + 1) * KT / parts);
+            w.partial = parts > 1 ? x * 2 * cus_per_xcd + slot : -1;
+            return true;
+        }
+    }
     const XcdShare sh = xcd_share(prefix[plan[0]], NT, x, KT, cus_per_xcd, allow_split);
     if (slot >= sh.full + sh.tail * sh.split) return false;
     if (slot < sh.full) {
@@ -142,6 +221,15 @@ __host__ __device__ __forceinline__ bool workgroup_item(const int32_t* __restric
 __host__ __device__ __forceinline__ bool fixup_item(const int32_t* __restrict__ plan, const int32_t* __restrict__ prefix, int NT,
                                                     int KT, int BM, int x, int q, int cus_per_xcd, int row_chunk, WorkItem& w,
                                                     int& first_partial, int& parts) {
+    const RoundSplit rs = round_share(plan, prefix[plan[0]], NT, x, BM);
+    if (rs.on) {
+        if (q >= rs.nbx + rs.nsx) return false;
+        parts = q < rs.nbx ? rs.big : rs.small;
+        if (parts == 1) return false;
+        locate_round_tile(plan, prefix, rs, x, q, BM, w);
+        first_partial = x * 2 * cus_per_xcd + (q < rs.nbx ? q * rs.big : rs.nbx * rs.big + (q - rs.nbx) * rs.small);
+        return true;
+    }
     const XcdShare sh = xcd_share(prefix[plan[0]], NT, x, KT, cus_per_xcd, true);
     if (q >= sh.tail) return false;
     locate_xcd_tile(plan, prefix, sh, x, sh.full + q, BM, row_chunk, w);

@@ -5,8 +5,8 @@
 namespace moe {
 
 constexpr int kFrontMaxRoutes = 12288;   // routes a workgroup sorts by itself (their expert ids fill 24 KB of LDS)
-constexpr int kFrontGroups = 256;        // workgroups: one per compute unit, each with at least one token
-constexpr int kFrontMaxTokens = 32;      // tokens a workgroup may own (front_fits keeps T below kFrontGroups times that)
+constexpr int kFrontGroups = 256;        // workgroups: one per compute unit, all but the first with at least one token
+constexpr int kFrontMaxTokens = 33;      // tokens a workgroup may own (front_fits keeps T below kFrontGroups - 1 times that)
 
 struct FrontArgs {
     const uint4* x;                      // [T] rows of units_per_row 16-byte pieces

@@ -4,8 +4,8 @@
 //
 // At these sizes each of the four launches it replaces takes 4.5-10 us, nearly all of it launch latency.  Here every
 // workgroup works out the whole batch's routing redundantly - gate into LDS, the counting sort of the routes - and
-// then writes only its own share: the gate outputs, positions and send rows of its tokens.  Workgroup 0 also writes
-// the expert and GPU tables, the last workgroup the tile plan.  Nothing passes between workgroups.  The first pieces
+// then writes only its own share: the gate outputs, positions and send rows of its tokens.  Workgroup 0 has no tokens
+// and writes the expert and GPU tables and the tile plan.  Nothing passes between workgroups.  The first pieces
 // of the workgroup's rows are loaded before anything else, so that they arrive while it routes.
 #include "dispatch_index.h"
 #include "ffn_plan.h"
@@ -24,7 +24,9 @@ __global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
     __shared__ int my_pos[kFrontMaxTokens * MOE_MAX_TOPK]; // positions of this workgroup's routes
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
     const int T = a.T, E = a.E, k = a.k, N = T * k;
-    const int t0 = (int)((long long)blockIdx.x * T / gridDim.x), t1 = (int)((long long)(blockIdx.x + 1) * T / gridDim.x);
+    const bool tables = blockIdx.x == 0;
+    const int groups = gridDim.x - 1, g = (int)blockIdx.x - 1;
+    const int t0 = tables ? T : (int)((long long)g * T / groups), t1 = tables ? T : (int)((long long)(g + 1) * T / groups);
     const int units = (t1 - t0) * a.units_per_row;
     const uint4* rows = a.x + (long long)t0 * a.units_per_row;
     uint4 pre[kFrontPrefetch];
@@ -96,14 +98,14 @@ __global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
     }
     for (int u = tid + kFrontPrefetch * kIndexThreads; u < units; u += kIndexThreads) put(u, rows[u]);
 
-    if (blockIdx.x == 0) index_write_tables(s, E, a.G, a.expert_counts, a.expert_start, a.gpu_counts, a.gpu_offsets);
-    if (blockIdx.x == gridDim.x - 1) {
+    if (tables) {
         int c = 0, st = 0;
         if (tid < E && (a.local_gpu < 0 || s.pl[tid] == a.local_gpu)) {
             c = s.tot[tid];
             st = s.start[tid];
         }
-        build_plan(plan_scratch, tid, c, st, tid, E, a.shape.bm0, a.shape.bm1, a.shape.choice, a.plan);
+        build_plan(plan_scratch, tid, c, st, tid, E, a.shape, a.plan);
+        index_write_tables(s, E, a.G, a.expert_counts, a.expert_start, a.gpu_counts, a.gpu_offsets);
     }
 }
 
@@ -113,7 +115,7 @@ static int front_lanes(int E) { return E <= 8 ? 1 : (E <= 64 ? 4 : 16); }
 bool front_fits(int T, int E, int k) {
     // every workgroup gates and sorts the whole batch: at most kFrontMaxRoutes routes and eight passes of the gate
     const long long N = (long long)T * k;
-    static_assert(8 * kIndexThreads <= kFrontGroups * kFrontMaxTokens, "a workgroup's tokens fit its tables");
+    static_assert(8 * kIndexThreads <= (kFrontGroups - 1) * kFrontMaxTokens, "a workgroup's tokens fit its tables");
     return T > 0 && N <= kFrontMaxRoutes && (long long)T * front_lanes(E) <= 8 * kIndexThreads;
 }
 
@@ -121,7 +123,7 @@ int launch_front(const FrontArgs& args, hipStream_t s) {
     FrontArgs a = args;
     a.ebits = 0;
     while ((1 << a.ebits) < a.E) ++a.ebits;
-    const int grid = a.T < kFrontGroups ? a.T : kFrontGroups;
+    const int grid = a.T < kFrontGroups ? a.T + 1 : kFrontGroups;
     LaunchTimer timer(MOE_K_FRONT, s);
 #define MOE_LAUNCH_FRONT(L, VPL)                                                                                        \
     do {                                                                                                                \

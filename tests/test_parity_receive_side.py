@@ -70,6 +70,48 @@ def test_expert_parallel_group_matches_oracle(lib, dtype, G, T_rank, d, f, E, k,
         assert e2e <= tol
 
 
+@pytest.mark.parametrize("dtype,d,f,E,segs", [
+    # (expert, rows): segments of one expert apart from each other, empty ones, an expert with one segment only
+    ("bf16", 64, 128, 4, [(2, 3), (0, 1), (2, 0), (1, 5), (2, 40), (0, 2)]),                       # streaming kernels
+    ("bf16", 128, 192, 3, [(1, 9), (0, 7)] * 10),                                                  # ... 160 rows, ten segments a bucket
+    ("bf16", 128, 192, 3, [(1, 9), (0, 7)] * 10 + [(2, 1)]),                                       # the first batch on tiles
+    ("bf16", 128, 1088, 3, [(0, 130), (2, 126), (0, 127), (2, 1), (1, 256), (0, 3)]),              # tiles across segments; 17 k tiles
+    ("bf16", 2048, 2048, 2, [(0, 300), (1, 20), (0, 201), (1, 90), (0, 12)]),                      # one round, cut along k
+    ("bf16", 64, 64, 2, [(0, 600), (1, 520), (0, 544), (1, 560)]),                                 # large segments stay buckets (tall tiles)
+    ("bf16", 64, 64, 256, [(e, 1 + e % 3) for e in range(255, -1, -1)]),                           # 256 buckets, nothing to merge
+    ("bf16", 64, 64, 2, [(i % 2, 1 + i % 5) for i in range(256)]),                                 # 128 segments a bucket
+    ("f32", 36, 100, 3, [(2, 3), (0, 31), (2, 33), (0, 1), (2, 0), (1, 64), (2, 30)]),
+])
+def test_segments_of_one_expert_in_any_order(lib, dtype, d, f, E, segs):
+    """moe_expert_ffn_segments over a buffer whose segments lie in an order of their own, with rows between them that
+    belong to none: those stay untouched, the others match the oracle."""
+    rng = np.random.default_rng(d + f + len(segs))
+    w = [synth.normal(d, i, s, s[1] ** -0.5, dtype) for i, s in ((2, (E, d, f)), (3, (E, d, f)), (4, (E, f, d)))]
+    se, sc = np.array(segs, dtype=np.int32).T.copy()
+    starts, at = np.zeros(len(segs), dtype=np.int32), 0
+    gaps = 2 if sc.sum() > 160 or sc.sum() < 100 else 0
+    for j in rng.permutation(len(segs)):
+        starts[j] = at
+        at += int(sc[j]) + (gaps if j % 2 else 0)
+    N = max(at, 1)
+    x = synth.normal(d + 1, 0, (N, d), 1.0, dtype)
+    dt = B.MOE_BF16 if dtype == "bf16" else B.MOE_F32
+    packed = torch.empty(B.moe_packed_weights_bytes(E, d, f, dt), dtype=torch.uint8, device="cuda")
+    B.moe_pack_weights(*[to_device(a) for a in w], E, d, f, dt, packed)
+    ws = torch.empty(B.moe_ffn_workspace_bytes(N, d, f, E, dt), dtype=torch.uint8, device="cuda").fill_(0xAA)
+    out = torch.full((N, d), 7.0, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+    dev = lambda a: torch.from_numpy(a).cuda()
+    B.moe_expert_ffn_segments(to_device(x), dt, N, d, f, E, packed, len(segs), dev(se), dev(sc), dev(starts), out, ws)
+    torch.cuda.synchronize()
+    ref = O.expert_ffn_segments(x, *w, se, sc, starts)
+    mine = np.zeros(N, dtype=bool)
+    for s, c in zip(starts, sc):
+        mine[s:s + c] = True
+    got, tol = as_f64(to_host(out)), TOL_BF16 if dtype == "bf16" else TOL_F32
+    assert rel_err(got[mine], np.asarray(ref)[mine]) <= tol
+    assert np.all(got[~mine] == 7.0)
+
+
 def test_receive_segments_table_edge_cases(lib):
     """moe_receive_segments against a host loop: uneven map, a destination without experts, negative counts, a table
     that is larger than needed (padded with empty segments at the end) and one that is too small (n_seg says so)."""

@@ -11,12 +11,13 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_every_k_tile_of_every_tile_has_exactly_one_owner(tmp_path):
+@pytest.mark.parametrize("defines", [[], ["-DWITH_ROUND_SPLIT"]])      # the second: launches of one round cut their tiles by cost
+def test_every_k_tile_of_every_tile_has_exactly_one_owner(tmp_path, defines):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not found")
     exe = str(tmp_path / "tile_schedule_check")
-    build = subprocess.run([hipcc, "--offload-arch=gfx950", "-O2", "-std=c++17", "-I" + os.path.join(ROOT, "include"),
+    build = subprocess.run([hipcc, "--offload-arch=gfx950", "-O2", "-std=c++17", *defines, "-I" + os.path.join(ROOT, "include"),
                             "-I" + os.path.join(ROOT, "paper_2502_06643_amd", "csrc"),
                             os.path.join(ROOT, "tests", "tile_schedule_check.hip"), "-o", exe],
                            capture_output=True, text=True, timeout=300)

@@ -58,6 +58,21 @@ static int check_case(std::mt19937& rng, long long& units) {
         mt_total += tiles[i];
     }
     prefix[n] = mt_total;
+#ifdef WITH_ROUND_SPLIT
+    // tiles of more than 128 rows and the others cut into any numbers of parts that fit two per compute unit
+    int n_small = 0;
+    for (int i = 0; i < n; ++i) n_small += (count[i] - 1) % kShortTileRows < kSmallTileRows ? 1 : 0;
+    if (BM == kShortTileRows) {
+        const int nb = mt_total - n_small, q = NT / kXcds, rem = NT % kXcds;
+        const int nbx = nb * q + (nb * rem + kXcds - 1) / kXcds, nsx = n_small * q + (n_small * rem + kXcds - 1) / kXcds;
+        const int big = 1 + rng() % kMaxSplit, small = 1 + rng() % kMaxSplit;
+        if (nbx + nsx <= cpx && nbx * big + nsx * small <= 2 * cpx && (big == 1 || KT / big >= kMinSplitKT) && (small == 1 || KT / small >= kMinSplitKT)) {
+            plan[kPlanSmallTiles] = 1 + n_small;
+            plan[kPlanBigParts] = big;
+            plan[kPlanSmallParts] = small;
+        }
+    }
+#endif
 
     const long long grid = ffn_grid((int)N, n, NT, BM, split, cpx);
     CHECK(grid > 0 && grid < (1ll << 31), "grid %lld", grid);

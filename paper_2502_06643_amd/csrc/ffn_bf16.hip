@@ -563,42 +563,71 @@ __global__ __launch_bounds__(kThreads) void ffn_bf16_kernel(const uint16_t* __re
     else ffn_tile<UP, SPLIT, 2, MERGED>(smem, A, Wp, expert_stride, K, npad, C, ldc, plan, partials, cus_per_xcd, row_chunk);
 }
 
-// adds the k parts of the split tail tiles in part order and writes the tiles; a workgroup handles
-// the j-th 32-row block of every wavefront of one tile (fm = 3 or 2 such blocks, by the plan's tile height)
+// Adds the k parts of the split tiles in part order and writes the tiles; a workgroup handles one fragment row (16
+// rows) of the j-th 32-row block of every wavefront of one tile (fm = 3 or 2 such blocks, by the plan's tile height).
+// Bound by memory latency: the partial sums of kFixupInFlight parts are fetched together.  Walking the parts one by
+// one, 32 rows a workgroup, took 22.8 us for 32 tiles of 7 parts (851 tokens, d 4096, f 3584, 2 of 8 experts); this
+// takes 10.9 us (with all parts of a round held in registers, one workgroup per compute unit: 12.5).
+constexpr int kFixupInFlight = 4;
+constexpr int kFixupStride = WTN + 8;             // staging row stride (elements), as in the epilogue
+constexpr int kFixupSmem = NW * 16 * kFixupStride * 2;
 __global__ __launch_bounds__(kThreads) void ffn_bf16_fixup_kernel(int K, int npad, uint16_t* __restrict__ C, int ldc,
                                                                   const int32_t* __restrict__ plan,
                                                                   const float* __restrict__ partials, int cus_per_xcd, int row_chunk) {
-    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[kFixupSmem / 2];
     const bool tall = plan[3] == 0;
     const int fm = tall ? 3 : 2, BM = 128 * fm;
     const size_t partial_floats = (size_t)BM * BN;
     const int32_t* prefix = plan + (tall ? kPlanTiles0 : kPlanTiles1);
     const int NT = npad / BN, KT = K / BK;
-    const int x = blockIdx.x % kXcds, q = (blockIdx.x / kXcds) / fm, j = (blockIdx.x / kXcds) % fm;
+    const int x = blockIdx.x % kXcds, slot = blockIdx.x / kXcds, q = slot / (2 * fm), a = slot % (2 * fm);
     WorkItem w;
     int first_partial, parts;
     if (!fixup_item(plan, prefix, NT, KT, BM, x, q, cus_per_xcd, row_chunk, w, first_partial, parts)) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (j >= active_blocks(w.rows, wave / WN, fm)) return;
-    f32x4 blk[2][FN];
+    const int row_base = block_row(a >> 1, wave / WN) + (a & 1) * 16;     // first tile row of this wavefront's fragment row
+    if (row_base >= w.rows) return;
+    const RowMap rm = row_map<true>(plan, w.bucket, w.first, w.rows);
+    f32x4 sum[FN];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int b = 0; b < FN; ++b)
 #pragma unroll
-        for (int b = 0; b < FN; ++b)
+        for (int v = 0; v < 4; ++v) sum[b][v] = 0.f;
+    const f32x4* src = reinterpret_cast<const f32x4*>(partials + (size_t)first_partial * partial_floats) + (size_t)a * FN * kThreads + tid;
+    for (int p0 = 0; p0 < parts; p0 += kFixupInFlight) {
+        f32x4 t[kFixupInFlight][FN];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) blk[h][b][v] = 0.f;
-    for (int part = 0; part < parts; ++part) {
-        const f32x4* src = reinterpret_cast<const f32x4*>(partials + (size_t)(first_partial + part) * partial_floats) + tid;
+        for (int u = 0; u < kFixupInFlight; ++u) {
+            const int p = min(p0 + u, parts - 1);        // past the last part: it is read again and not added
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+            for (int b = 0; b < FN; ++b) t[u][b] = src[(size_t)p * (partial_floats / 4) + (size_t)b * kThreads];
+        }
+        __builtin_amdgcn_sched_barrier(0);               // all of them under way before the first is used
+#pragma unroll
+        for (int u = 0; u < kFixupInFlight; ++u) {
+            if (p0 + u >= parts) break;
 #pragma unroll
             for (int b = 0; b < FN; ++b) {
-                const f32x4 t = src[(size_t)((2 * j + h) * FN + b) * kThreads];
-                blk[h][b][0] += t[0]; blk[h][b][1] += t[1]; blk[h][b][2] += t[2]; blk[h][b][3] += t[3];
+                sum[b][0] += t[u][b][0]; sum[b][1] += t[u][b][1]; sum[b][2] += t[u][b][2]; sum[b][3] += t[u][b][3];
             }
+        }
     }
-    epilogue_block<false>(blk[0], blk[1], block_row(j, wave / WN), smem, C, ldc, w, row_map<true>(plan, w.bucket, w.first, w.rows), wave, lane);
+    // the epilogue's way out (the staging tile belongs to this wavefront: no barrier)
+    uint16_t* stg = smem + wave * (16 * kFixupStride);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int b = 0; b < FN; ++b)
+            stg[(4 * (lane >> 4) + v) * kFixupStride + b * 16 + (lane & 15)] = __builtin_bit_cast(uint16_t, (__bf16)sum[b][v]);
+    const int col = w.nt * BN + (wave % WN) * WTN + (lane % 16) * 8;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const int r = it * 4 + lane / 16, gr = row_base + r;
+        if (gr < w.rows && col < ldc)
+            *reinterpret_cast<u32x4*>(C + (size_t)buffer_row(rm, gr) * ldc + col) =
+                *reinterpret_cast<const u32x4*>(stg + r * kFixupStride + (lane % 16) * 8);
+    }
 }
 
 template <typename Kernel>
@@ -639,7 +668,6 @@ int ffn_bf16_device_setup(int* cus_per_xcd) {
         if ((r = set_smem(&ffn_bf16_kernel<false, true, false>, launch_smem<false>())) != MOE_OK) return r;
         if ((r = set_smem(&ffn_bf16_kernel<true, false, true>, launch_smem<true>())) != MOE_OK) return r;
         if ((r = set_smem(&ffn_bf16_kernel<false, true, true>, launch_smem<false>())) != MOE_OK) return r;
-        if ((r = set_smem(&ffn_bf16_fixup_kernel, epilogue_bytes<false>())) != MOE_OK) return r;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
         st.cpx = cus >= kXcds ? (cus / kXcds < kMaxCusPerXcd ? cus / kXcds : kMaxCusPerXcd) : 32;
@@ -670,7 +698,7 @@ static int run_down(const FfnCall& c, int bm, int fm_max) {
                        c.chunk_down);
     int rc = check_launch("moe_expert_ffn_grouped down launch");
     if (rc != MOE_OK || !split_can_pay(c.f / BK)) return rc;
-    hipLaunchKernelGGL(ffn_bf16_fixup_kernel, dim3(kXcds * c.cpx * fm_max), dim3(kThreads), (epilogue_bytes<false>()), c.s, c.f,
+    hipLaunchKernelGGL(ffn_bf16_fixup_kernel, dim3(kXcds * c.cpx * fm_max * 2), dim3(kThreads), 0, c.s, c.f,
                        (int)npad2(c.d), (uint16_t*)c.out, c.d, c.plan, c.partials, c.cpx, c.chunk_down);
     return check_launch("moe_expert_ffn_grouped fix-up launch");
 }

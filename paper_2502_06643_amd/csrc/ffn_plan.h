@@ -100,7 +100,8 @@ struct PlanScratch {
 // rows into `big` parts, the others into `small`.  A k tile takes 1.3 us in the former (bound by the matrix pipes and
 // its 64 KB) and about 1 us in the latter (bound by its weight stream).  777 tokens at the Mixtral shape are 80 such
 // tiles and 96 small ones, 176 on 256 compute units: 312 us with the fix-up uncut, 275 with the 80 cut in two.
-// Called by one wavefront: lane (rounds, b) tries one or two rounds of parts (two fp32 partial tiles exist per compute
+// kSplitCost and kPartCost stand for the partial tiles' way through memory and the fix-up (10 us and 1.3 us a part;
+// twice and half of that chose about as well).  Called by one wavefront: lane (rounds, b) tries one or two rounds of parts (two fp32 partial tiles exist per compute
 // unit) with the big tiles in b parts.
 constexpr int kXcds = 8;
 constexpr int kMaxSplit = 8;
@@ -112,7 +113,7 @@ constexpr bool split_can_pay(int KT) {
     return parts > 1 && (KT - KT / parts) >= kMinSplitGain;
 }
 __device__ __forceinline__ void round_split(int lane, int nb, int ns, const PlanShape& shape, int32_t* __restrict__ plan) {
-    constexpr int kBigCost = 4, kSmallCost = 3;
+    constexpr int kBigCost = 4, kSmallCost = 3, kSplitCost = 32, kPartCost = 4;
     const int KT = shape.kt_down, cpx = shape.cus_per_xcd, q = shape.nt_down / kXcds, rem = shape.nt_down % kXcds;
     const int nbx = nb * q + (nb * rem + kXcds - 1) / kXcds, nsx = ns * q + (ns * rem + kXcds - 1) / kXcds;     // the fullest XCD
     const int whole = (nbx > 0 ? kBigCost : kSmallCost) * KT;
@@ -130,7 +131,9 @@ __device__ __forceinline__ void round_split(int lane, int nb, int ns, const Plan
                 sm = max(sm, 1);
             }
             const int ts = nsx > 0 ? kSmallCost * ((KT + sm - 1) / sm) : 0, t = rounds * (tb > ts ? tb : ts);
-            if (t <= whole - kBigCost * kMinSplitGain) { best = t; big = b; small = sm; }
+            // ... and what the partial tiles and the fix-up cost, in the same unit of a third of a microsecond
+            const int parts = max(b, sm), cost = t + kSplitCost + kPartCost * parts;
+            if (parts > 1 && cost < whole) { best = cost; big = b; small = sm; }
         }
         for (int m = 1; m < 2 * kMaxSplit; m <<= 1) {             // the shortest, then the fewest parts
             const int ot = __shfl_xor(best, m, 64), ob = __shfl_xor(big, m, 64), os = __shfl_xor(small, m, 64);

@@ -317,7 +317,7 @@ __device__ __forceinline__ void mainloop(f32x4 (&acc)[2 * FM][FN], uint16_t* sme
     constexpr int N_DMA = Loader<FM, MERGED>::N_DMA;
     const int wave_m = wave / WN, wave_n = wave % WN;
     Loader<FM, MERGED> ld;
-    const bool merged = MERGED && rm.off != nullptr;
+    const bool merged = MERGED && rm.merged;
     ld.Abase = merged ? A : A + (size_t)rm.row0 * K;
     ld.Bbase = Bbase + (size_t)(wave % NL) * 512;
     ld.lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem + (uint32_t)(wave % NL) * 1024u;
@@ -374,7 +374,7 @@ __device__ __forceinline__ void mainloop_small(f32x4 (&acc)[2 * FM][FN], uint16_
                                                const uint16_t* __restrict__ Bbase, int K, const WorkItem& w, const RowMap& rm,
                                                int wave, int lane, bool has_rows) {
     const int wave_m = wave / WN, wave_n = wave % WN;
-    const bool merged = rm.off != nullptr;
+    const bool merged = rm.merged;
     uint32_t a_voff[kSmallAPerWave], b_voff[B_PER_WAVE];
 #pragma unroll
     for (int j = 0; j < kSmallAPerWave; ++j) {

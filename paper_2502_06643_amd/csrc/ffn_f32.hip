@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
     const int nt = rem / mt_e, r0 = (rem - nt * mt_e) * kF32Tile;
     const int rows = min(kF32Tile, plan[kPlanCount + lo] - r0), n0 = nt * kF32Tile;
     const RowMap rm = row_map<true>(plan, lo, r0, rows);
-    const bool merged = rm.off != nullptr;
+    const bool merged = rm.merged;
     const float* We = packed + (size_t)plan[kPlanExpert + lo] * 3 * d * f;
     const float* Bbase = UP ? We : We + (size_t)2 * d * f;                // W1 (W3 follows it) or W2
     const float* Abase = merged ? A : A + (size_t)rm.row0 * K;

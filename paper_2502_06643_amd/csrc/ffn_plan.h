@@ -38,38 +38,59 @@ constexpr int kSmallTileRows = 128;
 // says that the bucket's rows from kPlanSegOff[j] on lie at kPlanSegDelta[j] + row.  The first segment of a bucket, and
 // only that, begins at row 0, and so does the entry past the last one: that is how a walk along the list ends.
 struct RowMap {
-    const int32_t* off;      // NULL: the rows follow each other
-    const int32_t* delta;
-    int row0;                // buffer row of row 0 of the tile (off == NULL)
+    bool merged;             // false: the rows follow each other
+    int row0;                // buffer row of row 0 of the tile (not merged)
     int first, last;         // the tile's rows within the bucket
-    int seg;                 // the segment that holds `first`
+    int delta;               // of the segment that holds `first`
+    int more;                // segments after that one that hold rows of the tile, at most 64 of them in ...
+    int off_lane, delta_lane;    // ... the wavefront's lanes
+    const int32_t* rest;     // entry after those 64 (more == 64)
 };
 
-// the map of rows first .. first + rows - 1 of listed bucket i
+// the map of rows first .. first + rows - 1 of listed bucket i; called by whole wavefronts, which fetch the bucket's
+// segments together: one round of memory latency instead of one per segment and row
 // (MAY_MERGE = false: the caller knows that nothing is merged)
 template <bool MAY_MERGE>
 __device__ __forceinline__ RowMap row_map(const int32_t* __restrict__ plan, int i, int first, int rows) {
     RowMap m;
     const int start = plan[kPlanStart + i];
-    m.off = nullptr;
-    m.delta = plan + kPlanSegDelta;
+    m.merged = MAY_MERGE && plan[kPlanMerged];
     m.row0 = start + first;
     m.first = first;
     m.last = first + rows - 1;
-    m.seg = start;
-    if (MAY_MERGE && plan[kPlanMerged]) {
-        m.off = plan + kPlanSegOff;
-        while (m.off[m.seg + 1] != 0 && m.off[m.seg + 1] <= first) ++m.seg;
+    m.more = m.off_lane = m.delta_lane = m.delta = 0;
+    m.rest = nullptr;
+    if (!m.merged) return m;
+    const int32_t* off = plan + kPlanSegOff;
+    const int lane = threadIdx.x & 63;
+    int seg = start;
+    for (;;) {                                            // skip the segments before the one that holds `first`
+        const int o = off[min(seg + 1 + lane, MOE_MAX_EXPERTS)];
+        const unsigned long long stop = __ballot(o == 0 || o > first);
+        seg += stop ? __builtin_ctzll(stop) : 64;
+        if (stop) break;
     }
+    const int j = min(seg + 1 + lane, MOE_MAX_EXPERTS);
+    m.off_lane = off[j];
+    m.delta_lane = plan[kPlanSegDelta + min(j, MOE_MAX_EXPERTS - 1)];
+    m.delta = plan[kPlanSegDelta + seg];
+    const unsigned long long stop = __ballot(m.off_lane == 0 || m.off_lane > m.last || j != seg + 1 + lane);
+    m.more = stop ? __builtin_ctzll(stop) : 64;
+    m.rest = off + seg + 65;
     return m;
 }
 
 // where row r of the tile lies in the buffer (0 <= r < rows)
 __device__ __forceinline__ int buffer_row(const RowMap& m, int r) {
-    if (m.off == nullptr) return m.row0 + r;
+    if (!m.merged) return m.row0 + r;
     const int b = m.first + r;
-    int at = m.delta[m.seg];
-    for (int j = m.seg + 1; m.off[j] != 0 && m.off[j] <= m.last; ++j) at = b >= m.off[j] ? m.delta[j] : at;
+    int at = m.delta;
+    for (int j = 0; j < m.more; ++j) {
+        const int o = __builtin_amdgcn_readlane(m.off_lane, j), d = __builtin_amdgcn_readlane(m.delta_lane, j);
+        at = b >= o ? d : at;
+    }
+    if (m.more == 64)                                     // many tiny segments: the rest of the list from memory
+        for (const int32_t* p = m.rest; *p != 0 && *p <= m.last; ++p) at = b >= *p ? p[kPlanSegDelta - kPlanSegOff] : at;
     return at + b;
 }
 
@@ -87,6 +108,7 @@ int launch_ffn_plan(const int32_t* counts, const int32_t* starts, const int32_t*
 
 constexpr int kF32TileRows = 32;                        // tile height of the fp32 path
 constexpr int kTallTileRows = 384, kShortTileRows = 256; // tile heights of the bf16 path
+constexpr int kSkinnyRows = 64;                         // rows a pass of its streaming kernels covers (bm1 of their plan)
 
 // Shared memory of build_plan: per group its rows and tiles, and the sums over the groups listed before it.
 struct PlanScratch {

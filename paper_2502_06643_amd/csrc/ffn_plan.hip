@@ -85,8 +85,10 @@ __global__ __launch_bounds__(kPlanThreads) void ffn_plan_kernel(const int32_t* _
 int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_resident, PlanShape* shape) {
     *shape = {kF32TileRows, kF32TileRows, 0, 0, 0, 0};
     if (dt == MOE_F32) return MOE_OK;
-    shape->bm0 = shape->bm1 = kShortTileRows;
+    shape->bm0 = kShortTileRows;
+    shape->bm1 = kSkinnyRows;
     if (N <= kFfnSkinnyMaxRows) return MOE_OK;
+    shape->bm1 = kShortTileRows;
     // Row tiles of 384 move about a sixth fewer bytes per flop than tiles of 256, but waste more on
     // ragged buckets and leave compute units idle when there are few tiles: 384 when the resident buckets
     // hold kLargeBucketRows rows or more on average.  When every row is in a resident bucket the host

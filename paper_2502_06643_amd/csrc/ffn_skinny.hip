@@ -22,7 +22,14 @@
 // to fill the chip, so the reduction is cut into `parts` k ranges that run as
 // separate workgroups and write fp32 partial sums; a small kernel adds the
 // parts in a fixed order (bitwise reproducible) and rounds to bf16.
-// Buckets of more than 64 rows are walked in passes of 64 rows.
+// Buckets of more than 64 rows are cut into tasks of 64 rows (the second one finds the weights in the L2).
+//
+// Few weights (a small expert, one resident expert of many) make few such tasks, each one long chain of k tiles at the
+// latency of memory.  With less than kSkinnyFewTasks of them a workgroup takes four panels instead of sixteen and its
+// wavefronts a quarter of the reduction each, added in wavefront order through LDS: four times the workgroups, a
+// quarter of the chain: one token, d 1536, f 896, one resident expert: layer 26.5 -> 20.6 us; 3 tokens, d 2432, f 2688, four
+// experts 33.8 -> 25.6; 8 tokens from each of 8 ranks, one Mixtral expert 161 -> 133
+// (121 with the rows' segments fetched together).  With 224 tasks (two Mixtral experts) it lost 1-4 %.
 #include "bf16.h"
 #include "ffn_plan.h"
 
@@ -31,25 +38,28 @@ namespace moe {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-constexpr int kSkinnyThreads = 256;
-constexpr int kSkinnyRows = 64;          // rows per pass (four 16-row fragments)
+constexpr int kSkinnyThreads = 256, kSkinnyWaves = kSkinnyThreads / 64;
+constexpr int kSkinnyFewTasks = 128;     // fewer than this: a workgroup of each splits the reduction among its wavefronts
+static_assert(kSkinnyRows == 64, "four 16-row fragments");
 constexpr int kSkinnyMaxParts = 16;
 constexpr int kSkinnyDownTasks = 512;    // workgroups the down projection is cut into
 
 // k parts of the down projection: two workgroups per compute unit (more, shorter parts were slower), at least 8 k tiles
-// each.  Decided on the device, which knows how many buckets there are.
-__device__ __forceinline__ int skinny_parts(int n_listed, int NT, int max_parts) {
-    const int tasks = n_listed * NT, parts = tasks > 0 ? (kSkinnyDownTasks + tasks - 1) / tasks : 1;
+// each.  Decided on the device, which knows how many tasks there are.
+__device__ __forceinline__ int skinny_parts(int n_chunks, int NT, int max_parts) {
+    const int tasks = n_chunks * NT, parts = tasks > 0 ? (kSkinnyDownTasks + tasks - 1) / tasks : 1;
     return parts < max_parts ? parts : max_parts;
 }
 
 __device__ __forceinline__ bf16x8 as_frag(const uint4& q) { return __builtin_bit_cast(bf16x8, q); }
 
-// one pass over MF * 16 rows starting at bucket row `row0`, k tiles [kt0, kt1)
-template <bool UP, int MF>
+// one pass over the task's n <= MF * 16 rows, k tiles [kt0, kt1)
+// grp: which four panels of the column tile; with SPLIT the workgroup's wavefronts share them and [kt0, kt1) is this
+// wavefront's share of the reduction, possibly empty (red: the wavefronts' partial sums of 16 rows)
+template <bool UP, int MF, bool SPLIT>
 __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int K, const uint4* __restrict__ Bp, const RowMap& rm, int n,
-                                            int row0, int kt0, int kt1, int nt, int wave, int lane, int ldc,
-                                            uint16_t* __restrict__ H, float* __restrict__ partial) {
+                                            int kt0, int kt1, int nt, int grp, int wave, int lane, int ldc,
+                                            uint16_t* __restrict__ H, float* __restrict__ partial, f32x4* red) {
     f32x4 acc[MF][4];
 #pragma unroll
     for (int m = 0; m < MF; ++m)
@@ -63,7 +73,7 @@ __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int 
     const uint4* Ap[MF];
 #pragma unroll
     for (int m = 0; m < MF; ++m) {
-        const int r = min(row0 + m * 16 + (lane & 15), n - 1);
+        const int r = min(m * 16 + (lane & 15), n - 1);
         Ap[m] = reinterpret_cast<const uint4*>(A + (size_t)buffer_row(rm, r) * K) + (lane >> 4);
     }
     uint4 a[2][MF * 2], b[2][8];
@@ -87,7 +97,7 @@ __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int 
                     acc[m][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(a[buf][m * 2 + ks]), as_frag(b[buf][p * 2 + ks]),
                                                                         acc[m][p], 0, 0, 0);
     };
-    load(kt0, 0);
+    if (!SPLIT || kt0 < kt1) load(kt0, 0);
     int kt = kt0;
     for (; kt + 2 <= kt1; kt += 2) {
         load(kt + 1, 1);
@@ -97,18 +107,56 @@ __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int 
     }
     if (kt < kt1) multiply(0);
 
+    if (SPLIT) {
+#pragma unroll
+        for (int m = 0; m < MF; ++m) {
+            __syncthreads();                                       // the rows before have been read by everyone
+#pragma unroll
+            for (int p = 0; p < 4; ++p) red[(wave * 4 + p) * 64 + lane] = acc[m][p];
+            __syncthreads();
+            const int rbase = m * 16 + 4 * (lane >> 4);
+            if (UP) {
+                // two outputs of each lane's four rows: panel pair wave % 2, rows 2 * (wave / 2) and the next
+                const int j = wave & 1, v0 = 2 * (wave >> 1), col = nt * 128 + grp * 32 + j * 16 + (lane & 15);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    float u = 0.f, g = 0.f;
+#pragma unroll
+                    for (int w = 0; w < kSkinnyWaves; ++w) {
+                        u += reinterpret_cast<const float*>(&red[(w * 4 + 2 * j) * 64 + lane])[v0 + i];
+                        g += reinterpret_cast<const float*>(&red[(w * 4 + 2 * j + 1) * 64 + lane])[v0 + i];
+                    }
+                    const float hv = u * __builtin_amdgcn_rcpf(1.0f + __expf(-u)) * g;
+                    const int r = rbase + v0 + i;
+                    if (r < n && col < ldc) H[(size_t)buffer_row(rm, r) * ldc + col] = __builtin_bit_cast(uint16_t, (__bf16)hv);
+                }
+            } else {
+                f32x4 sum = red[wave * 64 + lane];                 // panel `wave`
+#pragma unroll
+                for (int w = 1; w < kSkinnyWaves; ++w) {
+                    const f32x4 t = red[(w * 4 + wave) * 64 + lane];
+                    sum[0] += t[0]; sum[1] += t[1]; sum[2] += t[2]; sum[3] += t[3];
+                }
+                const int col = nt * 256 + grp * 64 + wave * 16 + (lane & 15);
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (rbase + v < n && col < ldc) partial[(size_t)buffer_row(rm, rbase + v) * ldc + col] = sum[v];
+            }
+        }
+        return;
+    }
     // accumulator v of a fragment: row 4 * (lane / 16) + v, column lane % 16
 #pragma unroll
     for (int m = 0; m < MF; ++m)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int r = row0 + m * 16 + 4 * (lane >> 4) + v;
+            const int r = m * 16 + 4 * (lane >> 4) + v;
             if (r >= n) continue;
             const size_t at = buffer_row(rm, r);
             if (UP) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
-                    const int col = nt * 128 + wave * 32 + j * 16 + (lane & 15);
+                    const int col = nt * 128 + grp * 32 + j * 16 + (lane & 15);
                     const float u = acc[m][2 * j][v], g = acc[m][2 * j + 1][v];
                     const float hv = u * __builtin_amdgcn_rcpf(1.0f + __expf(-u)) * g;    // silu(u) * g
                     if (col < ldc) H[at * ldc + col] = __builtin_bit_cast(uint16_t, (__bf16)hv);
@@ -116,49 +164,69 @@ __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int 
             } else {
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
-                    const int col = nt * 256 + wave * 64 + p * 16 + (lane & 15);
+                    const int col = nt * 256 + grp * 64 + p * 16 + (lane & 15);
                     if (col < ldc) partial[at * ldc + col] = acc[m][p][v];
                 }
             }
         }
 }
 
-// UP:   task = (listed expert, column tile);            writes H [N, f] bf16
-// DOWN: task = (listed expert, column tile, k part);    writes partial [parts][N, d] fp32
+// UP:   task = (64 rows of a listed expert, column tile);            writes H [N, f] bf16
+// DOWN: task = (64 rows of a listed expert, column tile, k part);    writes partial [parts][N, d] fp32
 template <bool UP>
 __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
                                                                     size_t expert_stride, int K, int NT, int ldc,
                                                                     const int32_t* __restrict__ plan, uint16_t* __restrict__ H,
                                                                     float* __restrict__ partial, int max_parts, int N) {
-    int task = blockIdx.x, parts = 1;
-    if (!UP) parts = skinny_parts(plan[0], NT, max_parts);
-    const int part = UP ? 0 : task % parts;
-    if (!UP) task /= parts;
-    const int nt = task % NT, i = task / NT;
-    if (i >= plan[0]) return;
-    const int e = plan[kPlanExpert + i], n = plan[kPlanCount + i];
-    const RowMap rm = row_map<true>(plan, i, 0, n);
-    const int KT = K / 64;
-    const int kt0 = UP ? 0 : (int)((long long)part * KT / parts), kt1 = UP ? KT : (int)((long long)(part + 1) * KT / parts);
+    __shared__ f32x4 red[kSkinnyWaves * 4 * 64];
+    const int n_chunks = plan[2], parts = UP ? 1 : skinny_parts(n_chunks, NT, max_parts);
+    const bool few = n_chunks * NT * parts < kSkinnyFewTasks;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // this wavefront's four panels (8 pieces of 1 KB) of k tile 0 of the column tile
-    const uint4* Bp = reinterpret_cast<const uint4*>(Wp + (size_t)e * expert_stride + (size_t)nt * ((size_t)K * 256)) + wave * 512 + lane;
-    float* my_partial = UP ? nullptr : partial + (size_t)part * N * ldc;
-    for (int row0 = 0; row0 < n; row0 += kSkinnyRows) {
-        const int mf = (min(kSkinnyRows, n - row0) + 15) >> 4;
-        if (mf == 1) skinny_pass<UP, 1>(A, K, Bp, rm, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
-        else if (mf == 2) skinny_pass<UP, 2>(A, K, Bp, rm, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
-        else if (mf == 3) skinny_pass<UP, 3>(A, K, Bp, rm, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
-        else skinny_pass<UP, 4>(A, K, Bp, rm, n, row0, kt0, kt1, nt, wave, lane, ldc, H, my_partial);
+    int task = blockIdx.x, grp = wave;
+    if (few) {
+        grp = task & 3;
+        task >>= 2;
     }
+    const int part = UP ? 0 : task % parts;
+    if (!UP) task /= parts;
+    const int nt = task % NT, chunk = task / NT;
+    if (chunk >= n_chunks) return;
+    int i = 0;
+    while (plan[kPlanTiles1 + i + 1] <= chunk) ++i;
+    const int e = plan[kPlanExpert + i], first = (chunk - plan[kPlanTiles1 + i]) * kSkinnyRows, n = min(kSkinnyRows, plan[kPlanCount + i] - first);
+    const RowMap rm = row_map<true>(plan, i, first, n);
+    const int KT = K / 64;
+    int kt0 = UP ? 0 : (int)((long long)part * KT / parts), kt1 = UP ? KT : (int)((long long)(part + 1) * KT / parts);
+    if (few) {
+        const int k0 = kt0, len = kt1 - kt0;
+        kt0 = k0 + len * wave / kSkinnyWaves;
+        kt1 = k0 + len * (wave + 1) / kSkinnyWaves;
+    }
+    // this wavefront's four panels (8 pieces of 1 KB) of k tile 0 of the column tile
+    const uint4* Bp = reinterpret_cast<const uint4*>(Wp + (size_t)e * expert_stride + (size_t)nt * ((size_t)K * 256)) + grp * 512 + lane;
+    float* my_partial = UP ? nullptr : partial + (size_t)part * N * ldc;
+    const int mf = (n + 15) >> 4;
+#define MOE_SKINNY_PASS(MF, SPLIT) skinny_pass<UP, MF, SPLIT>(A, K, Bp, rm, n, kt0, kt1, nt, grp, wave, lane, ldc, H, my_partial, red)
+    if (few) {
+        if (mf == 1) MOE_SKINNY_PASS(1, true);
+        else if (mf == 2) MOE_SKINNY_PASS(2, true);
+        else if (mf == 3) MOE_SKINNY_PASS(3, true);
+        else MOE_SKINNY_PASS(4, true);
+    } else {
+        if (mf == 1) MOE_SKINNY_PASS(1, false);
+        else if (mf == 2) MOE_SKINNY_PASS(2, false);
+        else if (mf == 3) MOE_SKINNY_PASS(3, false);
+        else MOE_SKINNY_PASS(4, false);
+    }
+#undef MOE_SKINNY_PASS
 }
 
 // out[row] = bf16(sum over parts, in part order) for the rows of the listed buckets; one workgroup per row
 __global__ __launch_bounds__(256) void ffn_skinny_reduce_kernel(const float* __restrict__ partial, int max_parts, int NT, int N, int d,
                                                                 const int32_t* __restrict__ plan, uint16_t* __restrict__ out) {
     const int row = blockIdx.x;
-    const int n_listed = plan[0], parts = skinny_parts(n_listed, NT, max_parts);
+    const int n_listed = plan[0], parts = skinny_parts(plan[2], NT, max_parts);
     bool listed = false;
     for (int i = threadIdx.x; i < n_listed; i += 256) {
         const int st = plan[kPlanStart + i], n = plan[kPlanCount + i];
@@ -193,7 +261,7 @@ __global__ __launch_bounds__(256) void ffn_skinny_combine_kernel(const float* __
                                                                  const int32_t* __restrict__ plan, CombineTail tail, uint16_t* __restrict__ out) {
     const int t = blockIdx.x, c = blockIdx.y * 1024 + threadIdx.x * 4;
     if (c >= d) return;
-    const int parts = skinny_parts(plan[0], NT, max_parts);
+    const int parts = skinny_parts(plan[2], NT, max_parts);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int j = 0; j < tail.k; ++j) {
         const int r = t * tail.k + j, e = tail.topk_idx[r];
@@ -216,15 +284,22 @@ __global__ __launch_bounds__(256) void ffn_skinny_combine_kernel(const float* __
     *reinterpret_cast<uint2*>((uint16_t*)tail.y + (size_t)t * d + c) = make_uint2(pack_bf16(acc.x, acc.y), pack_bf16(acc.z, acc.w));
 }
 
+// workgroups for at most `tasks` tasks: four each when there are few
+static int skinny_grid(int tasks) {
+    const int few = 4 * (tasks < kSkinnyFewTasks ? tasks : kSkinnyFewTasks);
+    return tasks > few ? tasks : few;
+}
+
 // E row groups; plan has been built.  H [N, f] bf16 and the fp32 partial area (scratch_bytes) come from the workspace.
 int launch_ffn_skinny(const void* a, int N, int d, int f, int E, const void* packed, size_t s13, size_t expert_stride,
                       const int32_t* plan, void* H, float* partial, size_t scratch_bytes, void* out, CombineTail* tail, hipStream_t s) {
     const int nt_up = (int)(round_up((size_t)2 * f, 256) / 256), nt_down = (int)(round_up((size_t)d, 256) / 256);
     const uint16_t* Wp = (const uint16_t*)packed;
+    const int chunks = N / kSkinnyRows + (E < N ? E : N);              // sum of ceil(n_e / 64) never exceeds this
     int rc;
     {
         LaunchTimer timer(MOE_K_FFN_UP, s);
-        hipLaunchKernelGGL(ffn_skinny_kernel<true>, dim3((unsigned)(E * nt_up)), dim3(kSkinnyThreads), 0, s, (const uint16_t*)a, Wp,
+        hipLaunchKernelGGL(ffn_skinny_kernel<true>, dim3((unsigned)skinny_grid(chunks * nt_up)), dim3(kSkinnyThreads), 0, s, (const uint16_t*)a, Wp,
                            expert_stride, d, nt_up, f, plan, (uint16_t*)H, (float*)nullptr, 1, N);
         if ((rc = check_launch("moe_expert_ffn_grouped up launch (small batch)")) != MOE_OK) return rc;
     }
@@ -232,11 +307,11 @@ int launch_ffn_skinny(const void* a, int N, int d, int f, int E, const void* pac
     while (max_parts > 1 && ((f / 64) / max_parts < 8 || (size_t)max_parts * N * d * sizeof(float) > scratch_bytes)) --max_parts;
     if ((size_t)max_parts * N * d * sizeof(float) > scratch_bytes)
         return fail(MOE_ERR_WORKSPACE, "moe_expert_ffn_grouped: partial sums of %d rows x %d do not fit the workspace", N, d);
-    // n buckets make n * nt_down * skinny_parts workgroups: fewer than kSkinnyDownTasks + n * nt_down, whatever n
-    const int tasks = E * nt_down, grid = tasks * max_parts < tasks + kSkinnyDownTasks ? tasks * max_parts : tasks + kSkinnyDownTasks;
+    // n chunks make n * nt_down * skinny_parts workgroups: fewer than kSkinnyDownTasks + n * nt_down, whatever n
+    const int tasks = chunks * nt_down, grid = tasks * max_parts < tasks + kSkinnyDownTasks ? tasks * max_parts : tasks + kSkinnyDownTasks;
     {
         LaunchTimer timer(MOE_K_FFN_DOWN, s);
-        hipLaunchKernelGGL(ffn_skinny_kernel<false>, dim3((unsigned)grid), dim3(kSkinnyThreads), 0, s,
+        hipLaunchKernelGGL(ffn_skinny_kernel<false>, dim3((unsigned)skinny_grid(grid)), dim3(kSkinnyThreads), 0, s,
                            (const uint16_t*)H, Wp + s13, expert_stride, f, nt_down, d, plan, (uint16_t*)nullptr, partial, max_parts, N);
         if ((rc = check_launch("moe_expert_ffn_grouped down launch (small batch)")) != MOE_OK) return rc;
         if (tail != nullptr) {

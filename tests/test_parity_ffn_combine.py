@@ -9,6 +9,7 @@ import pytest
 import torch
 
 from oracle import moe_oracle as O
+from paper_2502_06643_amd import binding as B
 from paper_2502_06643_amd import synth
 from paper_2502_06643_amd.layer import MoELayer, to_device, to_host
 from util import TOL_BF16, TOL_F32, as_f64, fro_err, rel_err
@@ -123,6 +124,24 @@ def test_ffn_random_shapes_and_routings(lib, seed):
             assert rel_err(got[is_local], ref[is_local]) <= TOL_BF16, case
             assert fro_err(got[is_local], ref[is_local]) <= TOL_BF16, case
         assert np.all(got[~is_local] == 7.0), case
+
+
+@pytest.mark.parametrize("sizes,d,f", [
+    ([1, 16, 17, 33, 0, 49, 20, 5, 3], 64, 1920),      # one k tile for four wavefronts; 8 buckets x 15 column tiles: the last few ...
+    ([1, 16, 17, 33, 0, 49, 20, 5, 3], 192, 2048),     # ... and x 16: the first that are many; three k tiles
+    ([130, 2, 0, 28], 320, 448),                       # three passes over a bucket; 5 and 7 k tiles
+    ([64, 65], 1024, 64),                              # columns past the packed tile's end, long up and short down projection
+])
+def test_ffn_decode_sized_with_few_weights(lib, sizes, d, f):
+    """Streaming kernels on both sides of the rule that lets a workgroup's wavefronts share four panels."""
+    E, T = len(sizes), sum(sizes)
+    assert T <= B.FFN_STREAMING_MAX_ROWS
+    x, w1, w3, w2, _, pl = make_problem(T + f, T, d, f, E, 1, 1, "bf16")
+    idx = np.random.default_rng(T).permutation(np.repeat(np.arange(E), sizes)).astype(np.int32)[:, None]
+    L = gpu_ffn(lib, x, w1, w3, w2, idx, pl, 1, -1, "bf16")
+    dsp = O.dispatch(x, idx, pl, 1)
+    ref = O.expert_ffn_grouped(dsp["send_buf"], w1, w3, w2, dsp["expert_counts"], dsp["expert_start"], pl, -1)
+    assert rel_err(as_f64(to_host(L.ffn_out)), ref) <= TOL_BF16
 
 
 def test_ffn_skewed_buckets_including_empty_and_single_row_experts(lib):

@@ -4,16 +4,16 @@
 // (writing them to memory is optional).
 //
 // bf16: a skinny GEMM on the matrix cores that is bound by reading x once.  A
-// workgroup owns 32 tokens; its 4 wavefronts split the reduction into four
-// contiguous quarters, each feeding v_mfma_f32_32x32x16_bf16 with the activation
+// workgroup owns 32 tokens; its wavefronts (4, in small batches 16) split the
+// reduction into contiguous shares, each feeding v_mfma_f32_32x32x16_bf16 with the activation
 // fragment (lane l: token l % 32, 8 consecutive k; fetched as whole lines and
 // re-ordered through a staging tile in LDS, see the kernel) and the
 // weight fragments from the pre-packed router matrix (moe_pack_router: for every
 // 16 reduction steps and every 32 experts one 1 KB block in B-fragment order, so
-// a fragment is one coalesced 16-byte load per lane).  The four partial sums are
-// added through LDS in wavefront order, so results are reproducible; the last
-// wavefront leaves the 32 x E logits in LDS (and in memory when asked to) and
-// all 256 threads run the gate's selection on them, 8 lanes per token.
+// a fragment is one coalesced 16-byte load per lane).  The partial sums are
+// added through LDS in wavefront order, so results are reproducible; the 32 x E
+// logits stay in LDS (and go to memory when asked to) and 256 threads run the
+// gate's selection on them, 8 lanes per token.
 // fp32: one workgroup per token, one thread per expert, sequential fp32 sum,
 // then 16 lanes select from the row in LDS.
 #include "gate_select.h"
@@ -62,18 +62,25 @@ int launch_pack_router(const void* w_g, int d, int E, moe_dtype_t dt, void* pack
     return check_launch("moe_pack_router launch");
 }
 
-// LDS of the bf16 kernel, in floats: four staging tiles of 32 tokens x 64 k (bf16), then the partial sums
-// [PANELS][16][64], then the logits [32 tokens][32 * PANELS + 4] (rows padded by 16 bytes), one after the other in
-// the same memory
-constexpr int router_lds_floats(int panels) { return 32 * (32 * panels + 4) > 4 * 32 * 64 / 2 ? 32 * (32 * panels + 4) : 4 * 32 * 64 / 2; }
+// LDS of the bf16 kernel, in floats: a staging tile of 32 tokens x 64 k (bf16) per wavefront, then the partial sums
+// [PANELS][16][64] (sixteen wavefronts: [16][16][64] of one panel), then the logits [32 tokens]
+// [32 * PANELS + 4] (rows padded by 16 bytes), one after the other in the same memory
+constexpr int router_lds_floats(int panels, int waves) {
+    const int stage = waves * 32 * 64 / 2, sums = (waves == 4 ? panels : waves) * 16 * 64, rows = 32 * (32 * panels + 4);
+    return stage > sums ? (stage > rows ? stage : rows) : (sums > rows ? sums : rows);
+}
 
-template <int PANELS, int KMAX>
-__global__ __launch_bounds__(256) void router_gate_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ packed,
+// WAVES wavefronts share the reduction: four when there are workgroups for every compute unit, sixteen when the batch is
+// small and a workgroup's chain of k steps, each at the latency of memory, is all there is.  Four / sixteen, us: d 4096, 8
+// experts, 170 tokens 9.9 / 7.2, 4000 14.0 / 8.8, 6000 16.2 / 15.4, 8192 17.6 / 18.4, 30000 39.5 / 55.7; d 3008, 128
+// experts, 170 tokens 21.0 / 14.0, 6000 37.2 / 18.7.
+template <int PANELS, int KMAX, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void router_gate_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ packed,
                                                                const float* __restrict__ bias, int T, int d, int E, int k,
                                                                float* __restrict__ logits, int32_t* __restrict__ topk_idx,
                                                                float* __restrict__ topk_w) {
     extern __shared__ __attribute__((aligned(16))) float red[];      // activation staging, then [PANELS][16][64] partial sums, then the logits
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = WAVES == 4 ? (int)(threadIdx.x >> 6) : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar with four: 17.4 -> 20.6 us at 10007 tokens
     const long long t0 = (long long)blockIdx.x * 32;
     const uint16_t* wlane = packed + (size_t)lane * 8;
     f32x16 acc[PANELS];
@@ -81,7 +88,7 @@ __global__ __launch_bounds__(256) void router_gate_bf16_kernel(const uint16_t* _
     for (int p = 0; p < PANELS; ++p)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[p][v] = 0.f;
-    // Each wavefront owns a contiguous quarter of the reduction and streams it in stages of 64 k: 32 tokens x
+    // Each wavefront owns a contiguous share of the reduction and streams it in stages of 64 k: 32 tokens x
     // 128 bytes, fetched as four fully coalesced 16-byte loads per lane (lane l: token 8 j + l / 8, 16-byte chunk
     // l % 8: whole 128-byte lines) into registers one stage ahead, written to a staging tile of its own in LDS
     // (no barrier: a wavefront's LDS accesses execute in order) whose eight 16-byte slots per row are XOR-swizzled
@@ -90,9 +97,10 @@ __global__ __launch_bounds__(256) void router_gate_bf16_kernel(const uint16_t* _
     // straight from memory instead costs four partly used lines per instruction.
     constexpr int KSTAGE = 64;
     uint16_t* stage = reinterpret_cast<uint16_t*>(red) + wave * (32 * KSTAGE);
-    const int KSW = d / 4;                               // k of this wavefront; d % 64 == 0 ...
-    const int n_stage = KSW / KSTAGE;                    // ... but KSW % 64 may be 0, 16, 32 or 48: the rest goes the direct way
-    const int kw0 = wave * KSW;
+    // this wavefront's k: whole steps of 16; what is left of the last stage of 64 goes the direct way
+    const int kw0 = WAVES == 4 ? wave * (d / 4) : (int)((long long)wave * (d / 16) / WAVES) * 16;
+    const int KSW = WAVES == 4 ? d / 4 : (int)((long long)(wave + 1) * (d / 16) / WAVES) * 16 - kw0;
+    const int n_stage = KSW / KSTAGE;
     u32x4 cur[4], nxt[4];                                // the stage being multiplied and the next one, in flight (two ahead measured the same)
     const int lr = lane >> 3, lc = lane & 7;
     auto fetch = [&](int st, u32x4 (&r)[4]) {
@@ -137,44 +145,68 @@ __global__ __launch_bounds__(256) void router_gate_bf16_kernel(const uint16_t* _
         }
     }
     __syncthreads();                                     // every wavefront is done with its staging tile: the partial sums overwrite them
-    // add the four partial sums in wavefront order
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w && w < 3) {
+    constexpr int RS = 32 * PANELS + 4;                   // row stride of the logits in LDS
+    if constexpr (WAVES == 4) {
+        // add the four partial sums in wavefront order
+        for (int w = 0; w < 4; ++w) {
+            if (wave == w && w < 3) {
 #pragma unroll
-            for (int p = 0; p < PANELS; ++p)
+                for (int p = 0; p < PANELS; ++p)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        float* slot = &red[(p * 16 + v) * 64 + lane];
+                        *slot = (w == 0) ? acc[p][v] : *slot + acc[p][v];
+                    }
+            }
+            if (w < 3) __syncthreads();
+        }
+        if (wave == 3) {
+            // accumulator v: token 8*(v/4) + 4*(lane/32) + v%4 of this workgroup, expert panel*32 + lane%32.
+            // First every partial sum is read (the logits overwrite the same LDS), then the logits are written.
+#pragma unroll
+            for (int p = 0; p < PANELS; ++p) {
+                const int e = p * 32 + (lane & 31);
+                const float b = (bias != nullptr && e < E) ? bias[e] : 0.f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[p][v] = red[(p * 16 + v) * 64 + lane] + acc[p][v] + b;
+            }
+            // (a wavefront's LDS accesses execute in program order, so these reads precede the writes below)
+#pragma unroll
+            for (int p = 0; p < PANELS; ++p) {
+                const int e = p * 32 + (lane & 31);
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    float* slot = &red[(p * 16 + v) * 64 + lane];
-                    *slot = (w == 0) ? acc[p][v] : *slot + acc[p][v];
+                    const int tl = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                    red[tl * RS + e] = acc[p][v];
+                    if (logits != nullptr && t0 + tl < T && e < E) logits[(t0 + tl) * E + e] = acc[p][v];
                 }
-        }
-        if (w < 3) __syncthreads();
-    }
-    constexpr int RS = 32 * PANELS + 4;                   // row stride of the logits in LDS
-    if (wave == 3) {
-        // accumulator v: token 8*(v/4) + 4*(lane/32) + v%4 of this workgroup, expert panel*32 + lane%32.
-        // First every partial sum is read (the logits overwrite the same LDS), then the logits are written.
-#pragma unroll
-        for (int p = 0; p < PANELS; ++p) {
-            const int e = p * 32 + (lane & 31);
-            const float b = (bias != nullptr && e < E) ? bias[e] : 0.f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[p][v] = red[(p * 16 + v) * 64 + lane] + acc[p][v] + b;
-        }
-        // (a wavefront's LDS accesses execute in program order, so these reads precede the writes below)
-#pragma unroll
-        for (int p = 0; p < PANELS; ++p) {
-            const int e = p * 32 + (lane & 31);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int tl = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                red[tl * RS + e] = acc[p][v];
-                if (logits != nullptr && t0 + tl < T && e < E) logits[(t0 + tl) * E + e] = acc[p][v];
             }
         }
+    } else {
+        // panel by panel: all partial sums side by side; wavefront w adds those of accumulator w, in wavefront order
+        static_assert(WAVES == 4 || WAVES == 16, "one accumulator row per wavefront");
+        float sum[PANELS];
+        const int tl = 8 * (wave >> 2) + 4 * (lane >> 5) + (wave & 3);
+#pragma unroll
+        for (int p = 0; p < PANELS; ++p) {
+            if (p > 0) __syncthreads();
+#pragma unroll
+            for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[p][v];
+            __syncthreads();
+            const int e = p * 32 + (lane & 31);
+            float t = red[wave * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) t += red[(w * 16 + wave) * 64 + lane];
+            sum[p] = t + ((bias != nullptr && e < E) ? bias[e] : 0.f);
+            if (logits != nullptr && t0 + tl < T && e < E) logits[(t0 + tl) * E + e] = sum[p];
+        }
+        __syncthreads();                                 // the sums have been read: the logits overwrite them
+#pragma unroll
+        for (int p = 0; p < PANELS; ++p) red[tl * RS + p * 32 + (lane & 31)] = sum[p];
     }
     __syncthreads();
     // the gate: 8 lanes per token, 4 * PANELS logits per lane
+    if (threadIdx.x >= 256) return;
     const int tl = threadIdx.x >> 3;
     gate_select<8, 4 * PANELS, KMAX, false>(red + tl * RS, true, threadIdx.x & 7, t0 + tl < T, t0 + tl, E, k, topk_idx, topk_w);
 }
@@ -198,14 +230,15 @@ __global__ __launch_bounds__(256) void router_gate_f32_kernel(const float* __res
     gate_select<16, MOE_MAX_EXPERTS / 16, KMAX, false>(row, true, threadIdx.x & 15, threadIdx.x < 16, t, E, k, topk_idx, topk_w);
 }
 
-template <int PANELS>
+constexpr int kRouterSmallTokens = 7168;      // 224 workgroups
+template <int PANELS, int WAVES>
 static void launch_fused(const uint16_t* x, const uint16_t* packed, const float* bias, int T, int d, int E, int k, float* logits,
                          int32_t* idx, float* w, hipStream_t s) {
-    const dim3 grid((unsigned)((T + 31) / 32)), block(256);
-    const size_t lds = router_lds_floats(PANELS) * sizeof(float);
-    if (k <= 2) hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, 2>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w);
-    else if (k <= 8) hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, 8>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w);
-    else hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, MOE_MAX_TOPK>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w);
+    const dim3 grid((unsigned)((T + 31) / 32)), block(64 * WAVES);
+    const size_t lds = router_lds_floats(PANELS, WAVES) * sizeof(float);
+    if (k <= 2) hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, 2, WAVES>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w);
+    else if (k <= 8) hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, 8, WAVES>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w);
+    else hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, MOE_MAX_TOPK, WAVES>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w);
 }
 
 int launch_router_gate(const void* x, moe_dtype_t dt, const void* packed, const float* bias, int T, int d, int E, int k,
@@ -214,15 +247,17 @@ int launch_router_gate(const void* x, moe_dtype_t dt, const void* packed, const 
     if (dt == MOE_BF16) {
         const uint16_t* xs = (const uint16_t*)x;
         const uint16_t* ps = (const uint16_t*)packed;
+        // sixteen wavefronts for small batches (see the kernel); past 128 experts their accumulators do not fit
+        const bool small = T <= kRouterSmallTokens;
         switch (padded_experts(E) / 32) {
-            case 1: launch_fused<1>(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
-            case 2: launch_fused<2>(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
-            case 3: launch_fused<3>(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
-            case 4: launch_fused<4>(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
-            case 5: launch_fused<5>(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
-            case 6: launch_fused<6>(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
-            case 7: launch_fused<7>(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
-            default: launch_fused<8>(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 1: (small ? launch_fused<1, 16> : launch_fused<1, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 2: (small ? launch_fused<2, 16> : launch_fused<2, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 3: (small ? launch_fused<3, 16> : launch_fused<3, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 4: (small ? launch_fused<4, 16> : launch_fused<4, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 5: (launch_fused<5, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 6: (launch_fused<6, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 7: (launch_fused<7, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            default: launch_fused<8, 4>(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
         }
     } else {
         const float* xf = (const float*)x;

@@ -68,6 +68,13 @@ def check(lib, x, w_g, bias, k):
     return err, float(clear.mean())
 
 
+@pytest.mark.parametrize("T,d,E,k", [(1, 64, 8, 2), (33, 192, 32, 1),      # fewer k steps of 16 than wavefronts, shares of one step
+                                     (100, 1088, 33, 6), (31, 1984, 96, 9), (65, 2048, 128, 8),      # one to four panels, ragged shares
+                                     (64, 512, 129, 4), (7168, 64, 8, 2), (7169, 64, 8, 2)])         # ... and where four wavefronts take over
+def test_small_batches_with_sixteen_wavefronts(lib, T, d, E, k):
+    check(lib, synth.normal(T, 0, (T, d), 1.0, "bf16"), synth.normal(d, 1, (d, E), d ** -0.5, "bf16"), np.linspace(-1, 1, E), k)
+
+
 @pytest.mark.parametrize("name", ["c1", "c1b", "c2", "c4", "c3"])
 def test_config_routers(lib, name):
     cfg = synth.config(name)

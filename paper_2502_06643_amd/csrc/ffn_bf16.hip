@@ -470,9 +470,9 @@ __device__ __forceinline__ void epilogue_block(const f32x4 (&blk0)[FN], const f3
     for (int it = 0; it < 32 / RPI; ++it) {
         const int r = it * RPI + lane / CPR;
         const int gr = row_base + r;
+        const size_t at = buffer_row(rm, min(gr, w.rows - 1));
         if (gr < w.rows && col < ldc)
-            *reinterpret_cast<u32x4*>(C + (size_t)buffer_row(rm, gr) * ldc + col) =
-                *reinterpret_cast<const u32x4*>(stg + r * RS + (lane % CPR) * 8);
+            *reinterpret_cast<u32x4*>(C + at * ldc + col) = *reinterpret_cast<const u32x4*>(stg + r * RS + (lane % CPR) * 8);
     }
 }
 
@@ -624,9 +624,9 @@ __global__ __launch_bounds__(kThreads) void ffn_bf16_fixup_kernel(int K, int npa
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const int r = it * 4 + lane / 16, gr = row_base + r;
+        const size_t at = buffer_row(rm, min(gr, w.rows - 1));
         if (gr < w.rows && col < ldc)
-            *reinterpret_cast<u32x4*>(C + (size_t)buffer_row(rm, gr) * ldc + col) =
-                *reinterpret_cast<const u32x4*>(stg + r * kFixupStride + (lane % 16) * 8);
+            *reinterpret_cast<u32x4*>(C + at * ldc + col) = *reinterpret_cast<const u32x4*>(stg + r * kFixupStride + (lane % 16) * 8);
     }
 }
 

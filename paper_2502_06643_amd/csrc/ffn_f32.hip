@@ -191,7 +191,8 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
         // accumulator v: row 8 * (v / 4) + 4 * (lane / 32) + v % 4, column lane % 32
         const int r = 8 * wave + 4 * (lane >> 5) + i, c = n0 + (lane & 31);
         const float u = sum[0];
-        if (r < rows && c < NC) C[(size_t)buffer_row(rm, r) * NC + c] = UP ? u / (1.0f + expf(-u)) * sum[NP - 1] : u;
+        const size_t at = buffer_row(rm, min(r, rows - 1));
+        if (r < rows && c < NC) C[at * NC + c] = UP ? u / (1.0f + expf(-u)) * sum[NP - 1] : u;
     }
 }
 

@@ -80,7 +80,10 @@ __device__ __forceinline__ RowMap row_map(const int32_t* __restrict__ plan, int 
     return m;
 }
 
-// where row r of the tile lies in the buffer (0 <= r < rows)
+// Where row r of the tile lies in the buffer (0 <= r < rows).  It reads the segments out of other lanes' registers, so
+// the whole wavefront calls it, outside any branch that only some lanes take (there the compiler may refill or copy a
+// register for the active lanes only): a store to a ragged tile clamps its row, asks for the address and then decides
+// whether to store.
 __device__ __forceinline__ int buffer_row(const RowMap& m, int r) {
     if (!m.merged) return m.row0 + r;
     const int b = m.first + r;

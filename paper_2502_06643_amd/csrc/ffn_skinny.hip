@@ -128,7 +128,8 @@ __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int 
                     }
                     const float hv = u * __builtin_amdgcn_rcpf(1.0f + __expf(-u)) * g;
                     const int r = rbase + v0 + i;
-                    if (r < n && col < ldc) H[(size_t)buffer_row(rm, r) * ldc + col] = __builtin_bit_cast(uint16_t, (__bf16)hv);
+                    const size_t at = buffer_row(rm, min(r, n - 1));
+                    if (r < n && col < ldc) H[at * ldc + col] = __builtin_bit_cast(uint16_t, (__bf16)hv);
                 }
             } else {
                 f32x4 sum = red[wave * 64 + lane];                 // panel `wave`
@@ -139,8 +140,10 @@ __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int 
                 }
                 const int col = nt * 256 + grp * 64 + wave * 16 + (lane & 15);
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (rbase + v < n && col < ldc) partial[(size_t)buffer_row(rm, rbase + v) * ldc + col] = sum[v];
+                for (int v = 0; v < 4; ++v) {
+                    const size_t at = buffer_row(rm, min(rbase + v, n - 1));
+                    if (rbase + v < n && col < ldc) partial[at * ldc + col] = sum[v];
+                }
             }
         }
         return;
@@ -151,8 +154,8 @@ __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int 
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int r = m * 16 + 4 * (lane >> 4) + v;
+            const size_t at = buffer_row(rm, min(r, n - 1));
             if (r >= n) continue;
-            const size_t at = buffer_row(rm, r);
             if (UP) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {

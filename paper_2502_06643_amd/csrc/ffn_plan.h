@@ -9,7 +9,9 @@
 // row-tile counts.  A GEMM workgroup turns a global row-tile index into
 // (expert, first row, row count) by scanning that prefix.
 #pragma once
+#include <type_traits>
 #include "common.h"
+#include "ffn_split.h"
 
 namespace moe {
 
@@ -30,7 +32,6 @@ static_assert(kPlanInts * sizeof(int32_t) <= kPlanBytes, "plan area too small");
 //             cut by cost (RoundSplit in ffn_tiles.h); [5] = 0: it is not
 //         [7] 1: the segments of one expert are merged into one bucket
 constexpr int kPlanSmallTiles = 4, kPlanBigParts = 5, kPlanSmallParts = 6, kPlanMerged = 7;
-constexpr int kSmallTileRows = 128;
 
 // Merged buckets.  On the receive side an expert's rows arrive as one segment per source GPU.  As buckets of their own
 // they stream the expert's weights once per segment and end in a ragged tile each, so segments of one expert form one
@@ -120,54 +121,31 @@ struct PlanScratch {
     int n, n_small, total1;
 };
 
-// Split of a down projection whose 256-row tiles all run in one round (at most one tile per compute unit).  The launch
-// then lasts as long as its longest tile, so tiles are cut along k by what they cost: a tile of more than kSmallTileRows
-// rows into `big` parts, the others into `small`.  A k tile takes 1.3 us in the former (bound by the matrix pipes and
-// its 64 KB) and about 1 us in the latter (bound by its weight stream).  777 tokens at the Mixtral shape are 80 such
-// tiles and 96 small ones, 176 on 256 compute units: 312 us with the fix-up uncut, 275 with the 80 cut in two.
-// kSplitCost and kPartCost stand for the partial tiles' way through memory and the fix-up (10 us and 1.3 us a part;
-// twice and half of that chose about as well).  Called by one wavefront: lane (rounds, b) tries one or two rounds of parts (two fp32 partial tiles exist per compute
-// unit) with the big tiles in b parts.
-constexpr int kXcds = 8;
-constexpr int kMaxSplit = 8;
-constexpr int kMinSplitKT = 8;                  // a k part is at least this many k tiles
-constexpr int kMinSplitGain = 16;               // k tiles of time a split tail must save to be worth its fix-up
-// whether any split of a reduction of KT k tiles can save that much
-constexpr bool split_can_pay(int KT) {
-    const int parts = KT / kMinSplitKT < kMaxSplit ? KT / kMinSplitKT : kMaxSplit;
-    return parts > 1 && (KT - KT / parts) >= kMinSplitGain;
-}
+// The cut of a one-round launch, for the plan's header; called by one wavefront, a lane per candidate.
 __device__ __forceinline__ void round_split(int lane, int nb, int ns, const PlanShape& shape, int32_t* __restrict__ plan) {
-    constexpr int kBigCost = 4, kSmallCost = 3, kSplitCost = 32, kPartCost = 4;
-    const int KT = shape.kt_down, cpx = shape.cus_per_xcd, q = shape.nt_down / kXcds, rem = shape.nt_down % kXcds;
-    const int nbx = nb * q + (nb * rem + kXcds - 1) / kXcds, nsx = ns * q + (ns * rem + kXcds - 1) / kXcds;     // the fullest XCD
-    const int whole = (nbx > 0 ? kBigCost : kSmallCost) * KT;
-    int best = whole, big = 0, small = 1;
-    if (nbx + nsx > 0 && nbx + nsx <= cpx) {
-        const int rounds = 1 + lane / kMaxSplit % 2, b = 1 + lane % kMaxSplit;
-        const int left = rounds * cpx - b * nbx;
-        if (left >= nsx && (b == 1 || (nbx > 0 && KT / b >= kMinSplitKT))) {
-            const int tb = nbx > 0 ? kBigCost * ((KT + b - 1) / b) : 0;
-            // the small tiles in as many parts as it takes not to outlast the big ones, as far as there is room
-            int sm = 1;
-            if (nsx > 0) {
-                sm = tb > 0 ? (kSmallCost * KT + tb - 1) / tb : kMaxSplit;
-                sm = min(min(sm, kMaxSplit), min(left / nsx, KT / kMinSplitKT));
-                sm = max(sm, 1);
-            }
-            const int ts = nsx > 0 ? kSmallCost * ((KT + sm - 1) / sm) : 0, t = rounds * (tb > ts ? tb : ts);
-            // ... and what the partial tiles and the fix-up cost, in the same unit of a third of a microsecond
-            const int parts = max(b, sm), cost = t + kSplitCost + kPartCost * parts;
-            if (parts > 1 && cost < whole) { best = cost; big = b; small = sm; }
-        }
-        for (int m = 1; m < 2 * kMaxSplit; m <<= 1) {             // the shortest, then the fewest parts
-            const int ot = __shfl_xor(best, m, 64), ob = __shfl_xor(big, m, 64), os = __shfl_xor(small, m, 64);
-            if (ot < best || (ot == best && ob + os < big + small)) { best = ot; big = ob; small = os; }
-        }
+    const RoundShape r = round_shape(nb, ns, shape.nt_down, shape.kt_down, shape.cus_per_xcd);
+    RoundCut best = round_candidate(r, lane % kRoundCandidates);
+    static_assert(kRoundCandidates == 16, "the lanes of one DPP row");
+    const auto across = [&](auto ctrl) {                   // the better one of this lane's and the other half of its group's
+        const int cost = __builtin_amdgcn_mov_dpp(best.cost, decltype(ctrl)::value, 0xF, 0xF, true);
+        const int how = __builtin_amdgcn_mov_dpp(best.big | best.small << 8 | best.rounds << 16, decltype(ctrl)::value, 0xF, 0xF, true);
+        best = better_cut(best, {cost, how & 255, how >> 8 & 255, how >> 16});
+    };
+    across(std::integral_constant<int, 0xB1>());           // neighbours, pairs, ...
+    across(std::integral_constant<int, 0x4E>());
+    across(std::integral_constant<int, 0x141>());          // ... halves of eight and the row mirrored: a half agrees by then
+    across(std::integral_constant<int, 0x140>());
+    if (best.big == 0) {                                   // wave-uniform
+        if (lane == 0) plan[kPlanBigParts] = 0;
+        return;
     }
+    const RoundCut even = even_cut(r);
+    const bool odd = lane & 1;                             // even lanes price the cut, odd ones the even split
+    const float cost = launch_cost(r, odd ? even.big : best.big, odd ? even.small : best.small, odd ? even.rounds : best.rounds);
+    const float other = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, cost), 0xB1, 0xF, 0xF, true));
     if (lane == 0) {
-        plan[kPlanBigParts] = big;
-        plan[kPlanSmallParts] = small;
+        plan[kPlanBigParts] = cost < other + kSearchCost ? best.big : 0;
+        plan[kPlanSmallParts] = best.small;
     }
 }
 

@@ -1,0 +1,154 @@
+// How a GEMM launch's tiles are dealt to the XCDs and cut along k: the even split of the last, partly filled round, and
+// the cut of a launch of one round by what its tiles cost.  Arithmetic only, for host and device.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace moe {
+
+constexpr int kXcds = 8;
+constexpr int kMaxSplit = 8;
+constexpr int kMinSplitKT = 8;                  // a k part is at least this many k tiles
+constexpr int kMinSplitGain = 16;               // k tiles of time a split tail must save to be worth its fix-up
+constexpr int kSmallTileRows = 128;             // a tile of at most this many rows is a small one
+// whether any split of a reduction of KT k tiles can save that much
+constexpr bool split_can_pay(int KT) {
+    const int parts = KT / kMinSplitKT < kMaxSplit ? KT / kMinSplitKT : kMaxSplit;
+    return parts > 1 && (KT - KT / parts) >= kMinSplitGain;
+}
+
+// r tiles (less than a round of them): the number of k parts to cut each into so that the parts (at most two per compute
+// unit: that many partial tiles exist) fill the compute units in as few, short rounds as possible; 1 unless the tiles then
+// last at most three quarters of a whole round ...
+__host__ __device__ __forceinline__ int even_split(int r, int KT, int cus_per_xcd) {
+    int best = 1, best_num = 1, best_den = 1;                   // time = best_num / best_den rounds
+#pragma unroll
+    for (int sp = 2; sp <= kMaxSplit; ++sp) {                   // every workgroup of a launch runs this: no division, no branch
+        const int rounds = r * sp > cus_per_xcd ? 2 : 1;
+        const bool better = r * sp <= 2 * cus_per_xcd && KT >= kMinSplitKT * sp && rounds * best_den < best_num * sp;
+        best = better ? sp : best;
+        best_num = better ? rounds : best_num;
+        best_den = better ? sp : best_den;
+    }
+    // ... and saves at least kMinSplitGain k tiles of time: the partial tiles and the fix-up launch cost
+    // about that much, so short reductions (the many-expert layer: 22 k tiles) run their tail whole
+    return r > 0 && 4 * best_num <= 3 * best_den && (best_den - best_num) * KT >= kMinSplitGain * best_den ? best : 1;
+}
+
+struct XcdShare {
+    int q, rem;          // column tiles owned outright by every XCD; left-over column tiles (NT % 8)
+    long long main;      // tiles of the owned columns: row tiles x q
+    long long rem_begin; // this XCD's first tile in the list of left-over-column tiles
+    int full;            // tiles run whole
+    int tail;            // tiles run in `split` k parts each
+    int split;
+};
+
+// The tiles of XCD x.  Every XCD owns NT / 8 column tiles of every expert outright, so each weight
+// panel is fetched through one L2 only and all XCDs get the same mix of large and small experts; the
+// tiles of the NT % 8 left-over column tiles are dealt to the XCDs in equal contiguous ranges.
+__host__ __device__ __forceinline__ XcdShare xcd_share(int MT, int NT, int x, int KT, int cus_per_xcd, bool allow_split) {
+    XcdShare s;
+    s.q = NT / kXcds;
+    s.rem = NT - s.q * kXcds;
+    s.main = (long long)MT * s.q;
+    const long long rem_total = (long long)MT * s.rem;
+    const long long chunk = (rem_total + kXcds - 1) / kXcds;
+    s.rem_begin = (long long)x * chunk;
+    long long rcnt = rem_total - s.rem_begin;
+    rcnt = rcnt < 0 ? 0 : (rcnt > chunk ? chunk : rcnt);
+    const long long cnt = s.main + rcnt;
+    s.full = (int)cnt;
+    s.tail = 0;
+    s.split = 1;
+    if (allow_split) {
+        const int r = (int)(cnt % cus_per_xcd), split = even_split(r, KT, cus_per_xcd);
+        if (split > 1) {
+            s.full = (int)cnt - r;
+            s.tail = r;
+            s.split = split;
+        }
+    }
+    return s;
+}
+
+// A down projection whose 256-row tiles all run in one round (at most one tile per compute unit) may cut its tiles along
+// k by what they cost: a tile of more than kSmallTileRows rows (a big one) into `big` parts, the others into `small`.
+//
+// Which cut: the shortest chain.  A k tile takes 1.3 us in a big tile (bound by the matrix pipes and its 64 KB) and about
+// 1 us in a small one (bound by its weight stream); the fix-up costs 10 us and 1.3 us a part (twice and half of that
+// chose about as well).  Unit: a third of a microsecond.
+// (One wavefront works this out while the front kernel's others write, so its divisions go through the reciprocal.)
+__host__ __device__ __forceinline__ float reciprocal(int v) {
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_amdgcn_rcpf((float)v);
+#else
+    return 1.0f / (float)v;
+#endif
+}
+// x / y of 0 <= x < 2^24, y > 0
+__host__ __device__ __forceinline__ int quotient(int x, int y) {
+    int q = (int)((float)x * reciprocal(y));             // off by one at most
+    q -= q * y > x ? 1 : 0;
+    return q + ((q + 1) * y <= x ? 1 : 0);
+}
+struct RoundShape { int nb, ns, nbx, nsx, NT, KT, cpx; };      // row tiles and, on the fullest XCD, tiles of either kind
+struct RoundCut { int cost, big, small, rounds; };             // big = 0: none
+constexpr int kRoundCandidates = 2 * kMaxSplit;
+constexpr int kBigCost = 4, kSmallCost = 3, kFixupCost = 32, kPartCost = 4;
+
+__host__ __device__ __forceinline__ RoundShape round_shape(int nb, int ns, int NT, int KT, int cpx) {
+    const int q = NT / kXcds, rem = NT % kXcds;
+    return {nb, ns, nb * q + (nb * rem + kXcds - 1) / kXcds, ns * q + (ns * rem + kXcds - 1) / kXcds, NT, KT, cpx};
+}
+
+// candidate c: one or two rounds of parts (two fp32 partial tiles exist per compute unit), the big tiles in 1 to kMaxSplit
+__host__ __device__ __forceinline__ RoundCut round_candidate(const RoundShape& r, int c) {
+    const int whole = (r.nbx > 0 ? kBigCost : kSmallCost) * r.KT, rounds = 1 + c / kMaxSplit, b = 1 + c % kMaxSplit;
+    const int left = rounds * r.cpx - b * r.nbx;
+    const RoundCut none = {whole, 0, 1, 1};
+    if (r.nbx + r.nsx == 0 || r.nbx + r.nsx > r.cpx || left < r.nsx || (b > 1 && (r.nbx == 0 || r.KT < kMinSplitKT * b))) return none;
+    const int tb = r.nbx > 0 ? kBigCost * quotient(r.KT + b - 1, b) : 0;
+    int sm = 1;
+    if (r.nsx > 0) {                                   // as many as it takes not to outlast the big ones, as far as there is room
+        const int fit = quotient(left, r.nsx), room = fit < r.KT / kMinSplitKT ? fit : r.KT / kMinSplitKT;
+        sm = tb > 0 ? quotient(kSmallCost * r.KT + tb - 1, tb) : kMaxSplit;
+        sm = sm < kMaxSplit ? sm : kMaxSplit;
+        sm = sm < room ? sm : room;
+        sm = sm > 1 ? sm : 1;
+    }
+    const int ts = r.nsx > 0 ? kSmallCost * quotient(r.KT + sm - 1, sm) : 0, parts = b > sm ? b : sm;
+    const int cost = rounds * (tb > ts ? tb : ts) + kFixupCost + kPartCost * parts;
+    if (parts == 1 || cost >= whole) return none;
+    return {cost, b, sm, rounds};
+}
+
+// the cheaper one, then the one of fewer parts
+__host__ __device__ __forceinline__ RoundCut better_cut(const RoundCut& a, const RoundCut& b) {
+    return b.cost < a.cost || (b.cost == a.cost && b.big + b.small < a.big + a.small) ? b : a;
+}
+
+// Whether: what the launch takes in all, in microseconds, against the even split of xcd_share, which runs otherwise.
+// That is the chain, but never less than the chip takes to pull all tiles' operands through its L1s (1.6 us a k tile with
+// every compute unit busy: 64 KB at 40 GB/s each), and what the partial tiles cost: 5 us for the fix-up, 0.8 us for the 256
+// KB a part of a big tile on every XCD writes and reads again, less for a small one's, which are mostly empty.
+// Predicted / measured down projection, us, d 4096: f 14336, 700 tokens, whole 294 / 288, in 2 and 1 parts 267 / 266; f 7168,
+// 1000 tokens, whole 149 / 157, in 3 and 2 parts 183 / 178; f 3584, 1000 tokens, whole 76 / 86, in 3 and 2 parts 115 / 107;
+// d 1024, f 4096, 16 experts, 1500 tokens, in 5 parts each 79 / 83, in 3 and 2 61 / 58.  (A cut only had to have a shorter
+// chain than uncut tiles once: the second and third of these ran cut.)
+__host__ __device__ __forceinline__ float launch_cost(const RoundShape& r, int big, int small, int rounds) {
+    constexpr float kBigTile = 1.3f, kSmallTile = 1.0f, kBusyTile = 1.6f, kFixup = 5.0f, kBigPart = 0.8f, kSmallPart = 0.3f;
+    const float tb = r.nbx > 0 ? kBigTile * reciprocal(big) : 0.f, ts = r.nsx > 0 ? kSmallTile * reciprocal(small) : 0.f;
+    const float chain = (float)rounds * (tb > ts ? tb : ts), busy = kBusyTile * (float)(r.nbx + r.nsx) * reciprocal(r.cpx);
+    const float parts = (big > 1 ? kBigPart * (float)(big * r.nbx) : 0.f) + (small > 1 ? kSmallPart * (float)(small * r.nsx) : 0.f);
+    return (float)r.KT * (chain > busy ? chain : busy) + (big > 1 || small > 1 ? kFixup + parts : 0.f);
+}
+constexpr float kSearchCost = 3.5f;                    // the even split is searched by every workgroup of the launch: 2 to 4.5 us where both cut alike
+
+// the even split of a launch of one round, as a cut
+__host__ __device__ __forceinline__ RoundCut even_cut(const RoundShape& r) {
+    const int rem = (r.nb + r.ns) * (r.NT % kXcds), tiles = (r.nb + r.ns) * (r.NT / kXcds) + (rem + kXcds - 1) / kXcds;    // of the fullest XCD
+    const int split = tiles < r.cpx ? even_split(tiles, r.KT, r.cpx) : 1;
+    return {0, split, split, tiles * split > r.cpx ? 2 : 1};
+}
+
+}  // namespace moe

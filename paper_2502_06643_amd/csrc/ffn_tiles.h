@@ -18,56 +18,6 @@ struct WorkItem {
     int partial;         // slot of the fp32 partial tile, or -1 for a whole tile
 };
 
-struct XcdShare {
-    int q, rem;          // column tiles owned outright by every XCD; left-over column tiles (NT % 8)
-    long long main;      // tiles of the owned columns: row tiles x q
-    long long rem_begin; // this XCD's first tile in the list of left-over-column tiles
-    int full;            // tiles run whole
-    int tail;            // tiles run in `split` k parts each
-    int split;
-};
-
-// The tiles of XCD x.  Every XCD owns NT / 8 column tiles of every expert outright, so each weight
-// panel is fetched through one L2 only and all XCDs get the same mix of large and small experts; the
-// tiles of the NT % 8 left-over column tiles are dealt to the XCDs in equal contiguous ranges.
-__host__ __device__ __forceinline__ XcdShare xcd_share(int MT, int NT, int x, int KT, int cus_per_xcd, bool allow_split) {
-    XcdShare s;
-    s.q = NT / kXcds;
-    s.rem = NT - s.q * kXcds;
-    s.main = (long long)MT * s.q;
-    const long long rem_total = (long long)MT * s.rem;
-    const long long chunk = (rem_total + kXcds - 1) / kXcds;
-    s.rem_begin = (long long)x * chunk;
-    long long rcnt = rem_total - s.rem_begin;
-    rcnt = rcnt < 0 ? 0 : (rcnt > chunk ? chunk : rcnt);
-    const long long cnt = s.main + rcnt;
-    s.full = (int)cnt;
-    s.tail = 0;
-    s.split = 1;
-    if (allow_split) {
-        // r tiles in the last round: cut each into sp k parts so that the r * sp parts (at most two per
-        // compute unit: that many partial tiles exist) fill the compute units in as few, short rounds as
-        // possible; taken when the tail then lasts at most three quarters of a whole round
-        const int r = (int)(cnt % cus_per_xcd);
-        if (r > 0) {
-            int best = 1, best_num = 1, best_den = 1;           // tail time = best_num / best_den rounds
-            for (int sp = 2; sp <= kMaxSplit; ++sp) {
-                if (r * sp > 2 * cus_per_xcd || KT / sp < kMinSplitKT) break;
-                const int rounds = (r * sp + cus_per_xcd - 1) / cus_per_xcd;
-                if (rounds * best_den < best_num * sp) { best = sp; best_num = rounds; best_den = sp; }
-            }
-            // ... and saves at least kMinSplitGain k tiles of time: the partial tiles and the fix-up launch cost
-            // about that much, so short reductions (the many-expert layer: 22 k tiles) run their tail whole
-            if (best > 1 && 4 * best_num <= 3 * best_den && (best_den - best_num) * KT >= kMinSplitGain * best_den) {
-                s.full = (int)cnt - r;
-                s.tail = r;
-                s.split = best;
-            }
-        }
-    }
-    return s;
-}
-
 // Tile order inside one expert: row tiles are taken in chunks of `row_chunk`, and within a chunk the
 // column tile advances before the chunk does, so the ~32 tiles that run together on an XCD form a
 // row_chunk x (32 / row_chunk) block that streams row_chunk activation panels and 32 / row_chunk

@@ -27,6 +27,45 @@ using namespace moe;
 
 struct Part { int bucket, mt, nt, kt0, kt1; };
 
+#ifdef WITH_ROUND_SPLIT
+static long long chosen_cuts = 0, cut_launches = 0;
+
+// round_split's choice (csrc/ffn_plan.h), candidate after candidate
+static RoundCut choose(const RoundShape& r) {
+    RoundCut best = round_candidate(r, 0);
+    for (int c = 1; c < kRoundCandidates; ++c) best = better_cut(best, round_candidate(r, c));
+    if (best.big == 0) return best;
+    const RoundCut even = even_cut(r);
+    if (!(launch_cost(r, best.big, best.small, best.rounds) < launch_cost(r, even.big, even.small, even.rounds) + kSearchCost)) best.big = 0;
+    return best;
+}
+
+// Launches that were measured both ways: cut by cost only where that was the faster way (down projection of 256 compute
+// units, us, even split or uncut / cut).
+static int check_measured_choices() {
+    struct Measured { int nb, ns, NT, KT; bool cut; };
+    const Measured table[] = {
+        {8, 4, 16, 112, false},    // d 4096, f 7168, 1000 tokens: 157 / 181
+        {7, 4, 16, 112, false},    // ... 927 tokens: 159 / 174
+        {8, 4, 16, 56, false},     // f 3584, 1000 tokens: 89 / 107
+        {8, 4, 16, 224, false},    // f 14336, 1000 tokens: 296 / 312
+        {5, 6, 16, 56, false},     // f 3584, 846 tokens: 82 / 85
+        {5, 6, 16, 224, true},     // f 14336, 700 tokens: 288 / 266
+        {5, 6, 16, 112, true},     // f 7168, 777 tokens: 153 / 145
+        {3, 6, 8, 64, true},       // d 2048, f 4096, 600 tokens: 72 / 54
+        {8, 4, 8, 64, true},       // ... 1000 tokens: 80 / 70
+        {12, 11, 4, 64, true},     // d 1024, f 4096, 16 experts, 1500 tokens: 83 / 58
+        {7, 4, 10, 42, true},      // d 2432, f 2688, 4 of 32 experts, 4000 tokens: 65 / 56 (the split is the same, it need not be searched)
+        {0, 4, 16, 224, true},     // f 14336, 4 of 8 experts, 300 tokens: 102 / 97
+    };
+    for (const Measured& m : table) {
+        const RoundCut c = choose(round_shape(m.nb, m.ns, m.NT, m.KT, 32));
+        CHECK((c.big > 0) == m.cut, "%d big and %d small row tiles, NT %d, KT %d: cut (%d, %d)", m.nb, m.ns, m.NT, m.KT, c.big, c.small);
+    }
+    return 0;
+}
+#endif
+
 static int check_case(std::mt19937& rng, long long& units) {
     const int bms[2] = {256, 384};
     const int nts[10] = {1, 2, 5, 8, 11, 16, 23, 32, 57, 112};
@@ -59,17 +98,25 @@ static int check_case(std::mt19937& rng, long long& units) {
     }
     prefix[n] = mt_total;
 #ifdef WITH_ROUND_SPLIT
-    // tiles of more than 128 rows and the others cut into any numbers of parts that fit two per compute unit
+    // tiles of more than 128 rows and the others cut apart: as the plan would choose, or else into any numbers of parts that fit two per compute unit
     int n_small = 0;
     for (int i = 0; i < n; ++i) n_small += (count[i] - 1) % kShortTileRows < kSmallTileRows ? 1 : 0;
     if (BM == kShortTileRows) {
-        const int nb = mt_total - n_small, q = NT / kXcds, rem = NT % kXcds;
-        const int nbx = nb * q + (nb * rem + kXcds - 1) / kXcds, nsx = n_small * q + (n_small * rem + kXcds - 1) / kXcds;
-        const int big = 1 + rng() % kMaxSplit, small = 1 + rng() % kMaxSplit;
-        if (nbx + nsx <= cpx && nbx * big + nsx * small <= 2 * cpx && (big == 1 || KT / big >= kMinSplitKT) && (small == 1 || KT / small >= kMinSplitKT)) {
+        const RoundShape r = round_shape(mt_total - n_small, n_small, NT, KT, cpx);
+        const RoundCut chosen = choose(r);
+        int big = 1 + rng() % kMaxSplit, small = 1 + rng() % kMaxSplit;
+        if (chosen.big > 0) {
+            big = chosen.big;
+            small = chosen.small;
+            ++chosen_cuts;
+        }
+        const bool fits = r.nbx + r.nsx <= cpx && r.nbx * big + r.nsx * small <= 2 * cpx && (big == 1 || KT / big >= kMinSplitKT) && (small == 1 || KT / small >= kMinSplitKT);
+        CHECK(fits || chosen.big == 0, "cut (%d, %d) of %d and %d tiles on %d compute units, %d k tiles", big, small, r.nbx, r.nsx, cpx, KT);
+        if (fits) {
             plan[kPlanSmallTiles] = 1 + n_small;
             plan[kPlanBigParts] = big;
             plan[kPlanSmallParts] = small;
+            if (split) ++cut_launches;
         }
     }
 #endif
@@ -154,11 +201,17 @@ int main(int argc, char** argv) {
     const int cases = argc > 1 ? std::atoi(argv[1]) : 2000;
     std::mt19937 rng(20250209);
     long long units = 0;
+#ifdef WITH_ROUND_SPLIT
+    if (check_measured_choices()) return 1;
+#endif
     for (int c = 0; c < cases; ++c)
         if (check_case(rng, units)) {
             std::printf("case %d\n", c);
             return 1;
         }
+#ifdef WITH_ROUND_SPLIT
+    CHECK(chosen_cuts > 0 && cut_launches > 0, "%lld cuts chosen, %lld launches cut", chosen_cuts, cut_launches);
+#endif
     std::printf("ok: %d launches, %lld k tiles owned exactly once\n", cases, units);
     return 0;
 }

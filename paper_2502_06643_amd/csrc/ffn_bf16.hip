@@ -648,6 +648,13 @@ struct FfnCall {
 template <bool UP>
 constexpr int launch_smem() { return smem_bytes<UP, 3>() > smem_bytes<UP, 2>() ? smem_bytes<UP, 3>() : smem_bytes<UP, 2>(); }
 
+static hipError_t compute_units_per_xcd(int dev, int* cpx) {
+    int cus = 0;
+    const hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    *cpx = cus >= kXcds ? (cus / kXcds < kMaxCusPerXcd ? cus / kXcds : kMaxCusPerXcd) : 32;
+    return e;
+}
+
 // Per-device set-up, done on the first call on each device (not during a stream capture: it calls
 // hipFuncSetAttribute): the LDS sizes of the kernels are raised and the compute units per XCD are read.
 // A failure is reported and tried again by the next call rather than remembered.
@@ -663,14 +670,13 @@ int ffn_bf16_device_setup(int* cus_per_xcd) {
     std::lock_guard<std::mutex> lock(mutex);
     Setup& st = setup[dev];
     if (!st.done) {
-        int r, cus = 0;
+        int r;
         if ((r = set_smem(&ffn_bf16_kernel<true, false, false>, launch_smem<true>())) != MOE_OK) return r;
         if ((r = set_smem(&ffn_bf16_kernel<false, true, false>, launch_smem<false>())) != MOE_OK) return r;
         if ((r = set_smem(&ffn_bf16_kernel<true, false, true>, launch_smem<true>())) != MOE_OK) return r;
         if ((r = set_smem(&ffn_bf16_kernel<false, true, true>, launch_smem<false>())) != MOE_OK) return r;
-        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        e = compute_units_per_xcd(dev, &st.cpx);
         if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
-        st.cpx = cus >= kXcds ? (cus / kXcds < kMaxCusPerXcd ? cus / kXcds : kMaxCusPerXcd) : 32;
         st.done = true;
     }
     *cus_per_xcd = st.cpx;
@@ -709,11 +715,18 @@ int launch_ffn_bf16(const void* a, int N, int d, int f, int E, const void* packe
     PlanShape shape;
     int rc = ffn_plan_shape(MOE_BF16, N, d, f, E, local_gpu < 0 && group_expert == nullptr, &shape);
     if (rc != MOE_OK) return rc;
-    // groups that may share an expert are merged; the row offsets of a merged bucket must fit 32 bits
+    // groups that may share an expert may be merged; the row offsets of a merged bucket must fit 32 bits
     const bool mergeable = group_expert != nullptr && (size_t)N * (d > f ? d : f) * 2 < ((size_t)1 << 32);
     if (!plan_ready) {
+        int dev = 0, cpx = 0;
+        if (mergeable) {
+            hipError_t e = hipGetDevice(&dev);
+            if (e == hipSuccess) e = compute_units_per_xcd(dev, &cpx);
+            if (e != hipSuccess) return hip_fail(e, "moe_expert_ffn_segments: compute units");
+        }
         rc = launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, shape,
-                             !mergeable ? 0 : (N <= kFfnSkinnyMaxRows ? 1 : 2), plan, s);
+                             !mergeable ? 0 : (N <= kFfnSkinnyMaxRows ? 1 : 2),
+                             {(int)(npad13(f) / BN), d / BK, (int)(npad2(d) / BN), f / BK, cpx}, plan, s);
         if (rc != MOE_OK) return rc;
     }
     if (N <= kFfnSkinnyMaxRows) {

@@ -105,10 +105,11 @@ __device__ __forceinline__ int buffer_row(const RowMap& m, int r) {
 // at least kLargeBucketRows rows on average, else bm1.
 constexpr int kLargeBucketRows = 544;     // measured crossover at the Mixtral shape: 512 rows per bucket favour 256-row tiles by 1 %, 640 favour 384 by 5 %
 // merge: what becomes of several groups with the same weights: 0 each stays a bucket, 1 they are merged, 2 they are
-// merged unless the groups are large enough for the tall tiles as they are
+// merged unless the groups are large enough for the tall tiles as they are; with merge_shape.cpx > 0 only where
+// merge_pays (1: the streaming kernels follow, 2: the tiled ones)
 int launch_ffn_plan(const int32_t* counts, const int32_t* starts, const int32_t* placement, int local_gpu,
-                    const int32_t* group_expert, int n_weights, int E, int N, const PlanShape& shape, int merge, int32_t* plan,
-                    hipStream_t s);
+                    const int32_t* group_expert, int n_weights, int E, int N, const PlanShape& shape, int merge, const MergeShape& merge_shape,
+                    int32_t* plan, hipStream_t s);
 
 constexpr int kF32TileRows = 32;                        // tile height of the fp32 path
 constexpr int kTallTileRows = 384, kShortTileRows = 256; // tile heights of the bf16 path

@@ -8,13 +8,13 @@ struct MergeScratch {
     int wt[MOE_MAX_EXPERTS], cnt[MOE_MAX_EXPERTS];           // per group
     int off[MOE_MAX_EXPERTS], idx[MOE_MAX_EXPERTS];          // ... its first row and its number among its bucket's segments
     int rows[MOE_MAX_EXPERTS], segs[MOE_MAX_EXPERTS];        // per expert
-    int total;
+    int pays;
 };
 
 __global__ __launch_bounds__(kPlanThreads) void ffn_plan_kernel(const int32_t* __restrict__ counts, const int32_t* __restrict__ starts,
                                                                 const int32_t* __restrict__ placement, int local_gpu,
                                                                 const int32_t* __restrict__ group_expert, int n_weights, int E, int N,
-                                                                PlanShape shape, int merge, int32_t* __restrict__ plan) {
+                                                                PlanShape shape, int merge, MergeShape merge_shape, int32_t* __restrict__ plan) {
     __shared__ PlanScratch scratch;
     __shared__ MergeScratch ms;
     const int e = threadIdx.x;
@@ -33,16 +33,39 @@ __global__ __launch_bounds__(kPlanThreads) void ffn_plan_kernel(const int32_t* _
             ms.cnt[e] = c;
             ms.off[e] = ms.idx[e] = ms.rows[e] = ms.segs[e] = 0;
         }
-        if (e == 0) ms.total = 0;
         const int n = __syncthreads_count(c > 0);
         if (c > 0) {
             atomicAdd(&ms.rows[wt], c);
             atomicAdd(&ms.segs[wt], 1);
-            atomicAdd(&ms.total, c);
         }
         __syncthreads();
         const int n_buckets = __syncthreads_count(e < MOE_MAX_EXPERTS && ms.segs[e & (MOE_MAX_EXPERTS - 1)] > 0);
-        if (n_buckets == n || (merge == 2 && ms.total >= (long long)kLargeBucketRows * n)) merge = 0;
+        if (n_buckets == n) merge = 0;
+        if (merge != 0 && e < 64) {
+            // One wavefront adds everything up and decides: sums of different values into one LDS address go lane by lane,
+            // 3 to 5 us for 64 segments
+            const int bm1_bits = __builtin_ctz(shape.bm1);    // 32, 64 or 256 rows
+            int total = 0;
+            Buckets apart = {0, 0}, merged = {0, 0};
+#pragma unroll
+            for (int i = 0; i < MOE_MAX_EXPERTS / 64; ++i) {
+                const int co = ms.cnt[i * 64 + e], ro = ms.rows[i * 64 + e];
+                total += co;
+                apart = {apart.tiles + ((co + shape.bm1 - 1) >> bm1_bits), max(apart.max_rows, co)};
+                merged = {merged.tiles + ((ro + shape.bm1 - 1) >> bm1_bits), max(merged.max_rows, ro)};
+            }
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) {
+                total += __shfl_xor(total, m, 64);
+                apart = {apart.tiles + __shfl_xor(apart.tiles, m, 64), max(apart.max_rows, __shfl_xor(apart.max_rows, m, 64))};
+                merged = {merged.tiles + __shfl_xor(merged.tiles, m, 64), max(merged.max_rows, __shfl_xor(merged.max_rows, m, 64))};
+            }
+            const bool pays = !(merge == 2 && total >= (long long)kLargeBucketRows * n) &&
+                              (merge_shape.cpx == 0 || merge_pays(merge_shape, apart, merged, merge == 1));
+            if (e == 0) ms.pays = pays;
+        }
+        __syncthreads();
+        if (merge != 0 && !ms.pays) merge = 0;
     }
     if (merge == 0) {
         build_plan(scratch, e, c, st, wt, E, shape, plan);
@@ -102,11 +125,11 @@ int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_re
 }
 
 int launch_ffn_plan(const int32_t* counts, const int32_t* starts, const int32_t* placement, int local_gpu,
-                    const int32_t* group_expert, int n_weights, int E, int N, const PlanShape& shape, int merge, int32_t* plan,
-                    hipStream_t s) {
+                    const int32_t* group_expert, int n_weights, int E, int N, const PlanShape& shape, int merge, const MergeShape& merge_shape,
+                    int32_t* plan, hipStream_t s) {
     LaunchTimer timer(MOE_K_FFN_PLAN, s);
     hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, counts, starts, placement, local_gpu, group_expert, n_weights, E, N,
-                       shape, merge, plan);
+                       shape, merge, merge_shape, plan);
     return check_launch("moe_expert_ffn_grouped plan launch");
 }
 

@@ -39,7 +39,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kSkinnyThreads = 256, kSkinnyWaves = kSkinnyThreads / 64;
-constexpr int kSkinnyFewTasks = 128;     // fewer than this: a workgroup of each splits the reduction among its wavefronts
 static_assert(kSkinnyRows == 64, "four 16-row fragments");
 constexpr int kSkinnyMaxParts = 16;
 constexpr int kSkinnyDownTasks = 512;    // workgroups the down projection is cut into

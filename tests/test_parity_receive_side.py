@@ -112,6 +112,34 @@ def test_segments_of_one_expert_in_any_order(lib, dtype, d, f, E, segs):
     assert np.all(got[~mine] == 7.0)
 
 
+@pytest.mark.parametrize("d,f,E,segs,merged", [
+    # whether the plan merges the segments of an expert, on both sides of its rule (256 compute units), and what it computes then
+    (64, 1408, 6, [(0, 6)] * 9 + [(0, 5)] + [(e, 3) for e in (1, 2, 3, 4, 5)], 0),                 # streaming, a bucket of 59 rows: apart
+    (64, 1408, 6, [(0, 4)] * 10 + [(e, 3) for e in (1, 2, 3, 4, 5)], 1),                           # ... of 40 rows
+    (64, 14336, 3, [(0, 4), (1, 2), (0, 2), (2, 1)], 0),                                           # four segments, three experts
+    (128, 1408, 3, [(i % 3, 20) for i in range(17)], 0),                                           # tiles: one round either way
+    (128, 2112, 3, [(i % 3, 1 + 7 * i % 60) for i in range(48)], 1),                               # ... more than two rounds
+    (64, 320, 2, [(i % 2, 1 + i % 5) for i in range(256)], 1),                                     # ... 128 segments a bucket
+    (64, 64, 2, [(0, 1000), (1, 600), (0, 544), (1, 560)], 0),                                     # enough rows a segment for tall tiles
+])
+def test_segments_merge_where_it_pays(lib, d, f, E, segs, merged):
+    w = [synth.normal(d, i, s, s[1] ** -0.5, "bf16") for i, s in ((2, (E, d, f)), (3, (E, d, f)), (4, (E, f, d)))]
+    se, sc = np.array(segs, dtype=np.int32).T.copy()
+    ss = np.concatenate([[0], np.cumsum(sc)[:-1]]).astype(np.int32)
+    N = int(sc.sum())
+    x = synth.normal(d + 1, 0, (N, d), 1.0, "bf16")
+    packed = torch.empty(B.moe_packed_weights_bytes(E, d, f, B.MOE_BF16), dtype=torch.uint8, device="cuda")
+    B.moe_pack_weights(*[to_device(a) for a in w], E, d, f, B.MOE_BF16, packed)
+    ws = torch.empty(B.moe_ffn_workspace_bytes(N, d, f, E, B.MOE_BF16), dtype=torch.uint8, device="cuda").fill_(0xAA)
+    out = torch.full((N, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    dev = lambda a: torch.from_numpy(a).cuda()
+    B.moe_expert_ffn_segments(to_device(x), B.MOE_BF16, N, d, f, E, packed, len(segs), dev(se), dev(sc), dev(ss), out, ws)
+    torch.cuda.synchronize()
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert int(ws[28:32].view(torch.int32)) == merged              # the plan's header
+    assert rel_err(as_f64(to_host(out)), O.expert_ffn_segments(x, *w, se, sc, ss)) <= TOL_BF16
+
+
 def test_receive_segments_table_edge_cases(lib):
     """moe_receive_segments against a host loop: uneven map, a destination without experts, negative counts, a table
     that is larger than needed (padded with empty segments at the end) and one that is too small (n_seg says so)."""

@@ -27,6 +27,38 @@ using namespace moe;
 
 struct Part { int bucket, mt, nt, kt0, kt1; };
 
+// Receives that were measured with their segments apart and merged (us): merged where that was the faster way.
+static int check_measured_merges() {
+    struct Measured { MergeShape m; Buckets apart, merged; bool streaming, merge; };
+    const MergeShape fine = {11, 32, 8, 22, 32}, mixtral = {112, 64, 16, 224, 32};
+    const Measured table[] = {
+        {fine, {17, 27}, {3, 211}, false, false},        // 54 / 94
+        {fine, {23, 99}, {10, 786}, false, false},       // 65 / 93
+        {fine, {30, 39}, {9, 289}, false, false},        // 80 / 95
+        {fine, {37, 53}, {9, 402}, false, true},         // 96 / 92
+        {fine, {28, 21}, {11, 81}, false, true},         // 77 / 70
+        {fine, {47, 40}, {8, 150}, false, true},         // 119 / 82
+        {fine, {167, 2428}, {118, 19338}, false, true},  // 522 / 460
+        {mixtral, {8, 40}, {2, 144}, false, true},       // 313 / 176
+        {mixtral, {8, 147}, {5, 287}, false, true},      // 422 / 390
+        {fine, {15, 9}, {6, 58}, true, false},           // 48 / 59
+        {fine, {17, 7}, {9, 23}, true, true},            // 55 / 51
+        {fine, {17, 9}, {12, 18}, true, false},          // 56 / 59
+        {fine, {20, 7}, {13, 13}, true, true},           // 62 / 56
+        {fine, {28, 18}, {12, 70}, true, false},         // 82 / 88
+        {fine, {27, 27}, {16, 53}, true, true},          // 96 / 90
+        {fine, {24, 15}, {9, 110}, true, true},          // 74 / 65
+        {fine, {17, 12}, {4, 94}, true, true},           // 54.5 / 52
+        {mixtral, {4, 4}, {3, 6}, true, false},          // 195 / 231
+        {mixtral, {5, 4}, {4, 6}, true, true},           // 280 / 258
+        {mixtral, {8, 10}, {2, 32}, true, true},         // 304 / 164
+    };
+    for (const Measured& c : table)
+        CHECK(merge_pays(c.m, c.apart, c.merged, c.streaming) == c.merge, "%d tiles, at most %d rows, to %d, at most %d", c.apart.tiles,
+              c.apart.max_rows, c.merged.tiles, c.merged.max_rows);
+    return 0;
+}
+
 #ifdef WITH_ROUND_SPLIT
 static long long chosen_cuts = 0, cut_launches = 0;
 
@@ -204,6 +236,7 @@ int main(int argc, char** argv) {
 #ifdef WITH_ROUND_SPLIT
     if (check_measured_choices()) return 1;
 #endif
+    if (check_measured_merges()) return 1;
     for (int c = 0; c < cases; ++c)
         if (check_case(rng, units)) {
             std::printf("case %d\n", c);

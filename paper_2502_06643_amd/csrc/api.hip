@@ -394,7 +394,7 @@ int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T,
     hipStream_t s = (hipStream_t)stream;
     PlanTask pt = {(int32_t*)ffn_workspace, local_gpu, {}};
     if ((rc = ffn_plan_shape(dt, N, d, f, E, local_gpu < 0, &pt.shape)) != MOE_OK) return rc;
-    if (front_fits(T, E, k)) {
+    if (front_fits(T, E, k, row_bytes)) {
         FrontArgs a;
         a.x = (const uint4*)x; a.logits = logits; a.T = T; a.E = E; a.k = k; a.G = G; a.local_gpu = local_gpu;
         a.units_per_row = row_bytes / 16; a.placement = placement; a.topk_idx = topk_idx; a.topk_w = topk_w; a.perm = perm;

@@ -112,11 +112,19 @@ __global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
 // lanes per token of the gate for E experts
 static int front_lanes(int E) { return E <= 8 ? 1 : (E <= 64 ? 4 : 16); }
 
-bool front_fits(int T, int E, int k) {
-    // every workgroup gates and sorts the whole batch: at most kFrontMaxRoutes routes and eight passes of the gate
+bool front_fits(int T, int E, int k, int row_bytes) {
+    // Every workgroup gates and sorts the whole batch by itself, which is what the launches it saves are worth only for so
+    // many passes of the gate: six with one lane per token, with more lanes (sorted lists) two up to top-2 and one beyond.
+    // And one workgroup a compute unit copies rows slower than a launch of its own, which shows past kFrontMaxBytes of them.
+    // Layer with a small FFN, us, separate launches / fused: 8 experts, top-2, d 4096, 4096 tokens (67 MB of rows) 157 / 156,
+    // 6144 (101 MB) 182 / 186; fp32, d 256, 6144 tokens (13 MB) 48.1 / 46.8; top-1, d 2048, 6144 tokens 96.2 / 95.2, 8192 102 / 103;
+    // 64 experts, top-2, d 1024, 512 tokens 46.5 / 45.2, 768 48.8 / 50.6; 64 experts, top-6, d 2048, 256 tokens 68.7 / 66.0,
+    // 512 72.1 / 72.3, 2048 115 / 137; 128 experts, top-8, d 1024, 64 tokens 46.2 / 44.0, 128 50.7 / 51.8, 512 64 / 86; 256
+    // experts, top-2, d 2048, 128 tokens 72.8 / 71.9, 256 75.2 / 79.4.
     const long long N = (long long)T * k;
-    static_assert(8 * kIndexThreads <= (kFrontGroups - 1) * kFrontMaxTokens, "a workgroup's tokens fit its tables");
-    return T > 0 && N <= kFrontMaxRoutes && (long long)T * front_lanes(E) <= 8 * kIndexThreads;
+    const int passes = front_lanes(E) == 1 ? kFrontMaxPasses : (k <= 2 ? 2 : 1);
+    static_assert(kFrontMaxPasses * kIndexThreads <= (kFrontGroups - 1) * kFrontMaxTokens, "a workgroup's tokens fit its tables");
+    return T > 0 && N <= kFrontMaxRoutes && N * row_bytes <= kFrontMaxBytes && (long long)T * front_lanes(E) <= (long long)passes * kIndexThreads;
 }
 
 int launch_front(const FrontArgs& args, hipStream_t s) {

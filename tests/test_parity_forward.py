@@ -20,12 +20,12 @@ OUTPUTS = ("topk_idx", "topk_w", "send_buf", "perm", "inv_perm", "expert_counts"
     ("bf16", 81, 64, 128, 8, 2, 4, 2),            # the first one past it
     ("bf16", 10, 128, 64, 256, 16, 8, 3),         # 16 lanes per token, 16 routes per token
     ("bf16", 255, 64, 64, 5, 3, 2, 1),            # logit rows that are no multiple of 16 bytes
-    ("bf16", 257, 64, 64, 64, 6, 8, 7),           # one workgroup owns two tokens
-    ("bf16", 2048, 64, 64, 64, 6, 8, 0),          # the last batch of the fused front: 12288 routes, eight gate passes
-    ("bf16", 2049, 64, 64, 64, 6, 8, 0),          # the first one past it
-    ("bf16", 6144, 4096, 64, 8, 2, 1, -1),        # 12288 routes again, more rows per workgroup than are prefetched
-    ("bf16", 512, 64, 64, 200, 1, 3, -1),         # eight gate passes of 16 lanes per token
-    ("bf16", 8192, 64, 64, 3, 1, 1, -1),          # 32 tokens per workgroup
+    ("bf16", 257, 64, 64, 64, 6, 8, 7),           # past the fused front (FUSED_FRONT below has its edges): gate and index kernels
+    ("bf16", 2048, 64, 64, 64, 6, 8, 0),
+    ("bf16", 2049, 64, 64, 64, 6, 8, 0),
+    ("bf16", 6144, 4096, 64, 8, 2, 1, -1),        # rows of 8 KB
+    ("bf16", 512, 64, 64, 200, 1, 3, -1),         # 16 lanes per token
+    ("bf16", 8192, 64, 64, 3, 1, 1, -1),
     ("bf16", 8193, 64, 64, 3, 2, 2, 1),           # the plan comes from the one-workgroup index kernel: 16386 routes are past it, ...
     ("bf16", 8192, 64, 64, 100, 2, 5, 1),         # ... 16384 the last
     ("bf16", 20000, 64, 64, 256, 2, 256, 255),    # ... and from the rank kernel, widest tables
@@ -35,6 +35,30 @@ OUTPUTS = ("topk_idx", "topk_w", "send_buf", "perm", "inv_perm", "expert_counts"
     ("f32", 1025, 36, 100, 9, 2, 2, 1),
 ])
 def test_forward_equals_the_four_calls(lib, dtype, T, d, f, E, k, G, local):
+    check_forward(dtype, T, d, f, E, k, G, local)
+
+
+FUSED_FRONT = [  # the last sizes of the fused front and the first ones past it
+    ((257, 64, 8, 2, 4, 1), True),                # one workgroup owns two tokens
+    ((256, 64, 64, 6, 8, 7), True), ((257, 64, 64, 6, 8, 7), False),            # one gate pass of 4 lanes per token
+    ((512, 64, 33, 2, 2, 0), True), ((513, 64, 33, 2, 2, 0), False),            # two of them up to top-2
+    ((64, 64, 256, 16, 8, 3), True), ((65, 64, 256, 16, 8, 3), False),          # 16 lanes per token
+    ((128, 64, 200, 1, 3, -1), True), ((129, 64, 200, 1, 3, -1), False),
+    ((6144, 1024, 8, 2, 1, -1), True), ((6145, 64, 8, 1, 1, -1), False),        # six passes of one lane; 25 tokens per workgroup, more rows than are prefetched
+    ((4608, 4096, 8, 2, 1, -1), True), ((4609, 4096, 8, 2, 1, -1), False),      # 72 MB of rows
+    ((1536, 64, 8, 8, 2, 1), True), ((1537, 64, 8, 8, 2, 1), False),            # 12288 routes
+]
+
+
+@pytest.mark.parametrize("shape,fused", FUSED_FRONT)
+def test_where_the_front_is_fused(lib, shape, fused):
+    T, d, E, k, G, local = shape
+    B.moe_timing_begin(1 << B.KERNEL_NAMES.index("front"), 64)
+    check_forward("bf16", T, d, 64, E, k, G, local)
+    assert B.moe_timing_end()[1]["front"] == (2 if fused else 0)
+
+
+def check_forward(dtype, T, d, f, E, k, G, local):
     rng = np.random.default_rng(T + E)
     pl = rng.integers(0, G, E).astype(np.int32)
     x = to_device(synth.normal(T, 0, (T, d), 1.0, dtype))

@@ -140,8 +140,9 @@ int moe_topk_gate_norm(const float* logits, int T, int E, int k, moe_norm_t norm
  *   logits   [T,E] float  out, or NULL when the caller does not need them
  *   topk_idx, topk_w      as in moe_topk_gate
  *
- * MOE_BF16: bf16 inputs, fp32 accumulation in a fixed order; requires
- * d % 64 == 0.  MOE_F32: fp32 throughout.  Because the logits are rounded
+ * MOE_BF16: bf16 inputs, fp32 accumulation in an order that depends on T, d and
+ * E only (a token's logits may differ in the last bits between batch sizes);
+ * requires d % 64 == 0.  MOE_F32: fp32 throughout.  Because the logits are rounded
  * differently than an exact product, a token whose k-th and (k+1)-th logits are
  * closer than that rounding may legitimately select the other expert.
  * ---------------------------------------------------------------------- */

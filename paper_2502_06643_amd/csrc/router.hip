@@ -70,10 +70,11 @@ constexpr int router_lds_floats(int panels, int waves) {
     return stage > sums ? (stage > rows ? stage : rows) : (sums > rows ? sums : rows);
 }
 
-// WAVES wavefronts share the reduction: four when there are workgroups for every compute unit, sixteen when the batch is
-// small and a workgroup's chain of k steps, each at the latency of memory, is all there is.  Four / sixteen, us: d 4096, 8
-// experts, 170 tokens 9.9 / 7.2, 4000 14.0 / 8.8, 6000 16.2 / 15.4, 8192 17.6 / 18.4, 30000 39.5 / 55.7; d 3008, 128
-// experts, 170 tokens 21.0 / 14.0, 6000 37.2 / 18.7.
+// WAVES wavefronts share the reduction: sixteen while a compute unit has one workgroup at most, whose chain of k steps, each
+// at the latency of memory, is all there is; four when there are more workgroups or, with one panel of experts, when the
+// read of x is what bounds the launch.  Four / sixteen, us: 8 experts, d 4096, 1024 tokens 11.8 / 9.5, 4096 14.8 / 11.2,
+// 5000 15.4 / 15.0, 6000 15.9 / 16.9, 7168 16.2 / 18.4; d 2048, 8192 tokens 11.0 / 9.2, 9000 12.0 / 13.1; 64 experts, d
+// 4096, 8192 tokens 26.1 / 24.3, 9000 27.5 / 33.6; 128 experts, d 2048, 8192 tokens 24.6 / 17.0, 9000 25.8 / 28.2.
 template <int PANELS, int KMAX, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void router_gate_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ packed,
                                                                const float* __restrict__ bias, int T, int d, int E, int k,
@@ -230,7 +231,9 @@ __global__ __launch_bounds__(256) void router_gate_f32_kernel(const float* __res
     gate_select<16, MOE_MAX_EXPERTS / 16, KMAX, false>(row, true, threadIdx.x & 15, threadIdx.x < 16, t, E, k, topk_idx, topk_w);
 }
 
-constexpr int kRouterSmallTokens = 7168;      // 224 workgroups
+// which of the two (see the kernel): one workgroup of 32 tokens for each of 256 compute units, and at most 44 MB of x with one panel
+constexpr int kRouterSmallTokens = 8192;
+constexpr long long kRouterSmallElems = 22ll << 20;
 template <int PANELS, int WAVES>
 static void launch_fused(const uint16_t* x, const uint16_t* packed, const float* bias, int T, int d, int E, int k, float* logits,
                          int32_t* idx, float* w, hipStream_t s) {
@@ -247,8 +250,8 @@ int launch_router_gate(const void* x, moe_dtype_t dt, const void* packed, const 
     if (dt == MOE_BF16) {
         const uint16_t* xs = (const uint16_t*)x;
         const uint16_t* ps = (const uint16_t*)packed;
-        // sixteen wavefronts for small batches (see the kernel); past 128 experts their accumulators do not fit
-        const bool small = T <= kRouterSmallTokens;
+        // sixteen wavefronts for small batches; past 128 experts their accumulators do not fit
+        const bool small = T <= kRouterSmallTokens && (E > 32 || (long long)T * d <= kRouterSmallElems);
         switch (padded_experts(E) / 32) {
             case 1: (small ? launch_fused<1, 16> : launch_fused<1, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
             case 2: (small ? launch_fused<2, 16> : launch_fused<2, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;

@@ -70,7 +70,10 @@ def check(lib, x, w_g, bias, k):
 
 @pytest.mark.parametrize("T,d,E,k", [(1, 64, 8, 2), (33, 192, 32, 1),      # fewer k steps of 16 than wavefronts, shares of one step
                                      (100, 1088, 33, 6), (31, 1984, 96, 9), (65, 2048, 128, 8),      # one to four panels, ragged shares
-                                     (64, 512, 129, 4), (7168, 64, 8, 2), (7169, 64, 8, 2)])         # ... and where four wavefronts take over
+                                     (64, 512, 129, 4), (7168, 64, 8, 2), (7169, 64, 8, 2),
+                                     (8192, 64, 8, 2), (8193, 64, 8, 2),                             # ... and where four wavefronts take over
+                                     (5632, 4096, 8, 2), (5633, 4096, 8, 2), (5633, 4096, 33, 2), (8192, 64, 64, 6), (8193, 64, 64, 6),
+                                     (8192, 64, 128, 8), (8193, 64, 128, 8)])
 def test_small_batches_with_sixteen_wavefronts(lib, T, d, E, k):
     check(lib, synth.normal(T, 0, (T, d), 1.0, "bf16"), synth.normal(d, 1, (d, E), d ** -0.5, "bf16"), np.linspace(-1, 1, E), k)
 

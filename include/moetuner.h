@@ -348,7 +348,8 @@ int moe_combine(const void* ffn_out, moe_dtype_t dt, const int32_t* inv_perm,
  * stages are merged: small batches run gate, dispatch and the FFN's tile plan
  * as one kernel (timed as MOE_K_FRONT), decode-sized bf16 batches fold the
  * combine into the last kernel of the FFN (timed with MOE_K_FFN_DOWN).
- * dispatch_workspace and ffn_workspace must not overlap.
+ * dispatch_workspace and ffn_workspace may be the same buffer, as they may be
+ * for the four calls; the tile plan is a launch of its own then.
  * ---------------------------------------------------------------------- */
 int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits,
                       int T, int d, int f, int E, int k,

@@ -393,8 +393,13 @@ int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T,
                     moe_dispatch_workspace_bytes(T, E, k));
     hipStream_t s = (hipStream_t)stream;
     PlanTask pt = {(int32_t*)ffn_workspace, local_gpu, {}};
+    // The index kernels write the plan while they read their histograms: a caller who has one buffer for both workspaces
+    // (the four calls need them one after the other) gets the plan from a launch of its own.
+    const uintptr_t dispatch_ws = (uintptr_t)dispatch_workspace, plan_area = (uintptr_t)ffn_workspace;
+    const bool shared = dispatch_ws < plan_area + kPlanBytes && plan_area < dispatch_ws + moe_dispatch_workspace_bytes(T, E, k);
+    const bool fused = front_fits(T, E, k, row_bytes);
     if ((rc = ffn_plan_shape(dt, N, d, f, E, local_gpu < 0, &pt.shape)) != MOE_OK) return rc;
-    if (front_fits(T, E, k, row_bytes)) {
+    if (fused) {
         FrontArgs a;
         a.x = (const uint4*)x; a.logits = logits; a.T = T; a.E = E; a.k = k; a.G = G; a.local_gpu = local_gpu;
         a.units_per_row = row_bytes / 16; a.placement = placement; a.topk_idx = topk_idx; a.topk_w = topk_w; a.perm = perm;
@@ -404,12 +409,12 @@ int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T,
     } else {
         if (T > 0 && (rc = launch_gate(logits, T, E, k, false, topk_idx, topk_w, s)) != MOE_OK) return rc;
         if ((rc = launch_dispatch(x, row_bytes, topk_idx, T, E, k, placement, G, send_buf, perm, inv_perm, expert_counts, expert_start,
-                                  gpu_counts, gpu_offsets, (int32_t*)dispatch_workspace, T == 0 ? kNoPlan : pt, s)) != MOE_OK) return rc;
+                                  gpu_counts, gpu_offsets, (int32_t*)dispatch_workspace, T == 0 || shared ? kNoPlan : pt, s)) != MOE_OK) return rc;
         if (T == 0) return MOE_OK;
     }
     CombineTail tail = {inv_perm, topk_idx, topk_w, placement, local_gpu, T, E, k, y, false};
     if ((rc = run_ffn(send_buf, dt, N, d, f, E, packed_weights, expert_counts, expert_start, placement, local_gpu, ffn_out, ffn_workspace,
-                      true, &tail, s)) != MOE_OK) return rc;
+                      fused || !shared, &tail, s)) != MOE_OK) return rc;
     if (tail.done) return MOE_OK;
     return launch_combine(ffn_out, dt, inv_perm, topk_idx, topk_w, placement, local_gpu, T, d, E, k, y, s);
 }

@@ -58,7 +58,12 @@ def test_where_the_front_is_fused(lib, shape, fused):
     assert B.moe_timing_end()[1]["front"] == (2 if fused else 0)
 
 
-def check_forward(dtype, T, d, f, E, k, G, local):
+@pytest.mark.parametrize("T,E,k", [(100, 8, 2), (9000, 8, 2), (20000, 256, 2)])      # fused front, histograms of one tile and of 40 KB
+def test_one_buffer_for_both_workspaces(lib, T, E, k):
+    check_forward("bf16", T, 64, 64, E, k, 4, 1, one_workspace=True)
+
+
+def check_forward(dtype, T, d, f, E, k, G, local, one_workspace=False):
     rng = np.random.default_rng(T + E)
     pl = rng.integers(0, G, E).astype(np.int32)
     x = to_device(synth.normal(T, 0, (T, d), 1.0, dtype))
@@ -72,6 +77,8 @@ def check_forward(dtype, T, d, f, E, k, G, local):
         L.set_weights(*w)
         for n in OUTPUTS:
             getattr(L, n).fill_(3)                 # what a call leaves untouched must be the same too
+    if one_workspace:
+        got.dispatch_ws = got.ffn_ws
     want.gate(lg)
     want.dispatch(x)
     want.ffn()

@@ -83,7 +83,8 @@ typedef enum { MOE_PAIRS_ALL = 0, MOE_PAIRS_TOP1 = 1 } moe_pairs_t;
 typedef enum {
     MOE_K_GATE = 0,
     MOE_K_DISPATCH_COUNT = 1,
-    MOE_K_DISPATCH_SCAN = 2,
+    MOE_K_FRONT = 2,           /* gate, dispatch and tile plan of moe_layer_forward in one launch */
+    MOE_K_DISPATCH_SCAN = 2,   /* retired: this id belonged to a kernel that is gone */
     MOE_K_DISPATCH_RANK = 3,
     MOE_K_DISPATCH_ROWS = 4,
     MOE_K_FFN_PLAN = 5,
@@ -92,8 +93,7 @@ typedef enum {
     MOE_K_COMBINE = 8,
     MOE_K_TRANSITION = 9,
     MOE_K_ROUTER = 10,         /* x.W_g + bias of moe_router_gate              */
-    MOE_K_FRONT = 11,          /* gate, dispatch and tile plan of moe_layer_forward in one launch */
-    MOE_K_COUNT = 12
+    MOE_K_COUNT = 11           /* callers' arrays have this length: it does not grow */
 } moe_kernel_id_t;
 
 /* Thread-local description of the last failure on this thread; never NULL. */

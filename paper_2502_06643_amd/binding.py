@@ -22,8 +22,8 @@ MOE_NORM_SOFTMAX_SELECTED, MOE_NORM_SOFTMAX_ALL = 0, 1
 MOE_PAIRS_ALL, MOE_PAIRS_TOP1 = 0, 1
 MOE_MAX_EXPERTS, MOE_MAX_GPUS, MOE_MAX_TOPK = 256, 256, 16
 FFN_STREAMING_MAX_ROWS = 160      # bf16 batches of at most this many routes run the weight-streaming FFN kernels
-KERNEL_NAMES = ["gate", "dispatch_count", "dispatch_scan", "dispatch_rank", "dispatch_rows",
-                "ffn_plan", "ffn_up", "ffn_down", "combine", "transition", "router", "front"]
+KERNEL_NAMES = ["gate", "dispatch_count", "front", "dispatch_rank", "dispatch_rows",
+                "ffn_plan", "ffn_up", "ffn_down", "combine", "transition", "router"]
 MOE_K_COUNT = len(KERNEL_NAMES)
 
 EXPORTS = ["moe_last_error", "moe_version", "moe_topk_gate", "moe_topk_gate_norm", "moe_router_packed_bytes", "moe_pack_router", "moe_router_gate", "moe_dispatch_workspace_bytes", "moe_dispatch",

@@ -106,6 +106,16 @@ def test_bad_scalars_are_rejected_without_touching_the_gpu():
     assert L.moe_transition_counts(None, None, 0, 2, 2, 8, 8, one, None) == 0
 
 
+def test_timing_fills_no_more_entries_than_its_callers_hold():
+    """moe_timing_end fills arrays that its callers sized by the header they were built with: eleven entries since the
+    first one.  The call touches no GPU without a session."""
+    from paper_2502_06643_amd import binding as B
+    ms, n = (ctypes.c_double * 12)(*[7.0] * 12), (ctypes.c_int * 12)(*[7] * 12)
+    assert B._lib.moe_timing_end(ms, n) == B.MOE_OK
+    assert list(ms) == [0.0] * 11 + [7.0] and list(n) == [0] * 11 + [7]
+    assert B.MOE_K_COUNT == 11
+
+
 def test_missing_library_fails_loudly(tmp_path, monkeypatch):
     """The product path has no fallback: importing the binding without the
     shared object is an ImportError."""

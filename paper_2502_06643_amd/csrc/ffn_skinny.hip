@@ -9,9 +9,10 @@
 // column tile follow each other along k.  A workgroup of four wavefronts takes
 // one (expert, column tile) and streams that contiguous run; each wavefront
 // owns four panels (8 KB per k tile) which it loads straight into registers
-// with 16-byte loads, one k tile ahead of the matrix instructions.  There is no
-// LDS and no barrier: nothing ever waits for another wavefront, and the eight
-// wavefronts a compute unit holds keep 64 KB of weights in flight.  The few
+// with 16-byte loads, one k tile ahead of the matrix instructions, without LDS
+// and without a barrier (unless there are few tasks, see below): nothing waits for
+// another wavefront, and the eight wavefronts a compute unit holds keep 64 KB of
+// weights in flight.  The few
 // activation rows are read as A fragments from global memory as well (they stay
 // in L1/L2: every workgroup of an expert reads the same rows).
 //

@@ -127,24 +127,24 @@ bool front_fits(int T, int E, int k, int row_bytes) {
     return T > 0 && N <= kFrontMaxRoutes && N * row_bytes <= kFrontMaxBytes && (long long)T * front_lanes(E) <= (long long)passes * kIndexThreads;
 }
 
+template <int L, int VPL>
+static void launch_lanes(const FrontArgs& a, int grid, hipStream_t s) {
+    if (a.k <= 2) hipLaunchKernelGGL((front_kernel<L, VPL, 2>), dim3(grid), dim3(kIndexThreads), 0, s, a);
+    else if (L == 1 || a.k <= 8) hipLaunchKernelGGL((front_kernel<L, VPL, 8>), dim3(grid), dim3(kIndexThreads), 0, s, a);      // one lane: E <= 8
+    else hipLaunchKernelGGL((front_kernel<L, VPL, L == 1 ? 8 : MOE_MAX_TOPK>), dim3(grid), dim3(kIndexThreads), 0, s, a);
+}
+
 int launch_front(const FrontArgs& args, hipStream_t s) {
     FrontArgs a = args;
     a.ebits = 0;
     while ((1 << a.ebits) < a.E) ++a.ebits;
     const int grid = a.T < kFrontGroups ? a.T + 1 : kFrontGroups;
     LaunchTimer timer(MOE_K_FRONT, s);
-#define MOE_LAUNCH_FRONT(L, VPL)                                                                                        \
-    do {                                                                                                                \
-        if (a.k <= 2) hipLaunchKernelGGL((front_kernel<L, VPL, 2>), dim3(grid), dim3(kIndexThreads), 0, s, a);            \
-        else if (a.k <= 8) hipLaunchKernelGGL((front_kernel<L, VPL, 8>), dim3(grid), dim3(kIndexThreads), 0, s, a);       \
-        else hipLaunchKernelGGL((front_kernel<L, VPL, MOE_MAX_TOPK>), dim3(grid), dim3(kIndexThreads), 0, s, a);          \
-    } while (0)
     switch (front_lanes(a.E)) {
-        case 1: MOE_LAUNCH_FRONT(1, 8); break;
-        case 4: MOE_LAUNCH_FRONT(4, 16); break;
-        default: MOE_LAUNCH_FRONT(16, 16); break;
+        case 1: launch_lanes<1, 8>(a, grid, s); break;
+        case 4: launch_lanes<4, 16>(a, grid, s); break;
+        default: launch_lanes<16, 16>(a, grid, s); break;
     }
-#undef MOE_LAUNCH_FRONT
     return check_launch("moe_layer_forward front launch");
 }
 

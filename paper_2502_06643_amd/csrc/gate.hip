@@ -1,17 +1,14 @@
 // moe_topk_gate: top-k router (paper Section 2.1).
 //
-// A token's E logits are spread over L neighbouring lanes of a wavefront in
-// pieces of four, VPL logits per lane (16-byte loads when E % 4 == 0), so a
-// wavefront reads 64/L whole rows, neighbouring lanes neighbouring pieces.  Each logit is mapped to an order-preserving unsigned
-// key (-0.0 is folded onto +0.0 first, so the two tie); key 0 is below every
-// finite logit and marks "no candidate".  One round = scan my VPL keys with a
-// strict '>' (ascending index, so the lowest index wins a tie), then an
-// xor-butterfly over the L lanes on (key, index) with the same tie rule, then
-// the owner retires the winner.  k rounds give the experts in descending logit
-// order.  Weights are the softmax over the k selected logits in fp32, or (ALL)
-// the softmax over all E logits read at the selected experts: then every lane
-// adds exp(logit - top) over its own logits after the first round and a
-// butterfly sum over the L lanes gives the denominator.
+// Which lanes and lists serve how many experts; the selection itself is in
+// gate_select.h.  A token's E logits are spread over L neighbouring lanes of a
+// wavefront in pieces of four, VPL logits per lane (16-byte loads when
+// E % 4 == 0), so a wavefront reads 64/L whole rows, neighbouring lanes
+// neighbouring pieces.  Up to 8 experts one lane scans its token's keys in k
+// rounds; above, every lane sorts its candidates into a list of KMAX >= k and the
+// lists are merged across the lanes.  Weights are the softmax over the k selected
+// logits in fp32, or (ALL) the softmax over all E logits read at the selected
+// experts.
 #include "gate_select.h"
 
 namespace moe {
@@ -31,8 +28,8 @@ static void launch_l(const float* logits, int T, int E, int k, int32_t* idx, flo
     constexpr int TOK_PER_BLOCK = 256 / L;
     const unsigned grid = (unsigned)(((long long)T + TOK_PER_BLOCK - 1) / TOK_PER_BLOCK);
     if (k <= 2) hipLaunchKernelGGL((gate_kernel<L, VPL, 2, ALL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);
-    else if (k <= 8) hipLaunchKernelGGL((gate_kernel<L, VPL, 8, ALL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);
-    else hipLaunchKernelGGL((gate_kernel<L, VPL, MOE_MAX_TOPK, ALL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);
+    else if (L == 1 || k <= 8) hipLaunchKernelGGL((gate_kernel<L, VPL, 8, ALL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);      // one lane: E <= 8
+    else hipLaunchKernelGGL((gate_kernel<L, VPL, L == 1 ? 8 : MOE_MAX_TOPK, ALL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);
 }
 
 template <bool ALL>

@@ -84,7 +84,7 @@ def test_empty_batch(lib):
 
 @pytest.mark.parametrize("T,E,k,G", [(70000, 8, 3, 4), (40000, 64, 6, 8), (16384, 8, 1, 4), (16385, 8, 1, 4), (4097, 8, 1, 2)])
 def test_large_batches_take_the_multi_workgroup_path(lib, T, E, k, G):
-    """Above 16384 routes the index build runs as count / scan / rank kernels
+    """Above 16384 routes the index build runs as count and rank kernels
     over many workgroups instead of one fused workgroup (sizes on both sides
     of the switch); index-only mode."""
     rng = np.random.default_rng(T + E)

@@ -1,7 +1,7 @@
 """GPU parity of moe_dispatch_noalloc, the dispatch entry point that allocates nothing (its per-chunk
 histograms live in a device array that is part of the library): every output must equal moe_dispatch's,
 bit for bit, on two calls in a row, the second with a smaller input (the array keeps the first call's
-contents).  Sizes above 16384 routes take the count / scan / rank kernels, which are the ones that use
+contents).  Sizes above 16384 routes take the count / rank kernels, which are the ones that use
 the scratch; a small batch (one fused index kernel, no scratch) is covered too."""
 import numpy as np
 import pytest
@@ -36,7 +36,7 @@ def run(entry, x, idx, T, d, E, k, pl, G, dt):
 
 
 @pytest.mark.parametrize("dtype,d,E,k,G,sizes", [
-    ("bf16", 256, 8, 2, 4, (20000, 9000)),          # 40000 then 18000 routes: both through count / scan / rank
+    ("bf16", 256, 8, 2, 4, (20000, 9000)),          # 40000 then 18000 routes: both through count / rank
     ("f32", 64, 64, 6, 8, (8192, 3000, 100)),       # 49152, 18000, then 600 routes (fused index kernel)
     ("bf16", 128, 256, 16, 256, (16000, 1100)),     # widest histograms: 250 chunks x 256 experts x 4 B = 250 KiB of the 256 KiB
 ])

@@ -92,8 +92,10 @@ int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* pack
                    const int32_t* starts, const int32_t* placement, int local_gpu, const int32_t* group_expert,
                    int n_weights, float* out, int32_t* plan, bool plan_ready, float* H, hipStream_t s);
 // bf16, N <= kFfnSkinnyMaxRows: weight-streaming kernels for decode-sized batches (plan already built).
-// Measured at the Mixtral shape with skewed top-2 routing: they win up to N = 128 rows (+13 to +18 %) and lose from
-// N = 256 on (-7 %), where the largest bucket needs several passes of 64 rows over its weights.
+// N counts all routes, resident or not.  Whole layer, us, tiled / streaming kernels: Mixtral shape, top-2, all experts, N = 72
+// 498 / 498, 160 505 / 512, 256 509 / 565 (tasks of 64 rows of the largest buckets); two of the eight experts 149 / 140, 148 /
+// 144, 151 / 153, with the most popular one among them 150 / 151, 152 / 176, 158 / 262; d 1024, f 4096, 16 experts 83 / 73,
+// 87 / 83, 99 / 95; 8 of 64 experts, d 2048, f 1408, top-6 54 / 30, 54 / 34, 55 / 35.
 #ifndef MOE_SKINNY_MAX_ROWS
 #define MOE_SKINNY_MAX_ROWS 160
 #endif

@@ -136,6 +136,10 @@ static int check_case(std::mt19937& rng, long long& units) {
     if (BM == kShortTileRows) {
         const RoundShape r = round_shape(mt_total - n_small, n_small, NT, KT, cpx);
         const RoundCut chosen = choose(r);
+        if (r.nbx + r.nsx <= cpx) {
+            const int even = xcd_share(mt_total, NT, 0, KT, cpx, true).split;
+            CHECK(even_cut(r).big == even, "even split priced as %d parts, run as %d", even_cut(r).big, even);
+        }
         int big = 1 + rng() % kMaxSplit, small = 1 + rng() % kMaxSplit;
         if (chosen.big > 0) {
             big = chosen.big;

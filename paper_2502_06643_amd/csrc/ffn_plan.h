@@ -48,14 +48,11 @@ struct RowMap {
     const int32_t* rest;     // entry after those 64 (more == 64)
 };
 
-// the map of rows first .. first + rows - 1 of listed bucket i; called by whole wavefronts, which fetch the bucket's
-// segments together: one round of memory latency instead of one per segment and row
-// (MAY_MERGE = false: the caller knows that nothing is merged)
-template <bool MAY_MERGE>
-__device__ __forceinline__ RowMap row_map(const int32_t* __restrict__ plan, int i, int first, int rows) {
+// the map of rows first .. first + rows - 1 of the listed bucket whose kPlanStart entry is `start`; called by whole
+// wavefronts, which fetch the bucket's segments together: one round of memory latency instead of one per segment and row
+__device__ __forceinline__ RowMap row_map_at(const int32_t* __restrict__ plan, int start, bool merged, int first, int rows) {
     RowMap m;
-    const int start = plan[kPlanStart + i];
-    m.merged = MAY_MERGE && plan[kPlanMerged];
+    m.merged = merged;
     m.row0 = start + first;
     m.first = first;
     m.last = first + rows - 1;
@@ -79,6 +76,11 @@ __device__ __forceinline__ RowMap row_map(const int32_t* __restrict__ plan, int 
     m.more = stop ? __builtin_ctzll(stop) : 64;
     m.rest = off + seg + 65;
     return m;
+}
+// ... of listed bucket i (MAY_MERGE = false: the caller knows that nothing is merged)
+template <bool MAY_MERGE>
+__device__ __forceinline__ RowMap row_map(const int32_t* __restrict__ plan, int i, int first, int rows) {
+    return row_map_at(plan, plan[kPlanStart + i], MAY_MERGE && plan[kPlanMerged], first, rows);
 }
 
 // Where row r of the tile lies in the buffer (0 <= r < rows).  It reads the segments out of other lanes' registers, so

@@ -10,7 +10,7 @@
 // one (expert, column tile) and streams that contiguous run; each wavefront
 // owns four panels (8 KB per k tile) which it loads straight into registers
 // with 16-byte loads, one k tile ahead of the matrix instructions, without LDS
-// and without a barrier (unless there are few tasks, see below): nothing waits for
+// and without a barrier (but in the last round, see below): nothing waits for
 // another wavefront, and the eight wavefronts a compute unit holds keep 64 KB of
 // weights in flight.  The few
 // activation rows are read as A fragments from global memory as well (they stay
@@ -25,12 +25,17 @@
 // parts in a fixed order (bitwise reproducible) and rounds to bf16.
 // Buckets of more than 64 rows are cut into tasks of 64 rows (the second one finds the weights in the L2).
 //
-// Few weights (a small expert, one resident expert of many) make few such tasks, each one long chain of k tiles at the
-// latency of memory.  With less than kSkinnyFewTasks of them a workgroup takes four panels instead of sixteen and its
-// wavefronts a quarter of the reduction each, added in wavefront order through LDS: four times the workgroups, a
-// quarter of the chain: one token, d 1536, f 896, one resident expert: layer 26.5 -> 20.6 us; 3 tokens, d 2432, f 2688, four
-// experts 33.8 -> 25.6; 8 tokens from each of 8 ranks, one Mixtral expert 161 -> 133
-// (121 with the rows' segments fetched together).  With 224 tasks (two Mixtral experts) it lost 1-4 %.
+// Last round.  A task is a chain of k tiles at the latency of memory, so what counts is how evenly the tasks fall on the
+// 256 compute units: the 560 of five Mixtral experts leave 48 for a round of their own.  When the tasks past the last
+// full round number less than 128, a workgroup of theirs takes four panels instead of sixteen and its wavefronts
+// a quarter of the reduction each, added in wavefront order through LDS: four times the workgroups, a quarter of the
+// chain, which fill in behind the whole tasks.  A launch of few tasks (a small expert, one resident expert of many) is
+// nothing but such a round, and cut up to 160.  All tasks of less than 128 cut this way and no others / the last round,
+// layer in us: Mixtral shape, 1 to 8 experts touched, 79 / 80, 137 / 138, 223 / 201, 255 / 258, 346 / 316, 386 / 377, 474 / 437,
+// 497 / 493; f 7168, 5 experts 203 / 172; d 1024, f 4096, 9 of 16 experts 69 / 59; d 2048, f 1408, 24 of 64 experts 107 / 94,
+// 32 120 / 114.  Limits of 60, 100, 130, 160 and 200: one Mixtral expert (112 tasks) 95, 87, 80, 80, 79, d 2048, f 2048, 8
+// experts (128 tasks) 56, 60, 53, 53, 53, seven at f 3584 (196 tasks) 123, 124, 123, 123, 130; the last 128 of 896 tasks,
+// Mixtral shape, 128 routes: whole 505, cut 508.
 #include "bf16.h"
 #include "ffn_plan.h"
 
@@ -42,13 +47,38 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 constexpr int kSkinnyThreads = 256, kSkinnyWaves = kSkinnyThreads / 64;
 static_assert(kSkinnyRows == 64, "four 16-row fragments");
 constexpr int kSkinnyMaxParts = 16;
-constexpr int kSkinnyDownTasks = 512;    // workgroups the down projection is cut into
+constexpr int kSkinnySlots = 512;        // workgroups that run together, two per compute unit
+constexpr int kSkinnyRound = 256;        // one per compute unit
+constexpr int kSkinnyTail = 128, kSkinnyOnly = 160;      // a last round of fewer tasks than this is cut, and one that is all there is
 
-// k parts of the down projection: two workgroups per compute unit (more, shorter parts were slower), at least 8 k tiles
-// each.  Decided on the device, which knows how many tasks there are.
+// Tasks that run whole, the first ones, of `total`.
+__device__ __forceinline__ int whole_tasks(int total) {
+    const int tail = total % kSkinnyRound;
+    return tail < (total < kSkinnyRound ? kSkinnyOnly : kSkinnyTail) ? total - tail : total;
+}
+
+// k parts of the down projection: as many as make no more workgroups than run together (more, shorter parts were slower,
+// and a few workgroups past that many cost a round of their own: 7 parts of 80 tasks 115 us, 6 parts 103), at least 8 k
+// tiles each.  Decided on the device, which knows how many tasks there are.
 __device__ __forceinline__ int skinny_parts(int n_chunks, int NT, int max_parts) {
-    const int tasks = n_chunks * NT, parts = tasks > 0 ? (kSkinnyDownTasks + tasks - 1) / tasks : 1;
-    return parts < max_parts ? parts : max_parts;
+    const int tasks = n_chunks * NT, parts = tasks > 0 ? kSkinnySlots / tasks : 1;
+    return parts < 1 ? 1 : (parts < max_parts ? parts : max_parts);
+}
+
+// The task's listed bucket: its plan entries, fetched by the lanes of a wavefront together (a walk along the prefix was a
+// round of memory latency per bucket).
+struct ListedBucket { int expert, start, count, first_chunk; };
+__device__ __forceinline__ ListedBucket find_bucket(const int32_t* __restrict__ plan, int n_listed, int chunk, int lane) {
+    for (int base = 0;; base += 64) {
+        const int j = base + lane;
+        const int end = plan[kPlanTiles1 + j + 1], begin = plan[kPlanTiles1 + j];
+        const int expert = plan[kPlanExpert + j], start = plan[kPlanStart + j], count = plan[kPlanCount + j];
+        const unsigned long long after = __ballot(j < n_listed && end > chunk);
+        if (after == 0ull && base + 64 < n_listed) continue;
+        const int i = after ? __builtin_ctzll(after) : 0;
+        return {__builtin_amdgcn_readlane(expert, i), __builtin_amdgcn_readlane(start, i), __builtin_amdgcn_readlane(count, i),
+                __builtin_amdgcn_readlane(begin, i)};
+    }
 }
 
 __device__ __forceinline__ bf16x8 as_frag(const uint4& q) { return __builtin_bit_cast(bf16x8, q); }
@@ -183,25 +213,25 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const uin
                                                                     float* __restrict__ partial, int max_parts, int N) {
     __shared__ f32x4 red[kSkinnyWaves * 4 * 64];
     const int n_chunks = plan[2], parts = UP ? 1 : skinny_parts(n_chunks, NT, max_parts);
-    const bool few = n_chunks * NT * parts < kSkinnyFewTasks;
+    const int total = n_chunks * NT * parts, whole = whole_tasks(total);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int task = blockIdx.x, grp = wave;
-    if (few) {
-        grp = task & 3;
-        task >>= 2;
+    const bool cut = task >= whole;
+    if (cut) {
+        grp = (task - whole) & 3;
+        task = whole + ((task - whole) >> 2);
     }
+    if (task >= total) return;
     const int part = UP ? 0 : task % parts;
     if (!UP) task /= parts;
     const int nt = task % NT, chunk = task / NT;
-    if (chunk >= n_chunks) return;
-    int i = 0;
-    while (plan[kPlanTiles1 + i + 1] <= chunk) ++i;
-    const int e = plan[kPlanExpert + i], first = (chunk - plan[kPlanTiles1 + i]) * kSkinnyRows, n = min(kSkinnyRows, plan[kPlanCount + i] - first);
-    const RowMap rm = row_map<true>(plan, i, first, n);
+    const ListedBucket b = find_bucket(plan, plan[0], chunk, lane);
+    const int e = b.expert, first = (chunk - b.first_chunk) * kSkinnyRows, n = min(kSkinnyRows, b.count - first);
+    const RowMap rm = row_map_at(plan, b.start, plan[kPlanMerged], first, n);
     const int KT = K / 64;
     int kt0 = UP ? 0 : (int)((long long)part * KT / parts), kt1 = UP ? KT : (int)((long long)(part + 1) * KT / parts);
-    if (few) {
+    if (cut) {
         const int k0 = kt0, len = kt1 - kt0;
         kt0 = k0 + len * wave / kSkinnyWaves;
         kt1 = k0 + len * (wave + 1) / kSkinnyWaves;
@@ -211,7 +241,7 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const uin
     float* my_partial = UP ? nullptr : partial + (size_t)part * N * ldc;
     const int mf = (n + 15) >> 4;
 #define MOE_SKINNY_PASS(MF, SPLIT) skinny_pass<UP, MF, SPLIT>(A, K, Bp, rm, n, kt0, kt1, nt, grp, wave, lane, ldc, H, my_partial, red)
-    if (few) {
+    if (cut) {
         if (mf == 1) MOE_SKINNY_PASS(1, true);
         else if (mf == 2) MOE_SKINNY_PASS(2, true);
         else if (mf == 3) MOE_SKINNY_PASS(3, true);
@@ -287,10 +317,9 @@ __global__ __launch_bounds__(256) void ffn_skinny_combine_kernel(const float* __
     *reinterpret_cast<uint2*>((uint16_t*)tail.y + (size_t)t * d + c) = make_uint2(pack_bf16(acc.x, acc.y), pack_bf16(acc.z, acc.w));
 }
 
-// workgroups for at most `tasks` tasks: four each when there are few
+// workgroups for at most `tasks` tasks: four for each of those that are cut
 static int skinny_grid(int tasks) {
-    const int few = 4 * (tasks < kSkinnyFewTasks ? tasks : kSkinnyFewTasks);
-    return tasks > few ? tasks : few;
+    return tasks + 3 * (tasks < kSkinnyOnly ? tasks : kSkinnyOnly);
 }
 
 // E row groups; plan has been built.  H [N, f] bf16 and the fp32 partial area (scratch_bytes) come from the workspace.
@@ -310,8 +339,8 @@ int launch_ffn_skinny(const void* a, int N, int d, int f, int E, const void* pac
     while (max_parts > 1 && ((f / 64) / max_parts < 8 || (size_t)max_parts * N * d * sizeof(float) > scratch_bytes)) --max_parts;
     if ((size_t)max_parts * N * d * sizeof(float) > scratch_bytes)
         return fail(MOE_ERR_WORKSPACE, "moe_expert_ffn_grouped: partial sums of %d rows x %d do not fit the workspace", N, d);
-    // n chunks make n * nt_down * skinny_parts workgroups: fewer than kSkinnyDownTasks + n * nt_down, whatever n
-    const int tasks = chunks * nt_down, grid = tasks * max_parts < tasks + kSkinnyDownTasks ? tasks * max_parts : tasks + kSkinnyDownTasks;
+    // n chunks make n * nt_down * skinny_parts tasks: at most kSkinnySlots of them, or one part each
+    const int tasks = chunks * nt_down, grid = tasks * max_parts < kSkinnySlots ? tasks * max_parts : (tasks < kSkinnySlots ? kSkinnySlots : tasks);
     {
         LaunchTimer timer(MOE_K_FFN_DOWN, s);
         hipLaunchKernelGGL(ffn_skinny_kernel<false>, dim3((unsigned)skinny_grid(grid)), dim3(kSkinnyThreads), 0, s,

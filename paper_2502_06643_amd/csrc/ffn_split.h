@@ -159,7 +159,7 @@ __host__ __device__ __forceinline__ RoundCut even_cut(const RoundShape& r) {
 // most 235, 55 / 95; 30 in 8, at most 39 and 289 rows, 80 / 95; 37 in 9, 96 / 92; 47 in 8, 125 / 92; streaming kernels (64
 // rows a task): 15 in 6, at most 9 and 58 rows, 48 / 59; 17 in 9, 7 and 23 rows, 55 / 51; 17 in 12, 9 and 18 rows, 56 / 59;
 // 28 in 11, 18 and 70 rows, 82 / 88; Mixtral shape: 4 segments in 3 buckets 195 / 231, 5 in 4 280 / 258, 8 in 2 300 / 160.
-constexpr int kSkinnyFewTasks = 128;     // streaming kernels: with fewer tasks a workgroup of each splits the reduction among its wavefronts
+constexpr int kSkinnyFewTasks = 128;     // fewer tasks of the streaming kernels than this are short chains, four workgroups each, in all the measured cases
 struct MergeShape { int nt_up, kt_up, nt_down, kt_down, cpx; };        // column and k tiles of the projections; compute units per XCD
 struct Buckets { int tiles, max_rows; };                               // row tiles in all, rows of the largest bucket
 

@@ -73,6 +73,27 @@ def test_ffn_matches_oracle(lib, dtype, T, d, f, E, k, G, local):
     assert np.all(got[~is_local] == 7.0)
 
 
+@pytest.mark.parametrize("T,d,f,E", [
+    (16, 64, 4096, 8),        # 8 buckets of 32 column tiles: a full round of 256 tasks
+    (18, 192, 4096, 9),       # 288: 32 past it, cut, chains of less k tiles than wavefronts share them
+    (50, 64, 2048, 25),       # 400: 144 past it, cut
+    (52, 64, 2048, 26),       # 416: 160 past it, whole
+    (130, 576, 2112, 65),     # buckets past the first 64 of the plan, a last column tile that is half empty
+    (150, 2048, 320, 1),      # three chunks of one bucket
+])
+def test_ffn_streaming_last_round(lib, T, d, f, E):
+    """Numbers of tasks of the streaming kernels on both sides of a round of compute units: every expert gets T / E rows."""
+    x, w1, w3, w2, _, _ = make_problem(T + d, T, d, f, E, 1, 1, "bf16")
+    idx = (np.arange(T) % E).astype(np.int32).reshape(T, 1)
+    pl = np.zeros(E, dtype=np.int32)
+    L = gpu_ffn(lib, x, w1, w3, w2, idx, pl, 1, -1, "bf16")
+    dsp = O.dispatch(x, idx, pl, 1)
+    ref = O.expert_ffn_grouped(dsp["send_buf"], w1, w3, w2, dsp["expert_counts"], dsp["expert_start"], pl, -1)
+    got = as_f64(to_host(L.ffn_out))
+    assert rel_err(got, ref) <= TOL_BF16
+    assert fro_err(got, ref) <= TOL_BF16
+
+
 @pytest.mark.parametrize("sizes,d,f", [
     ([1, 31, 32, 33, 0, 63, 64, 65, 129], 36, 100),   # bucket ends on every side of a tile, ragged last stage and columns
     ([1], 4, 4),                                      # the smallest problem there is

@@ -31,6 +31,8 @@
 // are padded so that all accesses are conflict-free.  Every XCD takes a
 // contiguous share of the tile list (expert -> column tile -> row tile), so that
 // the row tiles that share a weight panel run on one L2.
+//
+// Large batches take the bf16 matrix instruction on values split in three, see further down.
 #include "ffn_plan.h"
 
 namespace moe {
@@ -196,6 +198,256 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
     }
 }
 
+// ---- large batches: the same products on the bf16 matrix instruction -------------------------------------------------
+// An fp32 value is the sum of three bf16 values exactly (the value rounded, the remainder rounded, the rest), and the
+// bf16 instruction has sixteen times the fp32 one's rate: the six largest of the nine products of pieces, which leave out
+// 2^-25 of a product at most, come to 2.7 times it.  The instruction does not round its sums to nearest, so that a
+// chain of all of them is worse than fp32 (1.10e-6 of the result's norm where the fp32 kernel has 6.4e-7); a stage of 32 k
+// is therefore summed from zero, smallest products first, and added with a vector addition: 2.6e-7, the largest error
+// of an element 2.3e-6 against 4.7e-6 (d 1024, f 2816, 2000 routes; smaller in the same way at all sizes measured).
+//
+// A workgroup owns 64 rows x 64 columns of outputs, a wavefront 16 columns of it (of both products in the up
+// projection).  B goes from memory into the lanes that multiply it, 8 k of a column each, and is split there; A is
+// needed by all four wavefronts, so each splits 16 rows and hands the pieces on through LDS in operand order.
+// While a stage multiplies, the next is split and the one after is in flight, one barrier per stage; the
+// compiler would move the loads down to their use, hence the scheduling barriers.  Blocks of 16 rows past the bucket's
+// end are not multiplied.
+//
+// Bound by power for the up projection (the clock falls to 1.9 GHz) and by the loads and vector work of the narrower
+// tile for the down projection.  2000 routes in 8 skewed buckets, d 1024, f 2816, layer 377 -> 293 us; 4096 routes 721 ->
+// 501.  Both products staged through LDS 345; tiles of 128 rows 309, 512; 128 columns in the down projection 305, 515;
+// one stage in flight and four wavefronts a SIMD 291, 497, but 512 routes 174 for 147.
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+constexpr int kSplitBlocks = kF32SplitRows / 16;     // 16-row blocks of a tile
+constexpr int kSplitStage = 32;                      // k of a stage
+constexpr int kSplitCols = 64;                       // output columns of a tile
+static_assert(kSplitBlocks == kF32Waves, "a wavefront splits one block of A");
+
+// Whether the batch is large enough, every row being in a resident bucket: enough work to fill the chip with these tiles
+// and enough rows a bucket to fill a tile.  The fp32 kernel / this one, us, of 120 shapes: N d f = 0.54e9 61 / 62 (d and f
+// 512), 63 / 71 (1024); 1.07e9 94 / 85, 94 / 95; 1.48e9 (d 1024, f 2816) 116 / 118 with 128 rows a bucket, 135 / 149 with 64;
+// 1.6e9 124 / 113; 2.15e9 155 / 135; 2.95e9 218 / 193, 247 / 227 with 64 rows; from there on 1.1 to 1.4 times as fast.
+static bool split_pays(int N, int d, int f, int E) {
+    return (double)N * d * f >= 1.6e9 && N >= (long long)kF32SplitRows * E;
+}
+
+// 8 fp32 values -> their three bf16 pieces
+__device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&piece)[3]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = v[2 * i], b = v[2 * i + 1];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const f32x2 pair = {a, b};
+            const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2));
+            piece[p][i] = h;
+            a -= __uint_as_float(h << 16);
+            b -= __uint_as_float(h & 0xFFFF0000u);
+        }
+    }
+}
+
+template <bool UP>
+__global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __restrict__ A, const float* __restrict__ packed,
+                                                               int d, int f, float* __restrict__ C, const int32_t* __restrict__ plan) {
+    constexpr int NP = UP ? 2 : 1, A_UNITS = 3 * kSplitBlocks * 64;       // products; 16-byte units of A's pieces in a stage
+    __shared__ u32x4 smem[2 * A_UNITS];
+    const int K = UP ? d : f, NC = UP ? f : d;
+    const int NT = (NC + kSplitCols - 1) / kSplitCols;
+
+    // which tile: as above, by the tiles of kF32SplitRows rows
+    const int32_t* prefix = plan + kPlanTiles1;
+    const int n_listed = plan[0];
+    const long long total = (long long)prefix[n_listed] * NT, per_xcd = (total + kF32Xcds - 1) / kF32Xcds;
+    const long long slot = blockIdx.x / kF32Xcds, t = (long long)(blockIdx.x % kF32Xcds) * per_xcd + slot;
+    if (slot >= per_xcd || t >= total) return;
+    int lo = 0, hi = n_listed - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if ((long long)prefix[mid] * NT <= t) lo = mid; else hi = mid - 1;
+    }
+    const int mt_e = prefix[lo + 1] - prefix[lo];
+    const int rem = (int)(t - (long long)prefix[lo] * NT);
+    const int nt = rem / mt_e, r0 = (rem - nt * mt_e) * kF32SplitRows;
+    const int rows = min(kF32SplitRows, plan[kPlanCount + lo] - r0), n0 = nt * kSplitCols;
+    const RowMap rm = row_map<true>(plan, lo, r0, rows);
+    const bool merged = rm.merged;
+    const float* We = packed + (size_t)plan[kPlanExpert + lo] * 3 * d * f;
+    const float* Bbase = UP ? We : We + (size_t)2 * d * f;
+    const float* Abase = merged ? A : A + (size_t)rm.row0 * K;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // an operand of the instruction: lane l holds row (column) l % 16 and the 8 k from 8 * (l / 16).  Rows and columns past
+    // the tile's end re-read its last ones (their outputs are never stored)
+    const int kg = 8 * (lane >> 4), col = n0 + 16 * wave + (lane & 15), arow = min(16 * wave + (lane & 15), rows - 1);
+    const uint32_t a_off = (uint32_t)(merged ? buffer_row(rm, arow) : arow) * (uint32_t)K + (uint32_t)kg;
+    const uint32_t b_col = (uint32_t)min(col, NC - 1);
+    const uint32_t b_off = ((uint32_t)kg * (uint32_t)NC + b_col) * 4u;    // bytes
+    const int n_full = K / kSplitStage, n_stage = (K + kSplitStage - 1) / kSplitStage;
+    struct Raw { float a[8], b[NP][8]; };
+    auto fetch = [&](int s, Raw& r) {                                     // a whole stage
+        const int k0 = s * kSplitStage;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const float* b = Bbase + (size_t)p * d * f + (size_t)k0 * NC;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) r.b[p][u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b + (size_t)u * NC) + b_off);
+        }
+#pragma unroll
+        for (int h = 0; h < 8; h += 4) {
+            const float4 q = *reinterpret_cast<const float4*>(Abase + k0 + (a_off + h));
+            r.a[h] = q.x; r.a[h + 1] = q.y; r.a[h + 2] = q.z; r.a[h + 3] = q.w;
+        }
+    };
+    auto fetch_last = [&](int s, Raw& r) {                                // the one that the reduction ends in: k past the end count as zero
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int k = s * kSplitStage + kg + u;
+                const float q = Bbase[(size_t)p * d * f + (size_t)min(k, K - 1) * NC + b_col];
+                r.b[p][u] = k < K ? q : 0.f;
+            }
+#pragma unroll
+        for (int h = 0; h < 8; h += 4) {
+            const int k = s * kSplitStage + kg + h;
+            const float4 q = *reinterpret_cast<const float4*>(Abase + (a_off - kg + min(k, K - 4)));
+            const bool in = k < K;
+            r.a[h] = in ? q.x : 0.f; r.a[h + 1] = in ? q.y : 0.f; r.a[h + 2] = in ? q.z : 0.f; r.a[h + 3] = in ? q.w : 0.f;
+        }
+    };
+    struct Frags { u32x4 b[NP][3]; };
+    auto convert = [&](const Raw& r, Frags& fr, int buf) {
+        u32x4 pa[3];
+        split_eight(r.a, pa);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) smem[buf * A_UNITS + (q * kSplitBlocks + wave) * 64 + lane] = pa[q];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) split_eight(r.b[p], fr.b[p]);
+    };
+
+    f32x4 acc[kSplitBlocks][NP];
+#pragma unroll
+    for (int m = 0; m < kSplitBlocks; ++m)
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[m][p][v] = 0.f;
+    auto loop = [&](auto active) {
+        constexpr int NA = decltype(active)::value;                       // row blocks that hold rows of the bucket
+        constexpr int MG = NA < 4 / NP ? NA : 4 / NP;                     // row blocks at a time: up to four chains of matrix instructions
+        auto multiply = [&](const Frags& fr, int buf) {
+#pragma unroll
+            for (int m0 = 0; m0 < NA; m0 += MG) {
+                u32x4 a[MG][3];
+                f32x4 sum[MG][NP];
+#pragma unroll
+                for (int m = 0; m < MG; ++m)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) a[m][q] = smem[buf * A_UNITS + (q * kSplitBlocks + min(m0 + m, NA - 1)) * 64 + lane];
+                constexpr int piece_a[6] = {2, 0, 1, 1, 0, 0}, piece_b[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+#pragma unroll
+                    for (int m = 0; m < MG; ++m)
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+                            if (m0 + m < NA)
+                                sum[m][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[m][piece_a[q]]),
+                                                                                    __builtin_bit_cast(bf16x8, fr.b[p][piece_b[q]]),
+                                                                                    q == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum[m][p], 0, 0, 0);
+#pragma unroll
+                for (int m = 0; m < MG; ++m)
+#pragma unroll
+                    for (int p = 0; p < NP; ++p)
+                        if (m0 + m < NA)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) acc[m0 + m][p][v] += sum[m][p][v];
+            }
+        };
+        Raw even, odd;
+        Frags f0, f1;
+        auto get = [&](int s, Raw& r) { if (s < n_full) fetch(s, r); else if (s < n_stage) fetch_last(s, r); };
+        get(0, even);
+        get(1, odd);
+        convert(even, f0, 0);
+        __syncthreads();
+        int s = 0;
+        for (; s + 3 < n_full; s += 2) {
+            fetch(s + 2, even);
+            __builtin_amdgcn_sched_barrier(0);
+            convert(odd, f1, 1);                                          // its LDS was read before the last barrier
+            multiply(f0, 0);
+            __syncthreads();
+            fetch(s + 3, odd);
+            __builtin_amdgcn_sched_barrier(0);
+            convert(even, f0, 0);
+            multiply(f1, 1);
+            __syncthreads();
+        }
+        for (;; s += 2) {                                                 // up to four stages, the ragged one among them
+            get(s + 2, even);
+            if (s + 1 < n_stage) convert(odd, f1, 1);
+            multiply(f0, 0);
+            if (s + 1 >= n_stage) break;
+            __syncthreads();
+            get(s + 3, odd);
+            if (s + 2 < n_stage) convert(even, f0, 0);
+            multiply(f1, 1);
+            if (s + 2 >= n_stage) break;
+            __syncthreads();
+        }
+    };
+    const int blocks = (rows + 15) / 16;                                  // the same for all wavefronts
+    switch (blocks) {
+        case 1: loop(std::integral_constant<int, 1>()); break;
+        case 2: loop(std::integral_constant<int, 2>()); break;
+        case 3: loop(std::integral_constant<int, 3>()); break;
+        default: loop(std::integral_constant<int, 4>()); break;
+    }
+
+    // accumulator v of block m: row 16 m + 4 (lane / 16) + v, column lane % 16
+    constexpr float kMax = 3.4028234e38f;
+    bool finite = true;
+#pragma unroll
+    for (int m = 0; m < kSplitBlocks; ++m) {
+        if (m >= blocks) break;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = 16 * m + 4 * (lane >> 4) + v;
+            const size_t at = buffer_row(rm, min(r, rows - 1));
+            const float u = acc[m][0][v], g = acc[m][NP - 1][v];
+            if (r >= rows || col >= NC) continue;
+            finite &= fabsf(u) <= kMax && fabsf(g) <= kMax;
+            C[at * NC + col] = UP ? u / (1.0f + expf(-u)) * g : u;
+        }
+    }
+    if (__any(!finite)) {
+        // An operand that is infinite, or rounds to that, has no pieces that add up to it: the wavefront's outputs once more, in
+        // plain fp32 (a batch of nothing but NaN, d 1024, f 2816, 2000 routes: 31 ms)
+#pragma unroll 1
+        for (int i = 0; i < 4 * blocks; ++i) {
+            const int r = 16 * (i >> 2) + 4 * (lane >> 4) + (i & 3);
+            const size_t at = buffer_row(rm, min(r, rows - 1));
+            if (r >= rows || col >= NC) continue;
+            float u = 0.f, g = 0.f;
+#pragma unroll 1
+            for (int k = 0; k < K; ++k) {
+                const float a = A[at * K + k];
+                u = fmaf(a, Bbase[(size_t)k * NC + col], u);
+                if (UP) g = fmaf(a, Bbase[(size_t)d * f + (size_t)k * NC + col], g);
+            }
+            C[at * NC + col] = UP ? u / (1.0f + expf(-u)) * g : u;
+        }
+    }
+}
+
 int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* packed, const int32_t* counts,
                    const int32_t* starts, const int32_t* placement, int local_gpu, const int32_t* group_expert,
                    int n_weights, float* out, int32_t* plan, bool plan_ready, float* H, hipStream_t s) {
@@ -208,18 +460,21 @@ int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* pack
         rc = launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, shape, mergeable, {}, plan, s);
         if (rc != MOE_OK) return rc;
     }
-    const long long mt_max = (N + kF32Tile - 1) / kF32Tile + (E < N ? E : N);     // sum of ceil(n_e / 32) never exceeds this
-    auto grid_for = [&](int columns) { return (mt_max * ((columns + kF32Tile - 1) / kF32Tile) + kF32Xcds - 1) / kF32Xcds * kF32Xcds; };
+    const bool split = local_gpu < 0 && split_pays(N, d, f, E);
+    const int tile_rows = split ? kF32SplitRows : kF32Tile, tile_cols = split ? kSplitCols : kF32Tile;
+    const long long mt_max = (N + tile_rows - 1) / tile_rows + (E < N ? E : N);   // sum of ceil(n_e / tile_rows) never exceeds this
+    auto grid_for = [&](int columns) { return (mt_max * ((columns + tile_cols - 1) / tile_cols) + kF32Xcds - 1) / kF32Xcds * kF32Xcds; };
+    const auto up = split ? &ffn_f32_split_kernel<true> : &ffn_f32_kernel<true>, down = split ? &ffn_f32_split_kernel<false> : &ffn_f32_kernel<false>;
     if (grid_for(f) > 0x7FFFFFFFll || grid_for(d) > 0x7FFFFFFFll)
         return fail(MOE_ERR_UNSUPPORTED, "moe_expert_ffn_grouped: too many tiles for one launch");
     {
         LaunchTimer timer(MOE_K_FFN_UP, s);
-        hipLaunchKernelGGL(ffn_f32_kernel<true>, dim3((unsigned)grid_for(f)), dim3(256), 0, s, a, packed, d, f, H, plan);
+        hipLaunchKernelGGL(up, dim3((unsigned)grid_for(f)), dim3(256), 0, s, a, packed, d, f, H, plan);
         if ((rc = check_launch("moe_expert_ffn_grouped up launch")) != MOE_OK) return rc;
     }
     {
         LaunchTimer timer(MOE_K_FFN_DOWN, s);
-        hipLaunchKernelGGL(ffn_f32_kernel<false>, dim3((unsigned)grid_for(d)), dim3(256), 0, s, (const float*)H, packed, d, f, out, plan);
+        hipLaunchKernelGGL(down, dim3((unsigned)grid_for(d)), dim3(256), 0, s, (const float*)H, packed, d, f, out, plan);
         if ((rc = check_launch("moe_expert_ffn_grouped down launch")) != MOE_OK) return rc;
     }
     return MOE_OK;

@@ -113,7 +113,7 @@ int launch_ffn_plan(const int32_t* counts, const int32_t* starts, const int32_t*
                     const int32_t* group_expert, int n_weights, int E, int N, const PlanShape& shape, int merge, const MergeShape& merge_shape,
                     int32_t* plan, hipStream_t s);
 
-constexpr int kF32TileRows = 32;                        // tile height of the fp32 path
+constexpr int kF32TileRows = 32, kF32SplitRows = 64;    // tile heights of the fp32 path: small batches, large ones
 constexpr int kTallTileRows = 384, kShortTileRows = 256; // tile heights of the bf16 path
 constexpr int kSkinnyRows = 64;                         // rows a pass of its streaming kernels covers (bm1 of their plan)
 

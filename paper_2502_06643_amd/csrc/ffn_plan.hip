@@ -106,7 +106,7 @@ __global__ __launch_bounds__(kPlanThreads) void ffn_plan_kernel(const int32_t* _
 }
 
 int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_resident, PlanShape* shape) {
-    *shape = {kF32TileRows, kF32TileRows, 0, 0, 0, 0};
+    *shape = {kF32TileRows, kF32SplitRows, 0, 0, 0, 0};
     if (dt == MOE_F32) return MOE_OK;
     shape->bm0 = kShortTileRows;
     shape->bm1 = kSkinnyRows;

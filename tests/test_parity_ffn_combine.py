@@ -178,6 +178,45 @@ def test_ffn_skewed_buckets_including_empty_and_single_row_experts(lib):
     assert rel_err(as_f64(to_host(L.ffn_out)), ref) <= TOL_BF16
 
 
+@pytest.mark.parametrize("sizes,d,f", [
+    ([257, 273, 289, 305, 320, 0], 1060, 1100),       # one to four row blocks in the last tile; ragged last stages and columns
+    ([1000], 1024, 1632),                             # exact stages, an even and an odd number of them
+    ([2000, 2100], 20, 19600),                        # a reduction shorter than a stage
+    ([4100], 19600, 20),
+])
+def test_ffn_f32_split(lib, sizes, d, f):
+    """Batches large enough for the three-piece kernels; the fp32 bound of the other kernels holds with room: the
+    products left out are 2^-25 of a product, a tenth of what the sums round away."""
+    E, T = len(sizes), sum(sizes)
+    x, w1, w3, w2, _, _ = make_problem(T + d, T, d, f, E, 1, 1, "f32")
+    idx = np.random.default_rng(T).permutation(np.repeat(np.arange(E), sizes)).astype(np.int32)[:, None]
+    pl = np.zeros(E, dtype=np.int32)
+    L = gpu_ffn(lib, x, w1, w3, w2, idx, pl, 1, -1, "f32")
+    dsp = O.dispatch(x, idx, pl, 1)
+    ref = O.expert_ffn_grouped(dsp["send_buf"], w1, w3, w2, dsp["expert_counts"], dsp["expert_start"], pl, -1)
+    got = to_host(L.ffn_out)
+    assert rel_err(got, ref) <= TOL_F32
+    assert fro_err(got, ref) <= 1e-6
+
+
+def test_ffn_f32_split_infinite_and_huge(lib):
+    """Values that have no finite pieces: an infinity and a NaN stay in their rows, and a finite value that rounds past
+    the largest bf16 one is multiplied as what it is."""
+    T, d, f = 1024, 1024, 1600
+    x, w1, w3, w2, _, _ = make_problem(5, T, d, f, 1, 1, 1, "f32")
+    idx, pl = np.zeros((T, 1), dtype=np.int32), np.zeros(1, dtype=np.int32)
+    w1[0, 7], w3[0, 7] = 1e-37 * w1[0, 7], 1e-38 * w3[0, 7]
+    x[40, 3], x[700, 900], x[1023, 7] = np.inf, np.nan, 3.4e38
+    L = gpu_ffn(lib, x, w1, w3, w2, idx, pl, 1, -1, "f32")
+    got = to_host(L.ffn_out)
+    bad = np.zeros(T, dtype=bool)
+    bad[[40, 700]] = True
+    assert not np.isfinite(got[bad]).any()
+    with np.errstate(all="ignore"):
+        ref = O.expert_ffn_grouped(x[~bad], w1, w3, w2, np.array([T - 2], dtype=np.int32), np.zeros(1, dtype=np.int32), pl, -1)
+    assert rel_err(got[~bad], ref) <= TOL_F32
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_ffn_when_this_gpu_owns_no_expert_or_no_route(lib, dtype):
     """local_gpu owns no expert (the ILP forbids it, the library tolerates it), and a GPU whose experts got no route:

@@ -4,7 +4,7 @@
 // (writing them to memory is optional).
 //
 // bf16: a skinny GEMM on the matrix cores that is bound by reading x once.  A
-// workgroup owns 32 tokens; its wavefronts (4, in small batches 16) split the
+// workgroup owns up to 32 tokens; its wavefronts (4 to 16, see below) split the
 // reduction into contiguous shares, each feeding v_mfma_f32_32x32x16_bf16 with the activation
 // fragment (lane l: token l % 32, 8 consecutive k; fetched as whole lines and
 // re-ordered through a staging tile in LDS, see the kernel) and the
@@ -70,19 +70,20 @@ constexpr int router_lds_floats(int panels, int waves) {
     return stage > sums ? (stage > rows ? stage : rows) : (sums > rows ? sums : rows);
 }
 
-// WAVES wavefronts share the reduction: sixteen while a compute unit has one workgroup at most, whose chain of k steps, each
-// at the latency of memory, is all there is; four when there are more workgroups or, with one panel of experts, when the
-// read of x is what bounds the launch.  Four / sixteen, us: 8 experts, d 4096, 1024 tokens 11.8 / 9.5, 4096 14.8 / 11.2,
-// 5000 15.4 / 15.0, 6000 15.9 / 16.9, 7168 16.2 / 18.4; d 2048, 8192 tokens 11.0 / 9.2, 9000 12.0 / 13.1; 64 experts, d
-// 4096, 8192 tokens 26.1 / 24.3, 9000 27.5 / 33.6; 128 experts, d 2048, 8192 tokens 24.6 / 17.0, 9000 25.8 / 28.2.
+// WAVES wavefronts share the reduction, whose chain of k steps, each at the latency of memory, is all there is to a small
+// batch; with several workgroups on a compute unit the read of x is what bounds the launch (launch_router_gate has the rule).
+// Four / eight / sixteen, us: 8 experts, d 4096, 64 tokens 8.3 / 7.5 / 7.3, 4096 10.8 / 9.1 / 12.1, 6000 12.0 / 11.1 / 13.6,
+// 8192 14.1 / 17.7 / 18.8, 24000 39 / 44 / 50, d 2048, 10007 tokens 10.8 / 10.1 / 15.6; 64 experts, d 4096, 2048 tokens 21 /
+// 13.8 / 13.6, 8192 25.0 / 19.7 / 22.9, d 2048, 16384 20.8 / 18.6 / 23.9, 24000 31 / 37 / 35; 128 experts, d 4096, 2048 tokens
+// 34 / 26 / 20, 24000 90 / 87 / 87, 65536 207 / 186 / 232, d 1024, 65536 75 / 63 / 81.
 template <int PANELS, int KMAX, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void router_gate_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ packed,
+__global__ __launch_bounds__(64 * WAVES, WAVES == 8 && PANELS > 2 ? 4 : 1) void router_gate_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ packed,
                                                                const float* __restrict__ bias, int T, int d, int E, int k,
                                                                float* __restrict__ logits, int32_t* __restrict__ topk_idx,
-                                                               float* __restrict__ topk_w) {
+                                                               float* __restrict__ topk_w, int tokens) {
     extern __shared__ __attribute__((aligned(16))) float red[];      // activation staging, then [PANELS][16][64] partial sums, then the logits
     const int lane = threadIdx.x & 63, wave = WAVES == 4 ? (int)(threadIdx.x >> 6) : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar with four: 17.4 -> 20.6 us at 10007 tokens
-    const long long t0 = (long long)blockIdx.x * 32;
+    const long long t0 = (long long)blockIdx.x * tokens, last = min(t0 + tokens, (long long)T) - 1;
     const uint16_t* wlane = packed + (size_t)lane * 8;
     f32x16 acc[PANELS];
 #pragma unroll
@@ -102,39 +103,90 @@ __global__ __launch_bounds__(64 * WAVES) void router_gate_bf16_kernel(const uint
     const int kw0 = WAVES == 4 ? wave * (d / 4) : (int)((long long)wave * (d / 16) / WAVES) * 16;
     const int KSW = WAVES == 4 ? d / 4 : (int)((long long)(wave + 1) * (d / 16) / WAVES) * 16 - kw0;
     const int n_stage = KSW / KSTAGE;
-    u32x4 cur[4], nxt[4];                                // the stage being multiplied and the next one, in flight (two ahead measured the same)
-    const int lr = lane >> 3, lc = lane & 7;
-    auto fetch = [&](int st, u32x4 (&r)[4]) {
+    if constexpr (PANELS == 1 && WAVES <= 8) {
+        // Loads return in order, so a stage's weights are asked for one stage ahead and before the activations of the stage
+        // after that, two ahead: waiting for one stage leaves the next one's activations in flight.  With the weights asked for
+        // in the stage that needs them, behind the next stage's activations, every stage waited for both: 65536 tokens, d 4096,
+        // 8 experts 106 us, now 97.
+        u32x4 xr[3][4], wr[2][4];
+        const int lr = lane >> 3, lc = lane & 7;
+        const uint16_t* xl[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const long long t = min(t0 + 8 * j + lr, (long long)T - 1);          // tokens past the end re-read the last one
-            r[j] = *reinterpret_cast<const u32x4*>(x + t * d + kw0 + st * KSTAGE + lc * 8);
-        }
-    };
-    if (n_stage > 0) fetch(0, cur);
-    for (int st = 0; st < n_stage; ++st) {
-        if (st + 1 < n_stage) fetch(st + 1, nxt);
+        for (int j = 0; j < 4; ++j) xl[j] = x + min(t0 + 8 * j + lr, last) * d + kw0 + lc * 8;       // tokens past the workgroup's re-read its last one
+        auto fetch_x = [&](int st, u32x4 (&r)[4]) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int row = 8 * j + lr;
-            *reinterpret_cast<u32x4*>(stage + row * KSTAGE + ((lc ^ ((row >> 1) & 7)) * 8)) = cur[j];
-        }
-        const int ks0 = (kw0 + st * KSTAGE) / 16;
+            for (int j = 0; j < 4; ++j) r[j] = *reinterpret_cast<const u32x4*>(xl[j] + st * KSTAGE);
+        };
+        // lanes whose expert does not exist point past the descriptor: they move no bytes and get the zeros that stand there
+        const auto wsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(packed), 0, 32 * d * 2, 0x00020000);
+        const uint32_t woff = (lane & 31) < E ? (uint32_t)(kw0 / 16 * 64 + lane) * 16u : 0x80000000u;
+        auto fetch_w = [&](int st, u32x4 (&r)[4]) {
 #pragma unroll
-        for (int u = 0; u < KSTAGE / 16; ++u) {
-            const int row = lane & 31;
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(stage + row * KSTAGE + (((2 * u + (lane >> 5)) ^ ((row >> 1) & 7)) * 8));
+            for (int u = 0; u < 4; ++u) r[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wsrc, woff + (uint32_t)((st * 4 + u) * 1024), 0, 0));
+        };
+        auto multiply = [&](const u32x4 (&xs)[4], const u32x4 (&ws)[4]) {
 #pragma unroll
-            for (int p = 0; p < PANELS; ++p) {
-                const bf16x8 b = *reinterpret_cast<const bf16x8*>(wlane + ((size_t)(ks0 + u) * PANELS + p) * 512);
-                acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[p], 0, 0, 0);
+            for (int j = 0; j < 4; ++j) {
+                const int row = 8 * j + lr;
+                *reinterpret_cast<u32x4*>(stage + row * KSTAGE + ((lc ^ ((row >> 1) & 7)) * 8)) = xs[j];
+            }
+#pragma unroll
+            for (int u = 0; u < KSTAGE / 16; ++u) {
+                const int row = lane & 31;
+                const bf16x8 a = *reinterpret_cast<const bf16x8*>(stage + row * KSTAGE + (((2 * u + (lane >> 5)) ^ ((row >> 1) & 7)) * 8));
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, ws[u]), acc[0], 0, 0, 0);
+            }
+        };
+        if (n_stage > 0) {
+            fetch_x(0, xr[0]);
+            fetch_w(0, wr[0]);
+            fetch_x(min(1, n_stage - 1), xr[1]);
+            for (int st = 0; st < n_stage; st += 6) {    // buffers by stage number; past the end the last stage is fetched again
+#pragma unroll
+                for (int u = 0; u < 6; ++u) {
+                    fetch_w(min(st + u + 1, n_stage - 1), wr[(u + 1) & 1]);
+                    fetch_x(min(st + u + 2, n_stage - 1), xr[(u + 2) % 3]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(xr[u % 3], wr[u & 1]);
+                    if (st + u + 1 >= n_stage) break;
+                }
             }
         }
+    } else {
+        u32x4 cur[4], nxt[4];                            // the stage being multiplied and the next one, in flight
+        const int lr = lane >> 3, lc = lane & 7;
+        auto fetch = [&](int st, u32x4 (&r)[4]) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) cur[j] = nxt[j];
+            for (int j = 0; j < 4; ++j) {
+                const long long t = min(t0 + 8 * j + lr, last);          // tokens past the workgroup's re-read its last one
+                r[j] = *reinterpret_cast<const u32x4*>(x + t * d + kw0 + st * KSTAGE + lc * 8);
+            }
+        };
+        if (n_stage > 0) fetch(0, cur);
+        for (int st = 0; st < n_stage; ++st) {
+            if (st + 1 < n_stage) fetch(st + 1, nxt);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int row = 8 * j + lr;
+                *reinterpret_cast<u32x4*>(stage + row * KSTAGE + ((lc ^ ((row >> 1) & 7)) * 8)) = cur[j];
+            }
+            const int ks0 = (kw0 + st * KSTAGE) / 16;
+#pragma unroll
+            for (int u = 0; u < KSTAGE / 16; ++u) {
+                const int row = lane & 31;
+                const bf16x8 a = *reinterpret_cast<const bf16x8*>(stage + row * KSTAGE + (((2 * u + (lane >> 5)) ^ ((row >> 1) & 7)) * 8));
+#pragma unroll
+                for (int p = 0; p < PANELS; ++p) {
+                    const bf16x8 b = *reinterpret_cast<const bf16x8*>(wlane + ((size_t)(ks0 + u) * PANELS + p) * 512);
+                    acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[p], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) cur[j] = nxt[j];
+        }
     }
     {
-        const long long tr = min(t0 + (lane & 31), (long long)T - 1);
+        const long long tr = min(t0 + (lane & 31), last);
         const uint16_t* xrow = x + tr * d + 8 * (lane >> 5);
         for (int ks = (kw0 + n_stage * KSTAGE) / 16; ks < (kw0 + KSW) / 16; ++ks) {
             const bf16x8 a = *reinterpret_cast<const bf16x8*>(xrow + ks * 16);
@@ -179,15 +231,16 @@ __global__ __launch_bounds__(64 * WAVES) void router_gate_bf16_kernel(const uint
                 for (int v = 0; v < 16; ++v) {
                     const int tl = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
                     red[tl * RS + e] = acc[p][v];
-                    if (logits != nullptr && t0 + tl < T && e < E) logits[(t0 + tl) * E + e] = acc[p][v];
+                    if (logits != nullptr && t0 + tl <= last && e < E) logits[(t0 + tl) * E + e] = acc[p][v];
                 }
             }
         }
     } else {
-        // panel by panel: all partial sums side by side; wavefront w adds those of accumulator w, in wavefront order
-        static_assert(WAVES == 4 || WAVES == 16, "one accumulator row per wavefront");
-        float sum[PANELS];
-        const int tl = 8 * (wave >> 2) + 4 * (lane >> 5) + (wave & 3);
+        // panel by panel: all partial sums side by side; a wavefront adds those of 16 / WAVES accumulators, in wavefront order
+        static_assert(16 % WAVES == 0, "whole accumulators a wavefront");
+        constexpr int SHARE = 16 / WAVES;
+        float sum[PANELS][SHARE];
+        const auto token = [&](int i) { const int v = wave * SHARE + i; return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); };
 #pragma unroll
         for (int p = 0; p < PANELS; ++p) {
             if (p > 0) __syncthreads();
@@ -195,21 +248,27 @@ __global__ __launch_bounds__(64 * WAVES) void router_gate_bf16_kernel(const uint
             for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[p][v];
             __syncthreads();
             const int e = p * 32 + (lane & 31);
-            float t = red[wave * 64 + lane];
+            const float b = (bias != nullptr && e < E) ? bias[e] : 0.f;
 #pragma unroll
-            for (int w = 1; w < WAVES; ++w) t += red[(w * 16 + wave) * 64 + lane];
-            sum[p] = t + ((bias != nullptr && e < E) ? bias[e] : 0.f);
-            if (logits != nullptr && t0 + tl < T && e < E) logits[(t0 + tl) * E + e] = sum[p];
+            for (int i = 0; i < SHARE; ++i) {
+                float t = red[(wave * SHARE + i) * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < WAVES; ++w) t += red[(w * 16 + wave * SHARE + i) * 64 + lane];
+                sum[p][i] = t + b;
+                if (logits != nullptr && t0 + token(i) <= last && e < E) logits[(t0 + token(i)) * E + e] = sum[p][i];
+            }
         }
         __syncthreads();                                 // the sums have been read: the logits overwrite them
 #pragma unroll
-        for (int p = 0; p < PANELS; ++p) red[tl * RS + p * 32 + (lane & 31)] = sum[p];
+        for (int p = 0; p < PANELS; ++p)
+#pragma unroll
+            for (int i = 0; i < SHARE; ++i) red[token(i) * RS + p * 32 + (lane & 31)] = sum[p][i];
     }
     __syncthreads();
     // the gate: 8 lanes per token, 4 * PANELS logits per lane
     if (threadIdx.x >= 256) return;
     const int tl = threadIdx.x >> 3;
-    gate_select<8, 4 * PANELS, KMAX, false>(red + tl * RS, true, threadIdx.x & 7, t0 + tl < T, t0 + tl, E, k, topk_idx, topk_w);
+    gate_select<8, 4 * PANELS, KMAX, false>(red + tl * RS, true, threadIdx.x & 7, t0 + tl <= last, t0 + tl, E, k, topk_idx, topk_w);
 }
 
 template <int KMAX>
@@ -231,17 +290,30 @@ __global__ __launch_bounds__(256) void router_gate_f32_kernel(const float* __res
     gate_select<16, MOE_MAX_EXPERTS / 16, KMAX, false>(row, true, threadIdx.x & 15, threadIdx.x < 16, t, E, k, topk_idx, topk_w);
 }
 
-// which of the two (see the kernel): one workgroup of 32 tokens for each of 256 compute units, and at most 44 MB of x with one panel
-constexpr int kRouterSmallTokens = 8192;
-constexpr long long kRouterSmallElems = 22ll << 20;
+// Tokens of a workgroup with one panel of experts: as few, down to the number of experts (whose weights every workgroup
+// reads), as spread the batch over 256 compute units in whole rounds: 10007 tokens are 501 workgroups of 20 (15.9 us)
+// instead of 313 of 32 (17.8), of which 57 compute units have two; d 4096, 4096 tokens 256 of 16 (9.2) instead of 128 (12.8).
+constexpr int kRouterUnits = 256;
+static int router_tokens(int T, int E) {
+    const int rounds = (int)(((long long)T + 32 * kRouterUnits - 1) / (32 * kRouterUnits));
+    const int even = (int)(((long long)T + (long long)kRouterUnits * rounds - 1) / ((long long)kRouterUnits * rounds)), least = E < 8 ? 8 : E;
+    return even > least ? even : least;
+}
+// Wavefronts of a workgroup (measured at the kernel).  One panel of experts: sixteen for a handful of workgroups, eight up to
+// two of them a compute unit and 52 MB of x, then four.  Two panels: sixteen up to 96 workgroups, eight up to two
+// a compute unit.  Three and four: sixteen (whose weights a workgroup shares with itself only) up
+// to one a compute unit, then eight.  More than four panels: four, the accumulators of more do not fit.
+constexpr int kRouterFewTokens = 512;
+constexpr long long kRouterNearElems = 26ll << 20;
 template <int PANELS, int WAVES>
 static void launch_fused(const uint16_t* x, const uint16_t* packed, const float* bias, int T, int d, int E, int k, float* logits,
                          int32_t* idx, float* w, hipStream_t s) {
-    const dim3 grid((unsigned)((T + 31) / 32)), block(64 * WAVES);
+    const int tokens = PANELS == 1 && WAVES <= 8 ? router_tokens(T, E) : 32;
+    const dim3 grid((unsigned)((T + tokens - 1) / tokens)), block(64 * WAVES);
     const size_t lds = router_lds_floats(PANELS, WAVES) * sizeof(float);
-    if (k <= 2) hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, 2, WAVES>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w);
-    else if (k <= 8) hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, 8, WAVES>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w);
-    else hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, MOE_MAX_TOPK, WAVES>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w);
+    if (k <= 2) hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, 2, WAVES>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w, tokens);
+    else if (k <= 8) hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, 8, WAVES>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w, tokens);
+    else hipLaunchKernelGGL((router_gate_bf16_kernel<PANELS, MOE_MAX_TOPK, WAVES>), grid, block, lds, s, x, packed, bias, T, d, E, k, logits, idx, w, tokens);
 }
 
 int launch_router_gate(const void* x, moe_dtype_t dt, const void* packed, const float* bias, int T, int d, int E, int k,
@@ -250,13 +322,13 @@ int launch_router_gate(const void* x, moe_dtype_t dt, const void* packed, const 
     if (dt == MOE_BF16) {
         const uint16_t* xs = (const uint16_t*)x;
         const uint16_t* ps = (const uint16_t*)packed;
-        // sixteen wavefronts for small batches; past 128 experts their accumulators do not fit
-        const bool small = T <= kRouterSmallTokens && (E > 32 || (long long)T * d <= kRouterSmallElems);
+        const bool round = T <= 32 * kRouterUnits, two = T <= 64 * kRouterUnits;          // at most one (two) workgroups of 32 tokens a compute unit
+        const auto fused1 = T <= kRouterFewTokens ? launch_fused<1, 16> : (two && (long long)T * d <= kRouterNearElems ? launch_fused<1, 8> : launch_fused<1, 4>);
         switch (padded_experts(E) / 32) {
-            case 1: (small ? launch_fused<1, 16> : launch_fused<1, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
-            case 2: (small ? launch_fused<2, 16> : launch_fused<2, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
-            case 3: (small ? launch_fused<3, 16> : launch_fused<3, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
-            case 4: (small ? launch_fused<4, 16> : launch_fused<4, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 1: fused1(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 2: (T <= 3072 ? launch_fused<2, 16> : two ? launch_fused<2, 8> : launch_fused<2, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 3: (round ? launch_fused<3, 16> : launch_fused<3, 8>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
+            case 4: (round ? launch_fused<4, 16> : launch_fused<4, 8>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
             case 5: (launch_fused<5, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
             case 6: (launch_fused<6, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;
             case 7: (launch_fused<7, 4>)(xs, ps, bias, T, d, E, k, logits, idx, w, s); break;

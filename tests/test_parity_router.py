@@ -78,6 +78,18 @@ def test_small_batches_with_sixteen_wavefronts(lib, T, d, E, k):
     check(lib, synth.normal(T, 0, (T, d), 1.0, "bf16"), synth.normal(d, 1, (d, E), d ** -0.5, "bf16"), np.linspace(-1, 1, E), k)
 
 
+@pytest.mark.parametrize("T,d,E,k", [
+    (513, 1088, 8, 2), (2049, 64, 5, 1),           # eight tokens a workgroup, the last one with one; a share of less than a stage
+    (8193, 832, 8, 2), (9000, 64, 16, 4),          # two rounds of workgroups, 17 and 18 tokens each
+    (600, 448, 24, 3), (4000, 3136, 32, 2),        # as many tokens as experts, the whole panel; seven whole stages a share
+    (16385, 1792, 8, 2), (7000, 4096, 20, 6),      # four wavefronts past two rounds, and past the bytes
+    (3073, 192, 40, 2), (16384, 64, 64, 6), (16385, 64, 64, 6),
+    (8193, 320, 96, 9), (8200, 64, 128, 8),
+])
+def test_tokens_and_wavefronts_of_a_workgroup(lib, T, d, E, k):
+    check(lib, synth.normal(T, 0, (T, d), 1.0, "bf16"), synth.normal(d, 1, (d, E), d ** -0.5, "bf16"), np.linspace(-1, 1, E), k)
+
+
 @pytest.mark.parametrize("name", ["c1", "c1b", "c2", "c4", "c3"])
 def test_config_routers(lib, name):
     cfg = synth.config(name)

@@ -30,10 +30,11 @@
 // full round number less than 128, a workgroup of theirs takes four panels instead of sixteen and its wavefronts
 // a quarter of the reduction each, added in wavefront order through LDS: four times the workgroups, a quarter of the
 // chain, which fill in behind the whole tasks.  A launch of few tasks (a small expert, one resident expert of many) is
-// nothing but such a round, and cut up to 160.  All tasks of less than 128 cut this way and no others / the last round,
-// layer in us: Mixtral shape, 1 to 8 experts touched, 79 / 80, 137 / 138, 223 / 201, 255 / 258, 346 / 316, 386 / 377, 474 / 437,
-// 497 / 493; f 7168, 5 experts 203 / 172; d 1024, f 4096, 9 of 16 experts 69 / 59; d 2048, f 1408, 24 of 64 experts 107 / 94,
-// 32 120 / 114.  Limits of 60, 100, 130, 160 and 200: one Mixtral expert (112 tasks) 95, 87, 80, 80, 79, d 2048, f 2048, 8
+// nothing but such a round, and cut up to 160 if its chains are long (140 tasks of 10 k tiles: layer 40.9 us whole, 41.9 cut).
+// All tasks of less than 128 cut this way and no others / the last round, layer in us: Mixtral shape, 1 to 8 experts touched,
+// 79 / 80, 137 / 138, 223 / 201, 255 / 258, 346 / 316, 386 / 377, 474 / 437, 497 / 493; f 7168, 5 experts 203 / 172; d 1024, f
+// 4096, 9 of 16 experts 69 / 59; d 2048, f 1408, 24 of 64 experts 107 / 94, 32 120 / 114.  Limits of 60, 100, 130, 160 and 200:
+// one Mixtral expert (112 tasks) 95, 87, 80, 80, 79, d 2048, f 2048, 8
 // experts (128 tasks) 56, 60, 53, 53, 53, seven at f 3584 (196 tasks) 123, 124, 123, 123, 130; the last 128 of 896 tasks,
 // Mixtral shape, 128 routes: whole 505, cut 508.
 #include "bf16.h"
@@ -49,12 +50,14 @@ static_assert(kSkinnyRows == 64, "four 16-row fragments");
 constexpr int kSkinnyMaxParts = 16;
 constexpr int kSkinnySlots = 512;        // workgroups that run together, two per compute unit
 constexpr int kSkinnyRound = 256;        // one per compute unit
-constexpr int kSkinnyTail = 128, kSkinnyOnly = 160;      // a last round of fewer tasks than this is cut, and one that is all there is
+constexpr int kSkinnyTail = 128;         // a last round of fewer tasks than this is cut,
+constexpr int kSkinnyOnly = 160;         // ... and of fewer than this if it is all there is
+constexpr int kSkinnyLongChain = 24;     // ... with chains of at least so many k tiles
 
-// Tasks that run whole, the first ones, of `total`.
-__device__ __forceinline__ int whole_tasks(int total) {
+// Tasks that run whole, the first ones, of `total`; chain: k tiles of one.
+__device__ __forceinline__ int whole_tasks(int total, int chain) {
     const int tail = total % kSkinnyRound;
-    return tail < (total < kSkinnyRound ? kSkinnyOnly : kSkinnyTail) ? total - tail : total;
+    return tail < (total < kSkinnyRound && chain >= kSkinnyLongChain ? kSkinnyOnly : kSkinnyTail) ? total - tail : total;
 }
 
 // k parts of the down projection: as many as make no more workgroups than run together (more, shorter parts were slower,
@@ -213,7 +216,7 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const uin
                                                                     float* __restrict__ partial, int max_parts, int N) {
     __shared__ f32x4 red[kSkinnyWaves * 4 * 64];
     const int n_chunks = plan[2], parts = UP ? 1 : skinny_parts(n_chunks, NT, max_parts);
-    const int total = n_chunks * NT * parts, whole = whole_tasks(total);
+    const int total = n_chunks * NT * parts, whole = whole_tasks(total, K / (64 * parts));
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int task = blockIdx.x, grp = wave;

@@ -10,7 +10,7 @@
 
 namespace moe {
 
-template <bool BF16>
+template <bool BF16, int KMAX>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ ffn_out, const int32_t* __restrict__ inv_perm,
                                                       const int32_t* __restrict__ topk_idx, const float* __restrict__ topk_w,
                                                       const int32_t* __restrict__ placement, int local_gpu,
@@ -21,16 +21,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
     const long long t = u / units_per_row;
     const int c = (int)(u - t * units_per_row);
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int j = 0; j < k; ++j) {
-        const long long r = t * k + j;
-        if (local_gpu >= 0) {
-            const int e = topk_idx[r];
-            if ((unsigned)e >= (unsigned)E || placement[e] != local_gpu) continue;
-        }
-        const int p = inv_perm[r];
-        if ((unsigned)p >= (unsigned)N) continue;
-        const float w = topk_w[r];
-        const uint4 v = ffn_out[(long long)p * units_per_row + c];
+    auto add = [&](const uint4& v, float w) {
         if (BF16) {
             acc[0] = fmaf(w, bf16_lo(v.x), acc[0]); acc[1] = fmaf(w, bf16_hi(v.x), acc[1]);
             acc[2] = fmaf(w, bf16_lo(v.y), acc[2]); acc[3] = fmaf(w, bf16_hi(v.y), acc[3]);
@@ -40,6 +31,31 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
             acc[0] = fmaf(w, __uint_as_float(v.x), acc[0]); acc[1] = fmaf(w, __uint_as_float(v.y), acc[1]);
             acc[2] = fmaf(w, __uint_as_float(v.z), acc[2]); acc[3] = fmaf(w, __uint_as_float(v.w), acc[3]);
         }
+    };
+    // the token's k expert ids, positions and weights, then the owners, then the rows: three rounds of memory latency
+    // for up to KMAX routes instead of two or three per route (256 fp32 tokens, top-2: 3.7 -> 3.2 us)
+    for (int j0 = 0; j0 < k; j0 += KMAX) {
+        int ex[KMAX], p[KMAX];
+        float w[KMAX];
+        uint4 v[KMAX];
+#pragma unroll
+        for (int j = 0; j < KMAX; ++j) {
+            const long long r = t * k + min(j0 + j, k - 1);
+            ex[j] = local_gpu >= 0 ? topk_idx[r] : 0;
+            p[j] = inv_perm[r];
+            w[j] = topk_w[r];
+        }
+#pragma unroll
+        for (int j = 0; j < KMAX; ++j) {
+            const bool known = (unsigned)ex[j] < (unsigned)E;
+            const bool local = local_gpu < 0 || (known && placement[known ? ex[j] : 0] == local_gpu);
+            if (j0 + j >= k || !local || (unsigned)p[j] >= (unsigned)N) p[j] = -1;
+        }
+#pragma unroll
+        for (int j = 0; j < KMAX; ++j) v[j] = p[j] >= 0 ? ffn_out[(long long)p[j] * units_per_row + c] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int j = 0; j < KMAX; ++j)
+            if (p[j] >= 0) add(v[j], w[j]);
     }
     uint4 o;
     if (BF16) {
@@ -175,12 +191,10 @@ int launch_combine(const void* ffn_out, moe_dtype_t dt, const int32_t* inv_perm,
         if (bf) MOE_LAUNCH_TOKEN(true, 2, 1); else MOE_LAUNCH_TOKEN(false, 2, 1);
     } else if (units_per_row > 512 && units_per_row <= 1024) {
         if (bf) MOE_LAUNCH_TOKEN(true, 4, 1); else MOE_LAUNCH_TOKEN(false, 4, 1);
-    } else if (bf) {
-        hipLaunchKernelGGL(combine_kernel<true>, dim3((unsigned)grid), dim3(256), 0, s, (const uint4*)ffn_out, inv_perm, topk_idx,
-                           topk_w, placement, local_gpu, total_units, units_per_row, E, k, T * k, (uint4*)y);
     } else {
-        hipLaunchKernelGGL(combine_kernel<false>, dim3((unsigned)grid), dim3(256), 0, s, (const uint4*)ffn_out, inv_perm, topk_idx,
-                           topk_w, placement, local_gpu, total_units, units_per_row, E, k, T * k, (uint4*)y);
+        const auto kernel = bf ? (k <= 2 ? &combine_kernel<true, 2> : &combine_kernel<true, 8>) : (k <= 2 ? &combine_kernel<false, 2> : &combine_kernel<false, 8>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, s, (const uint4*)ffn_out, inv_perm, topk_idx, topk_w, placement, local_gpu,
+                           total_units, units_per_row, E, k, T * k, (uint4*)y);
     }
 #undef MOE_LAUNCH_TOKEN
     return check_launch("moe_combine launch");

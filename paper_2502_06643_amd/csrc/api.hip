@@ -398,7 +398,7 @@ int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T,
     const uintptr_t dispatch_ws = (uintptr_t)dispatch_workspace, plan_area = (uintptr_t)ffn_workspace;
     const bool shared = dispatch_ws < plan_area + kPlanBytes && plan_area < dispatch_ws + moe_dispatch_workspace_bytes(T, E, k);
     const bool fused = front_fits(T, E, k, row_bytes);
-    if ((rc = ffn_plan_shape(dt, N, d, f, E, local_gpu < 0, &pt.shape)) != MOE_OK) return rc;
+    if ((rc = ffn_plan_shape(dt, N, d, f, E, local_gpu < 0, false, &pt.shape)) != MOE_OK) return rc;
     if (fused) {
         FrontArgs a;
         a.x = (const uint4*)x; a.logits = logits; a.T = T; a.E = E; a.k = k; a.G = G; a.local_gpu = local_gpu;

@@ -84,22 +84,20 @@ size_t packed_bytes_bf16(int E, int d, int f);
 size_t ffn_bf16_scratch_bytes();      // fp32 partial tiles of the split tail, sized for the largest supported XCD
 int launch_pack_f32(const float* w1, const float* w3, const float* w2, int E, int d, int f, float* packed, hipStream_t s);
 int launch_pack_bf16(const void* w1, const void* w3, const void* w2, int E, int d, int f, void* packed, hipStream_t s);
-int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_resident, PlanShape* shape);
+bool ffn_streams(int N, int d, int f, int E, bool every_row_resident, bool segments);
+int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_resident, bool segments, PlanShape* shape);
 int ffn_bf16_device_setup(int* cus_per_xcd);      // of the tiled bf16 kernels, done by the first call on a device
 // E row groups (counts/starts); group g uses the weights of expert group_expert[g] of n_weights
 // (g itself when group_expert is NULL).  plan_ready: the plan has been built already (ffn_plan_shape's way)
 int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* packed, const int32_t* counts,
                    const int32_t* starts, const int32_t* placement, int local_gpu, const int32_t* group_expert,
                    int n_weights, float* out, int32_t* plan, bool plan_ready, float* H, hipStream_t s);
-// bf16, N <= kFfnSkinnyMaxRows: weight-streaming kernels for decode-sized batches (plan already built).
-// N counts all routes, resident or not.  Whole layer, us, tiled / streaming kernels: Mixtral shape, top-2, all experts, N = 72
+// bf16, ffn_streams(): weight-streaming kernels for batches of few rows (plan already built).
+// kFfnSkinnyMaxRows counts all routes, resident or not, whatever the shape.  Whole layer, us, tiled / streaming kernels: Mixtral shape, top-2, all experts, N = 72
 // 498 / 498, 160 505 / 512, 256 509 / 565 (tasks of 64 rows of the largest buckets); two of the eight experts 149 / 140, 148 /
 // 144, 151 / 153, with the most popular one among them 150 / 151, 152 / 176, 158 / 262; d 1024, f 4096, 16 experts 83 / 73,
 // 87 / 83, 99 / 95; 8 of 64 experts, d 2048, f 1408, top-6 54 / 30, 54 / 34, 55 / 35.
-#ifndef MOE_SKINNY_MAX_ROWS
-#define MOE_SKINNY_MAX_ROWS 160
-#endif
-constexpr int kFfnSkinnyMaxRows = MOE_SKINNY_MAX_ROWS;
+constexpr int kFfnSkinnyMaxRows = 160;
 // What the combine needs besides ffn_out; done: set when the FFN launches have written y as well.
 struct CombineTail {
     const int32_t* inv_perm; const int32_t* topk_idx; const float* topk_w; const int32_t* placement;

@@ -713,10 +713,12 @@ int launch_ffn_bf16(const void* a, int N, int d, int f, int E, const void* packe
                     const int32_t* starts, const int32_t* placement, int local_gpu, const int32_t* group_expert,
                     int n_weights, void* out, int32_t* plan, bool plan_ready, void* H, CombineTail* tail, hipStream_t s) {
     PlanShape shape;
-    int rc = ffn_plan_shape(MOE_BF16, N, d, f, E, local_gpu < 0 && group_expert == nullptr, &shape);
+    const bool segments = group_expert != nullptr, every_row_resident = local_gpu < 0 && !segments;
+    int rc = ffn_plan_shape(MOE_BF16, N, d, f, E, every_row_resident, segments, &shape);
     if (rc != MOE_OK) return rc;
+    const bool streams = ffn_streams(N, d, f, E, every_row_resident, segments);
     // groups that may share an expert may be merged; the row offsets of a merged bucket must fit 32 bits
-    const bool mergeable = group_expert != nullptr && (size_t)N * (d > f ? d : f) * 2 < ((size_t)1 << 32);
+    const bool mergeable = segments && (size_t)N * (d > f ? d : f) * 2 < ((size_t)1 << 32);
     if (!plan_ready) {
         int dev = 0, cpx = 0;
         if (mergeable) {
@@ -725,11 +727,11 @@ int launch_ffn_bf16(const void* a, int N, int d, int f, int E, const void* packe
             if (e != hipSuccess) return hip_fail(e, "moe_expert_ffn_segments: compute units");
         }
         rc = launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, shape,
-                             !mergeable ? 0 : (N <= kFfnSkinnyMaxRows ? 1 : 2),
+                             !mergeable ? 0 : (streams ? 1 : 2),
                              {(int)(npad13(f) / BN), d / BK, (int)(npad2(d) / BN), f / BK, cpx}, plan, s);
         if (rc != MOE_OK) return rc;
     }
-    if (N <= kFfnSkinnyMaxRows) {
+    if (streams) {
         // decode-sized batch: every weight is read once and hardly used; stream them without LDS or barriers
         const size_t s13 = npad13(f) * d, s2 = npad2(d) * f;
         float* partials = (float*)((char*)H + round_up((size_t)N * f * 2, 256));

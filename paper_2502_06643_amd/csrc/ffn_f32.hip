@@ -454,7 +454,7 @@ int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* pack
     int rc;
     if (!plan_ready) {
         PlanShape shape;
-        if ((rc = ffn_plan_shape(MOE_F32, N, d, f, E, false, &shape)) != MOE_OK) return rc;
+        if ((rc = ffn_plan_shape(MOE_F32, N, d, f, E, false, group_expert != nullptr, &shape)) != MOE_OK) return rc;
         // groups that may share an expert are merged; the row offsets of a merged bucket must fit 32 bits
         const bool mergeable = group_expert != nullptr && (size_t)N * (d > f ? d : f) < ((size_t)1 << 32);
         rc = launch_ffn_plan(counts, starts, placement, local_gpu, group_expert, n_weights, E, N, shape, mergeable, {}, plan, s);

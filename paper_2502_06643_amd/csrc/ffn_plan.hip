@@ -105,12 +105,35 @@ __global__ __launch_bounds__(kPlanThreads) void ffn_plan_kernel(const int32_t* _
     if (e == 0) plan[kPlanSegOff + n_segs] = 0;
 }
 
-int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_resident, PlanShape* shape) {
+// Which bf16 batches run the weight-streaming kernels: up to kFfnSkinnyMaxRows routes all of them (measured at that limit), and
+// up to 10 routes per expert, or 56 where the batch makes few chunks of rows, those whose experts are small.  Such a launch
+// of the tiled kernels is latency: staging and barriers of a few k tiles, with rows for a fraction of a tile, and a fix-up
+// launch.  With larger experts or more rows both are bound by the weights or by the products, and the tiled kernels' LDS
+// stages keep more of them in flight.  N counts all routes and the host does not know how many are resident, so
+// that a subset of the experts may have larger ones.  The same rule over d, f <= 4096 and E <= 64 only, where it was measured.
+// Layer, us, tiled / streaming: 8 experts, 376 routes, d 768, f 576 38 / 29, 216 routes, d 1344, f 1728 54 / 38; 16 experts, 372
+// routes, d 832, f 2240 71 / 57; 64 experts, 600 routes, d 2048, f 1408 172 / 172, 616, d 576, f 1536 70 / 64; 2 of 8 experts of
+// d 4096, f 3584, 162 to 400 routes 77 / 50; 8 of 64, d 2048, f 1408, 360 and 600 routes 56 / 32, 56 / 34.  Outside: 306 routes,
+// all of 8 experts, d 1984, f 3712 104 / 109; 600 routes, 2 of 8 experts with the most popular one, d 4096, f 3584 114 / 131; 840
+// routes, 13 of 64, d 2048, f 1408 74 / 86; all of 8, f 3584, 162 to 820 routes 150..204 / 174..271.  Inside, the worst
+// of 170 random ones: 18 of 64 experts, 243 routes, d 1472, f 1408 60 / 65, and 537 of 584 routes at one expert of 64 80 / 92.
+bool ffn_streams(int N, int d, int f, int E, bool every_row_resident, bool segments) {
+    if (N <= kFfnSkinnyMaxRows) return true;
+    const int weights = d <= 4096 && f <= 4096 ? d * f : 0;
+    if (segments || E > 64 || weights < 400000 || weights > (every_row_resident ? 6500000 : 16000000)) return false;
+    if (N > 10 * E && (N / kSkinnyRows + E > 21 || N > 56 * E)) return false;
+    // A launch of one workgroup on most compute units is neither cut nor has a second one to hide the memory's latency:
+    // 16 experts, 225 routes, d 1408, f 1664 67 / 72, 270, d 3776 133 / 140, 8 experts, 176, d 1280, f 2624 58 / 63 (221, 208 and 189 tasks).
+    const int tasks = (E + N / (2 * kSkinnyRows)) * ((f + 127) / 128);
+    return !every_row_resident || tasks <= 128 || tasks >= 250;
+}
+
+int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_resident, bool segments, PlanShape* shape) {
     *shape = {kF32TileRows, kF32SplitRows, 0, 0, 0, 0};
     if (dt == MOE_F32) return MOE_OK;
     shape->bm0 = kShortTileRows;
     shape->bm1 = kSkinnyRows;
-    if (N <= kFfnSkinnyMaxRows) return MOE_OK;
+    if (ffn_streams(N, d, f, E, every_row_resident, segments)) return MOE_OK;
     shape->bm1 = kShortTileRows;
     // Row tiles of 384 move about a sixth fewer bytes per flop than tiles of 256, but waste more on
     // ragged buckets and leave compute units idle when there are few tiles: 384 when the resident buckets

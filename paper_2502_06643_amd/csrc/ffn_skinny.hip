@@ -131,9 +131,9 @@ __device__ __forceinline__ void skinny_pass(const uint16_t* __restrict__ A, int 
                                                                         acc[m][p], 0, 0, 0);
     };
     // The next k tile's loads are in flight while a tile is multiplied; without the scheduling barriers the compiler
-    // moves them behind the products, and a conditional load in the loop makes it wait for all of them.  Mixtral shape, 5 and
-    // 8 experts touched, layer: 319 -> 311, 505 -> 491 us; 40 rows of 1 and of 2 experts 97 -> 89, 163 -> 154.  Four
-    // tiles in flight for 16 rows and three for 32 were no faster (317, 494).
+    // moves them behind the products, and a conditional load in the loop makes it wait for all of them.  Layer, Mixtral shape,
+    // medians of three processes in turn: 40 rows of 1, 2 and 4 experts 95 -> 90, 158 -> 150, 295 -> 275 us, 2 rows
+    // of 8 500 -> 495; d 1024, f 4096, 16 experts 89 -> 87.  Four tiles in flight for 16 rows and three for 32: no faster.
     if (!SPLIT || kt0 < kt1) load(kt0, 0);
     int kt = kt0;
     for (; kt + 3 <= kt1; kt += 2) {

@@ -94,6 +94,30 @@ def test_ffn_streaming_last_round(lib, T, d, f, E):
     assert fro_err(got, ref) <= TOL_BF16
 
 
+@pytest.mark.parametrize("N,d,f,E,G", [
+    (161, 640, 640, 16, 1),       # the first past the batches that always stream, smallest expert but for one
+    (383, 640, 640, 16, 1), (384, 640, 640, 16, 1),    # the last that makes few chunks and the first that makes many
+    (448, 576, 704, 8, 2), (449, 576, 704, 8, 2),      # 56 routes an expert and one more, every second expert resident
+    (640, 704, 576, 64, 4), (641, 704, 576, 64, 4),    # ten an expert
+    (200, 640, 576, 8, 1),        # experts below the smallest
+])
+def test_ffn_streaming_of_small_experts(lib, N, d, f, E, G):
+    """Both sides of the rule that gives batches of more than the decode-sized ones to the streaming kernels; half of the
+    routes go to one resident expert, in chunks of 64 rows, another one is empty."""
+    x, w1, w3, w2, idx, pl = make_problem(N + d, N, d, f, E, 1, G, "bf16")
+    idx[idx == G] = 0
+    idx[::2] = 0
+    local = -1 if G == 1 else 0
+    L = gpu_ffn(lib, x, w1, w3, w2, idx, pl, G, local, "bf16")
+    dsp = O.dispatch(x, idx, pl, G)
+    ref = O.expert_ffn_grouped(dsp["send_buf"], w1, w3, w2, dsp["expert_counts"], dsp["expert_start"], pl, local)
+    got = as_f64(to_host(L.ffn_out))
+    is_local = np.ones(N, dtype=bool) if local < 0 else (pl[idx.reshape(-1)[dsp["perm"]]] == local)
+    assert rel_err(got[is_local], ref[is_local]) <= TOL_BF16
+    assert fro_err(got[is_local], ref[is_local]) <= TOL_BF16
+    assert np.all(got[~is_local] == 7.0)
+
+
 @pytest.mark.parametrize("sizes,d,f", [
     ([1, 31, 32, 33, 0, 63, 64, 65, 129], 36, 100),   # bucket ends on every side of a tile, ragged last stage and columns
     ([1], 4, 4),                                      # the smallest problem there is

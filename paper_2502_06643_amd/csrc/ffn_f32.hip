@@ -413,8 +413,9 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
     }
 
     // accumulator v of block m: row 16 m + 4 (lane / 16) + v, column lane % 16
-    constexpr float kMax = 3.4028234e38f;
-    bool finite = true;
+    constexpr float kMax = 3.4028234e38f, kMin = 7.9e-31f;                // the second: 2^-100
+    const auto in_range = [](float v) { return fabsf(v) <= kMax && (fabsf(v) >= kMin || v == 0.f); };
+    bool exact = true;
 #pragma unroll
     for (int m = 0; m < kSplitBlocks; ++m) {
         if (m >= blocks) break;
@@ -424,13 +425,14 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
             const size_t at = buffer_row(rm, min(r, rows - 1));
             const float u = acc[m][0][v], g = acc[m][NP - 1][v];
             if (r >= rows || col >= NC) continue;
-            finite &= fabsf(u) <= kMax && fabsf(g) <= kMax;
+            exact &= in_range(u) && in_range(g);
             C[at * NC + col] = UP ? u / (1.0f + expf(-u)) * g : u;
         }
     }
-    if (__any(!finite)) {
-        // An operand that is infinite, or rounds to that, has no pieces that add up to it: the wavefront's outputs once more, in
-        // plain fp32 (a batch of nothing but NaN, d 1024, f 2816, 2000 routes: 31 ms)
+    if (__any(!exact)) {
+        // An operand that is infinite, or rounds to that, has no pieces that add up to it, and the last piece of one below 2^-110
+        // loses bits to the smallest bf16 value (2^-133), which counts where the sum is as small: the wavefront's outputs once
+        // more, in plain fp32 (a batch of nothing but NaN, d 1024, f 2816, 2000 routes: 31 ms)
 #pragma unroll 1
         for (int i = 0; i < 4 * blocks; ++i) {
             const int r = 16 * (i >> 2) + 4 * (lane >> 4) + (i & 3);

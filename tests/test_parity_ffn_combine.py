@@ -241,6 +241,22 @@ def test_ffn_f32_split_infinite_and_huge(lib):
     assert rel_err(got[~bad], ref) <= TOL_F32
 
 
+def test_ffn_f32_split_tiny(lib):
+    """Rows whose values lie near the smallest bf16 one (2e-36 in H: an absolute 2^-134 in each would be 2e-5 of it)."""
+    T, d, f = 1024, 1024, 1600
+    x, w1, w3, w2, _, _ = make_problem(6, T, d, f, 1, 1, 1, "f32")
+    tiny = np.zeros(T, dtype=bool)
+    tiny[[0, 17, 200, 1023]] = True
+    x[tiny] *= np.float32(2e-18)
+    idx, pl = np.zeros((T, 1), dtype=np.int32), np.zeros(1, dtype=np.int32)
+    got = to_host(gpu_ffn(lib, x, w1, w3, w2, idx, pl, 1, -1, "f32").ffn_out)
+    x = x.astype(np.float64)
+    a = x @ w1[0].astype(np.float64)
+    ref = (a / (1.0 + np.exp(-a)) * (x @ w3[0].astype(np.float64))) @ w2[0].astype(np.float64)
+    for rows in (tiny, ~tiny):
+        assert fro_err(got[rows], ref[rows]) <= 1e-6
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_ffn_when_this_gpu_owns_no_expert_or_no_route(lib, dtype):
     """local_gpu owns no expert (the ILP forbids it, the library tolerates it), and a GPU whose experts got no route:

@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
 }
 
 // ---- large batches: the same products on the bf16 matrix instruction -------------------------------------------------
-// An fp32 value is the sum of three bf16 values exactly (the value rounded, the remainder rounded, the rest), and the
+// An fp32 value from 2^-110 on is the sum of three bf16 values exactly (the value rounded, the remainder rounded, the rest), and the
 // bf16 instruction has sixteen times the fp32 one's rate: the six largest of the nine products of pieces, which leave out
 // 2^-25 of a product at most, come to 2.7 times it.  The instruction does not round its sums to nearest, so that a
 // chain of all of them is worse than fp32 (1.10e-6 of the result's norm where the fp32 kernel has 6.4e-7); a stage of 32 k

@@ -216,10 +216,12 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
 // end are not multiplied.
 //
 // Bound by power for the up projection (the clock falls to 1.9 GHz) and by the loads and vector work of the narrower
-// tile for the down projection.  2000 routes in 8 skewed buckets, d 1024, f 2816, layer 369 us on the fp32 kernel, 300 here; 4096
-// routes 712, 545.  A twentieth of that is the look at every operand (kSplitMin), without which these were 293 and 501 and
-// the alternatives: both products staged through LDS 345; tiles of 128 rows 309, 512; 128 columns in the down projection 305, 515;
-// one stage in flight and four wavefronts a SIMD 291, 497, but 512 routes 174 for 147.
+// tile for the down projection.  2000 routes in 8 skewed buckets, d 1024, f 2816, layer 369 us on the fp32 kernel, 302 here.  The look
+// at every operand (split_eight) is one instruction a pair; as a minimum of their magnitudes, three a pair, it made that 315.  Also
+// lost, the last four without that look (293 us, 4096 routes 501): B by buffer loads with the row in a scalar offset, which
+// saves the addresses but sends the 16 loads of a stage in one burst, 193 -> 202 us in the up projection; the remainders by
+// v_dot2_f32_bf16, exact and a sixth fewer vector instructions, 327 -> 341; both products staged through LDS 345;
+// tiles of 128 rows 309, 512; 128 columns in the down projection 305, 515; one stage in flight and four wavefronts a SIMD 291, 497, but 512 routes 174 for 147.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
@@ -243,24 +245,25 @@ static bool split_pays(int N, int d, int f, int E) {
     return (double)N * d * f >= 2.5e9 && N >= (long long)kF32SplitRows * E && tiles >= 400;
 }
 
-// 8 fp32 values -> their three bf16 pieces.  low: the least of twice the bits of every value's magnitude, less one, which
-// makes zero (whose pieces are exact) the largest there is.  (The compiler makes two minima of every three values: 319 us for 315.)
-constexpr uint32_t kSplitMin = ((127u - 110u) << 24) - 1u;      // of 2^-110, the smallest magnitude with three exact pieces
-__device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&piece)[3], uint32_t& low) {
+// 8 fp32 values -> their three bf16 pieces.  What is left of a value for the third piece has bits below that piece's last one
+// exactly if the three do not add up to the value (a magnitude below 2^-110 whose last bit lies under 2^-133): lost collects them.
+__device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&piece)[3], uint32_t& lost) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         float a = v[2 * i], b = v[2 * i + 1];
-        asm("v_min3_u32 %0, %1, %2, %0" : "+v"(low) : "v"(__float_as_uint(a) * 2u - 1u), "v"(__float_as_uint(b) * 2u - 1u));
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
+        for (int p = 0; p < 2; ++p) {
             const f32x2 pair = {a, b};
             const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2));
             piece[p][i] = h;
             a -= __uint_as_float(h << 16);
             b -= __uint_as_float(h & 0xFFFF0000u);
         }
+        piece[2][i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);     // the upper halves
+        lost |= __float_as_uint(a) | __float_as_uint(b);
     }
 }
+constexpr uint32_t kSplitLost = 0xFFFFu;
 
 template <bool UP>
 __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __restrict__ A, const float* __restrict__ packed,
@@ -333,14 +336,14 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
         }
     };
     struct Frags { u32x4 b[NP][3]; };
-    uint32_t a_low = ~0u, b_low = ~0u;                                    // of this lane's row of A and column of B
+    uint32_t a_lost = 0, b_lost = 0;                                      // of this lane's row of A and column of B
     auto convert = [&](const Raw& r, Frags& fr, int buf) {
         u32x4 pa[3];
-        split_eight(r.a, pa, a_low);
+        split_eight(r.a, pa, a_lost);
 #pragma unroll
         for (int q = 0; q < 3; ++q) smem[buf * A_UNITS + (q * kSplitBlocks + wave) * 64 + lane] = pa[q];
 #pragma unroll
-        for (int p = 0; p < NP; ++p) split_eight(r.b[p], fr.b[p], b_low);
+        for (int p = 0; p < NP; ++p) split_eight(r.b[p], fr.b[p], b_lost);
     };
 
     f32x4 acc[kSplitBlocks][NP];
@@ -402,15 +405,25 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
             multiply(f1, 1);
             __syncthreads();
         }
+        // Keeps the sums' additions in the block of the products that they read: moved into the block after the branch, two
+        // of them came too early after the last matrix instruction, which the compiler does not see on every path.
+        auto settle = [&]() {
+#pragma unroll
+            for (int m = 0; m < NA; ++m)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) asm volatile("" : "+v"(acc[m][p]));
+        };
         for (;; s += 2) {                                                 // up to four stages, the ragged one among them
             get(s + 2, even);
             if (s + 1 < n_stage) convert(odd, f1, 1);
             multiply(f0, 0);
+            settle();
             if (s + 1 >= n_stage) break;
             __syncthreads();
             get(s + 3, odd);
             if (s + 2 < n_stage) convert(even, f0, 0);
             multiply(f1, 1);
+            settle();
             if (s + 2 >= n_stage) break;
             __syncthreads();
         }
@@ -423,14 +436,14 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
         default: loop(std::integral_constant<int, 4>()); break;
     }
 
-    // which rows and columns have an operand below 2^-110: every wavefront knows its columns and a quarter of the rows
+    // which rows and columns have an operand without three exact pieces: every wavefront knows its columns and a quarter of the rows
     const auto of_16 = [](bool v) {                                       // bit i: any of lanes i, 16 + i, 32 + i, 48 + i
         const unsigned long long b = __ballot(v);
         const uint32_t h = (uint32_t)(b | b >> 32);
         return (h | h >> 16) & 0xFFFFu;
     };
     uint32_t* small = reinterpret_cast<uint32_t*>(smem);
-    const uint32_t my_rows = of_16(a_low < kSplitMin), my_cols = of_16(b_low < kSplitMin);
+    const uint32_t my_rows = of_16((a_lost & kSplitLost) != 0), my_cols = of_16((b_lost & kSplitLost) != 0);
     __syncthreads();                                                      // the pieces have been read by everyone
     small[wave] = my_rows;
     __syncthreads();
@@ -457,7 +470,7 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
     }
 
     // An operand that is infinite, or rounds to that, has no pieces that add up to it (it makes a NaN of all its sums), and
-    // those of one below 2^-110 fall short, which its partner may make any size: the outputs of such rows and columns once
+    // those of one below 2^-110 may fall short, which its partner may make any size: the outputs of such rows and columns once
     // more, and only these (a row's values are its own whatever the other rows of the tile are), on
     // the fp32 instruction.  A wavefront multiplies the blocks of 16 rows that hold some; a lane holds the four k
     // from 4 * (lane / 16) of every 16, and four partial sums share the reduction.  Layer of 2000 routes, d 1024, f 2816,

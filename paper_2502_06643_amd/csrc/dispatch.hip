@@ -42,10 +42,15 @@ static void route_chunks(long long N, int* steps, int* chunks) {
     *chunks = (int)((N + st * kIndexThreads - 1) / (st * kIndexThreads));
 }
 
-__global__ __launch_bounds__(kIndexThreads) void dispatch_count_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int steps,
+constexpr int kCountCopies = 256;        // LDS counters of a workgroup
+static_assert(kCountCopies >= MOE_MAX_EXPERTS && kCountCopies <= kIndexThreads, "a thread per counter");
+__global__ __launch_bounds__(kIndexThreads) void dispatch_count_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int steps, int copies,
                                                                        int32_t* __restrict__ block_counts) {
-    __shared__ int hist[MOE_MAX_EXPERTS];
-    for (int e = threadIdx.x; e < E; e += kIndexThreads) hist[e] = 0;
+    // few experts: several copies, picked by lane, because the lanes that hold the same expert queue on one address (8 experts,
+    // 2 M routes: 5.4 us with one copy, 4.0 with 32; 64 experts, 600 k routes: 3.1 with one, 3.4 with 4, 4.0 with 32)
+    __shared__ int hist[kCountCopies];
+    const int copy = threadIdx.x & (copies - 1);
+    if (threadIdx.x < kCountCopies) hist[threadIdx.x] = 0;
     __syncthreads();
     const long long base = (long long)blockIdx.x * kIndexThreads * steps + threadIdx.x;
     for (int i0 = 0; i0 < steps; i0 += 8) {
@@ -57,10 +62,16 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_count_kernel(const int
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if ((unsigned)e[u] < (unsigned)E) atomicAdd(&hist[e[u]], 1);
+            if ((unsigned)e[u] < (unsigned)E) atomicAdd(&hist[e[u] * copies + copy], 1);
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < E; e += kIndexThreads) block_counts[(size_t)blockIdx.x * E + e] = hist[e];
+    // adjacent lanes add up the copies of one expert (copies: a power of two up to 32)
+    const int i = threadIdx.x;
+    if (i < kCountCopies) {                              // whole wavefronts
+        int c = i < E * copies ? hist[i] : 0;
+        for (int m = 1; m < copies; m <<= 1) c += __shfl_xor(c, m, 64);
+        if (i < E * copies && (i & (copies - 1)) == 0) block_counts[(size_t)blockIdx.x * E + i / copies] = c;
+    }
 }
 
 // the tile plan of the expert FFN, by a workgroup that holds the totals and starts (all threads call this)
@@ -77,9 +88,14 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
 // Ranks the routes of one chunk.  Latency-bound: every workgroup adds up all chunks' histograms for itself
 // (at most kRankChunks x E counts, L2 hits, independent loads) instead of waiting for a scan kernel of one
 // workgroup, whose two dependent walks over up to 1024 histograms took 22 us at E = 64 (600 k routes; count, scan
-// and rank 34 us, count and rank now 12 us) and 6.6 us at E = 8 (2 M routes: 25 -> 18 us).
+// and rank 34 us, count and rank now 11.5 us) and 6.6 us at E = 8 (2 M routes: 25 -> 15.5 us).  Of the 11.4 us of the rank
+// kernel for 2 M routes the ranks are 1.5 (wave_rank; with the histograms read before them and a chain through LDS 13.4,
+// 64 experts, 600 k routes 9.0 -> 8.4), the scattered stores 1.5, the rest launch, loads and barriers.
 // The first workgroup also writes the tables; when a tile plan is wanted, it has no chunk and writes that too.
 constexpr int kRankBatch = 8;            // 64-route steps of a wavefront whose expert ids are in registers together
+constexpr int kRankHist = 16;            // histogram entries of a thread in flight together (up to 64 experts: all of them)
+// EB: bits of an expert id, for wave_rank; 0: more than 64 experts, counted in LDS
+template <int EB>
 __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits, int steps,
                                                                       const int32_t* __restrict__ block_counts,
                                                                       const int32_t* __restrict__ placement, int G,
@@ -104,7 +120,27 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
             exs[u] = (i0 + u < steps && r < N) ? topk_idx[r] : -1;
         }
     };
+    // all chunks' histograms: thread (expert, slice of the chunks), then the slices of a wavefront, then LDS.  The first
+    // entries are asked for before the routes are ranked and added up after that
+    const int EP = 1 << ebits, he = threadIdx.x & (EP - 1), slices = kIndexThreads >> ebits;
+    int first[kRankHist], all = 0, mine = 0;
+    auto fetch = [&](int b0, int (&c)[kRankHist]) {
+#pragma unroll
+        for (int u = 0; u < kRankHist; ++u) {
+            const int b = b0 + u * slices;
+            c[u] = he < E && b < chunks ? block_counts[(size_t)b * E + he] : 0;
+        }
+    };
+    auto add = [&](int b0, const int (&c)[kRankHist]) {
+#pragma unroll
+        for (int u = 0; u < kRankHist; ++u) {
+            all += c[u];
+            mine += b0 + u * slices < chunk ? c[u] : 0;
+        }
+    };
+    const int hist0 = threadIdx.x >> ebits;
     load(0);
+    fetch(hist0, first);
     index_clear(s, E);
     if ((int)threadIdx.x < E) {
         s.pl[threadIdx.x] = placement[threadIdx.x];
@@ -113,24 +149,31 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
     }
     __syncthreads();
 
-    // all chunks' histograms: thread (expert, slice of the chunks), then the slices of a wavefront, then LDS
-    const int EP = 1 << ebits, he = threadIdx.x & (EP - 1);
-    int all = 0, mine = 0;
-    if (he < E) {
-        const int slices = kIndexThreads >> ebits;
-        for (int b0 = threadIdx.x >> ebits; b0 < chunks; b0 += 16 * slices) {
-            int c[16];                                   // sixteen loads in flight (E = 64: all of them)
+    // this wavefront's own routes are counted and ranked in one go;
+    // the ranks stay in registers, those of a slice of more than kRankBatch steps wait in inv_perm
+    const bool spill = steps > kRankBatch;
+    int count = 0;
+    for (int i0 = 0;;) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int b = b0 + u * slices;
-                c[u] = b < chunks ? block_counts[(size_t)b * E + he] : 0;
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                all += c[u];
-                mine += b0 + u * slices < chunk ? c[u] : 0;
-            }
+        for (int u = 0; u < kRankBatch; ++u) {
+            loc[u] = 0;
+            if (i0 + u >= steps) continue;
+            const bool ok = (unsigned)exs[u] < (unsigned)E;
+            if constexpr (EB > 0) loc[u] = wave_rank<EB>(exs[u], ok, count);
+            else loc[u] = index_next(s.woff[wave], exs[u], ok, ebits, lower);     // a wavefront's LDS accesses execute in order
+            if (spill && ok) inv_perm[wbase + (long long)(i0 + u) * 64 + lane] = loc[u];
         }
+        i0 += kRankBatch;
+        if (i0 >= steps) break;
+        load(i0);
+    }
+    if (EB > 0 && lane < E) s.woff[wave][lane] = count;
+
+    add(hist0, first);
+    for (int b0 = hist0 + kRankHist * slices; b0 < chunks; b0 += kRankHist * slices) {
+        int more[kRankHist];
+        fetch(b0, more);
+        add(b0, more);
     }
     for (int m = EP; m < 64; m <<= 1) {
         all += __shfl_xor(all, m, 64);
@@ -139,22 +182,6 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
     if (he < E && lane < EP) {
         atomicAdd(&s.tot[he], all);
         atomicAdd(&before[he], mine);
-    }
-    // this wavefront's own routes are counted and ranked in one go (a wavefront's LDS accesses execute in order);
-    // the ranks stay in registers, those of a slice of more than kRankBatch steps wait in inv_perm
-    const bool spill = steps > kRankBatch;
-    for (int i0 = 0;;) {
-#pragma unroll
-        for (int u = 0; u < kRankBatch; ++u) {
-            loc[u] = 0;
-            if (i0 + u >= steps) continue;
-            const bool ok = (unsigned)exs[u] < (unsigned)E;
-            loc[u] = index_next(s.woff[wave], exs[u], ok, ebits, lower);
-            if (spill && ok) inv_perm[wbase + (long long)(i0 + u) * 64 + lane] = loc[u];
-        }
-        i0 += kRankBatch;
-        if (i0 >= steps) break;
-        load(i0);
     }
     __syncthreads();
     index_offsets(s, E, ebits, before);
@@ -300,12 +327,15 @@ int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T
         route_chunks(N, &steps, &chunks);
         {
             LaunchTimer timer(MOE_K_DISPATCH_COUNT, s);
-            hipLaunchKernelGGL(dispatch_count_kernel, dim3(chunks), dim3(kIndexThreads), 0, s, topk_idx, N, E, steps, block_counts);
+            int copies = E > 32 ? 1 : 32;
+            while (E * copies > kCountCopies) copies /= 2;
+            hipLaunchKernelGGL(dispatch_count_kernel, dim3(chunks), dim3(kIndexThreads), 0, s, topk_idx, N, E, steps, copies, block_counts);
             if ((rc = check_launch("moe_dispatch count launch")) != MOE_OK) return rc;
         }
         {
             LaunchTimer timer(MOE_K_DISPATCH_RANK, s);
-            hipLaunchKernelGGL(dispatch_rank_kernel, dim3(chunks + (plan_task.plan != nullptr ? 1 : 0)), dim3(kIndexThreads), 0, s, topk_idx, N, E, ebits, steps, block_counts,
+            const auto rank = ebits <= 3 ? &dispatch_rank_kernel<3> : (ebits <= 4 ? &dispatch_rank_kernel<4> : (ebits <= 6 ? &dispatch_rank_kernel<6> : &dispatch_rank_kernel<0>));
+            hipLaunchKernelGGL(rank, dim3(chunks + (plan_task.plan != nullptr ? 1 : 0)), dim3(kIndexThreads), 0, s, topk_idx, N, E, ebits, steps, block_counts,
                                placement, G, expert_counts, expert_start, gpu_counts, gpu_offsets, perm, inv_perm, plan_task);
             if ((rc = check_launch("moe_dispatch rank launch")) != MOE_OK) return rc;
         }

@@ -122,4 +122,29 @@ __device__ __forceinline__ int index_next(volatile int* my, int ex, bool ok, int
     return pos;
 }
 
+// The same without LDS, for up to 64 experts (2^EB >= E): lane e keeps the wavefront's routes of expert e so far in `count`.
+// Returns the rank of this lane's route among the wavefront's routes of its expert, and counts the 64 of this step.  A chain
+// through LDS (index_next: read, write, wait, for every 64 routes) took 3.2 of the 13.4 us of ranking 2 M routes.
+template <int EB>
+__device__ __forceinline__ int wave_rank(int ex, bool ok, int& count) {
+    static_assert(EB >= 1 && EB <= 6, "one lane per expert");
+    const int lane = threadIdx.x & 63;
+    const unsigned long long valid = __ballot(ok);
+    uint32_t mine_lo = (uint32_t)valid, mine_hi = (uint32_t)(valid >> 32);     // lanes with this lane's expert
+    uint32_t e_lo = mine_lo, e_hi = mine_hi;                                   // lanes with expert `lane`
+#pragma unroll
+    for (int b = 0; b < EB; ++b) {
+        const unsigned long long v = __ballot((ex >> b) & 1);
+        const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+        const uint32_t x = 0u - ((uint32_t)ex >> b & 1u), y = 0u - ((uint32_t)lane >> b & 1u);
+        mine_lo &= ~(lo ^ x);
+        mine_hi &= ~(hi ^ x);
+        e_lo &= ~(lo ^ y);
+        e_hi &= ~(hi ^ y);
+    }
+    const int before = __builtin_amdgcn_ds_bpermute((ex & 63) << 2, count);
+    count += __popc(e_lo) + __popc(e_hi);                                      // lanes from E on count what nobody asks for
+    return before + (int)__builtin_amdgcn_mbcnt_hi(mine_hi, __builtin_amdgcn_mbcnt_lo(mine_lo, 0u));
+}
+
 }  // namespace moe

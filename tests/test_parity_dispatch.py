@@ -103,6 +103,18 @@ def test_chunk_edges_of_the_multi_workgroup_path(lib, T, E, k, G):
     check(lib, None, idx, pl, G)
 
 
+@pytest.mark.parametrize("E", [1, 8, 9, 16, 17, 32, 33, 64, 65])
+def test_expert_counts_around_the_ranking_variants(lib, E):
+    """Ranks counted in lanes (three, four and six bits of an expert id) or in LDS, with one or several copies of the chunk's
+    histogram; one expert takes nearly everything in the second batch."""
+    rng = np.random.default_rng(E)
+    pl = rng.integers(0, 3, E).astype(np.int32)
+    check(lib, None, rng.integers(0, E, (16385 + E, 1)).astype(np.int32), pl, 3)
+    idx = np.full((300000, 1), E - 1, dtype=np.int32)
+    idx[::1000, 0] = 0
+    check(lib, None, idx, pl, 3)
+
+
 @pytest.mark.parametrize("name", ["c2", "c2b", "c3", "c4", "c5"])
 def test_config_shapes_full_size(lib, name):
     """Full-size batches with the skewed routing of the benchmark configs

@@ -49,9 +49,10 @@ __global__ __launch_bounds__(256) void placement_loads_kernel(const long long* _
 // One workgroup reads R once, all its loads independent, and adds every entry to its GPU pair's bin in LDS.
 // The G x G bins are done in stripes of g1 of at most kTrafficBins bins (one stripe up to G = 90); a small
 // table gets several copies, picked by lane, so that the lanes of a row, which mostly belong to few GPU
-// pairs, do not queue on one address.  Bound by the read of R (at most 512 KB by one compute unit) and one
-// LDS atomic per entry.  A thread per GPU pair that walked R's rows itself, load after load, took 408 us for
-// 64 experts on 8 GPUs; this takes 6 us (of which 4.5 are the launch).
+// pairs, do not queue on one address; neighbouring lanes add the copies up.  Bound by the read of R (at most
+// 512 KB by one compute unit) and one LDS atomic per entry; for the small tables of a layer by latency: launch, R, barriers.
+// A thread per GPU pair that walked R's rows itself, load after load, took 408 us for 64 experts on 8 GPUs; this
+// takes 4.4 (5.2 with up to 32 copies per bin added up by one thread and R read after the maps).
 constexpr int kTrafficThreads = 1024;
 constexpr int kTrafficBins = 8192;       // 64 KB of int64
 constexpr int kTrafficInFlight = 8;      // rows of R a thread fetches together
@@ -70,6 +71,16 @@ __global__ __launch_bounds__(kTrafficThreads) void placement_traffic_kernel(cons
     const int g2 = e2 < E_l1 ? pl_l1[e2] : -1;
     const bool col_ok = (unsigned)g2 < (unsigned)G;
     if (tid < E_l) row_gpu[tid] = pl_l[tid];
+    // the first rows are asked for before it is known who needs them: one round of memory latency
+    auto fetch = [&](int e1, long long (&r)[kTrafficInFlight]) {
+#pragma unroll
+        for (int u = 0; u < kTrafficInFlight; ++u) {
+            const int row = e1 + u * rows_per_step;
+            r[u] = row < E_l && e2 < E_l1 ? R[(size_t)row * E_l1 + e2] : 0;
+        }
+    };
+    long long first[kTrafficInFlight];
+    fetch(first_row, first);
     double local_max = 0.0;
     for (int s0 = 0; s0 < G; s0 += stripe) {
         const int rows = min(stripe, G - s0), n_bins = rows * G;
@@ -78,26 +89,27 @@ __global__ __launch_bounds__(kTrafficThreads) void placement_traffic_kernel(cons
         if (col_ok) {
             for (int e1 = first_row; e1 < E_l; e1 += rows_per_step * kTrafficInFlight) {
                 long long r[kTrafficInFlight];
-                int g[kTrafficInFlight];
+                if (e1 == first_row) {
 #pragma unroll
-                for (int u = 0; u < kTrafficInFlight; ++u) {
-                    const int row = e1 + u * rows_per_step;
-                    g[u] = row < E_l ? row_gpu[row] - s0 : -1;
-                    const bool in = (unsigned)g[u] < (unsigned)rows;
-                    if (!in) g[u] = -1;
-                    r[u] = in ? R[(size_t)row * E_l1 + e2] : 0;
+                    for (int u = 0; u < kTrafficInFlight; ++u) r[u] = first[u];
+                } else {
+                    fetch(e1, r);
                 }
 #pragma unroll
-                for (int u = 0; u < kTrafficInFlight; ++u)
-                    if (g[u] >= 0 && r[u] != 0)
-                        atomicAdd(&bins[(g[u] * G + g2) * copies + (tid & (copies - 1))], (unsigned long long)r[u]);
+                for (int u = 0; u < kTrafficInFlight; ++u) {
+                    const int row = e1 + u * rows_per_step, g = row < E_l ? row_gpu[row] - s0 : -1;
+                    if ((unsigned)g < (unsigned)rows && r[u] != 0)
+                        atomicAdd(&bins[(g * G + g2) * copies + (tid & (copies - 1))], (unsigned long long)r[u]);
+                }
             }
         }
         __syncthreads();
-        for (int p = tid; p < n_bins; p += kTrafficThreads) {
-            unsigned long long s = 0;
-            for (int c = 0; c < copies; ++c) s += bins[p * copies + ((c + tid) & (copies - 1))];
-            const size_t pair = (size_t)s0 * G + p;
+        // neighbouring lanes add up the copies of one bin (copies: a power of two up to 32); whole wavefronts
+        for (int i = tid; i < (n_bins * copies + 63) / 64 * 64; i += kTrafficThreads) {
+            unsigned long long s = i < n_bins * copies ? bins[i] : 0ull;
+            for (int m = 1; m < copies; m <<= 1) s += __shfl_xor(s, m, 64);
+            if (i >= n_bins * copies || (i & (copies - 1)) != 0) continue;
+            const size_t pair = (size_t)s0 * G + i / copies;
             C[pair] = (long long)s;
             const double cost = B ? (double)(long long)s / B[pair] : (double)(long long)s;
             local_max = cost > local_max ? cost : local_max;
@@ -134,7 +146,7 @@ int launch_placement_traffic(const int64_t* R, const int32_t* pl_l, const int32_
     while ((1 << col_bits) < E_l1) ++col_bits;
     const int stripe = G * G <= kTrafficBins ? G : kTrafficBins / G;
     int copies = 1;
-    while (copies < 32 && G * G * copies * 2 <= kTrafficBins) copies *= 2;
+    while (copies < 32 && G * G * copies * 2 <= kTrafficThreads) copies *= 2;      // a thread adds up at most one of them
     hipLaunchKernelGGL(placement_traffic_kernel, dim3(1), dim3(kTrafficThreads), 0, s, (const long long*)R, pl_l, pl_l1, E_l, E_l1, G,
                        col_bits, stripe, copies, (long long*)C, B, max_cost);
     return check_launch("moe_placement_traffic launch");

@@ -4,8 +4,8 @@
 //
 // At these sizes each of the four launches it replaces takes 4.5-10 us, nearly all of it launch latency.  Here every
 // workgroup works out the whole batch's routing redundantly - gate into LDS, the counting sort of the routes - and
-// then writes only its own share: the gate outputs, positions and send rows of its tokens.  Workgroup 0 has no tokens
-// and writes the expert and GPU tables and the tile plan.  Nothing passes between workgroups.  The first pieces
+// then writes only its own share: the gate outputs, positions and send rows of its tokens.  Workgroups 0 and 1 have no
+// tokens: the one writes the tile plan, the other the expert and GPU tables.  Nothing passes between workgroups.  The first pieces
 // of the workgroup's rows are loaded before anything else, so that they arrive while it routes.
 #include "dispatch_index.h"
 #include "ffn_plan.h"
@@ -14,6 +14,7 @@
 
 namespace moe {
 
+constexpr int kFrontTableGroups = 2;     // workgroups without tokens
 constexpr int kFrontPrefetch = 4;        // 16-byte pieces of x per thread that are loaded up front
 
 template <int L, int VPL, int KMAX>
@@ -24,9 +25,8 @@ __global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
     __shared__ int my_pos[kFrontMaxTokens * MOE_MAX_TOPK]; // positions of this workgroup's routes
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
     const int T = a.T, E = a.E, k = a.k, N = T * k;
-    const bool tables = blockIdx.x == 0;
-    const int groups = gridDim.x - 1, g = (int)blockIdx.x - 1;
-    const int t0 = tables ? T : (int)((long long)g * T / groups), t1 = tables ? T : (int)((long long)(g + 1) * T / groups);
+    const int groups = gridDim.x - kFrontTableGroups, g = (int)blockIdx.x - kFrontTableGroups;
+    const int t0 = g < 0 ? T : (int)((long long)g * T / groups), t1 = g < 0 ? T : (int)((long long)(g + 1) * T / groups);
     const int units = (t1 - t0) * a.units_per_row;
     const uint4* rows = a.x + (long long)t0 * a.units_per_row;
     uint4 pre[kFrontPrefetch];
@@ -65,6 +65,19 @@ __global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
     }
     __syncthreads();
     index_totals(s, E, a.ebits);
+    if (blockIdx.x == 0) {
+        int c = 0, st = 0;
+        if (tid < E && (a.local_gpu < 0 || s.pl[tid] == a.local_gpu)) {
+            c = s.tot[tid];
+            st = s.start[tid];
+        }
+        build_plan(plan_scratch, tid, c, st, tid, E, a.shape, a.plan);
+        return;
+    }
+    if (blockIdx.x == 1) {
+        index_write_tables(s, E, a.G, a.expert_counts, a.expert_start, a.gpu_counts, a.gpu_offsets);
+        return;
+    }
     // ... and walks it as far as this workgroup's own routes reach
     const int own0 = t0 * k, own1 = t1 * k;
     if (wbase < own1 && own0 < wend) {
@@ -97,16 +110,6 @@ __global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
         if (u < units) put(u, pre[i]);
     }
     for (int u = tid + kFrontPrefetch * kIndexThreads; u < units; u += kIndexThreads) put(u, rows[u]);
-
-    if (tables) {
-        int c = 0, st = 0;
-        if (tid < E && (a.local_gpu < 0 || s.pl[tid] == a.local_gpu)) {
-            c = s.tot[tid];
-            st = s.start[tid];
-        }
-        build_plan(plan_scratch, tid, c, st, tid, E, a.shape, a.plan);
-        index_write_tables(s, E, a.G, a.expert_counts, a.expert_start, a.gpu_counts, a.gpu_offsets);
-    }
 }
 
 // lanes per token of the gate for E experts
@@ -123,7 +126,7 @@ bool front_fits(int T, int E, int k, int row_bytes) {
     // experts, top-2, d 2048, 128 tokens 72.8 / 71.9, 256 75.2 / 79.4.
     const long long N = (long long)T * k;
     const int passes = front_lanes(E) == 1 ? kFrontMaxPasses : (k <= 2 ? 2 : 1);
-    static_assert(kFrontMaxPasses * kIndexThreads <= (kFrontGroups - 1) * kFrontMaxTokens, "a workgroup's tokens fit its tables");
+    static_assert(kFrontMaxPasses * kIndexThreads <= (kFrontGroups - kFrontTableGroups) * kFrontMaxTokens, "a workgroup's tokens fit its tables");
     return T > 0 && N <= kFrontMaxRoutes && N * row_bytes <= kFrontMaxBytes && (long long)T * front_lanes(E) <= (long long)passes * kIndexThreads;
 }
 
@@ -138,7 +141,7 @@ int launch_front(const FrontArgs& args, hipStream_t s) {
     FrontArgs a = args;
     a.ebits = 0;
     while ((1 << a.ebits) < a.E) ++a.ebits;
-    const int grid = a.T < kFrontGroups ? a.T + 1 : kFrontGroups;
+    const int grid = a.T < kFrontGroups - kFrontTableGroups ? a.T + kFrontTableGroups : kFrontGroups;
     LaunchTimer timer(MOE_K_FRONT, s);
     switch (front_lanes(a.E)) {
         case 1: launch_lanes<1, 8>(a, grid, s); break;

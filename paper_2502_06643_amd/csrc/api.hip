@@ -199,7 +199,7 @@ static int check_dispatch_args(const char* who, const void* x, moe_dtype_t dt, c
     return MOE_OK;
 }
 
-static const PlanTask kNoPlan = {nullptr, -1, {1, 1, 0, 0, 0, 0}};
+static const PlanTask kNoPlan = {nullptr, -1, {1, 1, 0, 0, 0, 0}, {}};
 
 int moe_dispatch(const void* x, moe_dtype_t dt, const int32_t* topk_idx, int T, int d, int E, int k,
                  const int32_t* placement, int G, void* send_buf, int32_t* perm, int32_t* inv_perm,
@@ -392,13 +392,14 @@ int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T,
         return fail(MOE_ERR_WORKSPACE, "%s: dispatch workspace %zu < %zu bytes", who, dispatch_workspace_bytes,
                     moe_dispatch_workspace_bytes(T, E, k));
     hipStream_t s = (hipStream_t)stream;
-    PlanTask pt = {(int32_t*)ffn_workspace, local_gpu, {}};
+    PlanTask pt = {(int32_t*)ffn_workspace, local_gpu, {}, {}};
     // The index kernels write the plan while they read their histograms: a caller who has one buffer for both workspaces
     // (the four calls need them one after the other) gets the plan from a launch of its own.
     const uintptr_t dispatch_ws = (uintptr_t)dispatch_workspace, plan_area = (uintptr_t)ffn_workspace;
     const bool shared = dispatch_ws < plan_area + kPlanBytes && plan_area < dispatch_ws + moe_dispatch_workspace_bytes(T, E, k);
     const bool fused = front_fits(T, E, k, row_bytes);
     if ((rc = ffn_plan_shape(dt, N, d, f, E, local_gpu < 0, false, &pt.shape)) != MOE_OK) return rc;
+    if (!fused && !shared && local_gpu >= 0) pt.late = ffn_late_shape(dt, N, d, f, E, T, k, G, pt.shape.cus_per_xcd);
     if (fused) {
         FrontArgs a;
         a.x = (const uint4*)x; a.logits = logits; a.T = T; a.E = E; a.k = k; a.G = G; a.local_gpu = local_gpu;
@@ -412,7 +413,7 @@ int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T,
                                   gpu_counts, gpu_offsets, (int32_t*)dispatch_workspace, T == 0 || shared ? kNoPlan : pt, s)) != MOE_OK) return rc;
         if (T == 0) return MOE_OK;
     }
-    CombineTail tail = {inv_perm, topk_idx, topk_w, placement, local_gpu, T, E, k, y, false};
+    CombineTail tail = {inv_perm, topk_idx, topk_w, placement, local_gpu, T, E, k, y, false, pt.late.T > 0 ? x : nullptr};
     if ((rc = run_ffn(send_buf, dt, N, d, f, E, packed_weights, expert_counts, expert_start, placement, local_gpu, ffn_out, ffn_workspace,
                       fused || !shared, &tail, s)) != MOE_OK) return rc;
     if (tail.done) return MOE_OK;

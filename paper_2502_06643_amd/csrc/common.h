@@ -45,8 +45,12 @@ void dispatch_geometry(long long N, int* items, int* nblocks);      // of the wo
 // launch_ffn_plan), and the column and k tiles of the down projection and the compute units per XCD (kt_down = 0: the
 // path that follows does not split it).
 struct PlanShape { int bm0, bm1, choice, nt_down, kt_down, cus_per_xcd; };
+// Rows of other GPUs' experts that the tiled bf16 projections copy on the compute units that they leave idle (ffn_late.h):
+// column and k tiles of both projections (nt_down = 0: the down projection fills the chip), bytes of a row, tokens.
+struct LateShape { int nt_up, kt_up, nt_down, kt_down, row_bytes, T, k; };
 // The tile plan as a by-product of the dispatch's index kernels, which hold all it needs; plan == NULL: none wanted.
-struct PlanTask { int32_t* plan; int local_gpu; PlanShape shape; };
+// late.T = 0: every row is copied before the FFN.
+struct PlanTask { int32_t* plan; int local_gpu; PlanShape shape; LateShape late; };
 int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T, int E, int k,
                     const int32_t* placement, int G, void* send_buf, int32_t* perm, int32_t* inv_perm,
                     int32_t* expert_counts, int32_t* expert_start, int32_t* gpu_counts,
@@ -86,6 +90,8 @@ int launch_pack_f32(const float* w1, const float* w3, const float* w2, int E, in
 int launch_pack_bf16(const void* w1, const void* w3, const void* w2, int E, int d, int f, void* packed, hipStream_t s);
 bool ffn_streams(int N, int d, int f, int E, bool segments);
 int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_resident, bool segments, PlanShape* shape);
+// T = 0: no rows are left to the projections
+LateShape ffn_late_shape(moe_dtype_t dt, int N, int d, int f, int E, int T, int k, int G, int cus_per_xcd);
 int ffn_bf16_device_setup(int* cus_per_xcd);      // of the tiled bf16 kernels, done by the first call on a device
 // E row groups (counts/starts); group g uses the weights of expert group_expert[g] of n_weights
 // (g itself when group_expert is NULL).  plan_ready: the plan has been built already (ffn_plan_shape's way)
@@ -102,6 +108,7 @@ constexpr int kFfnSkinnyMaxRows = 160;
 struct CombineTail {
     const int32_t* inv_perm; const int32_t* topk_idx; const float* topk_w; const int32_t* placement;
     int local_gpu, T, E, k; void* y; bool done;
+    const void* late_x;          // the tokens' rows, when the plan may leave some of them to the projections; NULL: it does not
 };
 int launch_ffn_skinny(const void* a, int N, int d, int f, int E, const void* packed, size_t s13, size_t expert_stride,
                       const int32_t* plan, void* H, float* partial, size_t scratch_bytes, void* out, CombineTail* tail, hipStream_t s);

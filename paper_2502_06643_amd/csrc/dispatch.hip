@@ -17,7 +17,7 @@
 // is a pure function of the route id.
 #include <mutex>
 #include "dispatch_index.h"
-#include "ffn_plan.h"
+#include "ffn_late.h"
 
 namespace moe {
 
@@ -82,7 +82,14 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
         c = s.tot[e];
         st = s.start[e];
     }
+    // this GPU's range of the sorted rows begins where the first of its experts with rows does; the totals are in the scratch
+    __shared__ int own_begin;
+    if (e == 0) own_begin = 0x7FFFFFFF;
     build_plan(scratch, e, c, st, e, E, pt.shape, pt.plan);
+    if (pt.late.T == 0) return;
+    if (c > 0) atomicMin(&own_begin, st);                // build_plan has barriers
+    __syncthreads();
+    if (e == 0) plan_late(pt.late, scratch.tiles, own_begin, scratch.total_rows, pt.shape.cus_per_xcd, pt.plan);
 }
 
 // Ranks the routes of one chunk.  Latency-bound: every workgroup adds up all chunks' histograms for itself
@@ -258,15 +265,25 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_index_kernel(const int
     if (pt.plan != nullptr) plan_from_tables(s, plan_scratch, E, pt);
 }
 
-// One thread per 16-byte unit of a source row: read once, write k times.
+// One thread per 16-byte unit of a source row: read once, write k times.  LATE: of the first tokens only the rows of this
+// GPU's experts; the projections copy the others (ffn_late.h).
+template <bool LATE>
 __global__ __launch_bounds__(256) void dispatch_rows_kernel(const uint4* __restrict__ x, long long total_units, int units_per_row,
                                                             int k, int N, const int32_t* __restrict__ inv_perm,
-                                                            uint4* __restrict__ send_buf) {
+                                                            uint4* __restrict__ send_buf, const int32_t* __restrict__ plan) {
     const long long u = (long long)blockIdx.x * 256 + threadIdx.x;
     if (u >= total_units) return;
     const long long t = u / units_per_row;
     const int c = (int)(u - t * units_per_row);
     const uint4 v = x[u];
+    if (LATE && t < plan[kPlanLateUp] + plan[kPlanLateDown]) {
+        const int own0 = plan[kPlanOwnBegin], own1 = plan[kPlanOwnEnd];
+        for (int j = 0; j < k; ++j) {
+            const int p = inv_perm[t * k + j];
+            if (p >= own0 && p < own1) send_buf[(long long)p * units_per_row + c] = v;
+        }
+        return;
+    }
     for (int j = 0; j < k; ++j) {
         const int p = inv_perm[t * k + j];
         if ((unsigned)p < (unsigned)N) send_buf[(long long)p * units_per_row + c] = v;
@@ -346,8 +363,9 @@ int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T
         const long long grid = (total_units + 255) / 256;
         if (grid > 0x7FFFFFFFll) return fail(MOE_ERR_UNSUPPORTED, "moe_dispatch: T*d too large for one launch");
         LaunchTimer timer(MOE_K_DISPATCH_ROWS, s);
-        hipLaunchKernelGGL(dispatch_rows_kernel, dim3((unsigned)grid), dim3(256), 0, s, (const uint4*)x, total_units,
-                           units_per_row, k, N, inv_perm, (uint4*)send_buf);
+        const auto rows = plan_task.late.T > 0 ? &dispatch_rows_kernel<true> : &dispatch_rows_kernel<false>;
+        hipLaunchKernelGGL(rows, dim3((unsigned)grid), dim3(256), 0, s, (const uint4*)x, total_units,
+                           units_per_row, k, N, inv_perm, (uint4*)send_buf, plan_task.plan);
         if ((rc = check_launch("moe_dispatch rows launch")) != MOE_OK) return rc;
     }
     return MOE_OK;

@@ -67,6 +67,7 @@
 // transposed through a per-wavefront LDS staging tile and written with
 // 16-byte stores that cover whole 128-byte lines.
 #include "ffn_tiles.h"
+#include "ffn_late.h"
 #include <mutex>
 
 namespace moe {
@@ -496,7 +497,7 @@ constexpr int smem_bytes() {
 
 // one workgroup's tile (or k part of a tile) on row tiles of 128 * FM rows
 template <bool UP, bool SPLIT, int FM, bool MERGED>
-__device__ __forceinline__ void ffn_tile(uint16_t* smem, const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
+__device__ __forceinline__ bool ffn_tile(uint16_t* smem, const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
                                          size_t expert_stride, int K, int npad, uint16_t* __restrict__ C, int ldc,
                                          const int32_t* __restrict__ plan, float* __restrict__ partials, int cus_per_xcd,
                                          int row_chunk) {
@@ -504,7 +505,7 @@ __device__ __forceinline__ void ffn_tile(uint16_t* smem, const uint16_t* __restr
     const int32_t* prefix = plan + (FM == 3 ? kPlanTiles0 : kPlanTiles1);
     const int NT = npad / BN, KT = K / BK;
     WorkItem w;
-    if (!workgroup_item(plan, prefix, NT, KT, BM, blockIdx.x, cus_per_xcd, row_chunk, SPLIT, w)) return;
+    if (!workgroup_item(plan, prefix, NT, KT, BM, blockIdx.x, cus_per_xcd, row_chunk, SPLIT, w)) return false;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -543,24 +544,28 @@ __device__ __forceinline__ void ffn_tile(uint16_t* smem, const uint16_t* __restr
                 for (int b = 0; b < FN; ++b) dst[(size_t)(a * FN + b) * kThreads] = acc[a][b];
             }
         }
-        return;
+        return true;
     }
     __syncthreads();                                  // the last tile's fragments have been read by everyone
     epilogue<UP, FM>(acc, smem, C, ldc, w, rm, wave, lane, nfrag);
+    return true;
 }
 
 // One launch serves both tile heights: the plan's header says which one this call uses (the host's
 // choice, or the plan kernel's own when only the device knows the bucket sizes), and every workgroup
 // takes that branch.  Registers and LDS are those of the larger tile either way; one workgroup fits a
 // compute unit with both.  MERGED: the plan may have merged the segments of an expert (then it chose the short tiles).
-template <bool UP, bool SPLIT, bool MERGED>
+template <bool UP, bool SPLIT, bool MERGED, bool LATE = false>
 __global__ __launch_bounds__(kThreads) void ffn_bf16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
                                                             size_t expert_stride, int K, int npad, uint16_t* __restrict__ C,
                                                             int ldc, const int32_t* __restrict__ plan, float* __restrict__ partials,
-                                                            int cus_per_xcd, int row_chunk) {
+                                                            int cus_per_xcd, int row_chunk, LateRows late) {
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    if (plan[3] == 0) ffn_tile<UP, SPLIT, 3, false>(smem, A, Wp, expert_stride, K, npad, C, ldc, plan, partials, cus_per_xcd, row_chunk);
-    else ffn_tile<UP, SPLIT, 2, MERGED>(smem, A, Wp, expert_stride, K, npad, C, ldc, plan, partials, cus_per_xcd, row_chunk);
+    const bool tall = plan[3] == 0;
+    bool tile;
+    if (tall) tile = ffn_tile<UP, SPLIT, 3, false>(smem, A, Wp, expert_stride, K, npad, C, ldc, plan, partials, cus_per_xcd, row_chunk);
+    else tile = ffn_tile<UP, SPLIT, 2, MERGED>(smem, A, Wp, expert_stride, K, npad, C, ldc, plan, partials, cus_per_xcd, row_chunk);
+    if (LATE && !tile) copy_late_rows(late, plan, UP, tall ? plan[1] : plan[2], npad / BN, cus_per_xcd, blockIdx.x);
 }
 
 // Adds the k parts of the split tiles in part order and writes the tiles; a workgroup handles one fragment row (16
@@ -640,9 +645,13 @@ struct FfnCall {
     const void* a; int N, d, f, E; const void* packed; void* out; int32_t* plan; void* H; hipStream_t s;
     int cpx, chunk_up, chunk_down;
     bool merge;
+    LateRows late;                // late.x == NULL: no rows to copy
     size_t s13, stride;
     float* partials;
-    long long grid_for(size_t npad, int bm, bool split) const { return ffn_grid(N, E, (long long)(npad / BN), bm, split, cpx); }
+    long long grid_for(size_t npad, int bm, bool split) const { 
+        const long long tiles = ffn_grid(N, E, (long long)(npad / BN), bm, split, cpx);
+        return late.x != nullptr && tiles < kXcds * cpx ? kXcds * cpx : tiles;          // a workgroup per compute unit, with or without a tile
+    }
 };
 
 template <bool UP>
@@ -674,7 +683,9 @@ int ffn_bf16_device_setup(int* cus_per_xcd) {
         if ((r = set_smem(&ffn_bf16_kernel<true, false, false>, launch_smem<true>())) != MOE_OK) return r;
         if ((r = set_smem(&ffn_bf16_kernel<false, true, false>, launch_smem<false>())) != MOE_OK) return r;
         if ((r = set_smem(&ffn_bf16_kernel<true, false, true>, launch_smem<true>())) != MOE_OK) return r;
+        if ((r = set_smem(&ffn_bf16_kernel<true, false, false, true>, launch_smem<true>())) != MOE_OK) return r;
         if ((r = set_smem(&ffn_bf16_kernel<false, true, true>, launch_smem<false>())) != MOE_OK) return r;
+        if ((r = set_smem(&ffn_bf16_kernel<false, true, false, true>, launch_smem<false>())) != MOE_OK) return r;
         e = compute_units_per_xcd(dev, &st.cpx);
         if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
         st.done = true;
@@ -687,10 +698,11 @@ int ffn_bf16_device_setup(int* cus_per_xcd) {
 static int run_up(const FfnCall& c, int bm) {
     const long long grid = c.grid_for(npad13(c.f), bm, false);
     if (grid > 0x7FFFFFFFll) return fail(MOE_ERR_UNSUPPORTED, "moe_expert_ffn_grouped: too many tiles for one launch");
-    const auto kernel = c.merge ? &ffn_bf16_kernel<true, false, true> : &ffn_bf16_kernel<true, false, false>;
+    const bool late = c.late.x != nullptr;
+    const auto kernel = c.merge ? &ffn_bf16_kernel<true, false, true> : (late ? &ffn_bf16_kernel<true, false, false, true> : &ffn_bf16_kernel<true, false, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreads), (launch_smem<true>()), c.s,
                        (const uint16_t*)c.a, (const uint16_t*)c.packed, c.stride, c.d, (int)npad13(c.f), (uint16_t*)c.H, c.f, c.plan,
-                       c.partials, c.cpx, c.chunk_up);
+                       c.partials, c.cpx, c.chunk_up, c.late);
     return check_launch("moe_expert_ffn_grouped up launch");
 }
 
@@ -698,10 +710,11 @@ static int run_down(const FfnCall& c, int bm, int fm_max) {
     const long long grid = c.grid_for(npad2(c.d), bm, true);
     if (grid > 0x7FFFFFFFll) return fail(MOE_ERR_UNSUPPORTED, "moe_expert_ffn_grouped: too many tiles for one launch");
     const uint16_t* W2 = (const uint16_t*)c.packed + c.s13;
-    const auto kernel = c.merge ? &ffn_bf16_kernel<false, true, true> : &ffn_bf16_kernel<false, true, false>;
+    const bool late = c.late.x != nullptr && !split_can_pay(c.f / BK);
+    const auto kernel = c.merge ? &ffn_bf16_kernel<false, true, true> : (late ? &ffn_bf16_kernel<false, true, false, true> : &ffn_bf16_kernel<false, true, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreads), (launch_smem<false>()), c.s,
                        (const uint16_t*)c.H, W2, c.stride, c.f, (int)npad2(c.d), (uint16_t*)c.out, c.d, c.plan, c.partials, c.cpx,
-                       c.chunk_down);
+                       c.chunk_down, c.late);
     int rc = check_launch("moe_expert_ffn_grouped down launch");
     if (rc != MOE_OK || !split_can_pay(c.f / BK)) return rc;
     hipLaunchKernelGGL(ffn_bf16_fixup_kernel, dim3(kXcds * c.cpx * fm_max * 2), dim3(kThreads), 0, c.s, c.f,
@@ -742,6 +755,8 @@ int launch_ffn_bf16(const void* a, int N, int d, int f, int E, const void* packe
     c.a = a; c.N = N; c.d = d; c.f = f; c.E = E; c.packed = packed; c.out = out; c.plan = plan; c.H = H; c.s = s;
     c.cpx = cpx;
     c.merge = mergeable;
+    c.late = {};
+    if (tail != nullptr && tail->late_x != nullptr) c.late = {(const uint4*)tail->late_x, (uint4*)const_cast<void*>(a), tail->inv_perm, tail->k, N, d / 8};
     c.chunk_up = row_chunk_for((size_t)N * d * 2);
     c.chunk_down = row_chunk_for((size_t)N * f * 2);
     c.s13 = npad13(f) * d;

@@ -1,0 +1,80 @@
+// Send rows copied during the expert FFN.  In a layer call on one GPU of several most rows of the send buffer go to other
+// GPUs (paper Section 2.2, the first all-to-all): nothing of this call reads them.  A layer of many small experts has
+// fewer output tiles here than the chip has compute units, so those rows are left to the workgroups that would be
+// idle in the two projections, as many as these copy in the time of a tile.
+//
+// 8192 tokens, 64 experts, top-6, 8 of them here, d 2048, f 1408: row copy 39 -> 13 us, projections 50 + 37 -> 59 + 50 (the copies
+// take bandwidth from the tiles), layer 151.9 -> 141.7.  Stores that stay out of the caches: 142 for 145 without.  80 KB a k tile
+// 148, 20 KB 150 (both without), four k tiles less for the copies to get under way: 7312 tokens, d 1536, f 704 123 -> 127.
+#pragma once
+#include "ffn_plan.h"
+
+namespace moe {
+
+// What a copying workgroup moves in the time of a k tile (1.3 us), bytes read and written.
+constexpr int kLateBytesPerKTile = 40 << 10;
+
+// Per XCD: compute units without a tile in a launch of MT x NT tiles that runs in one round; 0 when it takes longer.
+__host__ __device__ __forceinline__ int late_copiers(int MT, int NT, int cus_per_xcd) {
+    const XcdShare sh = xcd_share(MT, NT, 0, 0, cus_per_xcd, false);          // the first XCD has the largest share
+    return sh.full < cus_per_xcd ? cus_per_xcd - sh.full : 0;
+}
+
+// How many tokens' rows the two projections take: what fits beside their tiles.  foreign: routes of other GPUs.
+__host__ __device__ __forceinline__ void late_tokens(const LateShape& l, int MT, int foreign, int cus_per_xcd, int& up, int& down) {
+    up = down = 0;
+    if (l.T <= 0 || foreign <= 0) return;
+    const float token_bytes = (float)l.row_bytes * (1.0f + (float)foreign / (float)l.T);
+    const auto fit = [&](int NT, int KT, int left) {
+        const float n = (float)kXcds * (float)late_copiers(MT, NT, cus_per_xcd) * (float)KT * (float)kLateBytesPerKTile / token_bytes;
+        return n < (float)left ? (int)n : left;
+    };
+    up = fit(l.nt_up, l.kt_up, l.T);
+    if (l.nt_down > 0) down = fit(l.nt_down, l.kt_down, l.T - up);
+}
+
+// the plan's header entries; MT: row tiles of the height in use, own_rows and own_begin: this GPU's range of the sorted rows
+__device__ __forceinline__ void plan_late(const LateShape& l, int MT, int own_begin, int own_rows, int cus_per_xcd, int32_t* __restrict__ plan) {
+    int up, down;
+    late_tokens(l, MT, l.T * l.k - own_rows, cus_per_xcd, up, down);
+    plan[kPlanLateUp] = up;
+    plan[kPlanLateDown] = down;
+    plan[kPlanOwnBegin] = own_rows > 0 ? own_begin : 0;
+    plan[kPlanOwnEnd] = own_rows > 0 ? own_begin + own_rows : 0;
+}
+
+struct LateRows { const uint4* x; uint4* send; const int32_t* inv_perm; int k, N, units; };
+
+typedef __attribute__((ext_vector_type(4))) uint32_t late_u32x4;
+
+// Workgroup `block` of the up or the down projection, which has no tile: the rows of that launch's tokens outside this GPU's range.
+// A wavefront takes a token at a time: its row once, its positions one a lane.
+__device__ __forceinline__ void copy_late_rows(const LateRows& l, const int32_t* __restrict__ plan, bool up, int MT, int NT, int cus_per_xcd,
+                                               unsigned block) {
+    const int of_up = plan[kPlanLateUp], begin = up ? 0 : of_up, end = up ? of_up : of_up + plan[kPlanLateDown];
+    if (begin == end) return;
+    const int x = (int)(block % kXcds), idle = (int)(block / kXcds) - xcd_share(MT, NT, x, 0, cus_per_xcd, false).full;
+    const int copiers = late_copiers(MT, NT, cus_per_xcd);
+    if (idle < 0 || idle >= copiers) return;
+    const int own0 = plan[kPlanOwnBegin], own1 = plan[kPlanOwnEnd];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    for (int t = begin + (idle * kXcds + x) * waves + wave; t < end; t += copiers * kXcds * waves) {
+        const int at = lane < l.k ? l.inv_perm[(long long)t * l.k + lane] : -1;
+        const late_u32x4* row = reinterpret_cast<const late_u32x4*>(l.x) + (long long)t * l.units;
+        for (int c0 = lane; c0 - lane < l.units; c0 += 4 * 64) {
+            late_u32x4 v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = c0 + 64 * i < l.units ? row[c0 + 64 * i] : late_u32x4{0u, 0u, 0u, 0u};
+            for (int j = 0; j < l.k; ++j) {
+                const int p = __builtin_amdgcn_readlane(at, j);
+                if ((unsigned)p >= (unsigned)l.N || (p >= own0 && p < own1)) continue;
+                late_u32x4* out = reinterpret_cast<late_u32x4*>(l.send) + (long long)p * l.units;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (c0 + 64 * i < l.units) __builtin_nontemporal_store(v[i], out + c0 + 64 * i);      // nothing here reads them
+            }
+        }
+    }
+}
+
+}  // namespace moe

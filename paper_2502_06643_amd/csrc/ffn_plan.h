@@ -31,7 +31,10 @@ static_assert(kPlanInts * sizeof(int32_t) <= kPlanBytes, "plan area too small");
 //         [5], [6] k parts of the larger and of the small row tiles when the down projection runs in one round and is
 //             cut by cost (RoundSplit in ffn_tiles.h); [5] = 0: it is not
 //         [7] 1: the segments of one expert are merged into one bucket
+//         [8], [9] tokens whose rows for other GPUs the up and the down projection copy (the first tokens, those after
+//             them), [10], [11] this GPU's range of the sorted rows (ffn_late.h; only in a layer call that may have such rows)
 constexpr int kPlanSmallTiles = 4, kPlanBigParts = 5, kPlanSmallParts = 6, kPlanMerged = 7;
+constexpr int kPlanLateUp = 8, kPlanLateDown = 9, kPlanOwnBegin = 10, kPlanOwnEnd = 11;
 
 // Merged buckets.  On the receive side an expert's rows arrive as one segment per source GPU.  As buckets of their own
 // they stream the expert's weights once per segment and end in a ragged tile each, so segments of one expert form one
@@ -122,6 +125,7 @@ struct PlanScratch {
     int cnt[MOE_MAX_EXPERTS], tiles0[MOE_MAX_EXPERTS], tiles1[MOE_MAX_EXPERTS], segs[MOE_MAX_EXPERTS];
     int rank[MOE_MAX_EXPERTS], rows[MOE_MAX_EXPERTS], pre0[MOE_MAX_EXPERTS], pre1[MOE_MAX_EXPERTS], pre_segs[MOE_MAX_EXPERTS];
     int n, n_small, total1;
+    int tiles, total_rows;                               // of the tile height in use, of all listed groups
 };
 
 // The cut of a one-round launch, for the plan's header; called by one wavefront, a lane per candidate.
@@ -166,7 +170,7 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
         s.segs[e] = n_segs;
         s.rank[e] = s.rows[e] = s.pre0[e] = s.pre1[e] = s.pre_segs[e] = 0;
     }
-    if (e == 0) s.n = s.n_small = s.total1 = 0;
+    if (e == 0) s.n = s.n_small = s.total1 = s.tiles = s.total_rows = 0;
     __syncthreads();
     if (c > 0) {
         atomicAdd(&s.n, 1);
@@ -221,7 +225,10 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
             plan[0] = n;
             plan[1] = t0;
             plan[2] = t1;
-            plan[3] = shape.choice >= 0 ? shape.choice : ((long long)s.rows[e] + c >= (long long)kLargeBucketRows * n ? 0 : 1);
+            const int choice = shape.choice >= 0 ? shape.choice : ((long long)s.rows[e] + c >= (long long)kLargeBucketRows * n ? 0 : 1);
+            plan[3] = choice;
+            s.tiles = choice == 0 ? t0 : t1;
+            s.total_rows = s.rows[e] + c;
             plan[kPlanSmallTiles] = 1 + n_small;
             plan[kPlanMerged] = merged;
             plan[kPlanTiles0 + n] = t0;

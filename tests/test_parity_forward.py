@@ -63,6 +63,23 @@ def test_one_buffer_for_both_workspaces(lib, T, E, k):
     check_forward("bf16", T, 64, 64, E, k, 4, 1, one_workspace=True)
 
 
+@pytest.mark.parametrize("T,d,f,E,k,G,local,up,down", [
+    (2700, 2048, 1408, 64, 6, 8, 0, True, False),       # one workgroup's index kernel; the up projection takes all
+    (8192, 2048, 1408, 64, 6, 8, 5, True, True),        # rank kernel; both projections take some
+    (1501, 1344, 1024, 16, 4, 4, 1, True, False),       # 168 pieces a row
+    (1500, 4096, 512, 32, 2, 8, 3, True, False),        # 512 pieces a row
+    (1600, 1280, 4096, 64, 2, 16, 2, True, False),      # the down projection's tiles are cut along k
+    (700, 1280, 64, 16, 16, 200, 199, True, False),     # no expert here, 16 routes per token
+    (30000, 1280, 64, 32, 2, 8, 0, True, True),         # more than both can take
+    (4000, 1280, 4096, 16, 2, 2, 1, False, False),      # more tiles than compute units
+    (3000, 1216, 512, 16, 4, 4, 0, None, None),         # reductions too short to ask
+])
+def test_rows_copied_beside_the_projections(lib, T, d, f, E, k, G, local, up, down):
+    plan = check_forward("bf16", T, d, f, E, k, G, local).ffn_ws[:64].view(torch.int32).cpu()
+    if up is not None:                             # what the plan leaves to the two projections
+        assert (int(plan[8]) > 0) == up and (int(plan[9]) > 0) == down and int(plan[8]) + int(plan[9]) <= T
+
+
 def check_forward(dtype, T, d, f, E, k, G, local, one_workspace=False):
     rng = np.random.default_rng(T + E)
     pl = rng.integers(0, G, E).astype(np.int32)
@@ -89,6 +106,7 @@ def check_forward(dtype, T, d, f, E, k, G, local, one_workspace=False):
         for n in OUTPUTS:
             a, b = (getattr(L, n).reshape(-1).view(torch.uint8) for L in (got, want))
             assert torch.equal(a, b), f"call {rep}: {n}"
+    return got
 
 
 def test_forward_reports_bad_arguments(lib):

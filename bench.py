@@ -322,10 +322,11 @@ def main():
         alg_bytes = {
             "gate": T * (4 * E + 8 * k),
             "front": T * (4 * E + 8 * k) + T * d * elt + N * d * elt + 8 * N,
-            "dispatch_rows": T * d * elt + N * d * elt + 4 * N,
             "combine": n_local * d * elt + T * d * elt + 12 * N,
             "transition": 8 * N,
         }
+        if cfg.G == 1 or k < 3:                     # else some of the rows may have been copied beside the projections
+            alg_bytes["dispatch_rows"] = T * d * elt + N * d * elt + 4 * N
         alg_flops = {"ffn_up": 4.0 * d * f * n_local, "ffn_down": 2.0 * d * f * n_local}
         # the grouped GEMMs also stream every touched resident expert's weights once: the second bound, which is the
         # binding one when buckets are small (decode-sized batches, the many-expert layer)

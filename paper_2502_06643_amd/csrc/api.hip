@@ -399,7 +399,13 @@ int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T,
     const bool shared = dispatch_ws < plan_area + kPlanBytes && plan_area < dispatch_ws + moe_dispatch_workspace_bytes(T, E, k);
     const bool fused = front_fits(T, E, k, row_bytes);
     if ((rc = ffn_plan_shape(dt, N, d, f, E, local_gpu < 0, false, &pt.shape)) != MOE_OK) return rc;
-    if (!fused && !shared && local_gpu >= 0) pt.late = ffn_late_shape(dt, N, d, f, E, T, k, G, pt.shape.cus_per_xcd);
+    // Rows that the projections copy are read while these write H and ffn_out: a caller who has the same memory for the inputs
+    // gets every row copied first.
+    const auto apart = [&](const void* p, size_t n) {
+        const uintptr_t a = (uintptr_t)p, out = (uintptr_t)ffn_out, ws = (uintptr_t)ffn_workspace;
+        return (a + n <= out || out + (size_t)N * row_bytes <= a) && (a + n <= ws || ws + ffn_workspace_bytes <= a);
+    };
+    if (!fused && !shared && local_gpu >= 0 && apart(x, (size_t)T * row_bytes) && apart(inv_perm, (size_t)N * 4)) pt.late = ffn_late_shape(dt, N, d, f, E, T, k, G, pt.shape.cus_per_xcd);
     if (fused) {
         FrontArgs a;
         a.x = (const uint4*)x; a.logits = logits; a.T = T; a.E = E; a.k = k; a.G = G; a.local_gpu = local_gpu;

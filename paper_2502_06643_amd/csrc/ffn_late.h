@@ -4,7 +4,7 @@
 // idle in the two projections, as many as these copy in the time of a tile.
 //
 // 8192 tokens, 64 experts, top-6, 8 of them here, d 2048, f 1408: row copy 39 -> 13 us, projections 50 + 37 -> 59 + 50 (the copies
-// take bandwidth from the tiles), layer 151.9 -> 141.7.  Stores that stay out of the caches: 142 for 145 without.  80 KB a k tile
+// take bandwidth from the tiles), layer 151.3 -> 142 to 144.  Stores that stay out of the caches: 142 for 145 without.  80 KB a k tile
 // 148, 20 KB 150 (both without), four k tiles less for the copies to get under way: 7312 tokens, d 1536, f 704 123 -> 127.
 #pragma once
 #include "ffn_plan.h"

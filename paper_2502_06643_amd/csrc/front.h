@@ -5,10 +5,10 @@
 namespace moe {
 
 constexpr int kFrontMaxRoutes = 12288;   // routes a workgroup sorts by itself (their expert ids fill 24 KB of LDS)
-constexpr int kFrontGroups = 256;        // workgroups: one per compute unit, all but the first with at least one token
+constexpr int kFrontGroups = 256;        // workgroups: one per compute unit, all but the first two with at least one token
 constexpr int kFrontMaxPasses = 6;       // passes of the gate, of one token per thread
 constexpr long long kFrontMaxBytes = 72ll << 20; // of the send rows
-constexpr int kFrontMaxTokens = 25;      // tokens a workgroup may own (front_fits keeps T below kFrontGroups - 1 times that)
+constexpr int kFrontMaxTokens = 25;      // tokens a workgroup may own (front_fits keeps T within what the others own)
 
 struct FrontArgs {
     const uint4* x;                      // [T] rows of units_per_row 16-byte pieces

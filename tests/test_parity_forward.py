@@ -67,17 +67,37 @@ def test_one_buffer_for_both_workspaces(lib, T, E, k):
     (2700, 2048, 1408, 64, 6, 8, 0, True, False),       # one workgroup's index kernel; the up projection takes all
     (8192, 2048, 1408, 64, 6, 8, 5, True, True),        # rank kernel; both projections take some
     (1501, 1344, 1024, 16, 4, 4, 1, True, False),       # 168 pieces a row
-    (1500, 4096, 512, 32, 2, 8, 3, True, False),        # 512 pieces a row
-    (1600, 1280, 4096, 64, 2, 16, 2, True, False),      # the down projection's tiles are cut along k
+    (1500, 4096, 512, 32, 3, 8, 3, True, False),        # 512 pieces a row
+    (1600, 1280, 4096, 64, 4, 16, 2, True, False),      # the down projection's tiles are cut along k
     (700, 1280, 64, 16, 16, 200, 199, True, False),     # no expert here, 16 routes per token
-    (30000, 1280, 64, 32, 2, 8, 0, True, True),         # more than both can take
-    (4000, 1280, 4096, 16, 2, 2, 1, False, False),      # more tiles than compute units
+    (30000, 1280, 64, 32, 4, 8, 0, True, False),        # more than it can take, and no room beside the down projection
+    (2300, 1280, 4096, 16, 3, 2, 0, False, False),      # more tiles than compute units
     (3000, 1216, 512, 16, 4, 4, 0, None, None),         # reductions too short to ask
+    (5000, 2048, 512, 16, 2, 4, 0, None, None),         # two routes a token
 ])
 def test_rows_copied_beside_the_projections(lib, T, d, f, E, k, G, local, up, down):
     plan = check_forward("bf16", T, d, f, E, k, G, local).ffn_ws[:64].view(torch.int32).cpu()
     if up is not None:                             # what the plan leaves to the two projections
         assert (int(plan[8]) > 0) == up and (int(plan[9]) > 0) == down and int(plan[8]) + int(plan[9]) <= T
+
+
+def test_outputs_in_the_memory_of_the_inputs(lib):
+    """ffn_out begins where x does: x has been read when it is written, whoever copies the rows."""
+    T, d, f, E, k, G, local = 8192, 2048, 1408, 64, 6, 8, 5
+    rng = np.random.default_rng(T + E)
+    pl = rng.integers(0, G, E).astype(np.int32)
+    x = to_device(synth.normal(T, 0, (T, d), 1.0, "bf16"))
+    lg = torch.from_numpy(rng.standard_normal((T, E)).astype(np.float32)).cuda()
+    w = [to_device(synth.normal(T, i, s, s[1] ** -0.5, "bf16")) for i, s in ((2, (E, d, f)), (3, (E, d, f)), (4, (E, f, d)))]
+    got, want = (MoELayer(T, d, f, E, k, G, local, "bf16") for _ in range(2))
+    for L in (got, want):
+        L.set_placement(pl)
+        L.set_weights(*w)
+    want.forward(x, lg)
+    got.ffn_out[:T].copy_(x)
+    got.forward(got.ffn_out[:T], lg)
+    torch.cuda.synchronize()
+    assert torch.equal(got.send_buf, want.send_buf) and torch.equal(got.y, want.y)
 
 
 def check_forward(dtype, T, d, f, E, k, G, local, one_workspace=False):

@@ -95,8 +95,8 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
 // Ranks the routes of one chunk.  Latency-bound: every workgroup adds up all chunks' histograms for itself
 // (at most kRankChunks x E counts, L2 hits, independent loads) instead of waiting for a scan kernel of one
 // workgroup, whose two dependent walks over up to 1024 histograms took 22 us at E = 64 (600 k routes; count, scan
-// and rank 34 us, count and rank now 11.5 us) and 6.6 us at E = 8 (2 M routes: 25 -> 15.5 us).  Of the 11.4 us of the rank
-// kernel for 2 M routes the ranks are 1.5 (wave_rank; with the histograms read before them and a chain through LDS 13.4,
+// and rank 34 us, count and rank now 11.5 us) and 6.6 us at E = 8 (2 M routes: 25 -> 16 us).  Of the 11.4 to 12.8 us of the rank
+// kernel for 2 M routes the ranks are 1.5 (wave_rank; with the histograms read before them and a chain through LDS 12.9 to 13.4,
 // 64 experts, 600 k routes 9.0 -> 8.4), the scattered stores 1.5, the rest launch, loads and barriers.
 // The first workgroup also writes the tables; when a tile plan is wanted, it has no chunk and writes that too.
 constexpr int kRankBatch = 8;            // 64-route steps of a wavefront whose expert ids are in registers together

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void placement_loads_kernel(const long long* _
 // pairs, do not queue on one address; neighbouring lanes add the copies up.  Bound by the read of R (at most
 // 512 KB by one compute unit) and one LDS atomic per entry; for the small tables of a layer by latency: launch, R, barriers.
 // A thread per GPU pair that walked R's rows itself, load after load, took 408 us for 64 experts on 8 GPUs; this
-// takes 4.4 (5.2 with up to 32 copies per bin added up by one thread and R read after the maps).
+// takes 4.4 to 4.8 (5.0 to 5.2 with up to 32 copies per bin added up by one thread and R read after the maps).
 constexpr int kTrafficThreads = 1024;
 constexpr int kTrafficBins = 8192;       // 64 KB of int64
 constexpr int kTrafficInFlight = 8;      // rows of R a thread fetches together

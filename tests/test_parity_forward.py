@@ -81,9 +81,12 @@ def test_rows_copied_beside_the_projections(lib, T, d, f, E, k, G, local, up, do
         assert (int(plan[8]) > 0) == up and (int(plan[9]) > 0) == down and int(plan[8]) + int(plan[9]) <= T
 
 
-def test_outputs_in_the_memory_of_the_inputs(lib):
-    """ffn_out begins where x does: x has been read when it is written, whoever copies the rows."""
-    T, d, f, E, k, G, local = 8192, 2048, 1408, 64, 6, 8, 5
+@pytest.mark.parametrize("shared", ["x and ffn_out", "x and H", "send_buf and ffn_out, shifted", "send_buf is ffn_out"])
+def test_outputs_in_the_memory_of_the_inputs(lib, shared):
+    """Memory that the four calls may share, because each has read it when the next writes it: the same results, whoever copies
+    the rows.  In a call with memory of its own for everything both projections copy rows that lie under what they write here."""
+    T, d, f, E, k, G, local = 8192, 2048, 1408, 64, 6, 8, 0
+    N, row = T * k, d * 2
     rng = np.random.default_rng(T + E)
     pl = rng.integers(0, G, E).astype(np.int32)
     x = to_device(synth.normal(T, 0, (T, d), 1.0, "bf16"))
@@ -94,10 +97,23 @@ def test_outputs_in_the_memory_of_the_inputs(lib):
         L.set_placement(pl)
         L.set_weights(*w)
     want.forward(x, lg)
-    got.ffn_out[:T].copy_(x)
-    got.forward(got.ffn_out[:T], lg)
+    up, down, begin, end = want.ffn_ws[:64].view(torch.int32).cpu().tolist()[8:12]
+    assert up > 0 and down > 0 and begin == 0 and end > up + 1000      # this GPU's rows come first
+    send = want.send_buf.clone()
+    if shared == "x and ffn_out":                  # rows of x from `up` on lie under the down projection's
+        got.ffn_out[:T].copy_(x)
+        xs = got.ffn_out[:T]
+    elif shared == "x and H":                      # the first ones lie under the up projection's (H follows the plan's 8192 bytes)
+        xs = got.ffn_ws[8192:8192 + T * row].view(torch.bfloat16).view(T, d)
+        xs.copy_(x)
+    else:                                          # the down projection's rows where other GPUs' send rows, or its own, are
+        shift = end if shared.endswith("shifted") else 0
+        memory = torch.zeros((N + shift, d), dtype=torch.bfloat16, device="cuda")
+        got.send_buf, got.ffn_out, xs = memory[:N], memory[shift:], x
+        send[shift:shift + end] = want.ffn_out[:end]
+    got.forward(xs, lg)
     torch.cuda.synchronize()
-    assert torch.equal(got.send_buf, want.send_buf) and torch.equal(got.y, want.y)
+    assert torch.equal(got.y, want.y) and torch.equal(got.send_buf, send)
 
 
 def check_forward(dtype, T, d, f, E, k, G, local, one_workspace=False):

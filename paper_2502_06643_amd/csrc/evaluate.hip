@@ -8,6 +8,7 @@
 //                           max over GPU pairs of C / B                 (Eq. 8, one layer's term)
 // The tables are tiny (E <= 256, G <= 256), so each call is one workgroup, bound by its launch and by how many
 // dependent rounds of memory latency it makes (placement_loads with the tables in LDS: 5.4 -> 2.4 us at E = 64).
+#include <algorithm>
 #include "common.h"
 
 namespace moe {
@@ -49,14 +50,18 @@ __global__ __launch_bounds__(256) void placement_loads_kernel(const long long* _
 // One workgroup reads R once, all its loads independent, and adds every entry to its GPU pair's bin in LDS.
 // The G x G bins are done in stripes of g1 of at most kTrafficBins bins (one stripe up to G = 90); a small
 // table gets several copies, picked by lane, so that the lanes of a row, which mostly belong to few GPU
-// pairs, do not queue on one address; neighbouring lanes add the copies up.  Bound by the read of R (at most
+// pairs, do not queue on one address.  Bound by the read of R (at most
 // 512 KB by one compute unit) and one LDS atomic per entry; for the small tables of a layer by latency: launch, R, barriers.
-// A thread per GPU pair that walked R's rows itself, load after load, took 408 us for 64 experts on 8 GPUs; this
-// takes 4.4 to 4.8 (5.0 to 5.2 with up to 32 copies per bin added up by one thread and R read after the maps).
+// A thread per GPU pair that walked R's rows itself, load after load, took 408 us for 64 experts on 8 GPUs.
+// FEW: at most as many counters as threads, so that neighbouring lanes add up the copies of a bin, and the first rows asked for
+// before it is known who needs them: 64 experts on 8 GPUs 5.1 us without, 4.7 with.  Where that leaves the lanes of a GPU pair, whose
+// experts lie side by side in the usual map, less than a counter for two, they queue, and a thread adds up more copies of a bin
+// faster than lanes do in several rounds (256 contiguous experts on 32 GPUs 14.0 us; with a counter a bin 31, with 8 and lanes 17.2).
 constexpr int kTrafficThreads = 1024;
 constexpr int kTrafficBins = 8192;       // 64 KB of int64
 constexpr int kTrafficInFlight = 8;      // rows of R a thread fetches together
 
+template <bool FEW>
 __global__ __launch_bounds__(kTrafficThreads) void placement_traffic_kernel(const long long* __restrict__ R, const int32_t* __restrict__ pl_l,
                                                                             const int32_t* __restrict__ pl_l1, int E_l, int E_l1, int G,
                                                                             int col_bits, int stripe, int copies,
@@ -71,16 +76,14 @@ __global__ __launch_bounds__(kTrafficThreads) void placement_traffic_kernel(cons
     const int g2 = e2 < E_l1 ? pl_l1[e2] : -1;
     const bool col_ok = (unsigned)g2 < (unsigned)G;
     if (tid < E_l) row_gpu[tid] = pl_l[tid];
-    // the first rows are asked for before it is known who needs them: one round of memory latency
-    auto fetch = [&](int e1, long long (&r)[kTrafficInFlight]) {
+    long long first[kTrafficInFlight];
+    if (FEW) {
 #pragma unroll
         for (int u = 0; u < kTrafficInFlight; ++u) {
-            const int row = e1 + u * rows_per_step;
-            r[u] = row < E_l && e2 < E_l1 ? R[(size_t)row * E_l1 + e2] : 0;
+            const int row = first_row + u * rows_per_step;
+            first[u] = row < E_l && e2 < E_l1 ? R[(size_t)row * E_l1 + e2] : 0;
         }
-    };
-    long long first[kTrafficInFlight];
-    fetch(first_row, first);
+    }
     double local_max = 0.0;
     for (int s0 = 0; s0 < G; s0 += stripe) {
         const int rows = min(stripe, G - s0), n_bins = rows * G;
@@ -89,30 +92,39 @@ __global__ __launch_bounds__(kTrafficThreads) void placement_traffic_kernel(cons
         if (col_ok) {
             for (int e1 = first_row; e1 < E_l; e1 += rows_per_step * kTrafficInFlight) {
                 long long r[kTrafficInFlight];
-                if (e1 == first_row) {
-#pragma unroll
-                    for (int u = 0; u < kTrafficInFlight; ++u) r[u] = first[u];
-                } else {
-                    fetch(e1, r);
-                }
+                int g[kTrafficInFlight];
 #pragma unroll
                 for (int u = 0; u < kTrafficInFlight; ++u) {
-                    const int row = e1 + u * rows_per_step, g = row < E_l ? row_gpu[row] - s0 : -1;
-                    if ((unsigned)g < (unsigned)rows && r[u] != 0)
-                        atomicAdd(&bins[(g * G + g2) * copies + (tid & (copies - 1))], (unsigned long long)r[u]);
+                    const int row = e1 + u * rows_per_step;
+                    g[u] = row < E_l ? row_gpu[row] - s0 : -1;
+                    const bool in = (unsigned)g[u] < (unsigned)rows;
+                    if (!in) g[u] = -1;
+                    if (FEW && e1 == first_row) r[u] = first[u];
+                    else r[u] = in ? R[(size_t)row * E_l1 + e2] : 0;
                 }
+#pragma unroll
+                for (int u = 0; u < kTrafficInFlight; ++u)
+                    if (g[u] >= 0 && r[u] != 0)
+                        atomicAdd(&bins[(g[u] * G + g2) * copies + (tid & (copies - 1))], (unsigned long long)r[u]);
             }
         }
         __syncthreads();
-        // neighbouring lanes add up the copies of one bin (copies: a power of two up to 32); whole wavefronts
-        for (int i = tid; i < (n_bins * copies + 63) / 64 * 64; i += kTrafficThreads) {
-            unsigned long long s = i < n_bins * copies ? bins[i] : 0ull;
-            for (int m = 1; m < copies; m <<= 1) s += __shfl_xor(s, m, 64);
-            if (i >= n_bins * copies || (i & (copies - 1)) != 0) continue;
-            const size_t pair = (size_t)s0 * G + i / copies;
+        const auto put = [&](int p, unsigned long long s) {
+            const size_t pair = (size_t)s0 * G + p;
             C[pair] = (long long)s;
             const double cost = B ? (double)(long long)s / B[pair] : (double)(long long)s;
             local_max = cost > local_max ? cost : local_max;
+        };
+        if (FEW) {                                       // copies: a power of two up to 32
+            unsigned long long s = tid < n_bins * copies ? bins[tid] : 0ull;
+            for (int m = 1; m < copies; m <<= 1) s += __shfl_xor(s, m, 64);
+            if (tid < n_bins * copies && (tid & (copies - 1)) == 0) put(tid / copies, s);
+        } else {
+            for (int p = tid; p < n_bins; p += kTrafficThreads) {
+                unsigned long long s = 0;
+                for (int c = 0; c < copies; ++c) s += bins[p * copies + ((c + tid) & (copies - 1))];
+                put(p, s);
+            }
         }
         __syncthreads();                                 // the bins have been read before the next stripe clears them
     }
@@ -145,10 +157,16 @@ int launch_placement_traffic(const int64_t* R, const int32_t* pl_l, const int32_
     int col_bits = 0;
     while ((1 << col_bits) < E_l1) ++col_bits;
     const int stripe = G * G <= kTrafficBins ? G : kTrafficBins / G;
-    int copies = 1;
-    while (copies < 32 && G * G * copies * 2 <= kTrafficThreads) copies *= 2;      // a thread adds up at most one of them
-    hipLaunchKernelGGL(placement_traffic_kernel, dim3(1), dim3(kTrafficThreads), 0, s, (const long long*)R, pl_l, pl_l1, E_l, E_l1, G,
-                       col_bits, stripe, copies, (long long*)C, B, max_cost);
+    const auto copies_in = [&](int counters) {
+        int copies = 1;
+        while (copies < 32 && G * G * copies * 2 <= counters) copies *= 2;
+        return copies;
+    };
+    // lanes of a wavefront with the same bin where a GPU's experts are neighbours: its columns, and its rows as far as the wavefront has them
+    const int cols = (E_l1 + G - 1) / G, rows = std::min((E_l + G - 1) / G, std::max(64 >> col_bits, 1));
+    const bool few = G * G <= kTrafficThreads && 2 * copies_in(kTrafficThreads) >= cols * rows;
+    hipLaunchKernelGGL(few ? &placement_traffic_kernel<true> : &placement_traffic_kernel<false>, dim3(1), dim3(kTrafficThreads), 0, s, (const long long*)R,
+                       pl_l, pl_l1, E_l, E_l1, G, col_bits, stripe, copies_in(few ? kTrafficThreads : kTrafficBins), (long long*)C, B, max_cost);
     return check_launch("moe_placement_traffic launch");
 }
 

@@ -81,6 +81,14 @@ def test_traffic_stripes_and_copies(lib, E1, E2, G):
     np.testing.assert_array_equal(C, O.cluster_traffic(R[ok_a][:, ok_b], pa[ok_a], pb[ok_b], G) if ok_a.any() and ok_b.any() else 0 * C)
 
 
+@pytest.mark.parametrize("E1,E2,G", [(256, 256, 8), (40, 64, 32), (256, 128, 16), (66, 16, 31)])  # the most columns whose bins neighbouring lanes add up ...
+@pytest.mark.parametrize("more", [0, 1])                                               # ... and one more column or GPU than that
+def test_traffic_around_the_small_tables(lib, E1, E2, G, more):
+    if E2 + more <= 256:
+        test_traffic_stripes_and_copies(lib, E1, E2 + more, G)
+    test_traffic_stripes_and_copies(lib, E1, E2, G + more)
+
+
 def test_accumulate_counts_over_batches(lib):
     E = 8
     P = torch.zeros(E, dtype=torch.int64, device="cuda")

@@ -96,12 +96,11 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
 // (at most kRankChunks x E counts, L2 hits, independent loads) instead of waiting for a scan kernel of one
 // workgroup, whose two dependent walks over up to 1024 histograms took 22 us at E = 64 (600 k routes; count, scan
 // and rank 34 us, count and rank now 11.5 us) and 6.6 us at E = 8 (2 M routes: 25 -> 16 us).  Of the 11.4 to 12.8 us of the rank
-// kernel for 2 M routes the ranks are 1.5 (wave_rank; with the histograms read before them and a chain through LDS 12.9 to 13.4,
+// kernel for 2 M routes the ranks are 1.5 (wave_rank; with the histograms read before them and a chain through LDS 12.9 to 13.4;
 // 64 experts, 600 k routes 9.0 -> 8.4), the scattered stores 1.5, the rest launch, loads and barriers.
 // The first workgroup also writes the tables; when a tile plan is wanted, it has no chunk and writes that too.
 constexpr int kRankBatch = 8;            // 64-route steps of a wavefront whose expert ids are in registers together
-constexpr int kRankHist = 16;            // histogram entries of a thread in flight together (up to 64 experts: all of them)
-// EB: bits of an expert id, for wave_rank; 0: more than 64 experts, counted in LDS
+// EB: bits of an expert id, for wave_rank; 0: counted in LDS
 template <int EB>
 __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits, int steps,
                                                                       const int32_t* __restrict__ block_counts,
@@ -127,27 +126,46 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
             exs[u] = (i0 + u < steps && r < N) ? topk_idx[r] : -1;
         }
     };
-    // all chunks' histograms: thread (expert, slice of the chunks), then the slices of a wavefront, then LDS.  The first
-    // entries are asked for before the routes are ranked and added up after that
+    // all chunks' histograms: thread (expert, slice of the chunks), then the slices of a wavefront, then LDS.  Where the ranks
+    // are counted in lanes the first entries are asked for before the routes are ranked and added up after that; where
+    // both go through LDS the histograms come first (128 experts, 600 k routes 12.8 us for 12.2 the other way round)
+    constexpr int HIST = 16;                             // entries of a thread in flight together (up to 64 experts: all of them)
     const int EP = 1 << ebits, he = threadIdx.x & (EP - 1), slices = kIndexThreads >> ebits;
-    int first[kRankHist], all = 0, mine = 0;
-    auto fetch = [&](int b0, int (&c)[kRankHist]) {
+    int first[HIST], all = 0, mine = 0;
+    auto fetch = [&](int b0, int (&c)[HIST]) {
 #pragma unroll
-        for (int u = 0; u < kRankHist; ++u) {
+        for (int u = 0; u < HIST; ++u) {
             const int b = b0 + u * slices;
             c[u] = he < E && b < chunks ? block_counts[(size_t)b * E + he] : 0;
         }
     };
-    auto add = [&](int b0, const int (&c)[kRankHist]) {
+    auto add = [&](int b0, const int (&c)[HIST]) {
 #pragma unroll
-        for (int u = 0; u < kRankHist; ++u) {
+        for (int u = 0; u < HIST; ++u) {
             all += c[u];
             mine += b0 + u * slices < chunk ? c[u] : 0;
         }
     };
-    const int hist0 = threadIdx.x >> ebits;
+    int b0 = threadIdx.x >> ebits;
+    auto histograms = [&]() {
+        if (he < E) {
+            for (; b0 < chunks; b0 += HIST * slices) {
+                int c[HIST];
+                fetch(b0, c);
+                add(b0, c);
+            }
+        }
+        for (int m = EP; m < 64; m <<= 1) {
+            all += __shfl_xor(all, m, 64);
+            mine += __shfl_xor(mine, m, 64);
+        }
+        if (he < E && lane < EP) {
+            atomicAdd(&s.tot[he], all);
+            atomicAdd(&before[he], mine);
+        }
+    };
     load(0);
-    fetch(hist0, first);
+    if (EB > 0) fetch(b0, first);
     index_clear(s, E);
     if ((int)threadIdx.x < E) {
         s.pl[threadIdx.x] = placement[threadIdx.x];
@@ -156,6 +174,7 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
     }
     __syncthreads();
 
+    if (EB == 0) histograms();
     // this wavefront's own routes are counted and ranked in one go;
     // the ranks stay in registers, those of a slice of more than kRankBatch steps wait in inv_perm
     const bool spill = steps > kRankBatch;
@@ -174,21 +193,11 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
         if (i0 >= steps) break;
         load(i0);
     }
-    if (EB > 0 && lane < E) s.woff[wave][lane] = count;
-
-    add(hist0, first);
-    for (int b0 = hist0 + kRankHist * slices; b0 < chunks; b0 += kRankHist * slices) {
-        int more[kRankHist];
-        fetch(b0, more);
-        add(b0, more);
-    }
-    for (int m = EP; m < 64; m <<= 1) {
-        all += __shfl_xor(all, m, 64);
-        mine += __shfl_xor(mine, m, 64);
-    }
-    if (he < E && lane < EP) {
-        atomicAdd(&s.tot[he], all);
-        atomicAdd(&before[he], mine);
+    if (EB > 0) {
+        if (lane < E) s.woff[wave][lane] = count;
+        add(b0, first);
+        b0 += HIST * slices;
+        histograms();
     }
     __syncthreads();
     index_offsets(s, E, ebits, before);

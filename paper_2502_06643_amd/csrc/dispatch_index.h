@@ -35,17 +35,22 @@ __device__ __forceinline__ void index_clear(IndexTables& s, int E) {
 // Totals and per-wavefront counts -> expert starts and per-wavefront write offsets; `before` (in LDS, may be NULL):
 // routes of each expert that precede this workgroup's.  Called by all threads, after a barrier; ends with one.
 // The E x E comparisons of the starts are dealt to all threads (thread: expert, slice of the others), because one
-// wavefront walking E = 64 totals took 3.7 us, more than the ranking of its routes.
+// wavefront walking E = 64 totals took 3.7 us, more than the ranking of its routes.  The number of rounds is known before the
+// loop, so that their reads overlap whatever the compiler makes of the code around (asked in every round whether there is
+// a next, 2.1 us more at E = 256, where there are 64).
 __device__ __forceinline__ void index_offsets(IndexTables& s, int E, int ebits, const int* before) {
     const int EP = 1 << ebits, me = threadIdx.x & (EP - 1), slices = kIndexThreads >> ebits;
+    const int first = threadIdx.x >> ebits, rounds = (E << ebits) / kIndexThreads;   // in which every thread has an expert; one more in which some have
     int start = 0;
     if (me < E) {
         const int ge = s.pl[me];
+        const auto before_me = [&](int o) {
+            const int go = s.pl[o], to = s.tot[o];
+            return (go < ge) | ((go == ge) & (o < me)) ? to : 0;
+        };
 #pragma unroll 4
-        for (int o = threadIdx.x >> ebits; o < E; o += slices) {
-            const int go = s.pl[o];
-            start += ((go < ge) | ((go == ge) & (o < me))) ? s.tot[o] : 0;
-        }
+        for (int i = 0; i < rounds; ++i) start += before_me(first + i * slices);
+        if (first + rounds * slices < E) start += before_me(first + rounds * slices);
     }
     for (int m = EP; m < 64; m <<= 1) start += __shfl_xor(start, m, 64);
     if (me < E && (threadIdx.x & 63) < EP) atomicAdd(&s.start[me], start);          // cleared by index_clear

@@ -100,7 +100,8 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
 // 64 experts, 600 k routes 9.0 -> 8.4), the scattered stores 1.5, the rest launch, loads and barriers.
 // The first workgroup also writes the tables; when a tile plan is wanted, it has no chunk and writes that too.
 constexpr int kRankBatch = 8;            // 64-route steps of a wavefront whose expert ids are in registers together
-// EB: bits of an expert id, for wave_rank; 0: counted in LDS
+// EB: bits of an expert id, for wave_rank; 0: counted in LDS.  At most 64 registers, for two workgroups a compute unit: a layer call's
+// plan is one more than the 256 chunks (131072 tokens, 8 experts, top-2: with 76 registers the kernel 8.5 us, with 48 7.6)
 template <int EB>
 __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits, int steps,
                                                                       const int32_t* __restrict__ block_counts,
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
     // all chunks' histograms: thread (expert, slice of the chunks), then the slices of a wavefront, then LDS.  Where the ranks
     // are counted in lanes the first entries are asked for before the routes are ranked and added up after that; where
     // both go through LDS the histograms come first (128 experts, 600 k routes 12.8 us for 12.2 the other way round)
-    constexpr int HIST = 16;                             // entries of a thread in flight together (up to 64 experts: all of them)
+    constexpr int HIST = EB == 3 ? 2 : EB == 4 ? 4 : EB == 6 ? 8 : 16;        // up to 256 chunks over 1024 >> EB slices: 2, 4, 16 entries
     const int EP = 1 << ebits, he = threadIdx.x & (EP - 1), slices = kIndexThreads >> ebits;
     int first[HIST], all = 0, mine = 0;
     auto fetch = [&](int b0, int (&c)[HIST]) {

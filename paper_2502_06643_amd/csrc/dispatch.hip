@@ -44,13 +44,15 @@ static void route_chunks(long long N, int* steps, int* chunks) {
 
 constexpr int kCountCopies = 256;        // LDS counters of a workgroup
 static_assert(kCountCopies >= MOE_MAX_EXPERTS && kCountCopies <= kIndexThreads, "a thread per counter");
+// MANY: several copies of the histogram, picked by lane, because the lanes that hold the same expert queue on one address.  For few
+// experts and several steps a workgroup (8 experts, 2 M routes: 5.4 us with one copy, 4.0 with 32; 40000 routes 2.7 and 3.2; 64
+// experts, 600 k routes: 3.1 with one, 3.4 with 4, 4.0 with 32)
+template <bool MANY>
 __global__ __launch_bounds__(kIndexThreads) void dispatch_count_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int steps, int copies,
                                                                        int32_t* __restrict__ block_counts) {
-    // few experts: several copies, picked by lane, because the lanes that hold the same expert queue on one address (8 experts,
-    // 2 M routes: 5.4 us with one copy, 4.0 with 32; 64 experts, 600 k routes: 3.1 with one, 3.4 with 4, 4.0 with 32)
     __shared__ int hist[kCountCopies];
     const int copy = threadIdx.x & (copies - 1);
-    if (threadIdx.x < kCountCopies) hist[threadIdx.x] = 0;
+    if ((int)threadIdx.x < (MANY ? kCountCopies : E)) hist[threadIdx.x] = 0;
     __syncthreads();
     const long long base = (long long)blockIdx.x * kIndexThreads * steps + threadIdx.x;
     for (int i0 = 0; i0 < steps; i0 += 8) {
@@ -62,12 +64,13 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_count_kernel(const int
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if ((unsigned)e[u] < (unsigned)E) atomicAdd(&hist[e[u] * copies + copy], 1);
+            if ((unsigned)e[u] < (unsigned)E) atomicAdd(&hist[MANY ? e[u] * copies + copy : e[u]], 1);
     }
     __syncthreads();
-    // adjacent lanes add up the copies of one expert (copies: a power of two up to 32)
     const int i = threadIdx.x;
-    if (i < kCountCopies) {                              // whole wavefronts
+    if (!MANY) {
+        if (i < E) block_counts[(size_t)blockIdx.x * E + i] = hist[i];
+    } else if (i < kCountCopies) {                       // whole wavefronts: adjacent lanes add up the copies of one expert
         int c = i < E * copies ? hist[i] : 0;
         for (int m = 1; m < copies; m <<= 1) c += __shfl_xor(c, m, 64);
         if (i < E * copies && (i & (copies - 1)) == 0) block_counts[(size_t)blockIdx.x * E + i / copies] = c;
@@ -101,7 +104,7 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
 // The first workgroup also writes the tables; when a tile plan is wanted, it has no chunk and writes that too.
 constexpr int kRankBatch = 8;            // 64-route steps of a wavefront whose expert ids are in registers together
 // EB: bits of an expert id, for wave_rank; 0: counted in LDS.  At most 64 registers, for two workgroups a compute unit: a layer call's
-// plan is one more than the 256 chunks (131072 tokens, 8 experts, top-2: with 76 registers the kernel 8.5 us, with 48 7.6)
+// plan is one more than the 256 chunks (262144 tokens, 8 experts, top-2: with 76 registers the kernel 9.8 us, with 48 8.3)
 template <int EB>
 __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits, int steps,
                                                                       const int32_t* __restrict__ block_counts,
@@ -354,14 +357,19 @@ int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T
         route_chunks(N, &steps, &chunks);
         {
             LaunchTimer timer(MOE_K_DISPATCH_COUNT, s);
-            int copies = E > 32 ? 1 : 32;
+            int copies = 32;                             // a power of two
             while (E * copies > kCountCopies) copies /= 2;
-            hipLaunchKernelGGL(dispatch_count_kernel, dim3(chunks), dim3(kIndexThreads), 0, s, topk_idx, N, E, steps, copies, block_counts);
+            const bool many = E <= 32 && steps > 1;
+            hipLaunchKernelGGL(many ? &dispatch_count_kernel<true> : &dispatch_count_kernel<false>, dim3(chunks), dim3(kIndexThreads), 0, s,
+                               topk_idx, N, E, steps, copies, block_counts);
             if ((rc = check_launch("moe_dispatch count launch")) != MOE_OK) return rc;
         }
         {
             LaunchTimer timer(MOE_K_DISPATCH_RANK, s);
-            const auto rank = ebits <= 3 ? &dispatch_rank_kernel<3> : (ebits <= 4 ? &dispatch_rank_kernel<4> : (ebits <= 6 ? &dispatch_rank_kernel<6> : &dispatch_rank_kernel<0>));
+            // one step a wavefront (up to 262144 routes): counted in LDS, as one count does not queue and the code is short
+            // (8 experts, 16400 routes: dispatch 7.5 us, 8.2 in lanes; 64 experts, 131070 routes 8.5, 8.7)
+            const auto rank = steps == 1 || ebits > 6 ? &dispatch_rank_kernel<0>
+                              : (ebits <= 3 ? &dispatch_rank_kernel<3> : (ebits <= 4 ? &dispatch_rank_kernel<4> : &dispatch_rank_kernel<6>));
             hipLaunchKernelGGL(rank, dim3(chunks + (plan_task.plan != nullptr ? 1 : 0)), dim3(kIndexThreads), 0, s, topk_idx, N, E, ebits, steps, block_counts,
                                placement, G, expert_counts, expert_start, gpu_counts, gpu_offsets, perm, inv_perm, plan_task);
             if ((rc = check_launch("moe_dispatch rank launch")) != MOE_OK) return rc;

@@ -115,6 +115,13 @@ def test_expert_counts_around_the_ranking_variants(lib, E):
     check(lib, None, idx, pl, 3)
 
 
+@pytest.mark.parametrize("E", [8, 16, 32, 64, 65])
+@pytest.mark.parametrize("N", [262144, 262145])        # the last batch of one step a wavefront, which counts in LDS, and the first of two
+def test_around_the_second_step(lib, E, N):
+    rng = np.random.default_rng(E)
+    check(lib, None, rng.integers(0, E, (N, 1)).astype(np.int32), rng.integers(0, 3, E).astype(np.int32), 3)
+
+
 @pytest.mark.parametrize("name", ["c2", "c2b", "c3", "c4", "c5"])
 def test_config_shapes_full_size(lib, name):
     """Full-size batches with the skewed routing of the benchmark configs

@@ -46,8 +46,9 @@ void dispatch_geometry(long long N, int* items, int* nblocks);      // of the wo
 // path that follows does not split it).
 struct PlanShape { int bm0, bm1, choice, nt_down, kt_down, cus_per_xcd; };
 // Rows of other GPUs' experts that the tiled bf16 projections copy on the compute units that they leave idle (ffn_late.h):
-// column and k tiles of both projections (nt_down = 0: the down projection fills the chip), bytes of a row, tokens.
-struct LateShape { int nt_up, kt_up, nt_down, kt_down, row_bytes, T, k; };
+// column tiles of both projections, rows that an idle compute unit of every XCD reads or writes meanwhile (rows_down = 0: the down
+// projection fills the chip); tokens, routes a token, 1 / tokens.
+struct LateShape { int nt_up, nt_down; float rows_up, rows_down; int T, k; float per_token; int cus_per_xcd; };
 // The tile plan as a by-product of the dispatch's index kernels, which hold all it needs; plan == NULL: none wanted.
 // late.T = 0: every row is copied before the FFN.
 struct PlanTask { int32_t* plan; int local_gpu; PlanShape shape; LateShape late; };

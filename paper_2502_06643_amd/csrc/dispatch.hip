@@ -85,14 +85,7 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
         c = s.tot[e];
         st = s.start[e];
     }
-    // this GPU's range of the sorted rows begins where the first of its experts with rows does; the totals are in the scratch
-    __shared__ int own_begin;
-    if (e == 0) own_begin = 0x7FFFFFFF;
-    build_plan(scratch, e, c, st, e, E, pt.shape, pt.plan);
-    if (pt.late.T == 0) return;
-    if (c > 0) atomicMin(&own_begin, st);                // build_plan has barriers
-    __syncthreads();
-    if (e == 0) plan_late(pt.late, scratch.tiles, own_begin, scratch.total_rows, pt.shape.cus_per_xcd, pt.plan);
+    build_plan(scratch, e, c, st, e, E, pt.shape, pt.plan, false, 0, pt.late.T > 0);
 }
 
 // Ranks the routes of one chunk.  Latency-bound: every workgroup adds up all chunks' histograms for itself
@@ -101,7 +94,7 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
 // and rank 34 us, count and rank now 11.5 us) and 6.6 us at E = 8 (2 M routes: 25 -> 16 us).  Of the 11.4 to 12.8 us of the rank
 // kernel for 2 M routes the ranks are 1.5 (wave_rank; with the histograms read before them and a chain through LDS 12.9 to 13.4;
 // 64 experts, 600 k routes 9.0 -> 8.4), the scattered stores 1.5, the rest launch, loads and barriers.
-// The first workgroup also writes the tables; when a tile plan is wanted, it has no chunk and writes that too.
+// The workgroup of the first chunk also writes the tables; a tile plan is written by one more, which comes first.
 constexpr int kRankBatch = 8;            // 64-route steps of a wavefront whose expert ids are in registers together
 // EB: bits of an expert id, for wave_rank; 0: counted in LDS.  At most 64 registers, for two workgroups a compute unit: a layer call's
 // plan is one more than the 256 chunks (262144 tokens, 8 experts, top-2: with 76 registers the kernel 9.8 us, with 48 8.3)
@@ -222,9 +215,8 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
             inv_perm[r] = pos;
         }
     }
-    if (blockIdx.x != 0) return;
-    if (pt.plan != nullptr) plan_from_tables(s, plan_scratch, E, pt);
-    index_write_tables(s, E, G, expert_counts, expert_start, gpu_counts, gpu_offsets);
+    if (chunk < 0) plan_from_tables(s, plan_scratch, E, pt);
+    else if (chunk == 0) index_write_tables(s, E, G, expert_counts, expert_start, gpu_counts, gpu_offsets);
 }
 
 // Batches of up to kFusedMaxRoutes routes: count and rank in ONE workgroup of 16 wavefronts, each
@@ -279,23 +271,33 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_index_kernel(const int
 }
 
 // One thread per 16-byte unit of a source row: read once, write k times.  LATE: of the first tokens only the rows of this
-// GPU's experts; the projections copy the others (ffn_late.h).
+// GPU's experts; the projections copy the others (ffn_late.h), and read in the plan's header how many tokens that are.  x is
+// asked for before that is known: with the positions first, and no read of a token without a row to copy here, layers that take
+// late rows were 1.041 times as fast as without, not 1.055 (256 random ones, geometric mean).
 template <bool LATE>
 __global__ __launch_bounds__(256) void dispatch_rows_kernel(const uint4* __restrict__ x, long long total_units, int units_per_row,
                                                             int k, int N, const int32_t* __restrict__ inv_perm,
-                                                            uint4* __restrict__ send_buf, const int32_t* __restrict__ plan) {
+                                                            uint4* __restrict__ send_buf, LateShape late, const int32_t* __restrict__ plan,
+                                                            int32_t* __restrict__ plan_late) {
     const long long u = (long long)blockIdx.x * 256 + threadIdx.x;
     if (u >= total_units) return;
     const long long t = u / units_per_row;
     const int c = (int)(u - t * units_per_row);
     const uint4 v = x[u];
-    if (LATE && t < plan[kPlanLateUp] + plan[kPlanLateDown]) {
+    if (LATE) {
         const int own0 = plan[kPlanOwnBegin], own1 = plan[kPlanOwnEnd];
-        for (int j = 0; j < k; ++j) {
-            const int p = inv_perm[t * k + j];
-            if (p >= own0 && p < own1) send_buf[(long long)p * units_per_row + c] = v;
+        const LateTokens n = late_tokens(late, plan, own1 - own0);
+        if (u == 0) {
+            plan_late[0] = n.up;
+            plan_late[1] = n.down;
         }
-        return;
+        if (t < n.up + n.down) {
+            for (int j = 0; j < k; ++j) {
+                const int p = inv_perm[t * k + j];
+                if (p >= own0 && p < own1) send_buf[(long long)p * units_per_row + c] = v;
+            }
+            return;
+        }
     }
     for (int j = 0; j < k; ++j) {
         const int p = inv_perm[t * k + j];
@@ -383,7 +385,8 @@ int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T
         LaunchTimer timer(MOE_K_DISPATCH_ROWS, s);
         const auto rows = plan_task.late.T > 0 ? &dispatch_rows_kernel<true> : &dispatch_rows_kernel<false>;
         hipLaunchKernelGGL(rows, dim3((unsigned)grid), dim3(256), 0, s, (const uint4*)x, total_units,
-                           units_per_row, k, N, inv_perm, (uint4*)send_buf, plan_task.plan);
+                           units_per_row, k, N, inv_perm, (uint4*)send_buf, plan_task.late, plan_task.plan,
+                           plan_task.plan != nullptr ? plan_task.plan + kPlanLateUp : nullptr);
         if ((rc = check_launch("moe_dispatch rows launch")) != MOE_OK) return rc;
     }
     return MOE_OK;

@@ -4,8 +4,8 @@
 // idle in the two projections, as many as these copy in the time of a tile.
 //
 // 8192 tokens, 64 experts, top-6, 8 of them here, d 2048, f 1408: row copy 39 -> 13 us, projections 50 + 37 -> 59 + 50 (the copies
-// take bandwidth from the tiles), layer 151.3 -> 142 to 144.  Stores that stay out of the caches: 142 for 145 without.  80 KB a k tile
-// 148, 20 KB 150 (both without), four k tiles less for the copies to get under way: 7312 tokens, d 1536, f 704 123 -> 127.
+// take bandwidth from the tiles), layer 151.3 -> 144.  Stores that stay out of the caches: 142 for 145 without.  80 KB a k tile
+// 148, 20 KB 150 (both without).
 #pragma once
 #include "ffn_plan.h"
 
@@ -16,31 +16,27 @@ constexpr int kLateBytesPerKTile = 40 << 10;
 
 // Per XCD: compute units without a tile in a launch of MT x NT tiles that runs in one round; 0 when it takes longer.
 __host__ __device__ __forceinline__ int late_copiers(int MT, int NT, int cus_per_xcd) {
-    const XcdShare sh = xcd_share(MT, NT, 0, 0, cus_per_xcd, false);          // the first XCD has the largest share
-    return sh.full < cus_per_xcd ? cus_per_xcd - sh.full : 0;
+    if (MT > kXcds * cus_per_xcd) return 0;
+    const int tiles = MT * (NT / kXcds) + (MT * (NT % kXcds) + kXcds - 1) / kXcds;     // of the first XCD, which has the largest share (xcd_share)
+    return tiles < cus_per_xcd ? cus_per_xcd - tiles : 0;
 }
 
-// How many tokens' rows the two projections take: what fits beside their tiles.  foreign: routes of other GPUs.
-__host__ __device__ __forceinline__ void late_tokens(const LateShape& l, int MT, int foreign, int cus_per_xcd, int& up, int& down) {
-    up = down = 0;
-    if (l.T <= 0 || foreign <= 0) return;
-    const float token_bytes = (float)l.row_bytes * (1.0f + (float)foreign / (float)l.T);
-    const auto fit = [&](int NT, int KT, int left) {
-        const float n = (float)kXcds * (float)late_copiers(MT, NT, cus_per_xcd) * (float)KT * (float)kLateBytesPerKTile / token_bytes;
+// How many tokens' rows the two projections take: what fits beside their tiles.  The row copy works this out, in every thread: in
+// the index kernels it would lengthen a serial chain that everything waits for (rank kernel 1.2 to 1.7 us, one-workgroup kernel 0.2 to 0.7).
+struct LateTokens { int up, down; };
+__device__ __forceinline__ LateTokens late_tokens(const LateShape& l, const int32_t* __restrict__ plan, int own_rows) {
+    const int MT = plan[3] == 0 ? plan[1] : plan[2], foreign = l.T * l.k - own_rows;
+    // a token's rows: one read, and one written for each of its routes of other GPUs
+    const float tokens = __builtin_amdgcn_rcpf(__builtin_fmaf((float)foreign, l.per_token, 1.0f));
+    const auto fit = [&](int copiers, float rows, int left) {
+        const float n = (float)copiers * rows * tokens;
         return n < (float)left ? (int)n : left;
     };
-    up = fit(l.nt_up, l.kt_up, l.T);
-    if (l.nt_down > 0) down = fit(l.nt_down, l.kt_down, l.T - up);
-}
-
-// the plan's header entries; MT: row tiles of the height in use, own_rows and own_begin: this GPU's range of the sorted rows
-__device__ __forceinline__ void plan_late(const LateShape& l, int MT, int own_begin, int own_rows, int cus_per_xcd, int32_t* __restrict__ plan) {
-    int up, down;
-    late_tokens(l, MT, l.T * l.k - own_rows, cus_per_xcd, up, down);
-    plan[kPlanLateUp] = up;
-    plan[kPlanLateDown] = down;
-    plan[kPlanOwnBegin] = own_rows > 0 ? own_begin : 0;
-    plan[kPlanOwnEnd] = own_rows > 0 ? own_begin + own_rows : 0;
+    const int T = foreign > 0 ? l.T : 0;
+    LateTokens t;
+    t.up = fit(late_copiers(MT, l.nt_up, l.cus_per_xcd), l.rows_up, T);
+    t.down = fit(late_copiers(MT, l.nt_down, l.cus_per_xcd), l.rows_down, T - t.up);
+    return t;
 }
 
 struct LateRows { const uint4* x; uint4* send; const int32_t* inv_perm; int k, N, units; };

@@ -32,7 +32,8 @@ static_assert(kPlanInts * sizeof(int32_t) <= kPlanBytes, "plan area too small");
 //             cut by cost (RoundSplit in ffn_tiles.h); [5] = 0: it is not
 //         [7] 1: the segments of one expert are merged into one bucket
 //         [8], [9] tokens whose rows for other GPUs the up and the down projection copy (the first tokens, those after
-//             them), [10], [11] this GPU's range of the sorted rows (ffn_late.h; only in a layer call that may have such rows)
+//             them), [10], [11] this GPU's range of the sorted rows (only in a layer call that may have such rows; the first two
+//             are written by the row copy: ffn_late.h)
 constexpr int kPlanSmallTiles = 4, kPlanBigParts = 5, kPlanSmallParts = 6, kPlanMerged = 7;
 constexpr int kPlanLateUp = 8, kPlanLateDown = 9, kPlanOwnBegin = 10, kPlanOwnEnd = 11;
 
@@ -125,7 +126,7 @@ struct PlanScratch {
     int cnt[MOE_MAX_EXPERTS], tiles0[MOE_MAX_EXPERTS], tiles1[MOE_MAX_EXPERTS], segs[MOE_MAX_EXPERTS];
     int rank[MOE_MAX_EXPERTS], rows[MOE_MAX_EXPERTS], pre0[MOE_MAX_EXPERTS], pre1[MOE_MAX_EXPERTS], pre_segs[MOE_MAX_EXPERTS];
     int n, n_small, total1;
-    int tiles, total_rows;                               // of the tile height in use, of all listed groups
+    int first_row[MOE_MAX_EXPERTS / 64];                 // of the groups of a wavefront with rows (only when the range of all is asked for)
 };
 
 // The cut of a one-round launch, for the plan's header; called by one wavefront, a lane per candidate.
@@ -159,10 +160,11 @@ __device__ __forceinline__ void round_split(int lane, int nb, int ns, const Plan
 // Builds the plan with one workgroup of at least MOE_MAX_EXPERTS threads (a whole power of two), all of which must
 // call this: thread e brings group e's row count c (0: not listed; threads past the last group bring 0), its first
 // row st and the expert wt whose weights it multiplies with; with `merged`, group e is a merged bucket of n_segs
-// segments and its rank and place in the segment list are left in the scratch.  The E x E comparisons are dealt to all
+// segments and its rank and place in the segment list are left in the scratch; range: the range of rows of all groups, which is
+// contiguous, is wanted in the header.  The E x E comparisons are dealt to all
 // threads (thread: group, slice of the others); walked by one thread per group they took 5.5 us for E = 64.
 __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st, int wt, int E, const PlanShape& shape,
-                                           int32_t* __restrict__ plan, bool merged = false, int n_segs = 0) {
+                                           int32_t* __restrict__ plan, bool merged = false, int n_segs = 0, bool range = false) {
     if (e < MOE_MAX_EXPERTS) {
         s.cnt[e] = c;
         s.tiles0[e] = (c + shape.bm0 - 1) / shape.bm0;
@@ -170,7 +172,11 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
         s.segs[e] = n_segs;
         s.rank[e] = s.rows[e] = s.pre0[e] = s.pre1[e] = s.pre_segs[e] = 0;
     }
-    if (e == 0) s.n = s.n_small = s.total1 = s.tiles = s.total_rows = 0;
+    if (e == 0) s.n = s.n_small = s.total1 = 0;
+    if (range && e < MOE_MAX_EXPERTS) {                  // the groups with rows lie side by side, by number
+        const unsigned long long some = __ballot(c > 0);
+        if ((e & 63) == (some ? __builtin_ctzll(some) : 0)) s.first_row[e >> 6] = some ? st : 0x7FFFFFFF;
+    }
     __syncthreads();
     if (c > 0) {
         atomicAdd(&s.n, 1);
@@ -227,18 +233,24 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
             plan[2] = t1;
             const int choice = shape.choice >= 0 ? shape.choice : ((long long)s.rows[e] + c >= (long long)kLargeBucketRows * n ? 0 : 1);
             plan[3] = choice;
-            s.tiles = choice == 0 ? t0 : t1;
-            s.total_rows = s.rows[e] + c;
             plan[kPlanSmallTiles] = 1 + n_small;
             plan[kPlanMerged] = merged;
             plan[kPlanTiles0 + n] = t0;
             plan[kPlanTiles1 + n] = t1;
+            if (range) {
+                int begin = s.first_row[0];
+#pragma unroll
+                for (int w = 1; w < MOE_MAX_EXPERTS / 64; ++w) begin = min(begin, s.first_row[w]);
+                plan[kPlanOwnBegin] = begin;
+                plan[kPlanOwnEnd] = begin + s.rows[e] + c;
+            }
         }
     } else if (n == 0 && e == 0) {
         plan[0] = plan[1] = plan[2] = plan[kPlanMerged] = 0;
         plan[3] = shape.choice >= 0 ? shape.choice : 0;
         plan[kPlanSmallTiles] = 1;
         plan[kPlanTiles0] = plan[kPlanTiles1] = 0;
+        if (range) plan[kPlanOwnBegin] = plan[kPlanOwnEnd] = 0;
     }
     const int last_wave = (int)blockDim.x - 64;          // while the others write
     if (e >= last_wave) {

@@ -143,18 +143,20 @@ int ffn_plan_shape(moe_dtype_t dt, int N, int d, int f, int E, bool every_row_re
 }
 
 // The tiled bf16 kernels only; the down projection takes rows where none of its tiles is cut along k to fill the chip.  How
-// many tiles this GPU has, and so how many rows it can copy beside them, only the device knows (late_tokens).  Not asked about,
-// because the question costs 1 us: calls that with an even routing have two rounds of them or more, that have rows of less than
-// kMinBytes for others, whose tiles are over before the copies are under way (d 960, f 960, 16 experts, top-4, 6719 tokens
-// 100.8 us, with late rows 102), and with up to two routes a token, because its row is read once more (21 random layers
-// 0.997 times as fast in the median, the worst 0.99; with four and six routes 13 layers 0.99 to 1.06, 1.01 in the median).
+// many tiles this GPU has, and so how many rows it can copy beside them, only the device knows (late_tokens).  Not asked about:
+// calls that with an even routing have an eighth more than a round of tiles (where the rows of a GPU's experts are few, the routing decides; the
+// question itself costs 0.2 %); rows of less than kMinBytes for others, which are copied before the projections by the time
+// that these have slowed down (175 random layers of 8 to 48 MB 1.003 times as fast, the worst 0.976, of 80 MB and more see
+// ffn_late.h); reductions of fewer k tiles than kMinKTiles, whose tiles are over before the copies are under way (d 960, f 960, 16 experts,
+// top-4, 6719 tokens 100.8 us, with late rows 102); and up to two routes a token, because its row is read once more (21 random layers
+// 0.997 times as fast in the median, the worst 0.99; with three 43 layers 1.037, the worst 0.99).
 LateShape ffn_late_shape(moe_dtype_t dt, int N, int d, int f, int E, int T, int k, int G, int cus_per_xcd) {
-    constexpr long long kMinBytes = 8ll << 20;
+    constexpr long long kMinBytes = 80ll << 20;
     constexpr int kMinKTiles = 20, kMinRoutes = 3;
     LateShape l = {};
     if (dt != MOE_BF16 || G < 2 || k < kMinRoutes || d / 64 < kMinKTiles || ffn_streams(N, d, f, E, false)) return l;
     const long long row_tiles = N / G / kShortTileRows > E / G ? N / G / kShortTileRows : E / G;
-    if (row_tiles * ((f + 127) / 128) >= 2ll * kXcds * cus_per_xcd || (long long)(N - N / G) * d * 2 < kMinBytes) return l;
+    if (row_tiles * ((f + 127) / 128) >= 9ll * cus_per_xcd || (long long)(N - N / G) * d * 2 < kMinBytes) return l;
     const float per_kt = (float)kXcds * (float)kLateBytesPerKTile / ((float)d * 2.0f);
     l.nt_up = (f + 127) / 128;
     l.nt_down = (d + 255) / 256;

@@ -64,31 +64,42 @@ def test_one_buffer_for_both_workspaces(lib, T, E, k):
 
 
 @pytest.mark.parametrize("T,d,f,E,k,G,local,up,down", [
-    (2700, 2048, 1408, 64, 6, 8, 0, True, False),       # one workgroup's index kernel; the up projection takes all
-    (8192, 2048, 1408, 64, 6, 8, 5, True, True),        # rank kernel; both projections take some
-    (1501, 1344, 1024, 16, 4, 4, 1, True, False),       # 168 pieces a row
-    (1500, 4096, 512, 32, 3, 8, 3, True, False),        # 512 pieces a row
-    (1600, 1280, 4096, 64, 4, 16, 2, True, False),      # the down projection's tiles are cut along k
-    (700, 1280, 64, 16, 16, 200, 199, True, False),     # no expert here, 16 routes per token
-    (30000, 1280, 64, 32, 4, 8, 0, True, False),        # more than it can take, and no room beside the down projection
-    (2300, 1280, 4096, 16, 3, 2, 0, False, False),      # more tiles than compute units
-    (3000, 1216, 512, 16, 4, 4, 0, None, None),         # reductions too short to ask
-    (5000, 2048, 512, 16, 2, 4, 0, None, None),         # two routes a token
+    (2700, 4096, 512, 16, 6, 8, 0, True, False),        # one workgroup's index kernel; the up projection takes all
+    (9000, 2048, 1024, 32, 4, 4, 1, True, True),        # rank kernel; both projections take some
+    (11001, 1344, 256, 16, 4, 4, 1, True, False),       # 168 pieces a row
+    (4000, 4096, 512, 32, 3, 8, 3, True, False),        # 512 pieces a row
+    (2750, 4096, 2048, 16, 4, 16, 2, True, False),      # the down projection's tiles are cut along k
+    (2100, 1280, 64, 16, 16, 200, 199, True, False),    # no expert here, 16 routes per token
+    (26000, 1280, 64, 32, 4, 8, 0, True, True),         # more than they can take
+    (8192, 2048, 1408, 64, 6, 8, 5, False, False),      # tiles on more than three quarters of the compute units
+    (14000, 2048, 384, 8, 3, 2, 0, False, False),       # on nearly all
+    (12000, 1216, 512, 16, 4, 4, 0, None, None),        # reductions too short to ask
+    (14000, 2048, 512, 16, 2, 4, 0, None, None),        # two routes a token
+    (2700, 2048, 1408, 64, 6, 8, 0, None, None),        # few rows
 ])
 def test_rows_copied_beside_the_projections(lib, T, d, f, E, k, G, local, up, down):
     plan = check_forward("bf16", T, d, f, E, k, G, local).ffn_ws[:64].view(torch.int32).cpu()
     if up is not None:                             # what the plan leaves to the two projections
         assert (int(plan[8]) > 0) == up and (int(plan[9]) > 0) == down and int(plan[8]) + int(plan[9]) <= T
+    else:                                          # nobody has asked
+        assert plan[8:12].tolist() == [0x03030303] * 4
+
+
+def test_rows_copied_beside_the_projections_of_experts_mapped_nowhere(lib):
+    """Experts on GPUs that do not exist come first and last in the sorted order; their rows are copied like any other GPU's."""
+    pl = np.array([3, -1, 1, 4, 0, -7, 2, 1, 100, 0, 1, 3, 2, -1, 2, 4], dtype=np.int32)
+    plan = check_forward("bf16", 4500, 2048, 512, 16, 6, 4, 1, placement=pl).ffn_ws[:64].view(torch.int32).cpu()
+    assert int(plan[8]) > 0 and int(plan[10]) > 0
 
 
 @pytest.mark.parametrize("shared", ["x and ffn_out", "x and H", "send_buf and ffn_out, shifted", "send_buf is ffn_out"])
 def test_outputs_in_the_memory_of_the_inputs(lib, shared):
     """Memory that the four calls may share, because each has read it when the next writes it: the same results, whoever copies
     the rows.  In a call with memory of its own for everything both projections copy rows that lie under what they write here."""
-    T, d, f, E, k, G, local = 8192, 2048, 1408, 64, 6, 8, 0
+    T, d, f, E, k, G, local = 6000, 2048, 896, 32, 6, 4, 0
     N, row = T * k, d * 2
     rng = np.random.default_rng(T + E)
-    pl = rng.integers(0, G, E).astype(np.int32)
+    pl = (np.arange(E) * G // E).astype(np.int32)
     x = to_device(synth.normal(T, 0, (T, d), 1.0, "bf16"))
     lg = torch.from_numpy(rng.standard_normal((T, E)).astype(np.float32)).cuda()
     w = [to_device(synth.normal(T, i, s, s[1] ** -0.5, "bf16")) for i, s in ((2, (E, d, f)), (3, (E, d, f)), (4, (E, f, d)))]
@@ -116,9 +127,9 @@ def test_outputs_in_the_memory_of_the_inputs(lib, shared):
     assert torch.equal(got.y, want.y) and torch.equal(got.send_buf, send)
 
 
-def check_forward(dtype, T, d, f, E, k, G, local, one_workspace=False):
+def check_forward(dtype, T, d, f, E, k, G, local, one_workspace=False, placement=None):
     rng = np.random.default_rng(T + E)
-    pl = rng.integers(0, G, E).astype(np.int32)
+    pl = rng.integers(0, G, E).astype(np.int32) if placement is None else placement
     x = to_device(synth.normal(T, 0, (T, d), 1.0, dtype))
     lg = rng.standard_normal((T, E)).astype(np.float32)
     lg[T // 2] = np.round(lg[T // 2])              # ties
@@ -130,6 +141,7 @@ def check_forward(dtype, T, d, f, E, k, G, local, one_workspace=False):
         L.set_weights(*w)
         for n in OUTPUTS:
             getattr(L, n).fill_(3)                 # what a call leaves untouched must be the same too
+    got.ffn_ws.fill_(3)
     if one_workspace:
         got.dispatch_ws = got.ffn_ws
     want.gate(lg)

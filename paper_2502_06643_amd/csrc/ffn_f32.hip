@@ -406,7 +406,9 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
             __syncthreads();
         }
         // Keeps the sums' additions in the block of the products that they read: moved into the block after the branch, two
-        // of them came too early after the last matrix instruction, which the compiler does not see on every path.
+        // of them came too early after the last matrix instruction, which the compiler does not see on every path.  The loop above
+        // is one block, and its sums are needed on both ways out of it: there is nowhere to move them (held there too: up
+        // to 1 % slower).
         auto settle = [&]() {
 #pragma unroll
             for (int m = 0; m < NA; ++m)

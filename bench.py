@@ -325,7 +325,8 @@ def main():
             "combine": n_local * d * elt + T * d * elt + 12 * N,
             "transition": 8 * N,
         }
-        if cfg.G == 1 or k < 3:                     # else some of the rows may have been copied beside the projections
+        # bf16 layers on one GPU of several, past the sizes of the front: some of the rows may have been copied beside the projections
+        if cfg.G == 1 or cfg.local_gpu < 0 or k < 3 or cfg.dtype != "bf16" or n_all["front"]:
             alg_bytes["dispatch_rows"] = T * d * elt + N * d * elt + 4 * N
         alg_flops = {"ffn_up": 4.0 * d * f * n_local, "ffn_down": 2.0 * d * f * n_local}
         # the grouped GEMMs also stream every touched resident expert's weights once: the second bound, which is the

@@ -249,9 +249,10 @@ int moe_pack_weights(const void* w1, const void* w3, const void* w2,
  * (round to nearest even), accumulation is fp32; requires d % 64 == 0 and
  * f % 64 == 0.  MOE_F32: everything fp32; requires d % 4 == 0, f % 4 == 0.
  * Large fp32 batches (all rows resident, N d f >= 2.5e9, 64 rows an expert,
- * N / 64 * min(d, f) / 64 >= 400) are multiplied as sums of three bf16 values each, to less error than fp32
- * multiplication and addition leave, and in plain fp32 where a value is not
- * such a sum (magnitudes below 2^-110, or that round to infinity in bf16).
+ * N / 64 * min(d, f) / 64 >= 400) are multiplied as sums of three bf16 values
+ * each, to less error than fp32 multiplication and addition leave, and in
+ * plain fp32 where a value is not such a sum (magnitudes below 2^-110 that are
+ * no multiple of 2^-133, or that round to infinity in bf16).
  * Their last bits differ from those of the same rows in a smaller batch, or
  * on a GPU that holds a subset of the experts (local_gpu >= 0).
  *
@@ -353,7 +354,14 @@ int moe_combine(const void* ffn_out, moe_dtype_t dt, const int32_t* inv_perm,
  * errors.  The calls are enqueued back to back, and where the batch allows it
  * stages are merged: small batches run gate, dispatch and the FFN's tile plan
  * as one kernel (timed as MOE_K_FRONT), decode-sized bf16 batches fold the
- * combine into the last kernel of the FFN (timed with MOE_K_FFN_DOWN).
+ * combine into the last kernel of the FFN (timed with MOE_K_FFN_DOWN), and on
+ * one GPU of several (local_gpu >= 0, G >= 2, bf16, three routes a token and
+ * more) the FFN's kernels may copy send rows of other GPUs on compute units
+ * that they leave idle: that part of the copy is then timed with MOE_K_FFN_UP
+ * and MOE_K_FFN_DOWN, not MOE_K_DISPATCH_ROWS, and x and inv_perm are read and
+ * send_buf is written until the FFN ends.  Not so where x, inv_perm or send_buf
+ * share memory with ffn_out or ffn_workspace (send_buf may be ffn_out itself):
+ * such a call copies every row first.
  * dispatch_workspace and ffn_workspace may be the same buffer, as they may be
  * for the four calls; the tile plan is a launch of its own then.
  * ---------------------------------------------------------------------- */

@@ -90,22 +90,30 @@ __global__ __launch_bounds__(kTrafficThreads) void placement_traffic_kernel(cons
         for (int i = tid; i < n_bins * copies; i += kTrafficThreads) bins[i] = 0ull;
         __syncthreads();
         if (col_ok) {
-            for (int e1 = first_row; e1 < E_l; e1 += rows_per_step * kTrafficInFlight) {
+            const auto add = [&](int g, long long r) {
+                if ((unsigned)g < (unsigned)rows && r != 0)
+                    atomicAdd(&bins[(g * G + g2) * copies + (tid & (copies - 1))], (unsigned long long)r);
+            };
+            int e1 = first_row;
+            if (FEW) {
+#pragma unroll
+                for (int u = 0; u < kTrafficInFlight; ++u) {
+                    const int row = e1 + u * rows_per_step;
+                    add(row < E_l ? row_gpu[row] - s0 : -1, first[u]);
+                }
+                e1 += rows_per_step * kTrafficInFlight;
+            }
+            for (; e1 < E_l; e1 += rows_per_step * kTrafficInFlight) {
                 long long r[kTrafficInFlight];
                 int g[kTrafficInFlight];
 #pragma unroll
                 for (int u = 0; u < kTrafficInFlight; ++u) {
                     const int row = e1 + u * rows_per_step;
                     g[u] = row < E_l ? row_gpu[row] - s0 : -1;
-                    const bool in = (unsigned)g[u] < (unsigned)rows;
-                    if (!in) g[u] = -1;
-                    if (FEW && e1 == first_row) r[u] = first[u];
-                    else r[u] = in ? R[(size_t)row * E_l1 + e2] : 0;
+                    r[u] = (unsigned)g[u] < (unsigned)rows ? R[(size_t)row * E_l1 + e2] : 0;
                 }
 #pragma unroll
-                for (int u = 0; u < kTrafficInFlight; ++u)
-                    if (g[u] >= 0 && r[u] != 0)
-                        atomicAdd(&bins[(g[u] * G + g2) * copies + (tid & (copies - 1))], (unsigned long long)r[u]);
+                for (int u = 0; u < kTrafficInFlight; ++u) add(g[u], r[u]);
             }
         }
         __syncthreads();

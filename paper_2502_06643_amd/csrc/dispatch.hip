@@ -96,9 +96,9 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
 // 64 experts, 600 k routes 9.0 -> 8.4), the scattered stores 1.5, the rest launch, loads and barriers.
 // The workgroup of the first chunk also writes the tables; a tile plan is written by one more, which comes first.
 constexpr int kRankBatch = 8;            // 64-route steps of a wavefront whose expert ids are in registers together
-// EB: bits of an expert id, for wave_rank; 0: counted in LDS.  At most 64 registers, for two workgroups a compute unit: a layer call's
-// plan is one more than the 256 chunks (262144 tokens, 8 experts, top-2: with 76 registers the kernel 9.8 us, with 48 8.3)
-template <int EB>
+// EB: bits of an expert id, for wave_rank; 0: counted in LDS.  HIST: histogram entries of a thread in flight together; up to 256 chunks
+// over 1024 / 8, 16, 32 or 64 slices make 2, 4, 8 or 16 of them.
+template <int EB, int HIST>
 __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int32_t* __restrict__ topk_idx, int N, int E, int ebits, int steps,
                                                                       const int32_t* __restrict__ block_counts,
                                                                       const int32_t* __restrict__ placement, int G,
@@ -126,7 +126,6 @@ __global__ __launch_bounds__(kIndexThreads) void dispatch_rank_kernel(const int3
     // all chunks' histograms: thread (expert, slice of the chunks), then the slices of a wavefront, then LDS.  Where the ranks
     // are counted in lanes the first entries are asked for before the routes are ranked and added up after that; where
     // both go through LDS the histograms come first (128 experts, 600 k routes 12.8 us for 12.2 the other way round)
-    constexpr int HIST = EB == 3 ? 2 : EB == 4 ? 4 : EB == 6 ? 8 : 16;        // up to 256 chunks over 1024 >> EB slices: 2, 4, 16 entries
     const int EP = 1 << ebits, he = threadIdx.x & (EP - 1), slices = kIndexThreads >> ebits;
     int first[HIST], all = 0, mine = 0;
     auto fetch = [&](int b0, int (&c)[HIST]) {
@@ -368,11 +367,16 @@ int launch_dispatch(const void* x, int row_bytes, const int32_t* topk_idx, int T
         }
         {
             LaunchTimer timer(MOE_K_DISPATCH_RANK, s);
-            // one step a wavefront (up to 262144 routes): counted in LDS, as one count does not queue and the code is short
-            // (8 experts, 16400 routes: dispatch 7.5 us, 8.2 in lanes; 64 experts, 131070 routes 8.5, 8.7)
-            const auto rank = steps == 1 || ebits > 6 ? &dispatch_rank_kernel<0>
-                              : (ebits <= 3 ? &dispatch_rank_kernel<3> : (ebits <= 4 ? &dispatch_rank_kernel<4> : &dispatch_rank_kernel<6>));
-            hipLaunchKernelGGL(rank, dim3(chunks + (plan_task.plan != nullptr ? 1 : 0)), dim3(kIndexThreads), 0, s, topk_idx, N, E, ebits, steps, block_counts,
+            // Counted in LDS: one step a wavefront (up to 262144 routes), as one count does not queue and the code is short
+            // (8 experts, 16400 routes: dispatch 7.5 us, 8.2 in lanes; 64 experts, 131070 routes 8.5, 8.7); and more than 16 experts
+            // where there are more workgroups than compute units, a layer call's 256 chunks and the plan (131072 tokens, 32 experts,
+            // top-4: rank 8.8 us, 10.2 in lanes), as those in lanes have too many registers for two on a compute unit: 65 with 8
+            // histogram entries, 81 with 16.  Up to 16 experts 50 and 54 (262144 tokens, 8 experts, top-2: 8.4 us; 9.8 with 76)
+            const int groups = chunks + (plan_task.plan != nullptr ? 1 : 0);
+            const auto rank = steps == 1 || ebits > 6 || (ebits > 4 && groups > kRankChunks) ? &dispatch_rank_kernel<0, 16>
+                              : ebits <= 3 ? &dispatch_rank_kernel<3, 2> : ebits <= 4 ? &dispatch_rank_kernel<4, 4>
+                              : ebits <= 5 ? &dispatch_rank_kernel<6, 8> : &dispatch_rank_kernel<6, 16>;
+            hipLaunchKernelGGL(rank, dim3(groups), dim3(kIndexThreads), 0, s, topk_idx, N, E, ebits, steps, block_counts,
                                placement, G, expert_counts, expert_start, gpu_counts, gpu_offsets, perm, inv_perm, plan_task);
             if ((rc = check_launch("moe_dispatch rank launch")) != MOE_OK) return rc;
         }

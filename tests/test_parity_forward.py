@@ -29,6 +29,9 @@ OUTPUTS = ("topk_idx", "topk_w", "send_buf", "perm", "inv_perm", "expert_counts"
     ("bf16", 8193, 64, 64, 3, 2, 2, 1),           # the plan comes from the one-workgroup index kernel: 16386 routes are past it, ...
     ("bf16", 8192, 64, 64, 100, 2, 5, 1),         # ... 16384 the last
     ("bf16", 20000, 64, 64, 256, 2, 256, 255),    # ... and from the rank kernel, widest tables
+    ("bf16", 87381, 64, 64, 64, 6, 1, -1),        # 256 chunks of two steps and the plan: more workgroups than compute units, ...
+    ("bf16", 262144, 64, 64, 16, 2, 1, -1),       # ... with ranks counted in lanes
+    ("bf16", 100000, 64, 64, 33, 4, 2, 1),        # 196 of them
     ("f32", 9000, 16, 16, 8, 2, 1, -1),
     ("f32", 1, 4, 4, 1, 1, 1, -1),
     ("f32", 256, 128, 256, 8, 2, 4, 0),

@@ -91,9 +91,9 @@ __device__ __forceinline__ void plan_from_tables(const IndexTables& s, PlanScrat
 // Ranks the routes of one chunk.  Latency-bound: every workgroup adds up all chunks' histograms for itself
 // (at most kRankChunks x E counts, L2 hits, independent loads) instead of waiting for a scan kernel of one
 // workgroup, whose two dependent walks over up to 1024 histograms took 22 us at E = 64 (600 k routes; count, scan
-// and rank 34 us, count and rank now 11.5 us) and 6.6 us at E = 8 (2 M routes: 25 -> 16 us).  Of the 11.4 to 12.8 us of the rank
-// kernel for 2 M routes the ranks are 1.5 (wave_rank; with the histograms read before them and a chain through LDS 12.9 to 13.4;
-// 64 experts, 600 k routes 9.0 -> 8.4), the scattered stores 1.5, the rest launch, loads and barriers.
+// and rank 34 us, count and rank now 11.2 us) and 6.6 us at E = 8 (2 M routes: 25 -> 13.4 us).  Of the 10.7 us of the rank
+// kernel for 2 M routes the ranks are 1.5 (wave_rank; with the histograms read before them and a chain through LDS 12.4;
+// 64 experts, 600 k routes 9.5, 9.2 in lanes), the scattered stores 1.5, the rest launch, loads and barriers.
 // The workgroup of the first chunk also writes the tables; a tile plan is written by one more, which comes first.
 constexpr int kRankBatch = 8;            // 64-route steps of a wavefront whose expert ids are in registers together
 // EB: bits of an expert id, for wave_rank; 0: counted in LDS.  HIST: histogram entries of a thread in flight together; up to 256 chunks
@@ -283,6 +283,7 @@ __global__ __launch_bounds__(256) void dispatch_rows_kernel(const uint4* __restr
     const long long t = u / units_per_row;
     const int c = (int)(u - t * units_per_row);
     const uint4 v = x[u];
+    int begin = 0, end = N;                              // of the positions whose rows are copied here
     if (LATE) {
         const int own0 = plan[kPlanOwnBegin], own1 = plan[kPlanOwnEnd];
         const LateTokens n = late_tokens(late, plan, own1 - own0);
@@ -291,16 +292,13 @@ __global__ __launch_bounds__(256) void dispatch_rows_kernel(const uint4* __restr
             plan_late[1] = n.down;
         }
         if (t < n.up + n.down) {
-            for (int j = 0; j < k; ++j) {
-                const int p = inv_perm[t * k + j];
-                if (p >= own0 && p < own1) send_buf[(long long)p * units_per_row + c] = v;
-            }
-            return;
+            begin = own0;
+            end = own1;
         }
     }
     for (int j = 0; j < k; ++j) {
         const int p = inv_perm[t * k + j];
-        if ((unsigned)p < (unsigned)N) send_buf[(long long)p * units_per_row + c] = v;
+        if (p >= begin && p < end) send_buf[(long long)p * units_per_row + c] = v;
     }
 }
 

@@ -3,18 +3,17 @@
 // fewer output tiles here than the chip has compute units, so those rows are left to the workgroups that would be
 // idle in the two projections, as many as these copy in the time of a tile.
 //
-// 8192 tokens, 64 experts, top-6, 8 of them here, d 2048, f 1408: row copy 39 -> 20 us, projections 50 + 37 -> 59 + 44 (the copies
-// take bandwidth from the tiles), layer 151 -> 141.5.  Stores that stay out of the caches: 3 us less than without.  80 KB a k tile in both
-// projections 4 us more than 40, 20 KB 6 (both without).
+// 8192 tokens, 64 experts, top-6, 8 of them here, d 2048, f 1408: row copy 39 -> 13 us, projections 50 + 37 -> 59 + 50 (the copies
+// take bandwidth from the tiles), layer 151.3 -> 144.  Stores that stay out of the caches: 142 for 145 without.  80 KB a k tile
+// 148, 20 KB 150 (both without).  Over 376 random layers 1.053 times as fast as without (geometric mean), the worst 0.990; two builds
+// of the same code differ by up to 0.985 there.
 #pragma once
 #include "ffn_plan.h"
 
 namespace moe {
 
-// What a copying workgroup moves in the time of a k tile (1.3 us), KB read and written.  In the down projection, whose tiles wait for
-// memory more, half of that: 494 random layers 1.062 times as fast as without late rows either way (geometric mean), the worst 0.983, not 0.971
-// (7032 tokens, 128 experts, top-12, d 3968, f 1152: 300 us, 305, 310), and the layer above 141.5 us for 144.
-constexpr int kLateUpKB = 40, kLateDownKB = 20;
+// What a copying workgroup moves in the time of a k tile (1.3 us), bytes read and written.
+constexpr int kLateBytesPerKTile = 40 << 10;
 
 // Per XCD: compute units without a tile in a launch of MT x NT tiles that runs in one round; 0 when it takes longer.
 __host__ __device__ __forceinline__ int late_copiers(int MT, int NT, int cus_per_xcd) {

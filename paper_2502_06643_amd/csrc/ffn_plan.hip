@@ -157,11 +157,11 @@ LateShape ffn_late_shape(moe_dtype_t dt, int N, int d, int f, int E, int T, int 
     if (dt != MOE_BF16 || G < 2 || k < kMinRoutes || d / 64 < kMinKTiles || ffn_streams(N, d, f, E, false)) return l;
     const long long row_tiles = N / G / kShortTileRows > E / G ? N / G / kShortTileRows : E / G;
     if (row_tiles * ((f + 127) / 128) >= 9ll * cus_per_xcd || (long long)(N - N / G) * d * 2 < kMinBytes) return l;
-    const float per_kb = (float)kXcds * 1024.0f / ((float)d * 2.0f);
+    const float per_kt = (float)kXcds * (float)kLateBytesPerKTile / ((float)d * 2.0f);
     l.nt_up = (f + 127) / 128;
     l.nt_down = (d + 255) / 256;
-    l.rows_up = per_kb * (float)(kLateUpKB * (d / 64));
-    l.rows_down = split_can_pay(f / 64) ? 0.f : per_kb * (float)(kLateDownKB * (f / 64));
+    l.rows_up = per_kt * (float)(d / 64);
+    l.rows_down = split_can_pay(f / 64) ? 0.f : per_kt * (float)(f / 64);
     l.per_token = 1.0f / (float)T;
     l.cus_per_xcd = cus_per_xcd;
     l.T = T;

@@ -3,16 +3,18 @@
 // fewer output tiles here than the chip has compute units, so those rows are left to the workgroups that would be
 // idle in the two projections, as many as these copy in the time of a tile.
 //
-// 8192 tokens, 64 experts, top-6, 8 of them here, d 2048, f 1408: row copy 39 -> 13 us, projections 50 + 37 -> 59 + 50 (the copies
-// take bandwidth from the tiles), layer 151.3 -> 144.  Stores that stay out of the caches: 142 for 145 without.  80 KB a k tile
-// 148, 20 KB 150 (both without).  Over 376 random layers 1.053 times as fast as without (geometric mean), the worst 0.990; two builds
-// of the same code differ by up to 0.985 there.
+// 8192 tokens, 64 experts, top-6, 8 of them here, d 2048, f 1408: row copy 39 -> 14 us, projections 50 + 37 -> 59 + 50 (the copies
+// take bandwidth from the tiles), layer 151 -> 143.  Stores that stay out of the caches: 3 us less than without.  Random layers, with
+// buffers that change from call to call, so that the weights are not in a cache: 246 that leave rows to the projections 1.040
+// times as fast as without (geometric mean), the worst 0.984, 54 that ask and leave none 0.999.
 #pragma once
 #include "ffn_plan.h"
 
 namespace moe {
 
-// What a copying workgroup moves in the time of a k tile (1.3 us), bytes read and written.
+// What a copying workgroup moves in the time of a k tile (1.3 us), bytes read and written.  80 KB made the layer above 4 us slower, 20
+// KB 6.  20 KB in the down projection alone, whose tiles wait for memory more: the same 246 layers 1.037, the layer above 145, though where
+// one layer is called over and over with its weights in the Infinity Cache 141.
 constexpr int kLateBytesPerKTile = 40 << 10;
 
 // Per XCD: compute units without a tile in a launch of MT x NT tiles that runs in one round; 0 when it takes longer.

@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
 // end are not multiplied.
 //
 // Bound by power for the up projection (the clock falls to 1.9 GHz) and by the loads and vector work of the narrower
-// tile for the down projection.  2000 routes in 8 skewed buckets, d 1024, f 2816, layer 369 us on the fp32 kernel, 302 here.  The look
+// tile for the down projection.  2000 routes in 8 skewed buckets, d 1024, f 2816, layer 369 us on the fp32 kernel, 302 here (311 on another box).  The look
 // at every operand (split_eight) is one instruction a pair; as a minimum of their magnitudes, three a pair, it made that 315.  Also
 // lost, the last four without that look (293 us, 4096 routes 501): B by buffer loads with the row in a scalar offset, which
 // saves the addresses but sends the 16 loads of a stage in one burst, 193 -> 202 us in the up projection; the remainders by

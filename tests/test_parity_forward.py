@@ -95,10 +95,11 @@ def test_rows_copied_beside_the_projections_of_experts_mapped_nowhere(lib):
     assert int(plan[8]) > 0 and int(plan[10]) > 0
 
 
-@pytest.mark.parametrize("shared", ["x and ffn_out", "x and H", "send_buf and ffn_out, shifted", "send_buf is ffn_out"])
+@pytest.mark.parametrize("shared", ["x and ffn_out", "x and H", "inv_perm and H", "send_buf and ffn_out, shifted", "send_buf is ffn_out"])
 def test_outputs_in_the_memory_of_the_inputs(lib, shared):
-    """Memory that the four calls may share, because each has read it when the next writes it: the same results, whoever copies
-    the rows.  In a call with memory of its own for everything both projections copy rows that lie under what they write here."""
+    """Memory that the four calls may share, because each has read it when the next writes it, or writes other rows of it: the same
+    results, and nobody asks the projections to copy rows (but for the send buffer as ffn_out).  In a call with memory of its own
+    for everything both of them copy rows that lie under what they write here."""
     T, d, f, E, k, G, local = 6000, 2048, 896, 32, 6, 4, 0
     N, row = T * k, d * 2
     rng = np.random.default_rng(T + E)
@@ -114,12 +115,16 @@ def test_outputs_in_the_memory_of_the_inputs(lib, shared):
     up, down, begin, end = want.ffn_ws[:64].view(torch.int32).cpu().tolist()[8:12]
     assert up > 0 and down > 0 and begin == 0 and end > up + 1000      # this GPU's rows come first
     send = want.send_buf.clone()
+    got.ffn_ws.fill_(3)
     if shared == "x and ffn_out":                  # rows of x from `up` on lie under the down projection's
         got.ffn_out[:T].copy_(x)
         xs = got.ffn_out[:T]
     elif shared == "x and H":                      # the first ones lie under the up projection's (H follows the plan's 8192 bytes)
         xs = got.ffn_ws[8192:8192 + T * row].view(torch.bfloat16).view(T, d)
         xs.copy_(x)
+    elif shared == "inv_perm and H":               # under the rows of other GPUs, which the up projection leaves alone
+        at = 8192 + (end * f * 2 + 255) // 256 * 256
+        got.inv_perm, xs = got.ffn_ws[at:at + N * 4].view(torch.int32), x
     else:                                          # the down projection's rows where other GPUs' send rows, or its own, are
         shift = end if shared.endswith("shifted") else 0
         memory = torch.zeros((N + shift, d), dtype=torch.bfloat16, device="cuda")
@@ -128,6 +133,8 @@ def test_outputs_in_the_memory_of_the_inputs(lib, shared):
     got.forward(xs, lg)
     torch.cuda.synchronize()
     assert torch.equal(got.y, want.y) and torch.equal(got.send_buf, send)
+    asked = got.ffn_ws[:64].view(torch.int32).cpu().tolist()[8:12] != [0x03030303] * 4
+    assert asked == (shared == "send_buf is ffn_out")
 
 
 def check_forward(dtype, T, d, f, E, k, G, local, one_workspace=False, placement=None):

@@ -17,18 +17,27 @@
 // up / down in us: 231 / 128 (100 and 90 of the 157 TFLOP/s); 64 x 64 tiles with one
 // wavefront per 32 x 32 block 253 / 159, 32 x 64 tiles 243 / 145, 64-deep stages
 // 286 / 146; fused multiply-adds on 64 x 64 tiles, without matrix instructions,
-// 359 / 292.  Without loads and LDS writes this loop takes 189 / 101: the rest is
-// the copy to LDS.
+// 359 / 292.  Without loads and LDS writes that loop took 189 / 101: the rest was
+// the copy to LDS, of which only A's is left.
 //
-// Pipeline.  While stage s multiplies from registers, stage s + 1 is read from
-// LDS, s + 2 is written there and the loads of s + 3 and s + 4 are in flight, one
+// Weights.  The four k of a column lie side by side ([K / 4][columns][4] per matrix,
+// [W1 | W3 | W2] per expert), so that the 16 bytes that a thread fetches of a stage
+// are what its lane multiplies: B goes straight into registers, four stages ahead, a
+// wavefront reading 512 contiguous bytes of two such rows.  A goes through LDS
+// because a wavefront's 8 k of 32 rows are 32 bytes a row: fetched by the lanes that
+// multiply them, without LDS, layers took 1.0 to 1.65 times as long.  Both
+// operands through LDS, B row-major: 1064 tokens, top-2, d 500, f 400, 4 experts, up 30.5
+// us and down 18.5, now 27.4 and 17.0; 116 routes, f 2048, down 20.1, now 17.8, but up with its
+// five stages (d 152) 7.0, now 7.4.
+//
+// Pipeline.  While stage s multiplies, the A of stage s + 1 is read from LDS, that of
+// s + 2 is written there and the loads of s + 3 and s + 4 are in flight, one
 // barrier per stage.  The inner loop computes no addresses: a stage's position
 // goes into the scalar base, the lane's offset stays.
 //
-// Weights stay row-major as given ([W1 | W3 | W2] per expert).  A is read from
-// LDS as four consecutive k per lane, so matrix instruction q of a group of four
-// multiplies k = q and k = 4 + q, and B follows the same order.  Both LDS tiles
-// are padded so that all accesses are conflict-free.  Every XCD takes a
+// A is read from LDS as four consecutive k per lane, so matrix instruction q of a group of four
+// multiplies k = q and k = 4 + q, and B follows the same order.  The LDS tile
+// is padded so that all accesses are conflict-free.  Every XCD takes a
 // contiguous share of the tile list (expert -> column tile -> row tile), so that
 // the row tiles that share a weight panel run on one L2.
 //
@@ -46,23 +55,31 @@ constexpr int kF32Xcds = 8;
 
 size_t packed_bytes_f32(int E, int d, int f) { return (size_t)E * 3 * d * f * sizeof(float); }
 
+// per expert [W1 d*f | W3 d*f | W2 f*d]; a matrix of K rows and NC columns as [K / 4][NC][4]: the four k of a column side by side.
+// One thread per 16 bytes.
+__global__ __launch_bounds__(256) void pack_f32_kernel(const float* __restrict__ w1, const float* __restrict__ w3, const float* __restrict__ w2,
+                                                       int d, int f, long long units, long long total, float4* __restrict__ packed) {
+    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (o >= total) return;
+    const long long matrix = o / units, r = o - matrix * units, e = matrix / 3;      // units: 16-byte units of a matrix
+    const int which = (int)(matrix - 3 * e), NC = which == 2 ? d : f;
+    const long long q = r / NC;
+    const float* src = (which == 0 ? w1 : (which == 1 ? w3 : w2)) + e * units * 4 + q * 4 * NC + (r - q * NC);
+    packed[o] = make_float4(src[0], src[NC], src[2 * (size_t)NC], src[3 * (size_t)NC]);
+}
+
 int launch_pack_f32(const float* w1, const float* w3, const float* w2, int E, int d, int f, float* packed, hipStream_t s) {
-    // per expert: [W1 d*f | W3 d*f | W2 f*d], each matrix row-major as given
-    const size_t m = (size_t)d * f * sizeof(float);
-    const float* src[3] = {w1, w3, w2};
-    for (int i = 0; i < 3; ++i) {
-        hipError_t e = hipMemcpy2DAsync((char*)packed + i * m, 3 * m, src[i], m, m, E, hipMemcpyDeviceToDevice, s);
-        if (e != hipSuccess) return hip_fail(e, "moe_pack_weights copy");
-    }
-    return MOE_OK;
+    const long long units = (long long)d * f / 4, total = units * 3 * E, grid = (total + 255) / 256;
+    if (grid > 0x7FFFFFFFll) return fail(MOE_ERR_UNSUPPORTED, "moe_pack_weights: weights too large for one launch");
+    hipLaunchKernelGGL(pack_f32_kernel, dim3((unsigned)grid), dim3(256), 0, s, w1, w3, w2, d, f, units, total, (float4*)packed);
+    return check_launch("moe_pack_weights launch");
 }
 
 template <bool UP>
 __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ A, const float* __restrict__ packed,
                                                       int d, int f, float* __restrict__ C, const int32_t* __restrict__ plan) {
     constexpr int NP = UP ? 2 : 1;                                        // products
-    constexpr int AST = kF32Stage + 4, BST = kF32Tile + 8;                // row strides: 16 rows of A, and rows k and k + 4 of B, fall on distinct banks
-    constexpr int A_FLOATS = kF32Tile * AST, B_FLOATS = kF32Stage * BST, STAGE = A_FLOATS + NP * B_FLOATS;
+    constexpr int AST = kF32Stage + 4, STAGE = kF32Tile * AST;            // row stride: 16 rows of A fall on distinct banks
     constexpr int RED = kF32Waves * NP * 16 * 64;                         // partial sums [wavefront][product][16][64]
     static_assert(kF32Tile * kF32Stage == 4 * 256, "one 16-byte piece of each operand per thread and stage");
     __shared__ __attribute__((aligned(16))) float smem[2 * STAGE > RED ? 2 * STAGE : RED];
@@ -93,14 +110,15 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // A thread's piece of a stage: 4 consecutive k of a row of A, 4 columns of a k row of B.  Rows and columns past the
+    // A thread's piece of a stage: four consecutive k of a row of A and of a column of B.  The latter is what its lane multiplies:
+    // lane l of wavefront w holds the k from 8 w + 4 (l / 32) of row (column) l % 32.  Rows and columns past the
     // tile's end re-read its last ones (their outputs are never stored).  The last stage of a reduction that is no
     // multiple of 32 reads the last 32 k and counts those that came before it as zero; a reduction shorter than 32
     // re-reads its last k and counts that as zero.
-    const int ar = tid / 8, ak = (tid % 8) * 4, bk = tid / 8, bc = (tid % 8) * 4;
+    const int ar = tid / 8, ak = (tid % 8) * 4, bk = (tid / 32) * 4, bc = tid % 32;
     const int arow = min(ar, rows - 1);
     const uint32_t a_off = (uint32_t)(merged ? buffer_row(rm, arow) : arow) * (uint32_t)K + (uint32_t)min(ak, K - 4);
-    const uint32_t b_off = (uint32_t)min(bk, K - 1) * (uint32_t)NC + (uint32_t)min(n0 + bc, NC - 4);
+    const uint32_t b_off = (uint32_t)min(bk, K - 4) * (uint32_t)NC + 4u * (uint32_t)min(n0 + bc, NC - 1);
     const int k_last = max(K - kF32Stage, 0);
     struct Regs { float4 a, b[NP]; };
     auto fetch = [&](int s, Regs& r) {
@@ -109,69 +127,71 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
 #pragma unroll
         for (int p = 0; p < NP; ++p) r.b[p] = *reinterpret_cast<const float4*>(Bbase + (size_t)p * d * f + (size_t)k0 * NC + b_off);
     };
-    auto keep = [](const float4& v, bool in) { return make_float4(in ? v.x : 0.f, in ? v.y : 0.f, in ? v.z : 0.f, in ? v.w : 0.f); };
-    auto stage = [&](int s, Regs& r, float* buf) {
-        if ((s + 1) * kF32Stage > K) {                                    // wave-uniform: the ragged last stage only
-            const int k0 = min(s * kF32Stage, k_last), lo_k = s * kF32Stage - k0;
-            r.a = keep(r.a, ak >= lo_k && k0 + ak < K);
-#pragma unroll
-            for (int p = 0; p < NP; ++p) r.b[p] = keep(r.b[p], bk >= lo_k && k0 + bk < K);
-        }
-        *reinterpret_cast<float4*>(buf + ar * AST + ak) = r.a;
-#pragma unroll
-        for (int p = 0; p < NP; ++p) *reinterpret_cast<float4*>(buf + A_FLOATS + p * B_FLOATS + bk * BST + bc) = r.b[p];
+    // what counts of stage s: all, but in the ragged last one
+    auto keep = [&](int s, int k, float4& v) {
+        if ((s + 1) * kF32Stage <= K) return;                             // wave-uniform
+        const int k0 = min(s * kF32Stage, k_last);
+        const bool in = k >= s * kF32Stage - k0 && k0 + k < K;
+        v = make_float4(in ? v.x : 0.f, in ? v.y : 0.f, in ? v.z : 0.f, in ? v.w : 0.f);
     };
-    // this wavefront's operands of a stage: lane l holds row (column) l % 32 and the four k from 8 * wave + 4 * (l / 32)
-    struct Frags { float4 a; float b[NP][4]; };
+    auto stage = [&](int s, Regs& r, int buf, auto whole) {
+        if (!decltype(whole)::value) keep(s, ak, r.a);
+        *reinterpret_cast<float4*>(smem + buf * STAGE + ar * AST + ak) = r.a;
+    };
     const float* as = smem + (lane & 31) * AST + 8 * wave + 4 * (lane >> 5);
-    const float* bs = smem + A_FLOATS + (8 * wave + 4 * (lane >> 5)) * BST + (lane & 31);
-    auto read = [&](int buf, Frags& fr) {
-        fr.a = *reinterpret_cast<const float4*>(as + buf * STAGE);
-#pragma unroll
-        for (int p = 0; p < NP; ++p)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) fr.b[p][q] = bs[buf * STAGE + p * B_FLOATS + q * BST];
-    };
+    auto read = [&](int buf) { return *reinterpret_cast<const float4*>(as + buf * STAGE); };
     f32x16 acc[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[p][v] = 0.f;
-    auto multiply = [&](const Frags& fr) {
-        const float av[4] = {fr.a.x, fr.a.y, fr.a.z, fr.a.w};
+    auto multiply = [&](int s, const float4& a, Regs& r, auto whole) {
+        if (!decltype(whole)::value)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) keep(s, bk, r.b[p]);
+        const float av[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int p = 0; p < NP; ++p) acc[p] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[q], fr.b[p][q], acc[p], 0, 0, 0);
+            for (int p = 0; p < NP; ++p) {
+                const float bv[4] = {r.b[p].x, r.b[p].y, r.b[p].z, r.b[p].w};
+                acc[p] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[q], bv[q], acc[p], 0, 0, 0);
+            }
     };
 
     const int n_stage = (K + kF32Stage - 1) / kF32Stage;                  // stages past the end are fetched and staged, never multiplied
-    Regs even, odd;
-    Frags f0, f1;
-    fetch(0, even);
-    fetch(1, odd);
-    stage(0, even, smem);
-    fetch(2, even);
-    __syncthreads();
-    read(0, f0);
-    stage(1, odd, smem + STAGE);
-    fetch(3, odd);
-    __syncthreads();
-    for (int s = 0; s + 1 < n_stage; s += 2) {
-        read(1, f1);
+    Regs r[4];
+    float4 fa[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        fetch(i, r[i]);
         __builtin_amdgcn_sched_barrier(0);
-        multiply(f0);
-        stage(s + 2, even, smem);                                         // its previous contents were read before the last barrier
-        fetch(s + 4, even);
-        __syncthreads();
-        read(0, f0);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(f1);
-        stage(s + 3, odd, smem + STAGE);
-        fetch(s + 5, odd);
-        __syncthreads();
     }
-    if (n_stage & 1) multiply(f0);
+    const std::true_type whole;
+    const std::false_type ragged;
+    stage(0, r[0], 0, ragged);
+    __syncthreads();
+    fa[0] = read(0);
+    stage(1, r[1], 1, ragged);
+    __syncthreads();
+    auto step = [&](int s, int i, auto kind) {
+        fa[(i + 1) & 1] = read((i + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(s + i, fa[i & 1], r[i], kind);
+        stage(s + i + 2, r[(i + 2) & 3], i & 1, kind);                    // its previous contents were read before the last barrier
+        if (decltype(kind)::value || s + i + 4 < n_stage) fetch(s + i + 4, r[i]);
+        __syncthreads();
+    };
+    int s = 0;
+    for (; (s + 6) * kF32Stage <= K; s += 4)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) step(s, i, whole);
+    for (; s < n_stage; s += 4)                                           // the last ones
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (s + i >= n_stage) break;
+            step(s, i, ragged);
+        }
 
     // add the four partial sums in wavefront order; a wavefront finishes 4 of the 16 accumulator rows
     __syncthreads();                                                      // the stages have been read by everyone
@@ -215,13 +235,14 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
 // compiler would move the loads down to their use, hence the scheduling barriers.  Blocks of 16 rows past the bucket's
 // end are not multiplied.
 //
-// Bound by power for the up projection (the clock falls to 1.9 GHz) and by the loads and vector work of the narrower
-// tile for the down projection.  2000 routes in 8 skewed buckets, d 1024, f 2816, layer 369 us on the fp32 kernel, 302 here (311 on another box).  The look
-// at every operand (split_eight) is one instruction a pair; as a minimum of their magnitudes, three a pair, it made that 315.  Also
-// lost, the last four without that look (293 us, 4096 routes 501): B by buffer loads with the row in a scalar offset, which
-// saves the addresses but sends the 16 loads of a stage in one burst, 193 -> 202 us in the up projection; the remainders by
-// v_dot2_f32_bf16, exact and a sixth fewer vector instructions, 327 -> 341; both products staged through LDS 345;
-// tiles of 128 rows 309, 512; 128 columns in the down projection 305, 515; one stage in flight and four wavefronts a SIMD 291, 497, but 512 routes 174 for 147.
+// Bound by power for the up projection (the clock falls to 1.9 to 2.1 GHz) and by the loads and vector work of the narrower
+// tile for the down projection.  2000 routes in 8 skewed buckets, d 1024, f 2816, layer 369 us on the fp32 kernel; here, one change after
+// the other on one box: weights row-major, sixteen of a stage's eighteen loads four bytes wide, 301; the four k of a column side by side 287.
+// The look at every operand (split_eight) is one instruction a pair; as a minimum of their magnitudes, three a pair, it made 302 315.  Also
+// lost, with row-major weights and the last four without that look (293 us, 4096 routes 501): B by buffer loads with the row in a scalar
+// offset, 193 -> 202 us in the up projection; the remainders by v_dot2_f32_bf16, exact and a sixth fewer vector instructions,
+// 327 -> 341; both products staged through LDS 345; tiles of 128 rows 309, 512; 128 columns in the down projection 305, 515; one
+// stage in flight and four wavefronts a SIMD 291, 497, but 512 routes 174 for 147.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
@@ -301,17 +322,18 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
     const int kg = 8 * (lane >> 4), col = n0 + 16 * wave + (lane & 15), arow = min(16 * wave + (lane & 15), rows - 1);
     const uint32_t a_off = (uint32_t)(merged ? buffer_row(rm, arow) : arow) * (uint32_t)K + (uint32_t)kg;
     const uint32_t b_col = (uint32_t)min(col, NC - 1);
-    const uint32_t b_off = ((uint32_t)kg * (uint32_t)NC + b_col) * 4u;    // bytes
+    const uint32_t b_off = (uint32_t)kg * (uint32_t)NC + 4u * b_col;
     const int n_full = K / kSplitStage, n_stage = (K + kSplitStage - 1) / kSplitStage;
     struct Raw { float a[8], b[NP][8]; };
     auto fetch = [&](int s, Raw& r) {                                     // a whole stage
         const int k0 = s * kSplitStage;
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const float* b = Bbase + (size_t)p * d * f + (size_t)k0 * NC;
+        for (int p = 0; p < NP; ++p)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) r.b[p][u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b + (size_t)u * NC) + b_off);
-        }
+            for (int h = 0; h < 8; h += 4) {
+                const float4 q = *reinterpret_cast<const float4*>(Bbase + (size_t)p * d * f + (size_t)(k0 + h) * NC + b_off);
+                r.b[p][h] = q.x; r.b[p][h + 1] = q.y; r.b[p][h + 2] = q.z; r.b[p][h + 3] = q.w;
+            }
 #pragma unroll
         for (int h = 0; h < 8; h += 4) {
             const float4 q = *reinterpret_cast<const float4*>(Abase + k0 + (a_off + h));
@@ -322,10 +344,11 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
 #pragma unroll
         for (int p = 0; p < NP; ++p)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = s * kSplitStage + kg + u;
-                const float q = Bbase[(size_t)p * d * f + (size_t)min(k, K - 1) * NC + b_col];
-                r.b[p][u] = k < K ? q : 0.f;
+            for (int h = 0; h < 8; h += 4) {
+                const int k = s * kSplitStage + kg + h;
+                const float4 q = *reinterpret_cast<const float4*>(Bbase + (size_t)p * d * f + (size_t)min(k, K - 4) * NC + 4u * b_col);
+                const bool in = k < K;
+                r.b[p][h] = in ? q.x : 0.f; r.b[p][h + 1] = in ? q.y : 0.f; r.b[p][h + 2] = in ? q.z : 0.f; r.b[p][h + 3] = in ? q.w : 0.f;
             }
 #pragma unroll
         for (int h = 0; h < 8; h += 4) {
@@ -491,12 +514,10 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
                 const float4 t = *reinterpret_cast<const float4*>(a_row + at);
                 q.a[j] = make_float4(in ? t.x : 0.f, in ? t.y : 0.f, in ? t.z : 0.f, in ? t.w : 0.f);
 #pragma unroll
-                for (int p = 0; p < NP; ++p)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float t = Bbase[(size_t)p * d * f + (size_t)(at + i) * NC + b_col];
-                        q.b[p][j][i] = in ? t : 0.f;
-                    }
+                for (int p = 0; p < NP; ++p) {
+                    const float4 w = *reinterpret_cast<const float4*>(Bbase + (size_t)p * d * f + (size_t)at * NC + 4u * b_col);
+                    q.b[p][j][0] = in ? w.x : 0.f; q.b[p][j][1] = in ? w.y : 0.f; q.b[p][j][2] = in ? w.z : 0.f; q.b[p][j][3] = in ? w.w : 0.f;
+                }
             }
         };
         f32x4 sum[4][NP];

@@ -237,7 +237,8 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
 //
 // Bound by power for the up projection (the clock falls to 1.9 to 2.1 GHz) and by the loads and vector work of the narrower
 // tile for the down projection.  2000 routes in 8 skewed buckets, d 1024, f 2816, layer 369 us on the fp32 kernel; here, one change after
-// the other on one box: weights row-major, sixteen of a stage's eighteen loads four bytes wide, 301; the four k of a column side by side 287.
+// the other on one box: weights row-major, sixteen of a stage's eighteen loads four bytes wide, 301; the four k of a column side by side 287;
+// ragged tiles last (split_tile) 279.
 // The look at every operand (split_eight) is one instruction a pair; as a minimum of their magnitudes, three a pair, it made 302 315.  Also
 // lost, with row-major weights and the last four without that look (293 us, 4096 routes 501): B by buffer loads with the row in a scalar
 // offset, 193 -> 202 us in the up projection; the remainders by v_dot2_f32_bf16, exact and a sixth fewer vector instructions,
@@ -286,6 +287,67 @@ __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&piece)[
 }
 constexpr uint32_t kSplitLost = 0xFFFFu;
 
+// Which tile a workgroup owns: listed bucket, first row in it, column tile.  Every XCD first walks its contiguous share of the
+// full row tiles (bucket -> column tile -> row tile: those that share a weight panel run on one L2), then the buckets' last,
+// ragged ones, those of more 16-row blocks first, of which every XCD has the same mix.  The short ones run last because two or
+// three workgroups share a compute unit: one more full tile at the end keeps its compute unit busy for half as long again as the others.
+// Called by whole wavefronts, a lane per bucket.
+__device__ __forceinline__ bool split_tile(const int32_t* __restrict__ plan, int NT, int& bucket, int& r0, int& nt) {
+    const int n_listed = plan[0], lane = threadIdx.x & 63, x = blockIdx.x % kF32Xcds;
+    const long long slot = blockIdx.x / kF32Xcds;
+    const auto rows_of = [&](int i) { return i < n_listed ? plan[kPlanCount + i] : 0; };
+    const int rows0 = rows_of(lane);                                      // the first 64 buckets, mostly all there are
+    const auto rows_at = [&](int c) { return c == 0 ? rows0 : rows_of(c + lane); };
+    int ragged = 0;
+    for (int c = 0; c < n_listed; c += 64) ragged += __builtin_popcountll(__ballot(rows_at(c) % kF32SplitRows != 0));
+    const long long full = (long long)(plan[2] - ragged) * NT, per_xcd = (full + kF32Xcds - 1) / kF32Xcds, first = x * per_xcd;
+    const long long here = first >= full ? 0 : (full - first < per_xcd ? full - first : per_xcd);
+    if (slot < here) {
+        const long long t = first + slot;
+        int before = 0;                                                   // full row tiles of the buckets already passed
+        for (int c = 0; c < n_listed; c += 64) {
+            const int mine = rows_at(c) / kF32SplitRows;
+            int sum = mine;
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) {
+                const int o = __shfl_up(sum, m, 64);
+                sum += lane >= m ? o : 0;
+            }
+            const int i = __builtin_popcountll(__ballot((long long)(before + sum) * NT <= t));
+            if (i < 64) {
+                const int tiles = __builtin_amdgcn_readlane(mine, i), start = before + __builtin_amdgcn_readlane(sum, i) - tiles;
+                const int rem = (int)(t - (long long)start * NT);
+                bucket = c + i;
+                nt = rem / tiles;
+                r0 = (rem - nt * tiles) * kF32SplitRows;
+                return true;
+            }
+            before += __builtin_amdgcn_readlane(sum, 63);
+        }
+        return false;
+    }
+    const long long t = (slot - here) * kF32Xcds + x;
+    if (t >= (long long)ragged * NT) return false;
+    int rank = (int)(t / NT);
+    nt = (int)(t - (long long)rank * NT);
+    for (int blocks = kSplitBlocks; blocks > 0; --blocks)
+        for (int c = 0; c < n_listed; c += 64) {
+            const int rows = rows_at(c), over = rows % kF32SplitRows;
+            unsigned long long of_size = __ballot((over + 15) / 16 == blocks && over != 0);
+            const int count = __builtin_popcountll(of_size);
+            if (rank >= count) {
+                rank -= count;
+                continue;
+            }
+            for (; rank > 0; --rank) of_size &= of_size - 1;
+            const int i = __builtin_ctzll(of_size);
+            bucket = c + i;
+            r0 = __builtin_amdgcn_readlane(rows - over, i);
+            return true;
+        }
+    return false;
+}
+
 template <bool UP>
 __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __restrict__ A, const float* __restrict__ packed,
                                                                int d, int f, float* __restrict__ C, const int32_t* __restrict__ plan) {
@@ -294,20 +356,8 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
     const int K = UP ? d : f, NC = UP ? f : d;
     const int NT = (NC + kSplitCols - 1) / kSplitCols;
 
-    // which tile: as above, by the tiles of kF32SplitRows rows
-    const int32_t* prefix = plan + kPlanTiles1;
-    const int n_listed = plan[0];
-    const long long total = (long long)prefix[n_listed] * NT, per_xcd = (total + kF32Xcds - 1) / kF32Xcds;
-    const long long slot = blockIdx.x / kF32Xcds, t = (long long)(blockIdx.x % kF32Xcds) * per_xcd + slot;
-    if (slot >= per_xcd || t >= total) return;
-    int lo = 0, hi = n_listed - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if ((long long)prefix[mid] * NT <= t) lo = mid; else hi = mid - 1;
-    }
-    const int mt_e = prefix[lo + 1] - prefix[lo];
-    const int rem = (int)(t - (long long)prefix[lo] * NT);
-    const int nt = rem / mt_e, r0 = (rem - nt * mt_e) * kF32SplitRows;
+    int lo, r0, nt;
+    if (!split_tile(plan, NT, lo, r0, nt)) return;
     const int rows = min(kF32SplitRows, plan[kPlanCount + lo] - r0), n0 = nt * kSplitCols;
     const RowMap rm = row_map<true>(plan, lo, r0, rows);
     const bool merged = rm.merged;
@@ -574,7 +624,8 @@ int launch_ffn_f32(const float* a, int N, int d, int f, int E, const float* pack
     const bool split = local_gpu < 0 && split_pays(N, d, f, E);
     const int tile_rows = split ? kF32SplitRows : kF32Tile, tile_cols = split ? kSplitCols : kF32Tile;
     const long long mt_max = (N + tile_rows - 1) / tile_rows + (E < N ? E : N);   // sum of ceil(n_e / tile_rows) never exceeds this
-    auto grid_for = [&](int columns) { return (mt_max * ((columns + tile_cols - 1) / tile_cols) + kF32Xcds - 1) / kF32Xcds * kF32Xcds; };
+    // (the split kernel's two shares of an XCD are rounded up one by one)
+    auto grid_for = [&](int columns) { return (mt_max * ((columns + tile_cols - 1) / tile_cols) + (split ? 2 : 1) * kF32Xcds - 1) / kF32Xcds * kF32Xcds; };
     const auto up = split ? &ffn_f32_split_kernel<true> : &ffn_f32_kernel<true>, down = split ? &ffn_f32_split_kernel<false> : &ffn_f32_kernel<false>;
     if (grid_for(f) > 0x7FFFFFFFll || grid_for(d) > 0x7FFFFFFFll)
         return fail(MOE_ERR_UNSUPPORTED, "moe_expert_ffn_grouped: too many tiles for one launch");

@@ -231,19 +231,20 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
 // A workgroup owns 64 rows x 64 columns of outputs, a wavefront 16 columns of it (of both products in the up
 // projection).  B goes from memory into the lanes that multiply it, 8 k of a column each, and is split there; A is
 // needed by all four wavefronts, so each splits 16 rows and hands the pieces on through LDS in operand order.
-// While a stage multiplies, the next is split and the one after is in flight, one barrier per stage; the
-// compiler would move the loads down to their use, hence the scheduling barriers.  Blocks of 16 rows past the bucket's
+// Between the products of a stage the next one is split, and the one after is in flight, one barrier per stage; the
+// compiler would move the loads down to their use, and all products behind all of the split, hence the scheduling barriers.  Blocks of 16 rows past the bucket's
 // end are not multiplied.
 //
 // Bound by power for the up projection (the clock falls to 1.9 to 2.1 GHz) and by the loads and vector work of the narrower
 // tile for the down projection.  2000 routes in 8 skewed buckets, d 1024, f 2816, layer 369 us on the fp32 kernel; here, one change after
 // the other on one box: weights row-major, sixteen of a stage's eighteen loads four bytes wide, 301; the four k of a column side by side 287;
-// ragged tiles last (split_tile) 279.
-// The look at every operand (split_eight) is one instruction a pair; as a minimum of their magnitudes, three a pair, it made 302 315.  Also
+// ragged tiles last (split_tile) 279; the split of a stage between the products of the one before (stage) 270.
+// The look at every operand (split_pair) is one instruction a pair; as a minimum of their magnitudes, three a pair, it made 302 315.  Also
 // lost, with row-major weights and the last four without that look (293 us, 4096 routes 501): B by buffer loads with the row in a scalar
 // offset, 193 -> 202 us in the up projection; the remainders by v_dot2_f32_bf16, exact and a sixth fewer vector instructions,
 // 327 -> 341; both products staged through LDS 345; tiles of 128 rows 309, 512; 128 columns in the down projection 305, 515; one
-// stage in flight and four wavefronts a SIMD 291, 497, but 512 routes 174 for 147.
+// stage in flight and four wavefronts a SIMD 291, 497, but 512 routes 174 for 147.  Four stages of values under way where a tile has one
+// block of rows: nothing gained (25 us a tile), and the registers cost the other tiles a workgroup a compute unit.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
@@ -269,21 +270,21 @@ static bool split_pays(int N, int d, int f, int E) {
 
 // 8 fp32 values -> their three bf16 pieces.  What is left of a value for the third piece has bits below that piece's last one
 // exactly if the three do not add up to the value (a magnitude below 2^-110 whose last bit lies under 2^-133): lost collects them.
+__device__ __forceinline__ void split_pair(float a, float b, u32x4 (&piece)[3], int i, uint32_t& lost) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const f32x2 pair = {a, b};
+        const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2));
+        piece[p][i] = h;
+        a -= __uint_as_float(h << 16);
+        b -= __uint_as_float(h & 0xFFFF0000u);
+    }
+    piece[2][i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);     // the upper halves
+    lost |= __float_as_uint(a) | __float_as_uint(b);
+}
 __device__ __forceinline__ void split_eight(const float (&v)[8], u32x4 (&piece)[3], uint32_t& lost) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float a = v[2 * i], b = v[2 * i + 1];
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const f32x2 pair = {a, b};
-            const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2));
-            piece[p][i] = h;
-            a -= __uint_as_float(h << 16);
-            b -= __uint_as_float(h & 0xFFFF0000u);
-        }
-        piece[2][i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);     // the upper halves
-        lost |= __float_as_uint(a) | __float_as_uint(b);
-    }
+    for (int i = 0; i < 4; ++i) split_pair(v[2 * i], v[2 * i + 1], piece, i, lost);
 }
 constexpr uint32_t kSplitLost = 0xFFFFu;
 
@@ -458,6 +459,63 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
                             for (int v = 0; v < 4; ++v) acc[m0 + m][p][v] += sum[m][p][v];
             }
         };
+        // The products of one stage, and between them the split of the next: a matrix instruction keeps the matrix pipe busy for 16
+        // cycles, in which the wavefront issues three or four vector instructions.
+        auto stage = [&](const Frags& fr, int buf, const Raw& raw, Frags& next, int next_buf) {
+            constexpr int H = (NA + MG - 1) / MG, G = 6 * H, U = 4 + 4 * NP;       // groups of row blocks; of matrix instructions; pairs of values to split
+            constexpr int piece_a[6] = {2, 0, 1, 1, 0, 0}, piece_b[6] = {0, 2, 1, 0, 1, 0};
+            u32x4 a[2][MG][3], pa[3];
+            f32x4 sum[2][MG][NP];
+            auto read = [&](int h) {
+#pragma unroll
+                for (int m = 0; m < MG; ++m)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) a[h & 1][m][q] = smem[buf * A_UNITS + (q * kSplitBlocks + min(h * MG + m, NA - 1)) * 64 + lane];
+            };
+            auto add = [&](int h, int m, int p) {
+                if (h * MG + m < NA)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[h * MG + m][p][v] += sum[h & 1][m][p][v];
+            };
+            read(0);
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+#pragma unroll
+                for (int q = 0; q < 6; ++q) {
+                    const int g = 6 * h + q;
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int m = 0; m < MG; ++m)
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+                            if (h * MG + m < NA)
+                                sum[h & 1][m][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[h & 1][m][piece_a[q]]),
+                                                                                           __builtin_bit_cast(bf16x8, fr.b[p][piece_b[q]]),
+                                                                                           q == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum[h & 1][m][p], 0, 0, 0);
+                    if (q == 1 && h + 1 < H) read(h + 1);
+#pragma unroll
+                    for (int u = g * U / G; u < (g + 1) * U / G; ++u) {
+                        if (u < 4) split_pair(raw.a[2 * u], raw.a[2 * u + 1], pa, u, a_lost);
+                        else split_pair(raw.b[(u - 4) / 4][2 * (u % 4)], raw.b[(u - 4) / 4][2 * (u % 4) + 1], next.b[(u - 4) / 4], u % 4, b_lost);
+                        if (u == 3)
+#pragma unroll
+                            for (int i = 0; i < 3; ++i) smem[next_buf * A_UNITS + (i * kSplitBlocks + wave) * 64 + lane] = pa[i];
+                    }
+                    if (h > 0 && q < MG * NP) add(h - 1, q / NP, q % NP);
+#pragma unroll
+                    for (int i = 0; i < MG * NP; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                        if (UP && h == 0) __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);
+                        else __builtin_amdgcn_sched_group_barrier(0x2, 4, 0);
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < MG; ++m)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) add(H - 1, m, p);
+        };
         Raw even, odd;
         Frags f0, f1;
         auto get = [&](int s, Raw& r) { if (s < n_full) fetch(s, r); else if (s < n_stage) fetch_last(s, r); };
@@ -469,13 +527,11 @@ __global__ __launch_bounds__(256, 2) void ffn_f32_split_kernel(const float* __re
         for (; s + 3 < n_full; s += 2) {
             fetch(s + 2, even);
             __builtin_amdgcn_sched_barrier(0);
-            convert(odd, f1, 1);                                          // its LDS was read before the last barrier
-            multiply(f0, 0);
+            stage(f0, 0, odd, f1, 1);                                     // its LDS was read before the last barrier
             __syncthreads();
             fetch(s + 3, odd);
             __builtin_amdgcn_sched_barrier(0);
-            convert(even, f0, 0);
-            multiply(f1, 1);
+            stage(f1, 1, even, f0, 0);
             __syncthreads();
         }
         // Keeps the sums' additions in the block of the products that they read: moved into the block after the branch, two

@@ -35,7 +35,8 @@ static_assert(kPlanInts * sizeof(int32_t) <= kPlanBytes, "plan area too small");
 //             them), [10], [11] this GPU's range of the sorted rows (only in a layer call that may have such rows; the first two
 //             are written by the row copy: ffn_late.h)
 constexpr int kPlanSmallTiles = 4, kPlanBigParts = 5, kPlanSmallParts = 6, kPlanMerged = 7;
-constexpr int kPlanLateUp = 8, kPlanLateDown = 9, kPlanOwnBegin = 10, kPlanOwnEnd = 11;
+//         [12] row tiles of height bm1 in buckets of several, if the buckets of one are at least as many (mixed_tile in ffn_tiles.h); else 0
+constexpr int kPlanLateUp = 8, kPlanLateDown = 9, kPlanOwnBegin = 10, kPlanOwnEnd = 11, kPlanMixed = 12;
 
 // Merged buckets.  On the receive side an expert's rows arrive as one segment per source GPU.  As buckets of their own
 // they stream the expert's weights once per segment and end in a ragged tile each, so segments of one expert form one
@@ -125,7 +126,7 @@ constexpr int kSkinnyRows = 64;                         // rows a pass of its st
 struct PlanScratch {
     int cnt[MOE_MAX_EXPERTS], tiles0[MOE_MAX_EXPERTS], tiles1[MOE_MAX_EXPERTS], segs[MOE_MAX_EXPERTS];
     int rank[MOE_MAX_EXPERTS], rows[MOE_MAX_EXPERTS], pre0[MOE_MAX_EXPERTS], pre1[MOE_MAX_EXPERTS], pre_segs[MOE_MAX_EXPERTS];
-    int n, n_small, total1;
+    int n, n_small, n_single, total1;
     int first_row[MOE_MAX_EXPERTS / 64];                 // of the groups of a wavefront with rows (only when the range of all is asked for)
 };
 
@@ -172,7 +173,7 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
         s.segs[e] = n_segs;
         s.rank[e] = s.rows[e] = s.pre0[e] = s.pre1[e] = s.pre_segs[e] = 0;
     }
-    if (e == 0) s.n = s.n_small = s.total1 = 0;
+    if (e == 0) s.n = s.n_small = s.n_single = s.total1 = 0;
     if (range && e < MOE_MAX_EXPERTS) {                  // the groups with rows lie side by side, by number
         const unsigned long long some = __ballot(c > 0);
         if ((e & 63) == (some ? __builtin_ctzll(some) : 0)) s.first_row[e >> 6] = some ? st : 0x7FFFFFFF;
@@ -182,6 +183,7 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
         atomicAdd(&s.n, 1);
         atomicAdd(&s.total1, s.tiles1[e]);
         if (c - (s.tiles1[e] - 1) * shape.bm1 <= kSmallTileRows) atomicAdd(&s.n_small, 1);
+        if (c <= shape.bm1) atomicAdd(&s.n_single, 1);
     }
     int ebits = 0;
     while ((1 << ebits) < E) ++ebits;
@@ -235,6 +237,7 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
             plan[3] = choice;
             plan[kPlanSmallTiles] = 1 + n_small;
             plan[kPlanMerged] = merged;
+            plan[kPlanMixed] = 2 * s.n_single >= t1 ? t1 - s.n_single : 0;
             plan[kPlanTiles0 + n] = t0;
             plan[kPlanTiles1 + n] = t1;
             if (range) {
@@ -246,7 +249,7 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
             }
         }
     } else if (n == 0 && e == 0) {
-        plan[0] = plan[1] = plan[2] = plan[kPlanMerged] = 0;
+        plan[0] = plan[1] = plan[2] = plan[kPlanMerged] = plan[kPlanMixed] = 0;
         plan[3] = shape.choice >= 0 ? shape.choice : 0;
         plan[kPlanSmallTiles] = 1;
         plan[kPlanTiles0] = plan[kPlanTiles1] = 0;

@@ -21,18 +21,33 @@ __device__ __forceinline__ float from_orderable(uint32_t o) {
 // ---- two or more lanes per token: sorted lists ------------------------------------------------------------------
 // A candidate is one double whose bit pattern orders as (key, lower expert first): a biased exponent of 1, then the 32
 // bits of the key and 255 - expert.  No two are equal, so the selection is nothing but v_max_f64 / v_min_f64 (full
-// rate on this chip) without an index beside the value; an empty slot is 0.0, below every candidate.
-__device__ __forceinline__ double candidate(float v, int e) {
-    const uint32_t key = orderable(v);
-    return __builtin_bit_cast(double, ((uint64_t)(0x00100000u | (key >> 24)) << 32) | ((key << 8) | (uint32_t)(255 - e)));
+// rate on this chip) without an index beside the value; an empty slot has a biased exponent of 0, below every candidate.
+// flipped = 255 - expert.  Nothing here branches: a logit that is not there is made an empty slot at the end.
+__device__ __forceinline__ double candidate(float v, uint32_t flipped, bool have) {
+    const uint32_t u = __float_as_uint(v + 0.0f);             // -0.0 and +0.0 tie
+    const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+    const uint32_t hi = 0x00100000u | (key >> 24);
+    return __builtin_bit_cast(double, ((uint64_t)(have ? hi : 0u) << 32) | ((key << 8) | flipped));
 }
 __device__ __forceinline__ int candidate_expert(double c) { return 255 - (int)(__builtin_bit_cast(uint64_t, c) & 255u); }
 __device__ __forceinline__ float candidate_logit(double c) { return from_orderable((uint32_t)(__builtin_bit_cast(uint64_t, c) >> 8)); }
 
+// The larger and the smaller of two candidates.  Written out because the compiler, for which they may be signalling NaNs,
+// would pass what comes from another lane or from integer arithmetic through an instruction of its own first.
+__device__ __forceinline__ double larger(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double smaller(double a, double b) {
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
 __device__ __forceinline__ void order_pair(double& hi, double& lo) {
     const double a = hi, b = lo;
-    hi = __builtin_fmax(a, b);
-    lo = __builtin_fmin(a, b);
+    hi = larger(a, b);
+    lo = smaller(a, b);
 }
 
 // bitonic a[0..K) -> descending
@@ -45,25 +60,24 @@ __device__ __forceinline__ void merge_bitonic(double (&a)[K]) {
             if ((i & st) == 0) order_pair(a[i], a[i | st]);
 }
 
+// Batcher's odd-even merge sort (Knuth, The Art of Computer Programming, volume 3, 5.2.2, Algorithm M): 19 exchanges for 8
+// values, a bitonic sort has 24
 template <int K>
 __device__ __forceinline__ void sort_descending(double (&a)[K]) {
 #pragma unroll
-    for (int sz = 2; sz <= K; sz <<= 1)
+    for (int p = 1; p < K; p <<= 1)
 #pragma unroll
-        for (int st = sz >> 1; st > 0; st >>= 1)
+        for (int st = p; st > 0; st >>= 1)
 #pragma unroll
-            for (int i = 0; i < K; ++i)
-                if ((i & st) == 0) {
-                    if ((i & sz) == 0 || sz == K) order_pair(a[i], a[i | st]);
-                    else order_pair(a[i | st], a[i]);
-                }
+            for (int i = 0; i + st < K; ++i)
+                if (i >= st % p && (i - st % p) % (2 * st) < st && i / (2 * p) == (i + st) / (2 * p)) order_pair(a[i], a[i + st]);
 }
 
 // the K largest of two descending lists, descending
 template <int K>
 __device__ __forceinline__ void keep_largest(double (&a)[K], const double (&b)[K]) {
 #pragma unroll
-    for (int i = 0; i < K; ++i) a[i] = __builtin_fmax(a[i], b[K - 1 - i]);
+    for (int i = 0; i < K; ++i) a[i] = larger(a[i], b[K - 1 - i]);
     merge_bitonic<K>(a);
 }
 
@@ -76,6 +90,20 @@ __device__ __forceinline__ double lane_across(double v) {
     const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, ctrl, 0xF, 0xF, true);
     const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), ctrl, 0xF, 0xF, true);
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// lane i's value, in every lane of its group of L
+template <int L>
+__device__ __forceinline__ float of_lane(float v, int i) {
+    if constexpr (L == 2 || L == 4) {
+        const int w = __float_as_int(v);
+        const int r = L == 2 ? (i == 0 ? __builtin_amdgcn_mov_dpp(w, 0xA0, 0xF, 0xF, true) : __builtin_amdgcn_mov_dpp(w, 0xF5, 0xF, 0xF, true))
+                    : i == 0 ? __builtin_amdgcn_mov_dpp(w, 0x00, 0xF, 0xF, true) : i == 1 ? __builtin_amdgcn_mov_dpp(w, 0x55, 0xF, 0xF, true)
+                    : i == 2 ? __builtin_amdgcn_mov_dpp(w, 0xAA, 0xF, 0xF, true) : __builtin_amdgcn_mov_dpp(w, 0xFF, 0xF, 0xF, true);
+        return __int_as_float(r);
+    } else {
+        return __shfl(v, ((threadIdx.x & 63) & ~(L - 1)) + i, 64);
+    }
 }
 
 template <int M, int L, int K>
@@ -100,17 +128,26 @@ template <int L, int KMAX> constexpr int kGateSlots = (KMAX + L - 1) / L;
 //
 // Bound by instructions: one lane alone (E <= 8) takes k rounds of a scan that carries the index; several lanes sort
 // their candidates in lists of KMAX, merge the lists across lanes and share the exponentials, divisions and stores.
-// Rounds of a scan and a shuffle butterfly took 18.9 us for 100003 tokens, E = 64, k = 6; this takes 11.4 us.
-template <int L, int VPL, int KMAX, bool ALL, class Emit>
-__device__ __forceinline__ void gate_select_emit(const float* row, bool padded, int sub, bool live, int E, int k, Emit emit) {
+// Rounds of a scan and a shuffle butterfly took 18.9 us for 100003 tokens, E = 64, k = 6; bitonic sorts, a branch for each logit
+// and doubles that the compiler had quieted 11.1; candidates without branches, fewer exchanges and those written out 9.3; and without the
+// question which logits exist where all do (FULL) 8.8.
+// FULL: E == L * VPL.
+template <int L, int VPL, int KMAX, bool ALL, bool FULL, class Emit>
+__device__ __forceinline__ void gate_select_lanes(const float* row, bool padded, int sub, bool live, int E, int k, Emit emit) {
     static_assert(L >= 1 && L <= 16 && (KMAX & (KMAX - 1)) == 0 && MOE_MAX_EXPERTS <= 256, "DPP rows of 16 lanes, bitonic lists, 8-bit experts");
     constexpr int S = kGateSlots<L, KMAX>;
     const int e0 = sub * 4;                         // first logit of this lane; its i-th one is e0 + (i / 4) * 4 L + i % 4
     float v[VPL];
     bool have[VPL];
 #pragma unroll
-    for (int i = 0; i < VPL; ++i) { v[i] = 0.f; have[i] = live && e0 + (i / 4) * (4 * L) + i % 4 < E; }
-    if (live) {
+    for (int i = 0; i < VPL; ++i) { v[i] = 0.f; have[i] = FULL || (live && e0 + (i / 4) * (4 * L) + i % 4 < E); }
+    if (FULL) {                                     // a lane without a token selects from a row that exists, for nobody
+#pragma unroll
+        for (int c = 0; c < VPL / 4; ++c) {
+            const float4 q = *reinterpret_cast<const float4*>(row + e0 + 4 * L * c);
+            v[4 * c] = q.x; v[4 * c + 1] = q.y; v[4 * c + 2] = q.z; v[4 * c + 3] = q.w;
+        }
+    } else if (live) {
         if (padded || (E & 3) == 0) {
 #pragma unroll
             for (int c = 0; c < VPL / 4; ++c) {
@@ -162,18 +199,17 @@ __device__ __forceinline__ void gate_select_emit(const float* row, bool padded, 
             }
         }
     } else {
+        static_assert((L & (L - 1)) == 0, "the lane and the place in it are bits of their own in an expert's number");
+        const auto slot = [&](int i) { return i < VPL ? candidate(v[i < VPL ? i : 0], (uint32_t)(255 ^ e0) ^ (uint32_t)((i / 4) * (4 * L) + i % 4), have[i < VPL ? i : 0]) : 0.0; };
         double best[KMAX];
 #pragma unroll
-        for (int i = 0; i < KMAX; ++i) best[i] = i < VPL && have[i < VPL ? i : 0] ? candidate(v[i < VPL ? i : 0], e0 + (i / 4) * (4 * L) + i % 4) : 0.0;
+        for (int i = 0; i < KMAX; ++i) best[i] = slot(i);
         sort_descending<KMAX>(best);
 #pragma unroll
         for (int i0 = KMAX; i0 < VPL; i0 += KMAX) {
             double more[KMAX];
 #pragma unroll
-            for (int u = 0; u < KMAX; ++u) {
-                const int i = i0 + u;
-                more[u] = i < VPL && have[i < VPL ? i : 0] ? candidate(v[i < VPL ? i : 0], e0 + (i / 4) * (4 * L) + i % 4) : 0.0;
-            }
+            for (int u = 0; u < KMAX; ++u) more[u] = slot(i0 + u);
             sort_descending<KMAX>(more);
             keep_largest<KMAX>(best, more);
         }
@@ -196,15 +232,20 @@ __device__ __forceinline__ void gate_select_emit(const float* row, bool padded, 
             p_sel[i] = expf(candidate_logit(mine) - top);
         }
         if (!ALL) {
-            const int base = (threadIdx.x & 63) & ~(L - 1);
 #pragma unroll
             for (int j = 0; j < KMAX; ++j) {        // summed in slot order, in every lane
-                const float p = __shfl(p_sel[j / L], base + j % L, 64);
+                const float p = of_lane<L>(p_sel[j / L], j % L);
                 if (j < k) denom += p;
             }
         }
     }
     if (live) emit(e_sel, p_sel, denom);
+}
+
+template <int L, int VPL, int KMAX, bool ALL, class Emit>
+__device__ __forceinline__ void gate_select_emit(const float* row, bool padded, int sub, bool live, int E, int k, Emit emit) {
+    if (L > 1 && E == L * VPL) gate_select_lanes<L, VPL, KMAX, ALL, (L > 1)>(row, padded, sub, live, E, k, emit);
+    else gate_select_lanes<L, VPL, KMAX, ALL, false>(row, padded, sub, live, E, k, emit);
 }
 
 // writes this lane's slots of topk_idx[t][0..k) and topk_w[t][0..k)

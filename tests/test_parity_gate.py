@@ -46,6 +46,22 @@ def test_many_exact_ties_and_signed_zeros(lib, E, k):
     check(lib, np.full((64, E), -0.0, dtype=np.float32), k)
 
 
+@pytest.mark.parametrize("E,k", [(16, 4), (32, 8), (63, 6), (64, 6), (64, 16), (128, 8), (256, 16)])
+def test_masked_logits_and_denormals_in_lists(lib, E, k):
+    """Experts masked with -inf or the lowest value stay above the empty slots of the lists, by expert among themselves; a
+    negative zero ties with a positive one and denormals keep their order.  Weights as NumPy gives them."""
+    rng = np.random.default_rng(E + k)
+    lg = rng.standard_normal((301, E)).astype(np.float32)
+    lg[:, rng.permutation(E)[: E - k // 2]] = -np.inf                    # fewer experts left than are selected
+    lg[100:200][np.isinf(lg[100:200])] = np.finfo(np.float32).min
+    lg[200:] = rng.choice(np.array([-0.0, 0.0, 1e-44, -1e-44, 1e-39, -1e-39], dtype=np.float32), (101, E))
+    gi, gw = run_gate(lib, lg, k)
+    order = np.argsort(-lg.astype(np.float64), axis=1, kind="stable")[:, :k]
+    np.testing.assert_array_equal(gi, order)
+    p = np.exp(np.take_along_axis(lg.astype(np.float64), order, 1) - np.max(lg, axis=1, keepdims=True))
+    np.testing.assert_allclose(gw, p / p.sum(axis=1, keepdims=True), rtol=1e-5, atol=1e-30)
+
+
 @pytest.mark.parametrize("E,k", [(9, 1), (12, 3), (16, 16), (17, 2), (32, 9), (33, 8), (63, 7), (64, 16), (65, 4), (100, 2), (128, 8), (129, 9),
                                  (255, 16), (256, 1), (256, 8)])
 def test_every_lane_layout_and_list_length_with_ties(lib, E, k):

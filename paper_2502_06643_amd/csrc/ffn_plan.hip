@@ -27,13 +27,14 @@ __global__ __launch_bounds__(kPlanThreads) void ffn_plan_kernel(const int32_t* _
         // a bucket that does not lie inside [0,N), or names weights that do not exist, is ignored rather than trusted
         if (!local || c <= 0 || st < 0 || (long long)st + c > N || (unsigned)wt >= (unsigned)n_weights) c = 0;
     }
+    int n = 0;                                    // groups with rows
     if (merge != 0) {
         if (e < MOE_MAX_EXPERTS) {
             ms.wt[e] = wt;
             ms.cnt[e] = c;
             ms.off[e] = ms.idx[e] = ms.rows[e] = ms.segs[e] = 0;
         }
-        const int n = __syncthreads_count(c > 0);
+        n = __syncthreads_count(c > 0);
         if (c > 0) {
             atomicAdd(&ms.rows[wt], c);
             atomicAdd(&ms.segs[wt], 1);
@@ -101,8 +102,7 @@ __global__ __launch_bounds__(kPlanThreads) void ffn_plan_kernel(const int32_t* _
         plan[kPlanSegOff + j] = ms.off[e];
         plan[kPlanSegDelta + j] = st - ms.off[e];
     }
-    const int n_segs = __syncthreads_count(c > 0);
-    if (e == 0) plan[kPlanSegOff + n_segs] = 0;
+    if (e == 0) plan[kPlanSegOff + n] = 0;        // (a count here instead waited for the stores: 0.7 to 1.9 us)
 }
 
 // Which bf16 batches run the weight-streaming kernels: up to kFfnSkinnyMaxRows routes all of them (measured at that limit), and

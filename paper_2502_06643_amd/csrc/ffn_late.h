@@ -3,8 +3,8 @@
 // fewer output tiles here than the chip has compute units, so those rows are left to the workgroups that would be
 // idle in the two projections, as many as these copy in the time of a tile.
 //
-// 8192 tokens, 64 experts, top-6, 8 of them here, d 2048, f 1408: row copy 39 -> 14 us, projections 50 + 37 -> 59 + 50 (the copies
-// take bandwidth from the tiles), layer 151 -> 143.  Stores that stay out of the caches: 3 us less than without.  Random layers, with
+// 8192 tokens, 64 experts, top-6, 8 of them here, d 2048, f 1408: row copy 39 -> 14 us (9 since it looks this GPU's rows up in the sorted
+// order), projections 50 + 37 -> 59 + 50 (the copies take bandwidth from the tiles), layer 151 -> 143 (139).  Stores that stay out of the caches: 3 us less than without.  Random layers, with
 // buffers that change from call to call, so that the weights are not in a cache: 246 that leave rows to the projections 1.040
 // times as fast as without (geometric mean), the worst 0.984, 54 that ask and leave none 0.999.
 #pragma once

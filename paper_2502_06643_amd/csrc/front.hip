@@ -38,13 +38,13 @@ __global__ __launch_bounds__(kIndexThreads) void front_kernel(FrontArgs a) {
     index_clear(s, E);
     if (tid < E) s.pl[tid] = a.placement[tid];
 
-    // gate: L lanes per token, the whole batch
+    // gate: L lanes per token, the whole batch; one copy of the selection, which asks which logits exist (FULL in gate_select.h)
     const int sub = tid % L;
     for (int base = 0; base < T; base += kIndexThreads / L) {
         const int t = base + tid / L;
         const bool live = t < T;
         constexpr int S = kGateSlots<L, KMAX>;
-        gate_select_emit<L, VPL, KMAX, false>(a.logits + (long long)(live ? t : 0) * E, false, sub, live, E, k,
+        gate_select_emit<L, VPL, KMAX, false, false>(a.logits + (long long)(live ? t : 0) * E, false, sub, live, E, k,
                                               [&](const int (&e_sel)[S], const float (&p_sel)[S], float denom) {
 #pragma unroll
                                                   for (int i = 0; i < S; ++i)

@@ -13,23 +13,30 @@
 
 namespace moe {
 
-template <int L, int VPL, int KMAX, bool ALL>
+template <int L, int VPL, int KMAX, bool ALL, bool FULL>
 __global__ __launch_bounds__(256) void gate_kernel(const float* __restrict__ logits, int T, int E, int k,
                                                    int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
     constexpr int TOK_PER_BLOCK = 256 / L;
     const int sub = threadIdx.x % L;
     const long long t = (long long)blockIdx.x * TOK_PER_BLOCK + threadIdx.x / L;
     const bool live = t < T;
-    gate_select<L, VPL, KMAX, ALL>(logits + (live ? t : 0) * E, false, sub, live, t, E, k, topk_idx, topk_w);
+    gate_select<L, VPL, KMAX, ALL, FULL>(logits + (live ? t : 0) * E, false, sub, live, t, E, k, topk_idx, topk_w);
 }
 
-template <int L, int VPL, bool ALL>
-static void launch_l(const float* logits, int T, int E, int k, int32_t* idx, float* w, hipStream_t s) {
+template <int L, int VPL, bool ALL, bool FULL>
+static void launch_k(const float* logits, int T, int E, int k, int32_t* idx, float* w, hipStream_t s) {
     constexpr int TOK_PER_BLOCK = 256 / L;
     const unsigned grid = (unsigned)(((long long)T + TOK_PER_BLOCK - 1) / TOK_PER_BLOCK);
-    if (k <= 2) hipLaunchKernelGGL((gate_kernel<L, VPL, 2, ALL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);
-    else if (L == 1 || k <= 8) hipLaunchKernelGGL((gate_kernel<L, VPL, 8, ALL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);      // one lane: E <= 8
-    else hipLaunchKernelGGL((gate_kernel<L, VPL, L == 1 ? 8 : MOE_MAX_TOPK, ALL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);
+    if (k <= 2) hipLaunchKernelGGL((gate_kernel<L, VPL, 2, ALL, FULL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);
+    else if (L == 1 || k <= 8) hipLaunchKernelGGL((gate_kernel<L, VPL, 8, ALL, FULL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);      // one lane: E <= 8
+    else hipLaunchKernelGGL((gate_kernel<L, VPL, L == 1 ? 8 : MOE_MAX_TOPK, ALL, FULL>), dim3(grid), dim3(256), 0, s, logits, T, E, k, idx, w);
+}
+
+// whether every lane holds as many logits as it can is known here (FULL in gate_select.h); one lane alone asks anyway
+template <int L, int VPL, bool ALL>
+static void launch_l(const float* logits, int T, int E, int k, int32_t* idx, float* w, hipStream_t s) {
+    if (L > 1 && E == L * VPL) launch_k<L, VPL, ALL, (L > 1)>(logits, T, E, k, idx, w, s);
+    else launch_k<L, VPL, ALL, false>(logits, T, E, k, idx, w, s);
 }
 
 template <bool ALL>

@@ -130,10 +130,12 @@ template <int L, int KMAX> constexpr int kGateSlots = (KMAX + L - 1) / L;
 // their candidates in lists of KMAX, merge the lists across lanes and share the exponentials, divisions and stores.
 // Rounds of a scan and a shuffle butterfly took 18.9 us for 100003 tokens, E = 64, k = 6; bitonic sorts, a branch for each logit
 // and doubles that the compiler had quieted 11.1; candidates without branches, fewer exchanges and those written out 9.3; and without the
-// question which logits exist where all do (FULL) 8.8.
-// FULL: E == L * VPL.
+// question which logits exist where all do (FULL) 8.7.
+// FULL: E == L * VPL.  Where one copy of the selection can be had, the caller knows on the host: two of them and a branch in the kernels of
+// the front cost spilled scalar registers (44, 76 and 69 for 12, 55 and 35 with 4 lanes top-2 and top-8 and 16 lanes top-8) and cold
+// instruction fetches, layers of 1 to 64 tokens, 16 to 64 experts, top-2, 6.2 to 7.4 us for 5.8 to 7.0.
 template <int L, int VPL, int KMAX, bool ALL, bool FULL, class Emit>
-__device__ __forceinline__ void gate_select_lanes(const float* row, bool padded, int sub, bool live, int E, int k, Emit emit) {
+__device__ __forceinline__ void gate_select_emit(const float* row, bool padded, int sub, bool live, int E, int k, Emit emit) {
     static_assert(L >= 1 && L <= 16 && (KMAX & (KMAX - 1)) == 0 && MOE_MAX_EXPERTS <= 256, "DPP rows of 16 lanes, bitonic lists, 8-bit experts");
     constexpr int S = kGateSlots<L, KMAX>;
     const int e0 = sub * 4;                         // first logit of this lane; its i-th one is e0 + (i / 4) * 4 L + i % 4
@@ -242,12 +244,6 @@ __device__ __forceinline__ void gate_select_lanes(const float* row, bool padded,
     if (live) emit(e_sel, p_sel, denom);
 }
 
-template <int L, int VPL, int KMAX, bool ALL, class Emit>
-__device__ __forceinline__ void gate_select_emit(const float* row, bool padded, int sub, bool live, int E, int k, Emit emit) {
-    if (L > 1 && E == L * VPL) gate_select_lanes<L, VPL, KMAX, ALL, (L > 1)>(row, padded, sub, live, E, k, emit);
-    else gate_select_lanes<L, VPL, KMAX, ALL, false>(row, padded, sub, live, E, k, emit);
-}
-
 // writes this lane's slots of topk_idx[t][0..k) and topk_w[t][0..k)
 template <int L, int S>
 __device__ __forceinline__ void gate_store(long long t, int sub, int k, const int (&e_sel)[S], const float (&p_sel)[S], float denom,
@@ -265,11 +261,11 @@ __device__ __forceinline__ void gate_store(long long t, int sub, int k, const in
     }
 }
 
-template <int L, int VPL, int KMAX, bool ALL>
+template <int L, int VPL, int KMAX, bool ALL, bool FULL>
 __device__ __forceinline__ void gate_select(const float* row, bool padded, int sub, bool live, long long t, int E, int k,
                                             int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
     constexpr int S = kGateSlots<L, KMAX>;
-    gate_select_emit<L, VPL, KMAX, ALL>(row, padded, sub, live, E, k,
+    gate_select_emit<L, VPL, KMAX, ALL, FULL>(row, padded, sub, live, E, k,
                                         [&](const int (&e_sel)[S], const float (&p_sel)[S], float denom) {
                                             gate_store<L, S>(t, sub, k, e_sel, p_sel, denom, topk_idx, topk_w);
                                         });

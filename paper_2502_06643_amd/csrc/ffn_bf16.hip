@@ -118,46 +118,46 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint16_t* __restri
                                                         const uint16_t* __restrict__ w2, int d, int f,
                                                         long long units13, long long units2, long long total,
                                                         uint4* __restrict__ packed) {
-    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (o >= total) return;
-    const long long per_e = units13 + units2;
-    const long long e = o / per_e;
-    long long r = o - e * per_e;
-    const bool up = r < units13;
-    if (!up) r -= units13;
-    const int K = up ? d : f, ncols = up ? f : d;
-    const int KT = K / BK;
-    const int lane = (int)(r & 63);
-    const int kb = (int)((r >> 6) & 1);
-    const int p = (int)((r >> 7) & 15);
-    const long long tile = r >> 11;                 // nt * KT + kt
-    const int kt = (int)(tile % KT);
-    const long long panel = (tile / KT) * 16 + p;   // 16-column panel of the (interleaved) matrix
-    const uint16_t* src;
-    int col;
-    if (up) {
-        col = (int)(panel / 2) * kPanelCols + lane % 16;
-        src = ((panel & 1) ? w3 : w1) + (size_t)e * d * f;
-    } else {
-        col = (int)panel * kPanelCols + lane % 16;
-        src = w2 + (size_t)e * d * f;
-    }
-    const int k0 = kt * BK + kb * 32 + 8 * (lane / 16);
-    uint16_t v[8];
+    for (long long o = (long long)blockIdx.x * 256 + threadIdx.x; o < total; o += (long long)gridDim.x * 256) {
+        const long long per_e = units13 + units2;
+        const long long e = o / per_e;
+        long long r = o - e * per_e;
+        const bool up = r < units13;
+        if (!up) r -= units13;
+        const int K = up ? d : f, ncols = up ? f : d;
+        const int KT = K / BK;
+        const int lane = (int)(r & 63);
+        const int kb = (int)((r >> 6) & 1);
+        const int p = (int)((r >> 7) & 15);
+        const long long tile = r >> 11;                 // nt * KT + kt
+        const int kt = (int)(tile % KT);
+        const long long panel = (tile / KT) * 16 + p;   // 16-column panel of the (interleaved) matrix
+        const uint16_t* src;
+        int col;
+        if (up) {
+            col = (int)(panel / 2) * kPanelCols + lane % 16;
+            src = ((panel & 1) ? w3 : w1) + (size_t)e * d * f;
+        } else {
+            col = (int)panel * kPanelCols + lane % 16;
+            src = w2 + (size_t)e * d * f;
+        }
+        const int k0 = kt * BK + kb * 32 + 8 * (lane / 16);
+        uint16_t v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = (col < ncols) ? src[(size_t)(k0 + i) * ncols + col] : (uint16_t)0;
-    uint4 q;
-    q.x = v[0] | ((uint32_t)v[1] << 16); q.y = v[2] | ((uint32_t)v[3] << 16);
-    q.z = v[4] | ((uint32_t)v[5] << 16); q.w = v[6] | ((uint32_t)v[7] << 16);
-    packed[o] = q;
+        for (int i = 0; i < 8; ++i) v[i] = (col < ncols) ? src[(size_t)(k0 + i) * ncols + col] : (uint16_t)0;
+        uint4 q;
+        q.x = v[0] | ((uint32_t)v[1] << 16); q.y = v[2] | ((uint32_t)v[3] << 16);
+        q.z = v[4] | ((uint32_t)v[5] << 16); q.w = v[6] | ((uint32_t)v[7] << 16);
+        packed[o] = q;
+    }
 }
 
 int launch_pack_bf16(const void* w1, const void* w3, const void* w2, int E, int d, int f, void* packed, hipStream_t s) {
     const long long units13 = (long long)npad13(f) * d / 8, units2 = (long long)npad2(d) * f / 8;
     const long long total = (units13 + units2) * E;
-    const long long grid = (total + 255) / 256;
-    if (grid > 0x7FFFFFFFll) return fail(MOE_ERR_UNSUPPORTED, "moe_pack_weights: weights too large for one launch");
-    hipLaunchKernelGGL(pack_bf16_kernel, dim3((unsigned)grid), dim3(256), 0, s, (const uint16_t*)w1, (const uint16_t*)w3,
+    // one thread a unit of 16 bytes, and a loop past 2^30 of them: HIP launches fewer than 2^32 threads, 64 GiB of weights
+    const unsigned grid = (unsigned)(total < (1ll << 30) ? (total + 255) / 256 : 1 << 22);
+    hipLaunchKernelGGL(pack_bf16_kernel, dim3(grid), dim3(256), 0, s, (const uint16_t*)w1, (const uint16_t*)w3,
                        (const uint16_t*)w2, d, f, units13, units2, total, (uint4*)packed);
     return check_launch("moe_pack_weights launch");
 }

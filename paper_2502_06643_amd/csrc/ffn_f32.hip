@@ -56,22 +56,24 @@ constexpr int kF32Xcds = 8;
 size_t packed_bytes_f32(int E, int d, int f) { return (size_t)E * 3 * d * f * sizeof(float); }
 
 // per expert [W1 d*f | W3 d*f | W2 f*d]; a matrix of K rows and NC columns as [K / 4][NC][4]: the four k of a column side by side.
-// One thread per 16 bytes.
+// One thread per 16 bytes, blockIdx.y = matrix; a matrix of 2^30 units and more takes a loop over them, as HIP launches fewer than 2^32
+// threads along a dimension of the grid.
 __global__ __launch_bounds__(256) void pack_f32_kernel(const float* __restrict__ w1, const float* __restrict__ w3, const float* __restrict__ w2,
-                                                       int d, int f, long long units, long long total, float4* __restrict__ packed) {
-    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (o >= total) return;
-    const long long matrix = o / units, r = o - matrix * units, e = matrix / 3;      // units: 16-byte units of a matrix
-    const int which = (int)(matrix - 3 * e), NC = which == 2 ? d : f;
-    const long long q = r / NC;
-    const float* src = (which == 0 ? w1 : (which == 1 ? w3 : w2)) + e * units * 4 + q * 4 * NC + (r - q * NC);
-    packed[o] = make_float4(src[0], src[NC], src[2 * (size_t)NC], src[3 * (size_t)NC]);
+                                                       int d, int f, long long units, float4* __restrict__ packed) {
+    const int e = blockIdx.y / 3, which = blockIdx.y - 3 * e, NC = which == 2 ? d : f;
+    const float* src = (which == 0 ? w1 : (which == 1 ? w3 : w2)) + e * units * 4;
+    float4* out = packed + blockIdx.y * units;
+    for (long long r = (long long)blockIdx.x * 256 + threadIdx.x; r < units; r += (long long)gridDim.x * 256) {
+        const long long q = r >> 32 ? r / NC : (uint32_t)r / (uint32_t)NC;
+        const float* s = src + q * 4 * NC + (r - q * NC);
+        out[r] = make_float4(s[0], s[NC], s[2 * (size_t)NC], s[3 * (size_t)NC]);
+    }
 }
 
 int launch_pack_f32(const float* w1, const float* w3, const float* w2, int E, int d, int f, float* packed, hipStream_t s) {
-    const long long units = (long long)d * f / 4, total = units * 3 * E, grid = (total + 255) / 256;
-    if (grid > 0x7FFFFFFFll) return fail(MOE_ERR_UNSUPPORTED, "moe_pack_weights: weights too large for one launch");
-    hipLaunchKernelGGL(pack_f32_kernel, dim3((unsigned)grid), dim3(256), 0, s, w1, w3, w2, d, f, units, total, (float4*)packed);
+    const long long units = (long long)d * f / 4;
+    const unsigned grid = (unsigned)(units < (1ll << 30) ? (units + 255) / 256 : 1 << 22);
+    hipLaunchKernelGGL(pack_f32_kernel, dim3(grid, 3 * E), dim3(256), 0, s, w1, w3, w2, d, f, units, (float4*)packed);
     return check_launch("moe_pack_weights launch");
 }
 

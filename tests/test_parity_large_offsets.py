@@ -17,7 +17,7 @@ import torch
 from oracle import moe_oracle as O
 from paper_2502_06643_amd import synth
 from paper_2502_06643_amd.layer import MoELayer, to_device, to_host
-from util import TOL_BF16, as_f64, rel_err
+from util import TOL_BF16, TOL_F32, as_f64, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -197,3 +197,66 @@ def test_router_weights_past_4_GiB(lib):
     assert torch.equal(logits, want.float())
     del x, w, packed
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype,E", [("f32", 98), ("bf16", 196)])
+def test_packed_weights_of_more_than_2_to_32_units(lib, dtype, E):
+    """64.3 GiB of packed weights, more units of 16 bytes than HIP launches threads: the first, a middle and the last expert
+    against the oracle.  W1 and W3 are the same array, and W2 is another view of it."""
+    d, f, k = 4096, 14336, 1
+    assert E * 3 * d * f * (4 if dtype == "f32" else 2) > 16 << 32
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 92 GB")
+    g = torch.Generator(device="cuda").manual_seed(76)
+    w = torch.empty((E, d, f), dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+    for e in range(E):
+        w[e].normal_(0.0, d ** -0.5, generator=g)
+    dt = lib.MOE_F32 if dtype == "f32" else lib.MOE_BF16
+    packed = torch.empty(lib.moe_packed_weights_bytes(E, d, f, dt), dtype=torch.uint8, device="cuda")
+    lib.moe_pack_weights(w, w, w.view(E, f, d), E, d, f, dt, packed)
+    experts = [0, E // 2, E - 1]
+    x = synth.normal(76, 0, (9, d), 1.0, dtype)
+    counts, start = np.zeros(E, dtype=np.int32), np.zeros(E, dtype=np.int32)
+    counts[experts] = 3
+    start[1:] = np.cumsum(counts)[:-1]
+    pl = np.zeros(E, dtype=np.int32)
+    out = torch.zeros((9, d), dtype=w.dtype, device="cuda")
+    ws = torch.empty(lib.moe_ffn_workspace_bytes(9, d, f, E, dt), dtype=torch.uint8, device="cuda")
+    lib.moe_expert_ffn_grouped(to_device(x), dt, 9, d, f, E, packed, *[torch.from_numpy(a).cuda() for a in (counts, start, pl)], -1, out, ws)
+    torch.cuda.synchronize()
+    some = [to_host(w[e]) for e in experts]
+    del w, packed
+    torch.cuda.empty_cache()
+    w1, w2 = np.stack(some), np.stack([a.reshape(f, d) for a in some])
+    ref = O.expert_ffn_grouped(x, w1, w1, w2, np.full(3, 3, dtype=np.int32), np.array([0, 3, 6], dtype=np.int32), np.zeros(3, dtype=np.int32), -1)
+    assert rel_err(as_f64(to_host(out)), ref) <= (TOL_F32 if dtype == "f32" else TOL_BF16)
+
+
+def test_packed_matrix_of_more_than_2_to_30_units(lib):
+    """One expert whose matrices have 16 GiB each, so that a thread packs several units; against the same formula in fp64, a piece of
+    the reduction at a time."""
+    d, f, N = 65536, 65600, 3
+    assert d * f > 4 << 30
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 70 GB")
+    g = torch.Generator(device="cuda").manual_seed(77)
+    w = torch.empty((d, f), device="cuda")
+    for i in range(0, d, 4096):
+        w[i:i + 4096].normal_(0.0, d ** -0.5, generator=g)
+    packed = torch.empty(lib.moe_packed_weights_bytes(1, d, f, lib.MOE_F32), dtype=torch.uint8, device="cuda")
+    lib.moe_pack_weights(w, w, w.view(f, d), 1, d, f, lib.MOE_F32, packed)
+    x = torch.randn((N, d), generator=g, device="cuda")
+    i32 = lambda v: torch.tensor([v], dtype=torch.int32, device="cuda")
+    out = torch.zeros((N, d), device="cuda")
+    ws = torch.empty(lib.moe_ffn_workspace_bytes(N, d, f, 1, lib.MOE_F32), dtype=torch.uint8, device="cuda")
+    lib.moe_expert_ffn_grouped(x, lib.MOE_F32, N, d, f, 1, packed, i32(N), i32(0), i32(0), -1, out, ws)
+
+    def product(a, b):
+        return sum(a[:, i:i + 2048].double() @ b[i:i + 2048].double() for i in range(0, len(b), 2048))
+
+    up = product(x, w)
+    ref = product(up * torch.sigmoid(up) * up, w.view(f, d)).cpu().numpy()
+    got = out.cpu().numpy()
+    del w, packed
+    torch.cuda.empty_cache()
+    assert rel_err(got.astype(np.float64), ref) <= TOL_F32

@@ -360,8 +360,8 @@ int moe_combine(const void* ffn_out, moe_dtype_t dt, const int32_t* inv_perm,
  * that they leave idle: that part of the copy is then timed with MOE_K_FFN_UP
  * and MOE_K_FFN_DOWN, not MOE_K_DISPATCH_ROWS, and x and inv_perm are read and
  * send_buf is written until the FFN ends.  Not so where x, inv_perm or send_buf
- * share memory with ffn_out or ffn_workspace (send_buf may be ffn_out itself):
- * such a call copies every row first.
+ * share memory with ffn_out or ffn_workspace (send_buf may be ffn_out itself),
+ * or perm with send_buf: such a call copies every row first.
  * dispatch_workspace and ffn_workspace may be the same buffer, as they may be
  * for the four calls; the tile plan is a launch of its own then.
  * ---------------------------------------------------------------------- */

@@ -401,14 +401,16 @@ int moe_layer_forward(const void* x, moe_dtype_t dt, const float* logits, int T,
     if ((rc = ffn_plan_shape(dt, N, d, f, E, local_gpu < 0, false, &pt.shape)) != MOE_OK) return rc;
     // Rows that the projections copy are read and written while these write H and ffn_out: a caller who has part of the same
     // memory for the inputs or the send buffer gets every row copied first.  The send buffer as ffn_out is no such case: the
-    // rows copied are those that the projections leave alone.
+    // rows copied are those that the projections leave alone.  The row copy of such a call looks its rows up in perm, which a caller
+    // who has no use for it may have put under the send buffer: every row is copied by inv_perm then.
     const size_t rows_bytes = (size_t)N * row_bytes, ws_bytes = moe_ffn_workspace_bytes(N, d, f, E, dt);
     const auto apart = [](const void* p, size_t np, const void* q, size_t nq) {
         return (uintptr_t)p + np <= (uintptr_t)q || (uintptr_t)q + nq <= (uintptr_t)p;
     };
     const auto free_of_outputs = [&](const void* p, size_t n) { return apart(p, n, ffn_out, rows_bytes) && apart(p, n, ffn_workspace, ws_bytes); };
     const bool send_free = send_buf == ffn_out ? apart(send_buf, rows_bytes, ffn_workspace, ws_bytes) : free_of_outputs(send_buf, rows_bytes);
-    if (!fused && !shared && local_gpu >= 0 && send_free && free_of_outputs(x, (size_t)T * row_bytes) && free_of_outputs(inv_perm, (size_t)N * 4))
+    if (!fused && !shared && local_gpu >= 0 && send_free && free_of_outputs(x, (size_t)T * row_bytes) && free_of_outputs(inv_perm, (size_t)N * 4) &&
+        apart(perm, (size_t)N * 4, send_buf, rows_bytes))
         pt.late = ffn_late_shape(dt, N, d, f, E, T, k, G, pt.shape.cus_per_xcd);
     if (fused) {
         FrontArgs a;

@@ -95,7 +95,8 @@ def test_rows_copied_beside_the_projections_of_experts_mapped_nowhere(lib):
     assert int(plan[8]) > 0 and int(plan[10]) > 0
 
 
-@pytest.mark.parametrize("shared", ["x and ffn_out", "x and H", "inv_perm and H", "send_buf and ffn_out, shifted", "send_buf is ffn_out"])
+@pytest.mark.parametrize("shared", ["x and ffn_out", "x and H", "inv_perm and H", "send_buf and ffn_out, shifted", "send_buf is ffn_out",
+                                    "perm and send_buf"])
 def test_outputs_in_the_memory_of_the_inputs(lib, shared):
     """Memory that the four calls may share, because each has read it when the next writes it, or writes other rows of it: the same
     results, and nobody asks the projections to copy rows (but for the send buffer as ffn_out).  In a call with memory of its own
@@ -125,6 +126,8 @@ def test_outputs_in_the_memory_of_the_inputs(lib, shared):
     elif shared == "inv_perm and H":               # under the rows of other GPUs, which the up projection leaves alone
         at = 8192 + (end * f * 2 + 255) // 256 * 256
         got.inv_perm, xs = got.ffn_ws[at:at + N * 4].view(torch.int32), x
+    elif shared == "perm and send_buf":            # a sorted order that nobody wants, under this GPU's rows
+        got.perm, xs = got.send_buf.view(-1)[:2 * N].view(torch.int32), x
     else:                                          # the down projection's rows where other GPUs' send rows, or its own, are
         shift = end if shared.endswith("shifted") else 0
         memory = torch.zeros((N + shift, d), dtype=torch.bfloat16, device="cuda")

@@ -9,12 +9,12 @@
 // the up projection); its four wavefronts split every 32-deep stage of the
 // reduction among them, 8 k each, and add their partial sums through LDS in
 // wavefront order.  At 64 cycles per matrix instruction the operands of even so
-// small a tile arrive in time (12 KB per stage from L2, 3 LDS reads per two
-// instructions), and it is the small tile that keeps the chip busy: ragged
-// buckets waste at most 31 rows, the number of tiles divides well over 256
-// compute units, and four to seven workgroups share one, so that one's barrier
-// is another's turn.  Measured (2000 routes in 8 skewed buckets, d = 1024, f = 2816),
-// up / down in us: 231 / 128 (100 and 90 of the 157 TFLOP/s); 64 x 64 tiles with one
+// small a tile arrive in time (12 KB per stage from L2, one 16-byte LDS read per eight
+// instructions in the up projection, per four in the down), and it is the small tile that
+// keeps the chip busy: ragged buckets waste at most 31 rows, the number of tiles divides well over 256
+// compute units, and four workgroups (up) or seven (down) share one, so that one's barrier
+// is another's turn.  Measured when both operands went through LDS (2000 routes in 8 skewed buckets, d = 1024,
+// f = 2816), up / down in us: 231 / 128 (100 and 90 of the 157 TFLOP/s); 64 x 64 tiles with one
 // wavefront per 32 x 32 block 253 / 159, 32 x 64 tiles 243 / 145, 64-deep stages
 // 286 / 146; fused multiply-adds on 64 x 64 tiles, without matrix instructions,
 // 359 / 292.  Without loads and LDS writes that loop took 189 / 101: the rest was
@@ -27,8 +27,8 @@
 // because a wavefront's 8 k of 32 rows are 32 bytes a row: fetched by the lanes that
 // multiply them, without LDS, layers took 1.0 to 1.65 times as long.  Both
 // operands through LDS, B row-major: 1064 tokens, top-2, d 500, f 400, 4 experts, up 30.5
-// us and down 18.5, now 27.4 and 17.0; 116 routes, f 2048, down 20.1, now 17.8, but up with its
-// five stages (d 152) 7.0, now 7.4.
+// us and down 18.5, now 27.4 and 17.0; 116 routes of one expert, f 2048, down 15.7, now 14.9, up
+// by its one to eight stages (d 32 to 256) 5.3 to 8.5, now 5.4 to 8.0, five (d 152) 7.25, now 7.1.
 //
 // Pipeline.  While stage s multiplies, the A of stage s + 1 is read from LDS, that of
 // s + 2 is written there and the loads of s + 3 and s + 4 are in flight, one
@@ -195,8 +195,8 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
             step(s, i, ragged);
         }
 
-    // add the four partial sums in wavefront order; a wavefront finishes 4 of the 16 accumulator rows
-    __syncthreads();                                                      // the stages have been read by everyone
+    // add the four partial sums in wavefront order; a wavefront finishes 4 of the 16 accumulator rows.  They overwrite the stages, which
+    // everyone had read before the barrier that ends the last step; there is one, a reduction has at least one stage.
 #pragma unroll
     for (int p = 0; p < NP; ++p)
 #pragma unroll

@@ -179,11 +179,20 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
         if ((e & 63) == (some ? __builtin_ctzll(some) : 0)) s.first_row[e >> 6] = some ? st : 0x7FFFFFFF;
     }
     __syncthreads();
-    if (c > 0) {
-        atomicAdd(&s.n, 1);
-        atomicAdd(&s.total1, s.tiles1[e]);
-        if (c - (s.tiles1[e] - 1) * shape.bm1 <= kSmallTileRows) atomicAdd(&s.n_small, 1);
-        if (c <= shape.bm1) atomicAdd(&s.n_single, 1);
+    const unsigned long long listed = __ballot(c > 0);
+    // Added up per wavefront: sums of different values into one LDS address go lane by lane.  64 experts, top-6, us: rank kernel of
+    // 8000 tokens 8.4 -> 6.6, one-workgroup kernel of 2000 15.2 -> 13.6, front of 64 9.7 -> 8.3; 8 experts as before.
+    if (listed != 0) {
+        const int tiles = c > 0 ? s.tiles1[e] : 0;
+        const unsigned long long small = __ballot(c > 0 && c - (tiles - 1) * shape.bm1 <= kSmallTileRows), single = __ballot(c > 0 && c <= shape.bm1);
+        int total = tiles;
+        for (int m = 1; m < 64 && m < E; m <<= 1) total += __shfl_xor(total, m, 64);        // of the first power of two from E on
+        if ((e & 63) == 0) {
+            atomicAdd(&s.n, __popcll(listed));
+            atomicAdd(&s.n_small, __popcll(small));
+            atomicAdd(&s.n_single, __popcll(single));
+            atomicAdd(&s.total1, total);
+        }
     }
     int ebits = 0;
     while ((1 << ebits) < E) ++ebits;

@@ -140,6 +140,26 @@ def test_outputs_in_the_memory_of_the_inputs(lib, shared):
     assert asked == (shared == "send_buf is ffn_out")
 
 
+@pytest.mark.parametrize("T,E,k,G,local", [
+    (800, 8, 2, 1, -1), (3000, 8, 2, 1, -1), (5000, 8, 2, 2, 1),           # written by the front; more and fewer buckets of one row tile
+    (900, 128, 4, 1, -1), (1300, 16, 4, 1, -1), (2103, 32, 2, 2, 0), (700, 256, 4, 3, 1),        # by the one-workgroup index kernel
+    (8000, 64, 6, 1, -1), (9000, 8, 2, 1, -1), (20000, 256, 2, 1, -1),     # by the rank kernel
+])
+def test_tiles_counted_by_the_plan(lib, T, E, k, G, local):
+    """The plan's header: row tiles of 256, those of at most 128 rows, and those of buckets of several tiles if the buckets of one are
+    at least as many (else 0)."""
+    L = check_forward("bf16", T, 64, 64, E, k, G, local)
+    counts = L.expert_counts.cpu().numpy()
+    if local >= 0:
+        counts = counts[L.placement.cpu().numpy() == local]
+    counts = counts[counts > 0]
+    tiles, single = -(-counts // 256), int((counts <= 256).sum())
+    plan = L.ffn_ws[:64].view(torch.int32).cpu().tolist()
+    assert plan[0] == len(counts) and plan[2] == tiles.sum()
+    assert plan[4] == 1 + ((counts - 1) % 256 < 128).sum()
+    assert plan[12] == (tiles.sum() - single if 2 * single >= tiles.sum() else 0)
+
+
 def check_forward(dtype, T, d, f, E, k, G, local, one_workspace=False, placement=None):
     rng = np.random.default_rng(T + E)
     pl = rng.integers(0, G, E).astype(np.int32) if placement is None else placement

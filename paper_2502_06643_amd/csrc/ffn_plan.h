@@ -122,6 +122,9 @@ constexpr int kF32TileRows = 32, kF32SplitRows = 64;    // tile heights of the f
 constexpr int kTallTileRows = 384, kShortTileRows = 256; // tile heights of the bf16 path
 constexpr int kSkinnyRows = 64;                         // rows a pass of its streaming kernels covers (bm1 of their plan)
 
+// kPlanMixed of a plan of `tiles` row tiles of which `single` are buckets of one (mixed_tile in ffn_tiles.h: why the line lies there)
+__host__ __device__ __forceinline__ int mixed_rows(int tiles, int single) { return 2 * single >= tiles ? tiles - single : 0; }
+
 // Shared memory of build_plan: per group its rows and tiles, and the sums over the groups listed before it.
 struct PlanScratch {
     int cnt[MOE_MAX_EXPERTS], tiles0[MOE_MAX_EXPERTS], tiles1[MOE_MAX_EXPERTS], segs[MOE_MAX_EXPERTS];
@@ -246,7 +249,7 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
             plan[3] = choice;
             plan[kPlanSmallTiles] = 1 + n_small;
             plan[kPlanMerged] = merged;
-            plan[kPlanMixed] = 2 * s.n_single >= t1 ? t1 - s.n_single : 0;
+            plan[kPlanMixed] = mixed_rows(t1, s.n_single);
             plan[kPlanTiles0 + n] = t0;
             plan[kPlanTiles1 + n] = t1;
             if (range) {

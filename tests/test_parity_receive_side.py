@@ -209,6 +209,42 @@ def test_receive_segments_table_edge_cases(lib):
         B.moe_receive_segments(dev(counts), dev(pl), E, G, 0, 257, se, sc, ss, off, n)        # more than the segment FFN takes
 
 
+@pytest.mark.parametrize("E,G,dest,own,cuts", [
+    # the experts of dest; table sizes beside one that is just large enough
+    (256, 1, 0, range(256), (255, 193, 65, 1)),                                 # 256 segments of one source
+    (256, 4, 2, range(2, 256, 4), (255, 129, 128, 100)),                        # 16 experts in each of the four groups of 64
+    (256, 3, 1, [0, 63, 64, 65, 127, 128, 191, 192, 254, 255], (31, 25, 20)),   # at the ends of the groups, 30 segments
+    (200, 5, 4, range(150, 200), (249, 130, 64)),                               # none in the first group
+    (130, 13, 0, [5, 66, 67, 128, 129], (66, 63)),                              # 65 segments
+    (256, 100, 99, [70, 250], (256, 199, 129, 3)),                              # more sources than a wavefront has lanes
+    (80, 256, 7, [79], (255, 200)),                                             # one segment a source
+    (256, 256, 7, [3, 200], (256,)),                                            # 512 segments, more than any table holds
+    (256, 70, 5, [], (1, 256)),                                                 # no expert here
+])
+def test_receive_segments_across_wavefronts(lib, E, G, dest, own, cuts):
+    """More than 64 experts, segments or sources: ranks, starts and totals that are carried from one wavefront to the next.  A table that
+    is too small holds the first segments; a source whose first segment fits begins there, the others at the table's total."""
+    rng = np.random.default_rng(E + G)
+    own = list(own)
+    pl = np.full(E, (dest + 1) % G, dtype=np.int32)
+    pl[own] = dest
+    counts = rng.integers(0, 50, (G, E)).astype(np.int32)
+    counts[rng.random((G, E)) < 0.2] = 0
+    want_e, want_c = np.array(own * G, dtype=np.int32), counts[:, own].reshape(-1)
+    ends = np.concatenate([[0], np.cumsum(want_c)])
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    for max_seg in (min(256, max(1, len(want_e))), *cuts):
+        se, sc, ss, off, n = (torch.full((m,), -1, dtype=torch.int32, device="cuda") for m in (max_seg, max_seg, max_seg, G + 1, 1))
+        lib.moe_receive_segments(dev(counts), dev(pl), E, G, dest, max_seg, se, sc, ss, off, n)
+        torch.cuda.synchronize()
+        m = min(max_seg, len(want_e))
+        assert int(n.cpu()[0]) == len(want_e)
+        np.testing.assert_array_equal(se.cpu().numpy()[:m], want_e[:m])
+        np.testing.assert_array_equal(sc.cpu().numpy(), np.concatenate([want_c[:m], np.zeros(max_seg - m, dtype=np.int32)]))
+        np.testing.assert_array_equal(ss.cpu().numpy(), np.concatenate([ends[:m], np.full(max_seg - m, ends[m])]))
+        np.testing.assert_array_equal(off.cpu().numpy(), ends[np.minimum(np.arange(G + 1) * len(own), m)])
+
+
 def test_segments_entry_point_edge_cases(lib):
     d, f, E = 64, 128, 4
     w1 = synth.normal(1, 2, (E, d, f), 1 / np.sqrt(d), "f32")

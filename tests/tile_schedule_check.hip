@@ -6,8 +6,10 @@
 // Built and run by tests/test_tile_schedule.py.
 #include "ffn_tiles.h"
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <functional>
 #include <map>
 #include <random>
 #include <tuple>
@@ -26,6 +28,8 @@ using namespace moe;
     } while (0)
 
 struct Part { int bucket, mt, nt, kt0, kt1; };
+
+static long long mixed_launches = 0, mixed_cuts = 0;      // launches whose plan spreads buckets of one row tile among the others; with parts of such tiles
 
 // Receives that were measured with their segments apart and merged (us): merged where that was the faster way.
 static int check_measured_merges() {
@@ -114,6 +118,14 @@ static int check_case(std::mt19937& rng, long long& units) {
         const int kind = rng() % 4;
         count[i] = kind == 0 ? 1 + rng() % 40 : (kind == 1 ? 1 + rng() % 400 : (kind == 2 ? 1 + rng() % 3000 : BM * (1 + rng() % 4)));
         if (n > 64) count[i] = 1 + rng() % 300;
+    }
+    // listed by size, as build_plan (csrc/ffn_plan.h) does, whose rule then says whether the tiles are mixed; otherwise any order and the header without it
+    const bool by_size = rng() % 2;
+    if (by_size) {
+        for (int i = 2; i < n; ++i) count[i] = 1 + count[i] % BM;        // mostly buckets of one row tile
+        std::sort(count.begin(), count.end(), std::greater<int>());
+    }
+    for (int i = 0; i < n; ++i) {
         start[i] = (int)N + (int)(rng() % 3);            // gaps between buckets are allowed
         N = start[i] + count[i];
         tiles[i] = (count[i] + BM - 1) / BM;
@@ -129,6 +141,12 @@ static int check_case(std::mt19937& rng, long long& units) {
         mt_total += tiles[i];
     }
     prefix[n] = mt_total;
+    if (by_size) {
+        const int single = (int)std::count_if(count.begin(), count.end(), [&](int c) { return c <= BM; });
+        plan[kPlanMixed] = mixed_rows(mt_total, single);
+        CHECK(plan[kPlanMixed] == (single >= mt_total - single ? prefix[n - single] : 0), "%d of %d row tiles by themselves: %d", single, mt_total, plan[kPlanMixed]);
+    }
+    const bool mixed = BM == kShortTileRows && plan[kPlanMixed] > 0 && NT >= kXcds;
 #ifdef WITH_ROUND_SPLIT
     // tiles of more than 128 rows and the others cut apart: as the plan would choose, or else into any numbers of parts that fit two per compute unit
     int n_small = 0;
@@ -229,6 +247,8 @@ static int check_case(std::mt19937& rng, long long& units) {
             CHECK(at == KT, "parts end at k tile %d of %d", at, KT);
         }
     if (split) CHECK(parts_seen == partial_of.size(), "%zu parts fixed up, %zu written", parts_seen, partial_of.size());
+    mixed_launches += mixed;
+    mixed_cuts += mixed && plan[kPlanBigParts] == 0 && !partial_of.empty();
     (void)active;
     return 0;
 }
@@ -249,6 +269,7 @@ int main(int argc, char** argv) {
 #ifdef WITH_ROUND_SPLIT
     CHECK(chosen_cuts > 0 && cut_launches > 0, "%lld cuts chosen, %lld launches cut", chosen_cuts, cut_launches);
 #endif
+    CHECK(mixed_launches > cases / 50 && mixed_cuts > cases / 200, "%lld mixed launches, %lld cut", mixed_launches, mixed_cuts);
     std::printf("ok: %d launches, %lld k tiles owned exactly once\n", cases, units);
     return 0;
 }

@@ -107,7 +107,8 @@ static int check_case(std::mt19937& rng, long long& units) {
     const int nts[10] = {1, 2, 5, 8, 11, 16, 23, 32, 57, 112};
     const int kts[8] = {4, 9, 22, 32, 64, 100, 224, 448};
     const int cpxs[4] = {32, 38, 48, 4};
-    const int BM = bms[rng() % 2], NT = nts[rng() % 10], KT = kts[rng() % 8], cpx = cpxs[rng() % 4];
+    const bool by_size = rng() % 2;                       // of buckets listed by size, as build_plan (csrc/ffn_plan.h) does, whose rule then says whether tiles are mixed
+    const int BM = by_size ? kShortTileRows : bms[rng() % 2], NT = nts[rng() % 10], KT = kts[rng() % 8], cpx = cpxs[rng() % 4];
     const int row_chunk = (rng() % 2) ? 8 : 4;
     const bool split = rng() % 2;
     const int n = 1 + (int)(rng() % ((rng() % 8 == 0) ? 256 : 12));
@@ -119,8 +120,6 @@ static int check_case(std::mt19937& rng, long long& units) {
         count[i] = kind == 0 ? 1 + rng() % 40 : (kind == 1 ? 1 + rng() % 400 : (kind == 2 ? 1 + rng() % 3000 : BM * (1 + rng() % 4)));
         if (n > 64) count[i] = 1 + rng() % 300;
     }
-    // listed by size, as build_plan (csrc/ffn_plan.h) does, whose rule then says whether the tiles are mixed; otherwise any order and the header without it
-    const bool by_size = rng() % 2;
     if (by_size) {
         for (int i = 2; i < n; ++i) count[i] = 1 + count[i] % BM;        // mostly buckets of one row tile
         std::sort(count.begin(), count.end(), std::greater<int>());
@@ -146,7 +145,7 @@ static int check_case(std::mt19937& rng, long long& units) {
         plan[kPlanMixed] = mixed_rows(mt_total, single);
         CHECK(plan[kPlanMixed] == (single >= mt_total - single ? prefix[n - single] : 0), "%d of %d row tiles by themselves: %d", single, mt_total, plan[kPlanMixed]);
     }
-    const bool mixed = BM == kShortTileRows && plan[kPlanMixed] > 0 && NT >= kXcds;
+    const bool mixed = plan[kPlanMixed] > 0 && NT >= kXcds;
 #ifdef WITH_ROUND_SPLIT
     // tiles of more than 128 rows and the others cut apart: as the plan would choose, or else into any numbers of parts that fit two per compute unit
     int n_small = 0;
@@ -269,7 +268,7 @@ int main(int argc, char** argv) {
 #ifdef WITH_ROUND_SPLIT
     CHECK(chosen_cuts > 0 && cut_launches > 0, "%lld cuts chosen, %lld launches cut", chosen_cuts, cut_launches);
 #endif
-    CHECK(mixed_launches > cases / 50 && mixed_cuts > cases / 200, "%lld mixed launches, %lld cut", mixed_launches, mixed_cuts);
+    CHECK(mixed_launches > cases / 10 && mixed_cuts > cases / 100, "%lld mixed launches, %lld cut", mixed_launches, mixed_cuts);
     std::printf("ok: %d launches, %lld k tiles owned exactly once\n", cases, units);
     return 0;
 }

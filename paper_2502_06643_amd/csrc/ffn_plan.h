@@ -125,11 +125,24 @@ constexpr int kSkinnyRows = 64;                         // rows a pass of its st
 // kPlanMixed of a plan of `tiles` row tiles of which `single` are buckets of one (mixed_tile in ffn_tiles.h: why the line lies there)
 __host__ __device__ __forceinline__ int mixed_rows(int tiles, int single) { return 2 * single >= tiles ? tiles - single : 0; }
 
+// The plan's counts in one word, so that one LDS operation adds a group to all: groups with rows, those of one row tile of bm1, those whose
+// last tile has at most kSmallTileRows rows (up to 256 each, 9 bits), and row tiles of bm1 (fewer than 2^31 / kF32TileRows + 256, 27 bits).
+struct PlanSums {
+    unsigned long long v;
+    static __device__ __forceinline__ unsigned long long of(int tiles, bool single, bool small) {
+        return ((unsigned long long)tiles << 27) | ((unsigned)small << 18) | ((unsigned)single << 9) | 1u;
+    }
+    __device__ __forceinline__ int listed() const { return (int)v & 511; }
+    __device__ __forceinline__ int single() const { return (int)(v >> 9) & 511; }
+    __device__ __forceinline__ int small() const { return (int)(v >> 18) & 511; }
+    __device__ __forceinline__ int tiles() const { return (int)(v >> 27); }
+};
+
 // Shared memory of build_plan: per group its rows and tiles, and the sums over the groups listed before it.
 struct PlanScratch {
     int cnt[MOE_MAX_EXPERTS], tiles0[MOE_MAX_EXPERTS], tiles1[MOE_MAX_EXPERTS], segs[MOE_MAX_EXPERTS];
     int rank[MOE_MAX_EXPERTS], rows[MOE_MAX_EXPERTS], pre0[MOE_MAX_EXPERTS], pre1[MOE_MAX_EXPERTS], pre_segs[MOE_MAX_EXPERTS];
-    int n, n_small, n_single, total1;
+    unsigned long long sums;                             // four counts in one word (PlanSums)
     int first_row[MOE_MAX_EXPERTS / 64];                 // of the groups of a wavefront with rows (only when the range of all is asked for)
 };
 
@@ -176,26 +189,21 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
         s.segs[e] = n_segs;
         s.rank[e] = s.rows[e] = s.pre0[e] = s.pre1[e] = s.pre_segs[e] = 0;
     }
-    if (e == 0) s.n = s.n_small = s.n_single = s.total1 = 0;
+    if (e == 0) s.sums = 0;
     if (range && e < MOE_MAX_EXPERTS) {                  // the groups with rows lie side by side, by number
         const unsigned long long some = __ballot(c > 0);
         if ((e & 63) == (some ? __builtin_ctzll(some) : 0)) s.first_row[e >> 6] = some ? st : 0x7FFFFFFF;
     }
     __syncthreads();
-    const unsigned long long listed = __ballot(c > 0);
-    // Added up per wavefront: sums of different values into one LDS address go lane by lane.  64 experts, top-6, us: rank kernel of
-    // 8000 tokens 8.4 -> 6.6, one-workgroup kernel of 2000 15.2 -> 13.6, front of 64 9.7 -> 8.3; 8 experts as before.
-    if (listed != 0) {
-        const int tiles = c > 0 ? s.tiles1[e] : 0;
-        const unsigned long long small = __ballot(c > 0 && c - (tiles - 1) * shape.bm1 <= kSmallTileRows), single = __ballot(c > 0 && c <= shape.bm1);
-        int total = tiles;
-        for (int m = 1; m < 64 && m < E; m <<= 1) total += __shfl_xor(total, m, 64);        // of the first power of two from E on
-        if ((e & 63) == 0) {
-            atomicAdd(&s.n, __popcll(listed));
-            atomicAdd(&s.n_small, __popcll(small));
-            atomicAdd(&s.n_single, __popcll(single));
-            atomicAdd(&s.total1, total);
-        }
+    // One LDS operation.  Four sums, one of them of different values and so, as the compiler has it, a loop over the lanes / ballots and
+    // exchanges per wavefront / this, us: 64 experts, top-6, front of 64 tokens 10.2 / 8.5 / 8.4, one-workgroup kernel of 2000 16.3 /
+    // 14.8 / 14.6, plan of 64 received segments 5.3 / 5.8 / 5.3; front of 1000 fp32 tokens, 8 experts, whose weights have swept the kernel's
+    // instructions out of the caches, 9.5 / 10.1 / 9.4.
+    if (c > 0) {
+        const int tiles = s.tiles1[e];
+        int at = 0;
+        asm("" : "+v"(at));                              // could differ by lane, for all the compiler knows: no loop
+        atomicAdd(&s.sums + at, PlanSums::of(tiles, c <= shape.bm1, c - (tiles - 1) * shape.bm1 <= kSmallTileRows));
     }
     int ebits = 0;
     while ((1 << ebits) < E) ++ebits;
@@ -229,7 +237,8 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
         atomicAdd(&s.pre_segs[me], sg);
     }
     __syncthreads();
-    const int n = s.n, n_small = s.n_small;
+    const PlanSums sums = {s.sums};
+    const int n = sums.listed(), n_small = sums.small();
     if (c > 0) {
         r = s.rank[e];
         t0 = s.pre0[e];
@@ -249,7 +258,7 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
             plan[3] = choice;
             plan[kPlanSmallTiles] = 1 + n_small;
             plan[kPlanMerged] = merged;
-            plan[kPlanMixed] = mixed_rows(t1, s.n_single);
+            plan[kPlanMixed] = mixed_rows(t1, sums.single());
             plan[kPlanTiles0 + n] = t0;
             plan[kPlanTiles1 + n] = t1;
             if (range) {
@@ -269,7 +278,7 @@ __device__ __forceinline__ void build_plan(PlanScratch& s, int e, int c, int st,
     }
     const int last_wave = (int)blockDim.x - 64;          // while the others write
     if (e >= last_wave) {
-        if (shape.kt_down > 0) round_split(e - last_wave, s.total1 - n_small, n_small, shape, plan);
+        if (shape.kt_down > 0) round_split(e - last_wave, sums.tiles() - n_small, n_small, shape, plan);
         else if (e == last_wave) plan[kPlanBigParts] = 0;
     }
 }

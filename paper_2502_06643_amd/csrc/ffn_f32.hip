@@ -239,8 +239,9 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
 //
 // Bound by power for the up projection (the clock falls to 1.9 to 2.1 GHz) and by the loads and vector work of the narrower
 // tile for the down projection.  2000 routes in 8 skewed buckets, d 1024, f 2816, layer 369 us on the fp32 kernel; here, one change after
-// the other on one box: weights row-major, sixteen of a stage's eighteen loads four bytes wide, 301; the four k of a column side by side 287;
-// ragged tiles last (split_tile) 279; the split of a stage between the products of the one before (stage) 270.
+// the other on one GPU: weights row-major, sixteen of a stage's eighteen loads four bytes wide, 301; the four k of a column side by side 287;
+// ragged tiles last (split_tile) 279; the split of a stage between the products of the one before (stage) 270.  First against last on
+// two other GPUs: 303 and 272, 309 and 279.
 // The look at every operand (split_pair) is one instruction a pair; as a minimum of their magnitudes, three a pair, it made 302 315.  Also
 // lost, with row-major weights and the last four without that look (293 us, 4096 routes 501): B by buffer loads with the row in a scalar
 // offset, 193 -> 202 us in the up projection; the remainders by v_dot2_f32_bf16, exact and a sixth fewer vector instructions,
